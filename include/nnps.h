@@ -15,13 +15,12 @@
  * w = max(cell_size, R)(1 + 2^-30) (cell link list, Fig. 3b), sorted by cell, and
  * stored as FP16 coordinates relative to their cell centre (Eq. 6 scale, [-1, 1]).
  * A pair's squared distance is evaluated in FP16 from the two relative coordinates
- * plus the integer offset of the two cells (Eq. 7, with the factor 1/2 Eq. 7 drops).
- * Pairs whose FP16 r2 lies within a guard band of the cutoff are decided again in
- * FP64 from the caller's positions, so the neighbour set is exactly the binary64
+ * plus the integer offset of the two cells (Eq. 7, with the factor 1/2 Eq. 7 drops): on
+ * the matrix cores, each coordinate split into two FP16 parts and the sums in FP32, or (in
+ * dense cells) by packed FP16 arithmetic. Pairs within the evaluation's error bound of the
+ * cutoff are decided again in FP64, so the neighbour set is exactly the binary64
  * one above. FP64 arithmetic on the GPU is used for cell assignment, that recheck, and
- * one subtraction per coordinate for each emitted FP32 distance: of two fixed-point
- * positions (integers below 2^52 held as doubles, so exact) in the block path, of the
- * two FP64 positions in the dense-cell path; the neighbour test itself is FP16.
+ * per particle (or, in dense cells, pair) for the emitted FP32 distances.
  *
  * Memory: every pointer named d_* is device memory on the context's device.
  * The caller owns positions and all outputs; the library owns the context and
@@ -66,14 +65,14 @@ typedef enum nnps_status {
 
 typedef enum nnps_mode {
     NNPS_MODE_FP16_RCLL = 0,      /* FP16 relative coordinates + FP64 guard-band recheck */
-    NNPS_MODE_FP64_BASELINE = 1,  /* FP64 cell list: the binary64 predicate on every candidate,
-                                     read from sorted FP64 positions in global memory (one lane
-                                     per target), with the same cell build, work blocks, dense
-                                     and long-row paths and fill as the FP16 mode; distances
-                                     (float)sqrt(r2) in binary64 */
-    NNPS_MODE_RECHECK_ALL = 2,    /* debug: FP16 pass plus FP64 on every candidate; the FP64
-                                     decision is used and FP16 disagreements outside the band
-                                     are counted (must be 0) */
+    NNPS_MODE_FP64_BASELINE = 1,  /* FP64 cell list: every candidate tested in binary64 (on the
+                                     matrix cores in work blocks, those within the rounding
+                                     error of the cutoff by the predicate itself), with the same
+                                     cell build, work blocks, dense and long-row paths and fill
+                                     as the FP16 mode; distances (float)sqrt(r2) in binary64 */
+    NNPS_MODE_RECHECK_ALL = 2,    /* debug: decided in FP64; the statistics test every candidate
+                                     in packed FP16 as well and count the disagreements outside
+                                     the band (must be 0) */
     NNPS_MODE_FP32_RCLL = 3       /* FP32 relative coordinates (Eq. 6-7 in single precision) +
                                      FP64 recheck in a guard band of 2^-15 squared cell widths;
                                      dense cells and long rows are decided in FP64; distances
@@ -93,7 +92,9 @@ typedef struct nnps_problem {
     double radius;
 } nnps_problem;
 
-/* Statistics of the last count pass on a cell structure (nnps_stats_get). */
+/* Statistics of the last count pass on a cell structure (nnps_stats_get). Those of the
+ * packed-FP16 (or FP32) test are made when they are asked for, from the structure's own
+ * arrays: no count pass pays for them. */
 typedef struct nnps_stats {
     int64_t n;
     int64_t nnz;                    /* total neighbour pairs (directed, self excluded) */
@@ -212,8 +213,8 @@ nnps_status nnps_search(nnps_ctx *ctx, nnps_cells *cells, const nnps_problem *pr
                         const double *d_pos, int64_t *d_row_ptr, int32_t *d_col, float *d_dist,
                         int64_t capacity, int64_t *nnz_out, void *stream);
 
-/* Sums the last count pass's per-block statistics on `stream` (the count pass leaves
- * them per block, so a search step does not pay for the sum), waits for the stream and
+/* Makes the last count pass's statistics on `stream` (a pass of the packed-FP16 or FP32
+ * test over the blocks, for which a search step does not pay), waits for the stream and
  * copies them; all zero if nothing was counted since the last build.
  * Returns any device-detected error (NNPS_EDOMAIN, NNPS_ECAPACITY, NNPS_EUNSUPPORTED). */
 nnps_status nnps_stats_get(nnps_cells *cells, nnps_stats *out, void *stream);

@@ -21,7 +21,7 @@ struct Launch {
 hipError_t launch_fill_i32(int* p, int64_t m, int v, hipStream_t st);
 hipError_t launch_fill2_i32(int* p, int64_t m, int* q, int64_t k, int v, hipStream_t st);
 int row_segments(int ncx);  // pieces a row of ncx cells is walked in
-hipError_t launch_assign(const Launch& L, double* X, uint32_t* key, int* slot, int* cell_count, int* err,
+hipError_t launch_assign(const Launch& L, uint32_t* key, int* slot, int* cell_count, int* err,
                          hipStream_t st);
 hipError_t launch_place(int ntot, const uint32_t* key, const int* slot, const int* cell_start, uint32_t* skey,
                         int* perm, hipStream_t st);
@@ -30,9 +30,8 @@ hipError_t launch_scan_i32_i64(const int* in, int64_t m, int64_t* out, int64_t* 
 int64_t scan_partials_needed(int64_t m);
 int radix_tiles(int n);
 size_t radix_table_entries(int n);
-hipError_t launch_pack(const Launch& L, const uint32_t* skey, const int* perm, const double* X, ushort4* q4,
-                       double* spos, float4* rq, int* inv, hipStream_t st, uint32_t* skey_out = nullptr,
-                       int* perm_out = nullptr);
+hipError_t launch_pack(const Launch& L, const uint32_t* skey, const int* perm, double* spos, float4* rq, int* inv,
+                       hipStream_t st, uint32_t* skey_out = nullptr, int* perm_out = nullptr);
 
 // Incremental update of a built structure (see k_upd_move): device tables of one update.
 struct Update {
@@ -46,9 +45,9 @@ struct Update {
     uint32_t* skey2;          // [ntot] new order: cell keys
     int* perm2;               // [ntot] new order: particle indices
 };
-// U1: move (when the set has displacements), fixed point, cells, migrant flags and counts.
-hipError_t launch_update_move(const Launch& L, const uint32_t* skey, const int* inv, double* X, const Update& u,
-                              int* err, hipStream_t st);
+// U1: move (when the set has displacements), cells, migrant flags and counts.
+hipError_t launch_update_move(const Launch& L, const uint32_t* skey, const int* inv, const Update& u, int* err,
+                              hipStream_t st);
 // U2: new cell occupancies and starts (cell_start is rewritten; the old one goes to cs_old).
 hipError_t launch_update_cells(const Launch& L, int* cell_start, int* cnt, const Update& u, int64_t* partial,
                                hipStream_t st);
@@ -101,10 +100,8 @@ struct SearchArgs {
     const uint32_t* skey;     // sorted global cell keys
     const int* perm;          // sorted position -> global particle index
     const int* cell_start;    // [ncell_tot + 1]
-    const ushort4* q4;        // sorted FP16 relative coordinates (+ c_x mod 2^16)
-    const double* spos;       // sorted FP64 positions [ntot][4] (FP64 and FP32 modes)
-    const float4* rq;         // sorted FP32 relative coordinates + packed cell bits (FP32 mode)
-    const double* X;          // fixed-point positions (exact integers), global index, stride x_stride(dim)
+    const double* spos;       // sorted FP64 positions [ntot][4], the fourth the particle index (int64 bits)
+    const float4* rq;         // sorted FP32 relative coordinates + packed cell bits
     const int* bstart;        // block starts [nblk + 1]
     const int* bset;          // set of each block [nblk]
     const int* nblk;          // device pointer to the block count
@@ -112,6 +109,8 @@ struct SearchArgs {
     int* counts_s;            // the same by sorted position (the fill reads them in block order)
     int64_t* rsort;           // each particle's row start in its set's output, by sorted position
     int* bdesc;               // [nblk_max][24] per-block descriptors the count pass leaves for the fill
+    uint16_t* branks;         // [nblk_max][union limit] ranks of each block's union by original index
+                              // (the order of its candidate bits)
     int* heavy;               // sorted positions of long rows
     int* nheavy;
     unsigned long long* stats;      // [kStCount] totals
@@ -146,6 +145,8 @@ hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st);
 hipError_t launch_fill(const SearchArgs& a, int nblk_max, hipStream_t st);
 hipError_t launch_long_rows(const SearchArgs& a, int grid, hipStream_t st);
 hipError_t launch_dense(const SearchArgs& a, bool fill, hipStream_t st);
-hipError_t launch_stats(const SearchArgs& a, hipStream_t st);
+// The last count's statistics, summed into a.stats. The block path's count decides on the
+// matrix cores and tallies nothing: its statistics are made here.
+hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st);
 
 }  // namespace nnps

@@ -24,9 +24,16 @@ __device__ __forceinline__ float exact_i64_to_f32(int64_t v)
 }
 
 // ---------------------------------------------------------------------------
-// A1: cell assignment in FP64. X = rint((p - lo) * 2^F / w) (round half to even; an
-// integer below 2^52, stored exactly as a double per particle with stride x_stride, so
-// differences of two X are exact in binary64), cell = X >> F, global key = coff + cx + ncx (cy +
+// Fixed-point position of a coordinate: X = rint((p - lo) * 2^F / w) (round half to even; an
+// integer below 2^52). The assignment takes the cell X >> F from it and the pack the
+// relative coordinate; both compute it from the position (three operations) rather than
+// pass it through memory.
+__device__ __forceinline__ int64_t fixed_point(double p, double lo, double s)
+{
+    return static_cast<int64_t>(rint(__dmul_rn(__dsub_rn(p, lo), s)));
+}
+
+// A1: cell assignment in FP64: cell = X >> F, global key = coff + cx + ncx (cy +
 // ncy cz). Positions outside [lo, hi] (or NaN) raise the domain flag and are treated as
 // lo so every index stays in range. Each particle also takes a slot in its cell (the
 // cell's count before it), which places it in the sort by cell: runs of consecutive
@@ -34,8 +41,7 @@ __device__ __forceinline__ float exact_i64_to_f32(int64_t v)
 template <int DIM>
 __global__ void __launch_bounds__(256)
 k_assign(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int nsets, int ntot,
-         double* __restrict__ X, uint32_t* __restrict__ key, int* __restrict__ slot, int* __restrict__ cell_count,
-         int* __restrict__ err)
+         uint32_t* __restrict__ key, int* __restrict__ slot, int* __restrict__ cell_count, int* __restrict__ err)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= ntot) return;
@@ -51,10 +57,7 @@ k_assign(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
                 bad = true;
                 p = fr.lo[k];
             }
-            const double d = __dsub_rn(p, fr.lo[k]);
-            const double t = rint(__dmul_rn(d, fr.s));  // an integer below 2^52
-            X[static_cast<size_t>(i) * x_stride(DIM) + k] = t;
-            c[k] = static_cast<int64_t>(t) >> fr.F;
+            c[k] = fixed_point(p, fr.lo[k], fr.s) >> fr.F;
         }
         return static_cast<uint32_t>(sd.coff + c[0] + fr.nc[0] * (c[1] + fr.nc[1] * c[2]));
     };
@@ -422,20 +425,22 @@ k_radix_scatter(const uint32_t* __restrict__ kin, const int* __restrict__ vin,
 }
 
 // ---------------------------------------------------------------------------
-// A4: pack in sorted order. q_k = f16(f32(D_k) 2^(1-F)) with D_k = X_k - c_k 2^F - 2^(F-1),
-// the Eq. 6 relative coordinate in [-1, 1]; the fourth half holds c_x mod 2^16.
-// The FP64 baseline instead gets a sorted copy of the caller's positions.
+// A4: pack in sorted order. q_k = f32(D_k) 2^(1-F) with D_k = X_k - c_k 2^F - 2^(F-1), the
+// Eq. 6 relative coordinate in [-1, 1], in f32 (the passes that compute in FP16 round it to
+// FP16 as they load it), with the cell indices mod 2^10 per axis (the cells of a block's
+// candidate union lie fewer than 2^10 apart, so differences mod 2^10 recover the offsets).
+// Beside it the FP64 position and the particle index, one 32-byte record per particle: the
+// FP64 predicates and the distances of every mode read these, contiguous in sorted order.
 template <int DIM>
 __global__ void __launch_bounds__(256)
 k_pack(const SetDesc* __restrict__ sets, const int* __restrict__ coffs, int nsets, int ntot,
-       const uint32_t* __restrict__ skey, const int* __restrict__ perm, const double* __restrict__ X,
-       ushort4* __restrict__ q4, double* __restrict__ spos, float4* __restrict__ rq, int* __restrict__ inv,
-       uint32_t* __restrict__ skey_out, int* __restrict__ perm_out)
+       const uint32_t* __restrict__ skey, const int* __restrict__ perm, double* __restrict__ spos,
+       float4* __restrict__ rq, int* __restrict__ inv, uint32_t* __restrict__ skey_out, int* __restrict__ perm_out)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= ntot) return;
     const int o = perm[p];
-    if (inv) inv[o] = p;
+    inv[o] = p;
     // the incremental update places into a second pair of arrays: copied back here
     if (perm_out) {
         perm_out[p] = o;
@@ -443,29 +448,26 @@ k_pack(const SetDesc* __restrict__ sets, const int* __restrict__ coffs, int nset
     }
     auto pack = [&](const SetDesc& sd) {
         const Frame& fr = sd.fr;
-        if (spos) {
-#pragma unroll
-            for (int k = 0; k < DIM; ++k)
-                spos[static_cast<size_t>(p) * 4 + k] = sd.pos[static_cast<size_t>(o - sd.poff) * DIM + k];
-        }
-        uint16_t h[4] = {0, 0, 0, 0};
+        double x[3] = {0.0, 0.0, 0.0};
         float q32[3] = {0.0f, 0.0f, 0.0f};
         uint32_t cbits = 0;
         const float scale = __builtin_ldexpf(1.0f, 1 - fr.F);
 #pragma unroll
+        for (int k = 0; k < DIM; ++k) x[k] = sd.pos[static_cast<size_t>(o - sd.poff) * DIM + k];
+#pragma unroll
         for (int k = 0; k < DIM; ++k) {
-            const int64_t x = static_cast<int64_t>(X[static_cast<size_t>(o) * x_stride(DIM) + k]);
-            const int64_t c = x >> fr.F;
-            const int64_t D = x - (c << fr.F) - (int64_t(1) << (fr.F - 1));
+            // as the assignment: a position outside the box counts as lo
+            const double pk = (x[k] >= fr.lo[k] && x[k] <= fr.hi[k]) ? x[k] : fr.lo[k];
+            const int64_t X = fixed_point(pk, fr.lo[k], fr.s);
+            const int64_t c = X >> fr.F;
+            const int64_t D = X - (c << fr.F) - (int64_t(1) << (fr.F - 1));
             q32[k] = exact_i64_to_f32(D) * scale;  // exact power-of-two scaling
-            h[k] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(q32[k]));
-            if (k == 0) h[3] = static_cast<uint16_t>(c & 0xFFFF);
             cbits |= static_cast<uint32_t>(c & 1023) << (10 * k);
         }
-        q4[p] = make_ushort4(h[0], h[1], h[2], h[3]);
-        // FP32 mode: the coordinate in f32 and the cell indices mod 2^10 (a pair's cell
-        // offsets are -1, 0 or 1 per axis, which their differences mod 2^10 recover)
-        if (rq) rq[p] = make_float4(q32[0], q32[1], q32[2], __builtin_bit_cast(float, cbits));
+        double2* sp = reinterpret_cast<double2*>(spos + static_cast<size_t>(p) * 4);
+        sp[0] = make_double2(x[0], x[1]);
+        sp[1] = make_double2(x[2], __builtin_bit_cast(double, static_cast<int64_t>(o)));
+        rq[p] = make_float4(q32[0], q32[1], q32[2], __builtin_bit_cast(float, cbits));
     };
     // a wavefront inside one set reads the set's fields with scalar loads
     const int s = find_set(coffs, nsets, static_cast<int>(skey[p]));
@@ -485,8 +487,8 @@ k_pack(const SetDesc* __restrict__ sets, const int* __restrict__ coffs, int nset
 // migrants are re-binned: the sorted order is kept, stayers keep their relative order in
 // their cell, and each cell's migrants are appended after its stayers.
 
-// U1 (per particle, in the caller's order so positions, displacements and fixed-point
-// positions stream): move, recompute X and the cell. A displacement component that would
+// U1 (per particle, in the caller's order so positions and displacements stream): move,
+// recompute the cell. A displacement component that would
 // take the particle out of [lo, hi] is applied with its sign flipped (a reflection at the
 // box faces). A particle whose cell changed is a migrant: bit inv[i] of `mig` is set, it
 // counts out of its old cell and takes an arrival slot in its new one. Every particle's
@@ -494,8 +496,7 @@ k_pack(const SetDesc* __restrict__ sets, const int* __restrict__ coffs, int nset
 template <int DIM>
 __global__ void __launch_bounds__(256)
 k_upd_move(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int nsets, int ntot,
-           const uint32_t* __restrict__ skey, const int* __restrict__ inv, double* __restrict__ X,
-           uint32_t* __restrict__ knew, uint32_t* __restrict__ mig, int* __restrict__ leave,
+           const uint32_t* __restrict__ skey, const int* __restrict__ inv, uint32_t* __restrict__ knew, uint32_t* __restrict__ mig, int* __restrict__ leave,
            int* __restrict__ arrive, int* __restrict__ aslot, int* __restrict__ err)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -529,7 +530,6 @@ k_upd_move(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int 
             for (int k = 0; k < DIM; ++k) pos[static_cast<size_t>(li) * DIM + k] = p[k];
         }
         int64_t c[3] = {0, 0, 0};
-        double t[DIM];
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
             double pk = p[k];
@@ -537,11 +537,8 @@ k_upd_move(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int 
                 bad = true;
                 pk = lo[k];
             }
-            t[k] = rint(__dmul_rn(__dsub_rn(pk, lo[k]), scale));
-            c[k] = static_cast<int64_t>(t[k]) >> F;
+            c[k] = fixed_point(pk, lo[k], scale) >> F;
         }
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) X[static_cast<size_t>(i) * x_stride(DIM) + k] = t[k];
         return static_cast<uint32_t>(coff + c[0] + ncx * (c[1] + ncy * c[2]));
     };
     // a wavefront inside one set reads the set's fields with scalar loads
@@ -614,7 +611,7 @@ k_upd_place(int ntot, const uint32_t* __restrict__ skey, const int* __restrict__
 
 // ---------------------------------------------------------------------------
 // Work blocks, one wavefront per segment of 64 cells of a row of cells of a set: walking
-// the segment in x, a block is a run of at most fr.bmax consecutive sorted particles whose
+// the segment in x, a block is a run of at most kWave consecutive sorted particles whose
 // cells span at most fr.xwin cells; it starts where the previous one ended (so blocks are
 // full unless the span, the segment or the row ends them). A run of dense cells (the
 // dense-cell path's) is one block that the block kernels skip. The walk runs twice: the
@@ -636,7 +633,7 @@ k_row_blocks(const SetDesc* __restrict__ sets, const int* __restrict__ roffs, in
     const SetDesc& sd = sets[s];
     const int ncx = sd.fr.nc[0];
     const int span = sd.fr.xwin;
-    const int bmax = sd.fr.bmax;
+    constexpr int bmax = kWave;
     const int nseg = (ncx + kRowSegment - 1) / kRowSegment;
     const int rs = r - roffs[s];
     const int g0 = sd.coff + (rs / nseg) * ncx;
@@ -942,15 +939,15 @@ hipError_t launch_place(int ntot, const uint32_t* key, const int* slot, const in
     return hipGetLastError();
 }
 
-hipError_t launch_assign(const Launch& L, double* X, uint32_t* key, int* slot, int* cell_count, int* err,
+hipError_t launch_assign(const Launch& L, uint32_t* key, int* slot, int* cell_count, int* err,
                          hipStream_t st)
 {
     if (L.ntot == 0) return hipSuccess;
     const dim3 g((L.ntot + 255) / 256), b(256);
     if (L.dim == 2)
-        hipLaunchKernelGGL(k_assign<2>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, X, key, slot, cell_count, err);
+        hipLaunchKernelGGL(k_assign<2>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, key, slot, cell_count, err);
     else
-        hipLaunchKernelGGL(k_assign<3>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, X, key, slot, cell_count, err);
+        hipLaunchKernelGGL(k_assign<3>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, key, slot, cell_count, err);
     return hipGetLastError();
 }
 
@@ -996,30 +993,30 @@ hipError_t radix_sort_kv_dev(int n, const int* ndev, int keybits, uint32_t* k0, 
 
 size_t radix_table_entries(int n) { return static_cast<size_t>(radix_tiles(n)) << kRsMaxBits; }
 
-hipError_t launch_pack(const Launch& L, const uint32_t* skey, const int* perm, const double* X, ushort4* q4,
-                       double* spos, float4* rq, int* inv, hipStream_t st, uint32_t* skey_out, int* perm_out)
+hipError_t launch_pack(const Launch& L, const uint32_t* skey, const int* perm, double* spos, float4* rq, int* inv,
+                       hipStream_t st, uint32_t* skey_out, int* perm_out)
 {
     if (L.ntot == 0) return hipSuccess;
     const dim3 g((L.ntot + 255) / 256), b(256);
     if (L.dim == 2)
-        hipLaunchKernelGGL(k_pack<2>, g, b, 0, st, L.sets, L.coffs, L.nsets, L.ntot, skey, perm, X, q4, spos, rq, inv,
+        hipLaunchKernelGGL(k_pack<2>, g, b, 0, st, L.sets, L.coffs, L.nsets, L.ntot, skey, perm, spos, rq, inv,
                            skey_out, perm_out);
     else
-        hipLaunchKernelGGL(k_pack<3>, g, b, 0, st, L.sets, L.coffs, L.nsets, L.ntot, skey, perm, X, q4, spos, rq, inv,
+        hipLaunchKernelGGL(k_pack<3>, g, b, 0, st, L.sets, L.coffs, L.nsets, L.ntot, skey, perm, spos, rq, inv,
                            skey_out, perm_out);
     return hipGetLastError();
 }
 
-hipError_t launch_update_move(const Launch& L, const uint32_t* skey, const int* inv, double* X, const Update& u,
-                              int* err, hipStream_t st)
+hipError_t launch_update_move(const Launch& L, const uint32_t* skey, const int* inv, const Update& u, int* err,
+                              hipStream_t st)
 {
     if (L.ntot == 0) return hipSuccess;
     const dim3 g((L.ntot + 255) / 256), b(256);
     if (L.dim == 2)
-        hipLaunchKernelGGL(k_upd_move<2>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, skey, inv, X, u.knew, u.mig,
+        hipLaunchKernelGGL(k_upd_move<2>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, skey, inv, u.knew, u.mig,
                            u.leave, u.arrive, u.aslot, err);
     else
-        hipLaunchKernelGGL(k_upd_move<3>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, skey, inv, X, u.knew, u.mig,
+        hipLaunchKernelGGL(k_upd_move<3>, g, b, 0, st, L.sets, L.poffs, L.nsets, L.ntot, skey, inv, u.knew, u.mig,
                            u.leave, u.arrive, u.aslot, err);
     return hipGetLastError();
 }

@@ -43,10 +43,6 @@ struct DevBuf {
     T* as() const { return static_cast<T*>(p); }
 };
 
-// Modes that keep sorted FP64 positions (the FP64 test, and the FP32 mode's dense cells
-// and long rows).
-bool uses_spos(int mode) { return mode == NNPS_MODE_FP64_BASELINE || mode == NNPS_MODE_FP32_RCLL; }
-
 // Round a double to binary32 toward -inf (dir -1), nearest-even (0) or +inf (+1).
 float f32_dir(double x, int dir)
 {
@@ -134,7 +130,6 @@ nnps_status frame_of(const nnps_problem* p, Frame* fr, int block_target)
     fr->w = w;
     fr->s = s;
     fr->R2 = p->radius * p->radius;
-    fr->dist_scale = static_cast<float>(ldexp(w, -F));
     const double rho = p->radius / w;
     const double rho2 = rho * rho;
     const double band = ldexp(1.0, -7);
@@ -158,15 +153,20 @@ nnps_status frame_of(const nnps_problem* p, Frame* fr, int block_target)
         const double ucap = p->dim == 3 ? kUnion3 : kUnion2;
         xwin = std::min(xwin, static_cast<int>(0.85 * ucap / (rows * occ)) - 2);
     }
-    fr->xwin = std::max(1, std::min(kMaxXWin, xwin));
-    // targets per block: at most what keeps the block's CSR entries (targets times the
-    // expected neighbours, occupancy times the radius ball in cell units) at 85 % of the
-    // fill's entry limit
-    const double ball = p->dim == 3 ? 4.18879020478639 * rho * rho * rho : 3.14159265358979 * rho * rho;
-    const double nb = occ * ball;
-    const double fcap = p->dim == 3 ? kFlat3 : kFlat2;
-    const int bm = nb > 0.0 ? static_cast<int>(0.85 * fcap / nb) : kWave;
-    fr->bmax = std::max(8, std::min(kWave, bm));
+    fr->xwin = std::max(1, std::min(p->mode == NNPS_MODE_FP16_RCLL || p->mode == NNPS_MODE_FP32_RCLL ? kMfmaXWin : kMaxXWin, xwin));
+    // the fill's positions in quanta 2^-kq: neighbours (at most w apart) differ by fewer than
+    // 2^31 of them, and the whole box by fewer than 2^51. A difference of two then errs by at
+    // most one quantum per axis, 2^-23 of a distance of sqrt(3) 2^23 quanta (0.03 w at most
+    // unless the box has more than 2^20 cells along an axis), below which the fill recomputes
+    // in binary64; as it does for every pair of cells so wide that the quantum would leave
+    // FP32's range
+    double extent = w;
+    for (int k = 0; k < p->dim; ++k) extent = std::max(extent, p->hi[k] - p->lo[k]);
+    const int k31 = 30 - ilogb(w);
+    const int kq = std::max(-127, std::min({k31, 50 - ilogb(extent), 149}));
+    fr->inv_quantum = ldexp(1.0, kq);
+    fr->quantum = ldexpf(1.0f, -kq);
+    fr->near2 = kq <= k31 ? 3.0f * 0x1p46f : INFINITY;
     return NNPS_OK;
 }
 
@@ -282,8 +282,8 @@ struct nnps_cells {
     uint64_t buf_gen = 0;                 // bumps whenever a device buffer moves
     uint32_t* skey = nullptr;
     int* perm = nullptr;
-    DevBuf counts_s, rsort, bdesc;
-    DevBuf d_sets, d_offs, X, k0, k1, v0, v1, cell_count, cell_start, q4, spos, rq, boff, bstart, bset,
+    DevBuf counts_s, rsort, bdesc, branks;
+    DevBuf d_sets, d_offs, k0, k1, v0, v1, cell_count, cell_start, spos, rq, boff, bstart, bset,
         counts, table, partial, stats, blk_stats, cbits, err, heavy, nheavy, rowg, nnz, sink;
     // dense-cell path (see DenseBuild)
     bool dense = false;         // the tuning allows the dense-cell path
@@ -367,19 +367,6 @@ size_t dense_bits_bound(const nnps_cells* c)
     return static_cast<size_t>(mib) << 20;
 }
 
-// Sorted FP64 positions: always in the FP64 and FP32 modes; in the FP16 modes while the
-// dense-cell path runs (its fill stages the candidates' positions from them, contiguous in
-// sorted order, instead of gathering them by original index). The pack and the search
-// passes of one step see the same answer unless a synchronising call in between finds
-// that the dense cells are gone; the dense fill then gathers from the caller's positions.
-double* spos_of(const nnps_cells* c)
-{
-    if (uses_spos(c->mode)) return c->spos.as<double>();
-    if (c->dense && c->dense_seen != 0 && c->spos.p && c->spos.cap >= static_cast<size_t>(c->ntot) * 4 * sizeof(double))
-        return c->spos.as<double>();
-    return nullptr;
-}
-
 Launch launch_of(const nnps_cells* c)
 {
     Launch L{};
@@ -403,10 +390,8 @@ SearchArgs args_of(const nnps_cells* c)
     a.skey = c->skey;
     a.perm = c->perm;
     a.cell_start = c->cell_start.as<int>();
-    a.q4 = c->q4.as<ushort4>();
-    a.spos = spos_of(c);
-    a.rq = c->mode == NNPS_MODE_FP32_RCLL ? c->rq.as<float4>() : nullptr;
-    a.X = c->X.as<double>();
+    a.spos = c->spos.as<double>();
+    a.rq = c->rq.as<float4>();
     a.bstart = c->bstart.as<int>();
     a.bset = c->bset.as<int>();
     a.nblk = c->boff.as<int>() + c->nrows_tot;
@@ -414,6 +399,7 @@ SearchArgs args_of(const nnps_cells* c)
     a.counts_s = c->counts_s.as<int>();
     a.rsort = c->rsort.as<int64_t>();
     a.bdesc = c->bdesc.as<int>();
+    a.branks = c->branks.as<uint16_t>();
     a.heavy = c->heavy.as<int>();
     a.nheavy = c->nheavy.as<int>();
     a.stats = c->stats.as<unsigned long long>();
@@ -533,7 +519,7 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         const int64_t nseg = nrows * row_segments(fr.nc[0]);
         // blocks: full ones, at most one per span of xwin cells and one per row segment
         // ending early, and around each run of dense cells one marker plus one cut short
-        int64_t b = fr.n / fr.bmax + nrows * ((fr.nc[0] + fr.xwin - 1) / fr.xwin) + nseg;
+        int64_t b = fr.n / kWave + nrows * ((fr.nc[0] + fr.xwin - 1) / fr.xwin) + nseg;
         if (c->dense && c->dense_seen != 0)  // the build will use the dense-cell path
             b += 2 * std::min<int64_t>(fr.ncell, stencil * fr.n / (static_cast<int64_t>(c->dthresh) + 1));
         nblk_bound += std::min<int64_t>(fr.n, b);
@@ -560,7 +546,6 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     const int64_t scan_m = std::max<int64_t>({static_cast<int64_t>(nn) + 1, static_cast<int64_t>(nc) + 1,
                                               static_cast<int64_t>(table_n),
                                               static_cast<int64_t>(c->nrows_tot) + 1});
-    const bool base = uses_spos(c->mode);
     const int cw = c->dim == 3 ? kCandWords3 : kCandWords2;
     struct Need {
         DevBuf* b;
@@ -568,15 +553,14 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     } need[] = {
         {&c->d_sets, sizeof(SetDesc) * nsets},
         {&c->d_offs, sizeof(int) * 3 * (nsets + 1)},
-        {&c->X, nn * x_stride(c->dim) * sizeof(int64_t)},
         {&c->k0, nn * 4}, {&c->k1, nn * 4}, {&c->v0, nn * 4}, {&c->v1, nn * 4},
         {&c->cell_count, (nc + 1) * 4}, {&c->cell_start, (nc + 1) * 4},
-        {&c->q4, nn * sizeof(ushort4)},
-        {&c->spos, (base || (c->dense && c->dense_seen != 0)) ? nn * 4 * sizeof(double) : 0},
-        {&c->rq, c->mode == NNPS_MODE_FP32_RCLL ? nn * sizeof(float4) : 0},
+        {&c->spos, nn * 4 * sizeof(double)},
+        {&c->rq, nn * sizeof(float4)},
         {&c->boff, (static_cast<size_t>(c->nrows_tot) + 1) * 4}, {&c->bstart, (nn + 2) * 4}, {&c->bset, (nn + 1) * 4},
         {&c->counts, nn * 4}, {&c->counts_s, nn * 4}, {&c->rsort, nn * 8},
         {&c->bdesc, static_cast<size_t>(std::max(c->nblk_max, 1) + kXcdPad) * kBlockDescInts * 4},
+        {&c->branks, static_cast<size_t>(std::max(c->nblk_max, 1)) * (c->dim == 3 ? kUnion3 : kUnion2) * 2},
         {&c->table, table_n * 4},
         {&c->partial, static_cast<size_t>(scan_partials_needed(scan_m) + 1) * 8},
         {&c->stats, kStCount * 8},
@@ -638,7 +622,7 @@ nnps_status enqueue_update(nnps_cells* c, hipStream_t s)
     const int64_t zero = 2 * (static_cast<int64_t>(c->ncell_tot) + 1) + (c->ntot + 31) / 32;
     HIP_TRY(launch_fill2_i32(u.leave, zero, c->err.as<int>(), 1, 0, s));
     tm.begin(NNPS_PHASE_ASSIGN, s);
-    HIP_TRY(launch_update_move(L, c->skey, c->inv.as<int>(), c->X.as<double>(), u, c->err.as<int>(), s));
+    HIP_TRY(launch_update_move(L, c->skey, c->inv.as<int>(), u, c->err.as<int>(), s));
     tm.end(NNPS_PHASE_ASSIGN, s);
     tm.begin(NNPS_PHASE_CELLSCAN, s);
     HIP_TRY(launch_update_cells(L, c->cell_start.as<int>(), c->cell_count.as<int>(), u, c->partial.as<int64_t>(), s));
@@ -647,10 +631,8 @@ nnps_status enqueue_update(nnps_cells* c, hipStream_t s)
     HIP_TRY(launch_update_place(L, c->skey, c->perm, c->cell_start.as<int>(), u, s));
     tm.end(NNPS_PHASE_SORT, s);
     tm.begin(NNPS_PHASE_PACK, s);
-    HIP_TRY(launch_pack(L, u.skey2, u.perm2, c->X.as<double>(), c->q4.as<ushort4>(),
-                        spos_of(c),
-                        c->mode == NNPS_MODE_FP32_RCLL ? c->rq.as<float4>() : nullptr,
-                        c->inv.as<int>(), s, c->skey, c->perm));
+    HIP_TRY(launch_pack(L, u.skey2, u.perm2, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), s, c->skey,
+                        c->perm));
     tm.end(NNPS_PHASE_PACK, s);
     return enqueue_build_tail(c, s);
 }
@@ -662,8 +644,7 @@ nnps_status enqueue_build(nnps_cells* c, hipStream_t s)
     PhaseTimer& tm = c->timer;
     HIP_TRY(launch_fill2_i32(c->cell_count.as<int>(), static_cast<int64_t>(c->ncell_tot) + 1, c->err.as<int>(), 1, 0, s));
     tm.begin(NNPS_PHASE_ASSIGN, s);
-    HIP_TRY(launch_assign(L, c->X.as<double>(), c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_count.as<int>(),
-                          c->err.as<int>(), s));
+    HIP_TRY(launch_assign(L, c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_count.as<int>(), c->err.as<int>(), s));
     tm.end(NNPS_PHASE_ASSIGN, s);
     tm.begin(NNPS_PHASE_CELLSCAN, s);
     HIP_TRY(launch_scan_i32_i32(c->cell_count.as<int>(), c->ncell_tot, c->cell_start.as<int>(),
@@ -678,10 +659,7 @@ nnps_status enqueue_build(nnps_cells* c, hipStream_t s)
     c->skey = kf;
     c->perm = vf;
     tm.begin(NNPS_PHASE_PACK, s);
-    HIP_TRY(launch_pack(L, c->skey, c->perm, c->X.as<double>(), c->q4.as<ushort4>(),
-                        spos_of(c),
-                        c->mode == NNPS_MODE_FP32_RCLL ? c->rq.as<float4>() : nullptr,
-                        c->inv.as<int>(), s));
+    HIP_TRY(launch_pack(L, c->skey, c->perm, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), s));
     tm.end(NNPS_PHASE_PACK, s);
     return enqueue_build_tail(c, s);
 }
@@ -941,13 +919,13 @@ void nnps_cells_destroy(nnps_cells* c)
     if (!c) return;
     DeviceGuard g(c->ctx->device);
     if (c->upload_pending) (void)hipEventSynchronize(c->upload_done);
-    DevBuf* all[] = {&c->d_sets, &c->d_offs, &c->X, &c->k0, &c->k1, &c->v0, &c->v1, &c->cell_count,
-                     &c->cell_start, &c->q4, &c->spos, &c->rq, &c->boff, &c->bstart, &c->bset, &c->counts,
+    DevBuf* all[] = {&c->d_sets, &c->d_offs, &c->k0, &c->k1, &c->v0, &c->v1, &c->cell_count,
+                     &c->cell_start, &c->spos, &c->rq, &c->boff, &c->bstart, &c->bset, &c->counts,
                      &c->table, &c->partial, &c->stats, &c->blk_stats, &c->cbits, &c->err, &c->heavy,
                      &c->nheavy, &c->rowg, &c->nnz, &c->sink, &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
                      &c->ucell, &c->dn, &c->ecnt, &c->epos, &c->uk0, &c->uk1, &c->uv0, &c->uv1, &c->inv,
                      &c->ucount, &c->dstats, &c->dseen, &c->uleave, &c->ucs_old,
-                     &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc};
+                     &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc, &c->branks, &c->dbn, &c->dboff, &c->dbits};
     for (DevBuf* b : all) b->release();
     c->timer.release();
     c->graph.reset();
@@ -1450,7 +1428,7 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
     // the sums of the last count pass's per-block (and dense-path) statistics; none
     // before a count
     HIP_TRY(launch_fill_i32(c->stats.as<int>(), 2 * kStCount, 0, s));
-    if (c->counted) HIP_TRY(launch_stats(args_of(c), s));
+    if (c->counted) HIP_TRY(launch_stats(args_of(c), c->nblk_max, s));
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(st, c->stats.p, sizeof(st), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(&err, c->err.p, 4, hipMemcpyDeviceToHost));

@@ -10,22 +10,20 @@ namespace nnps {
 constexpr int kWave = 64;
 // Candidate positions staged in LDS per chunk in the count pass (even).
 constexpr int kStage = 512;
-// Fill pass: largest candidate union of a block (staged whole and ranked by original
-// index) and largest number of CSR entries of a block; blocks above either limit send
-// their rows to the long-row path.
+// Largest candidate union of a block (ranked by original index in the count pass, staged
+// whole in the fill); blocks above it send their rows to the long-row path.
 constexpr int kUnion2 = 512;
 constexpr int kUnion3 = 1024;
-constexpr int kFlat2 = 2048;
-constexpr int kFlat3 = 4608;
 // Accepted-candidate bits the count pass keeps per target, indexed by the candidate's
 // position in the block's union (32 positions per word), stored word-major so a
 // wavefront's stores coalesce. Blocks with a larger union take the long-row path.
 constexpr int kCandWords2 = kUnion2 / 32;
 constexpr int kCandWords3 = kUnion3 / 32;
-// Fixed-point positions are stored per particle, padded to a power of two of int64.
-__host__ __device__ constexpr int x_stride(int dim) { return dim == 3 ? 4 : 2; }
 // Largest x-span (cells) of a work block; keeps staged cell offsets exact in FP16.
 constexpr int kMaxXWin = 256;
+// The same where the matrix cores test in FP16 or FP32: the recheck band there grows with the square of the
+// span (2^-18 of twice the squared half widths), to about 0.01 squared cell widths at 48.
+constexpr int kMfmaXWin = 48;
 // Dense-cell path: candidates staged per chunk, targets per work unit (a workgroup of
 // four wavefronts, 64 targets each) and the default thresholds.
 constexpr int kDenseChunk = 1024;
@@ -80,11 +78,13 @@ struct Frame {
     double w;           // cell width
     double s;           // 2^F / w
     double R2;          // fl(R*R)
-    float dist_scale;   // (float)(w * 2^-F)
     int xwin;           // largest x-span of a work block, in cells
-    int bmax;           // most targets of a work block (<= 64)
     uint16_t t_lo, t_hi, t_mid;  // FP16 thresholds on r2 = 4|delta|^2 (bit patterns)
     float t32_lo, t32_hi, t32_mid;  // FP32 thresholds on the same r2
+    // FP32 distances of the fill: positions in units of quantum = 2^-k, a power of two; pairs
+    // nearer than near2 (squared, in quanta) are taken in binary64
+    double inv_quantum;
+    float quantum, near2;
 };
 
 // One particle set of a launch. All sets of a launch share one global particle index

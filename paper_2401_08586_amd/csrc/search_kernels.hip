@@ -1,14 +1,13 @@
-// Neighbour search over the sorted cell structure: the 3^d-cell stencil test in
-// packed FP16 (relative coordinates, Eq. 6-7 with the factor 1/2 Eq. 7 drops), the
-// FP64 guard-band recheck, the count pass and the fill pass with per-row ascending
-// order and wave-cooperative CSR writes; plus the plain FP64 cell-list baseline.
+// Neighbour search over the sorted cell structure: the 3^d-cell stencil test (relative
+// coordinates, Eq. 6-7 with the factor 1/2 Eq. 7 drops) on the matrix cores, with a binary64
+// recheck near the cutoff, the count pass and the fill pass with per-row ascending order and
+// wave-cooperative CSR writes; the dense-cell and long-row paths; the statistics.
 //
-// Work decomposition: a block is one wavefront of up to 64 consecutive sorted targets
-// inside one (y, z) row of cells. Cells along x are contiguous in sorted order, so a
-// target's candidates are 3^(d-1) contiguous runs ("row segments"), one per (dy, dz),
-// each covering cells x-1..x+1. The block stages the union of its row segments in LDS
-// (chunks of kStage positions) as pair records: two candidates' x, y, z and 2(c_x - base)
-// per 16 bytes, so one packed-FP16 instruction tests two candidates.
+// Work decomposition: a block is up to 64 consecutive sorted targets inside one (y, z) row of
+// cells. Cells along x are contiguous in sorted order, so a block's candidates are 3^(d-1)
+// contiguous runs ("row segments"), one per (dy, dz): its union.
+#include <algorithm>
+
 #include "build_kernels.h"
 
 namespace nnps {
@@ -35,53 +34,82 @@ __device__ __forceinline__ double r2_fp64(const double* pi, const double* pj)
     return r2;
 }
 
+// The same against the particle at sorted position j.
 template <int DIM>
-__device__ __forceinline__ bool recheck(const double* __restrict__ pos, const double* pi, int oj,
-                                        double R2)
+__device__ __forceinline__ bool recheck_sorted(const double* __restrict__ spos, const double* pi, int j, double R2)
 {
-    double pj[3];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) pj[k] = pos[static_cast<size_t>(oj) * DIM + k];
-    return r2_fp64<DIM>(pi, pj) <= R2;
+    return r2_fp64<DIM>(pi, spos + static_cast<size_t>(j) * 4) <= R2;
 }
 
-// FP32 distance from the fixed-point positions: the displacement of two exact integers
-// below 2^52 is exact in binary64 and is rounded once to FP32.
+// FP32 distance from binary64 positions: the displacement in quanta (a power of two, so no
+// rounding, and no overflow of the squares), rounded once to FP32 per axis.
 template <int DIM>
-__device__ __forceinline__ float dist_fixed(const double* __restrict__ X, int oi, int oj, float scale)
+__device__ __forceinline__ float dist_near(const double* pi, const double* pj, double inv_quantum, float quantum)
 {
     float s2 = 0.0f;
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
-        const double d = X[static_cast<size_t>(oj) * x_stride(DIM) + k] - X[static_cast<size_t>(oi) * x_stride(DIM) + k];
-        const float f = static_cast<float>(d);
+        const float f = static_cast<float>((pj[k] - pi[k]) * inv_quantum);
         s2 = s2 + f * f;
     }
-    return __builtin_amdgcn_sqrtf(s2) * scale;  // <= 1 ulp; s2 >= 1 or 0
+    return __builtin_amdgcn_sqrtf(s2) * quantum;  // <= 1 ulp, then exact
+}
+
+// A coordinate in quanta (Frame::quantum), the low 32 bits: rounded to an integer in the low
+// bits of 1.5 2^52 + x.
+__device__ __forceinline__ int in_quanta(double x, double lo, double inv_quantum)
+{
+    const double q = __dadd_rn(__dmul_rn(__dsub_rn(x, lo), inv_quantum), 0x1.8p52);
+    return static_cast<int>(static_cast<uint32_t>(__builtin_bit_cast(uint64_t, q)));
+}
+
+// Squared distance in quanta of two positions in quanta, neighbours (fewer than 2^31 apart):
+// the difference mod 2^32 is exact, and is rounded once to FP32.
+template <int DIM>
+__device__ __forceinline__ float quanta2(const int4& i, const int4& j)
+{
+    auto diff = [](int x, int y) {
+        return static_cast<float>(static_cast<int>(static_cast<uint32_t>(x) - static_cast<uint32_t>(y)));
+    };
+    const float dx = diff(j.x, i.x), dy = diff(j.y, i.y);
+    float s2 = dx * dx + dy * dy;
+    if (DIM == 3) {
+        const float dz = diff(j.z, i.z);
+        s2 = s2 + dz * dz;
+    }
+    return s2;
 }
 
 template <int DIM>
-__device__ __forceinline__ float dist_fp64(const double* __restrict__ pos, int oi, int oj)
+__device__ __forceinline__ float dist_fp64(const double* pi, const double* pj)
 {
-    double pi[3], pj[3];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-        pi[k] = pos[static_cast<size_t>(oi) * DIM + k];
-        pj[k] = pos[static_cast<size_t>(oj) * DIM + k];
-    }
     return static_cast<float>(__dsqrt_rn(r2_fp64<DIM>(pi, pj)));
 }
 
+// Data-parallel-primitive step: lane i receives v of the lane that `CTRL` names, or `old`
+// where there is none (rows of 16 lanes outside `ROWS` keep `old`).
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp(int old, int v)
+{
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xF, false);
+}
+// Folds v over the wavefront's lanes (all active) in lane order with op and its identity:
+// lane i ends with the fold of lanes 0..i, in six steps that use no LDS.
+template <typename Op>
+__device__ __forceinline__ int wave_fold_i32(int v, int identity, Op&& op)
+{
+    v = op(v, dpp<0x111>(identity, v));       // row_shr:1
+    v = op(v, dpp<0x112>(identity, v));       // row_shr:2
+    v = op(v, dpp<0x114>(identity, v));       // row_shr:4
+    v = op(v, dpp<0x118>(identity, v));       // row_shr:8
+    v = op(v, dpp<0x142, 0xA>(identity, v));  // row_bcast:15 into rows 1 and 3
+    v = op(v, dpp<0x143, 0xC>(identity, v));  // row_bcast:31 into rows 2 and 3
+    return v;
+}
 __device__ __forceinline__ int wave_excl_scan_i32(int v, int* total)
 {
-    const int lane = threadIdx.x & 63;
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += u;
-    }
-    *total = __shfl(inc, 63, 64);
+    const int inc = wave_fold_i32(v, 0, [](int x, int y) { return x + y; });
+    *total = __builtin_amdgcn_readlane(inc, 63);
     return inc - v;
 }
 
@@ -183,8 +211,8 @@ struct Geom {
 // indices and the NSEG segment union offsets.
 constexpr int kDescInts = kBlockDescInts;
 
-template <int DIM>
-__device__ __forceinline__ void write_desc(const SearchArgs& a, const Geom<DIM>& g, int b)
+template <int DIM, typename G>
+__device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int b)
 {
     const int lane = threadIdx.x & 63;
     int v = 0;
@@ -206,46 +234,14 @@ __device__ __forceinline__ void write_desc_dense(const SearchArgs& a, int b)
     if ((threadIdx.x & 63) == 4) a.bdesc[static_cast<size_t>(b) * kDescInts + 4] = 1;
 }
 
-// The fill's view of a block, from its descriptor (lane = target).
-template <int DIM>
-struct FillGeom {
-    static constexpr int NSEG = Geom<DIM>::NSEG;
-    static constexpr int SELF = Geom<DIM>::SELF;
-    int p0, p1, p, U, pself;
-    bool active;
-    int seg_g0[NSEG], seg_base[NSEG];
-    const SetDesc* sd;
-    __device__ __forceinline__ void init(const SearchArgs& a, const int* __restrict__ d)
-    {
-        const int lane = threadIdx.x & 63;
-        p0 = d[0];
-        p1 = d[1];
-        sd = a.L.sets + d[2];
-        U = d[3];
-#pragma unroll
-        for (int r = 0; r < NSEG; ++r) {
-            seg_g0[r] = d[5 + r];
-            seg_base[r] = d[5 + NSEG + r];
-        }
-        p = p0 + lane;
-        active = p < p1;
-        pself = seg_base[SELF] + (p - seg_g0[SELF]);
-    }
-    __device__ __forceinline__ int global_of_any(int posl) const
-    {
-        int gi = posl - seg_base[0] + seg_g0[0];
-#pragma unroll
-        for (int k = 1; k < NSEG; ++k)
-            if (posl >= seg_base[k]) gi = posl - seg_base[k] + seg_g0[k];
-        return gi;
-    }
-};
-
 // The fields of a set a kernel uses in its loops, read once into registers. Read through
 // the set table instead, they would be loaded again after every store (the compiler
 // cannot tell the stores from the table), each time waiting on memory. The outputs are
 // global-address-space pointers, so their stores are plain global stores.
 #define NNPS_GLOBAL __attribute__((address_space(1)))
+// Memory that no kernel of the launch writes: uniform reads become scalar loads wherever
+// they stand.
+#define NNPS_CONST __attribute__((address_space(4)))
 struct SetView {
     const NNPS_GLOBAL double* pos;
     const NNPS_GLOBAL int64_t* row_ptr;
@@ -294,19 +290,24 @@ __device__ __forceinline__ bool dense_block(const SearchArgs& a, int b)
     return a.wdense && a.wdense[a.skey[a.bstart[b]]];
 }
 
-// Stage logical positions [cb, ce) as pair records; with ORIG also the original indices.
-template <int DIM, bool ORIG>
-__device__ __forceinline__ void stage(const SearchArgs& a, const Geom<DIM>& g, int cb, int ce,
-                                      uint4* srec, int* sorig)
+// A particle's FP16 relative coordinates (Eq. 6) from its f32 record: x, y, z, and its cell
+// index along x mod 2^10.
+__device__ __forceinline__ ushort4 q16_of(const float4& v)
+{
+    auto h = [](float f) { return __builtin_bit_cast(uint16_t, static_cast<_Float16>(f)); };
+    return make_ushort4(h(v.x), h(v.y), h(v.z), static_cast<uint16_t>(__builtin_bit_cast(uint32_t, v.w) & 1023u));
+}
+
+// Stage logical positions [cb, ce) as pair records.
+template <int DIM>
+__device__ __forceinline__ void stage(const SearchArgs& a, const Geom<DIM>& g, int cb, int ce, uint4* srec)
 {
     const int lane = threadIdx.x & 63;
     const int m0 = cb >> 1, m1 = (ce + 1) >> 1;
-    const uint16_t base16 = static_cast<uint16_t>(g.sx0 & 0xFFFF);
     // a chunk is at most kStage / 128 records per lane: every gather is issued before
     // the first record is built
     constexpr int RPL = kStage / 128;
     ushort4 v[RPL][2];
-    int o[RPL][2];
 #pragma unroll
     for (int i = 0; i < RPL; ++i) {
         const int m = m0 + lane + 64 * i;
@@ -314,11 +315,9 @@ __device__ __forceinline__ void stage(const SearchArgs& a, const Geom<DIM>& g, i
         for (int h = 0; h < 2; ++h) {
             const int posl = 2 * m + h;
             v[i][h] = make_ushort4(0, 0, 0, 0);
-            o[i][h] = 0;
             if (m < m1 && posl < ce) {
                 const int gi = g.global_of_any(posl);
-                v[i][h] = a.q4[gi];
-                if (ORIG) o[i][h] = a.perm[gi];
+                v[i][h] = q16_of(a.rq[gi]);
             }
         }
     }
@@ -331,14 +330,14 @@ __device__ __forceinline__ void stage(const SearchArgs& a, const Geom<DIM>& g, i
         for (int h = 0; h < 2; ++h) {
             const int posl = 2 * m + h;
             if (posl < ce) {
-                const uint16_t rel = static_cast<uint16_t>(v[i][h].w - base16);
-                const _Float16 cx2 = static_cast<_Float16>(2 * static_cast<int>(rel));
+                // the union spans fewer than 2^10 cells in x
+                const int rel = (static_cast<int>(v[i][h].w) - g.sx0) & 1023;
+                const _Float16 cx2 = static_cast<_Float16>(2 * rel);
                 const uint32_t sh = 16u * h;
                 w0 |= static_cast<uint32_t>(v[i][h].x) << sh;
                 w1 |= static_cast<uint32_t>(v[i][h].y) << sh;
                 w2 |= static_cast<uint32_t>(v[i][h].z) << sh;
                 w3 |= static_cast<uint32_t>(__builtin_bit_cast(uint16_t, cx2)) << sh;
-                if (ORIG) sorig[posl - cb] = o[i][h];
             }
         }
         srec[m - m0] = make_uint4(w0, w1, w2, w3);
@@ -381,39 +380,26 @@ __device__ __forceinline__ uint32_t r2_pair(const Target16<DIM>& t, h2 ay, h2 az
 }
 
 struct Tally {
-    int cnt = 0;
     unsigned long long cand = 0, band = 0, fpos = 0, fneg = 0, odis = 0;
 };
 
-// Classify one candidate (FP16 bits r2h at union position posl);
-// returns whether j is a neighbour. MODE 0: three-way test with FP64 recheck in the
-// band; MODE 2: FP64 decides every candidate.
+// Tallies one candidate (FP16 bits r2h at union position posl). MODE 0: band pairs against
+// the FP64 predicate; MODE 2: every candidate.
 template <int DIM, int MODE>
-__device__ __forceinline__ bool classify(const SearchArgs& a, const Geom<DIM>& g, const double* pi,
-                                         int posl, uint32_t r2h, Tally& t, const int* sorig,
-                                         int cb, int* oj_out)
+__device__ __forceinline__ void classify(const SearchArgs& a, const Geom<DIM>& g, const double* pi, int posl,
+                                         uint32_t r2h, Tally& t)
 {
     const Frame& fr = g.fr;
-    if (MODE == 2) t.cand++;  // MODE 0 counts candidates from the lane's ranges
     const bool in16 = r2h < fr.t_lo;
     const bool band = !in16 && r2h <= fr.t_hi;
-    bool nb;
-    int oj = -1;
     if (MODE == 2 || band) {
-        oj = sorig ? sorig[posl - cb] : a.perm[g.global_of_any(posl)];
-        const bool truth = recheck<DIM>(g.sd->pos, pi, oj - g.sd->poff, fr.R2);
+        const bool truth = recheck_sorted<DIM>(a.spos, pi, g.global_of_any(posl), fr.R2);
         const bool naive = r2h <= fr.t_mid;
         t.band += band;
         t.fpos += naive && !truth;
         t.fneg += !naive && truth;
         if (MODE == 2) t.odis += !band && (in16 != truth);
-        nb = truth;
-    } else {
-        nb = in16;
     }
-    if (nb && oj < 0 && sorig) oj = sorig[posl - cb];
-    *oj_out = oj;
-    return nb;
 }
 
 // ---------------------------------------------------------------------------
@@ -460,211 +446,67 @@ __device__ __forceinline__ uint32_t span8(int a, int b)
 constexpr uint32_t kInvLo = 0x7C00u, kInvHi = 0x7C000000u;
 constexpr int kGroup = 8;  // pair records per group in the FP16 count loop
 
-// Per-lane queue of band pairs (logical position and FP16 r2 bits), held in registers
-// and rechecked after the loop so the FP64 work runs with the lanes converged. Band
-// pairs are rare (about two per target in 3D); a full queue makes the caller recheck
-// on the spot.
-struct BandQueue {
-    static constexpr int kCap = 4;
-    int p0 = 0, p1 = 0, p2 = 0, p3 = 0;
-    uint32_t r0 = 0, r1 = 0, r2 = 0, r3 = 0;
-    int n = 0;
-    // a shift register, so no entry is ever addressed by a runtime index
-    __device__ __forceinline__ bool push(int posl, uint32_t r2h)
-    {
-        if (n >= kCap) return false;
-        p3 = p2; p2 = p1; p1 = p0; p0 = posl;
-        r3 = r2; r2 = r1; r1 = r0; r0 = r2h;
-        ++n;
-        return true;
-    }
-    template <typename F>
-    __device__ __forceinline__ void drain(F&& f) const
-    {
-        if (n > 0) f(p0, r0);
-        if (n > 1) f(p1, r1);
-        if (n > 2) f(p2, r2);
-        if (n > 3) f(p3, r3);
-    }
-};
-
-// Per-lane queue of groups holding band candidates: the group's row segment and first
-// pair (r << 27 | pair) and its 16 band bits in position order; a shift register in
-// registers, drained once per staged chunk.
-struct BandGroups {
-    static constexpr int kCap = 4;
-    uint32_t a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-    uint32_t b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-    int n = 0;
-    __device__ __forceinline__ bool push(uint32_t where, uint32_t bits)
-    {
-        if (n >= kCap) return false;
-        a3 = a2; a2 = a1; a1 = a0; a0 = where;
-        b3 = b2; b2 = b1; b1 = b0; b0 = bits;
-        ++n;
-        return true;
-    }
-    template <typename F>
-    __device__ __forceinline__ void drain(F&& f)
-    {
-        if (n > 0) f(a0, b0);
-        if (n > 1) f(a1, b1);
-        if (n > 2) f(a2, b2);
-        if (n > 3) f(a3, b3);
-        n = 0;
-    }
-};
-
-// Visit the pair records covering logical positions [lo, hi) of one row segment:
-// the first and last records may hold a position outside the range, which is masked.
-template <typename F>
-__device__ __forceinline__ void for_pairs(int lo, int hi, F&& body)
+// ---------------------------------------------------------------------------
+// Statistics of the last count pass, made when they are asked for (the count pass decides on
+// the matrix cores and tallies nothing): one wavefront per block, lane = target, over the
+// target's own stencil ranges, from the structure's arrays only. Each writes its block's five
+// sums.
+template <int DIM>
+__device__ __forceinline__ void write_stats(const SearchArgs& a, const Geom<DIM>& g, int b, Tally& t)
 {
-    int m = lo >> 1;
-    const int mend = (hi + 1) >> 1;
-    if (m < mend) {
-        const uint32_t inv = ((lo & 1) ? kInvLo : 0u) | ((2 * m + 1 >= hi) ? kInvHi : 0u);
-        body(m, inv);
-        ++m;
+    if (g.active) {  // candidates: the lane's ranges minus itself
+        int total = 0;
+#pragma unroll
+        for (int r = 0; r < Geom<DIM>::NSEG; ++r) total += g.lb[r] - g.la[r];
+        t.cand += total - 1;
     }
-    const int mlast = (hi & 1) ? mend - 1 : mend;
-    for (; m < mlast; ++m) body(m, 0u);
-    if (m < mend) body(m, kInvHi);
+    unsigned long long v[5] = {t.cand, t.band, t.fpos, t.fneg, t.odis};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const unsigned long long sum = wave_sum_u64(v[k]);
+        if ((threadIdx.x & 63) == 0) a.blk_stats[static_cast<size_t>(b) * 5 + k] = sum;
+    }
 }
 
-// ---------------------------------------------------------------------------
-// Per-lane record of accepted candidates, one bit per candidate in the lane's own
-// candidate order (row segment by row segment). Kept in LDS during the count pass and
-// written out word-major (cbits[w * n + p]) so the fill pass never repeats the test.
-template <int DIM>
-struct CandBits {
-    static constexpr int CW = DIM == 3 ? kCandWords3 : kCandWords2;
-    static constexpr int NSEG = Geom<DIM>::NSEG;
-    uint32_t* w;
-    int total;  // the lane's candidates (its own stencil ranges)
-    int nw;     // words of the block's union
-    bool keep;
-    // Bits are indexed by union position; the block's tables (CW + 1 words per lane, the
-    // last one padding) are cleared by the whole wavefront.
-    __device__ __forceinline__ void init(const Geom<DIM>& g, uint32_t* lds)
-    {
-        const int lane = threadIdx.x & 63;
-        w = lds + lane * (CW + 1);
-        total = 0;
-#pragma unroll
-        for (int r = 0; r < NSEG; ++r) total += g.lb[r] - g.la[r];
-        keep = g.active && g.U <= 32 * CW;
-        nw = (g.U + 31) >> 5;
-        static_assert((64 * (CW + 1)) % 4 == 0, "the tables clear as 16-byte words");
-        uint4* z = reinterpret_cast<uint4*>(lds);
-        for (int k = lane; k < 64 * (CW + 1) / 4; k += 64) z[k] = make_uint4(0, 0, 0, 0);
-    }
-    __device__ __forceinline__ void set(int posl)
-    {
-        if (keep) atomicOr(&w[posl >> 5], 1u << (posl & 31));
-    }
-    __device__ __forceinline__ void clear(int posl)
-    {
-        if (keep) atomicAnd(&w[posl >> 5], ~(1u << (posl & 31)));
-    }
-    // Bits of up to 4 consecutive positions starting at posl (bit k = position posl + k),
-    // with no branch on the bits: two unconditional ORs, the second into the next word
-    // (the padding word after the union's last one).
-    __device__ __forceinline__ void put(int posl, uint32_t bits)
-    {
-        if (!keep) return;
-        const int wd = posl >> 5, sh = posl & 31;
-        atomicOr(&w[wd], bits << sh);
-        atomicOr(&w[wd + 1], sh ? bits >> (32 - sh) : 0u);
-    }
-    // Bits of 16 consecutive positions starting at posl (bit k = position posl + k).
-    __device__ __forceinline__ void put16(int posl, uint32_t bits)
-    {
-        if (!keep) return;
-        const int wd = posl >> 5, sh = posl & 31;
-        atomicOr(&w[wd], bits << sh);
-        atomicOr(&w[wd + 1], sh ? bits >> (32 - sh) : 0u);
-    }
-    __device__ __forceinline__ void store(const SearchArgs& a, int p) const
-    {
-        if (!keep) return;
-        for (int k = 0; k < nw; ++k) a.cbits[static_cast<size_t>(k) * a.L.ntot + p] = w[k];
-    }
-};
-
-// Count pass, FP16 relative coordinates (MODE 0; MODE 2 decides every candidate in FP64).
-template <int DIM, int MODE, bool HALF>
-__global__ void __launch_bounds__(64)
-k_count16(SearchArgs a)
+// The block of a statistics kernel, or -1 (no block, or one of the dense-cell path, whose
+// sums are cleared).
+__device__ __forceinline__ int stats_block(const SearchArgs& a)
 {
-    using CB = CandBits<DIM>;
+    const int b = xcd_block(*a.nblk);
+    if (b < 0 || !dense_block(a, b)) return b;
+    if ((threadIdx.x & 63) < 5) a.blk_stats[static_cast<size_t>(b) * 5 + (threadIdx.x & 63)] = 0;
+    return -1;
+}
+
+// The packed-FP16 test (MODE 0: band pairs against the FP64 predicate; MODE 2, recheck-all:
+// every candidate).
+template <int DIM, int MODE>
+__global__ void __launch_bounds__(64)
+k_stats16(SearchArgs a)
+{
     // pair records of the staged chunk, and kGroup more that the last group of a range may
     // read past the chunk (their bits are masked)
     __shared__ uint4 srec[kStage / 2 + kGroup];
-    // half lists: the staged candidates' original indices (same padding)
-    __shared__ __attribute__((aligned(16))) int corig[HALF ? kStage + 2 * kGroup : 1];
-    __shared__ uint32_t lbits[64 * (CB::CW + 1)];
-    const int b = xcd_block(*a.nblk);
+    const int b = stats_block(a);
     if (b < 0) return;
-    const int lane = threadIdx.x & 63;
-    if (dense_block(a, b)) {
-        if (lane < 5) a.blk_stats[static_cast<size_t>(b) * 5 + lane] = 0;
-        write_desc_dense(a, b);
-        return;
-    }
     Geom<DIM> g;
     g.init(a, b);
-    write_desc(a, g, b);
-    const Frame& fr = g.fr;
     const int pp = g.active ? g.p : g.p1 - 1;
-    const int oi = a.perm[pp];
-    const double* spos_set = g.sd->pos;
-    const int poff = g.sd->poff;
     double pi[3] = {0, 0, 0};
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) pi[k] = spos_set[static_cast<size_t>(oi - poff) * DIM + k];
+    for (int k = 0; k < DIM; ++k) pi[k] = a.spos[static_cast<size_t>(pp) * 4 + k];
     Target16<DIM> tg;
-    tg.init(a.q4[pp], g.x, g.sx0);
+    tg.init(q16_of(a.rq[pp]), g.x, g.sx0);
     Thresh th;
-    th.init(fr);
-    CB cb_;
-    cb_.init(g, lbits);
-    BandQueue bq;
-    uint32_t cnt = 0;
+    th.init(g.fr);
     Tally t;
-    // band candidates of a queued group (staged in the current chunk): FP16 r2 bits into the
-    // position queue, or, when that is full, the FP64 recheck on the spot
-    BandGroups bg;
-    int cbase = 0;  // first position of the staged chunk
-    auto band_group = [&](uint32_t where, uint32_t bits) {
-        const int r = static_cast<int>(where >> 27);
-        const int mg = static_cast<int>(where & 0x7FFFFFFu);
-        const int dy = r % 3 - 1, dz = DIM == 3 ? r / 3 - 1 : 0;
-        const h2 ay = splat(tg.qiy + static_cast<_Float16>(-2 * dy));
-        const h2 az = splat(tg.qiz + static_cast<_Float16>(-2 * dz));
-        uint32_t bb = bits;
-        while (bb) {
-            const int k = __builtin_ctz(bb);
-            bb &= bb - 1u;
-            const int posl = 2 * mg + k;
-            const uint32_t rb = r2_pair<DIM>(tg, ay, az, srec[(posl >> 1) - (cbase >> 1)]);
-            const uint32_t r2h = (rb >> (16 * (posl & 1))) & 0xFFFFu;
-            if (!bq.push(posl, r2h) && posl != g.pself) {
-                int oj;
-                if (classify<DIM, 0>(a, g, pi, posl, r2h, t, nullptr, cbase, &oj) && (!HALF || oj > oi)) {
-                    ++cnt;
-                    cb_.set(posl);
-                }
-            }
-        }
-    };
     for (int cb = 0; cb < g.U; cb += kStage) {
         const int ce = min(g.U, cb + kStage);
-        cbase = cb;
         __syncthreads();
-        stage<DIM, HALF>(a, g, cb, ce, srec, corig);
+        stage<DIM>(a, g, cb, ce, srec);
         __syncthreads();
         if (!g.active) continue;
+        const uint4* rec = srec - (cb >> 1);
 #pragma unroll
         for (int r = 0; r < Geom<DIM>::NSEG; ++r) {
             const int lo = max(g.la[r], cb), hi = min(g.lb[r], ce);
@@ -672,32 +514,12 @@ k_count16(SearchArgs a)
             const int dy = r % 3 - 1, dz = DIM == 3 ? r / 3 - 1 : 0;
             const h2 ay = splat(tg.qiy + static_cast<_Float16>(-2 * dy));
             const h2 az = splat(tg.qiz + static_cast<_Float16>(-2 * dz));
-            if constexpr (MODE == 2) {
-                const int selfp = (r == Geom<DIM>::SELF) ? g.pself : -1;
-                for_pairs(lo, hi, [&](int m, uint32_t inv) {
-                    const uint32_t rb = r2_pair<DIM>(tg, ay, az, srec[m - (cb >> 1)]);
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int posl = 2 * m + h;
-                        if (((inv >> (16 * h)) & 0xFFFF) || posl == selfp) continue;
-                        int oj;
-                        if (classify<DIM, MODE>(a, g, pi, posl, (rb >> (16 * h)) & 0xFFFF, t, nullptr, cb,
-                                                &oj) &&
-                            (!HALF || oj > oi)) {
-                            ++cnt;
-                            cb_.set(posl);
-                        }
-                    }
-                });
-            } else {
-                // kGroup pair records (2 kGroup positions) at a time: the bits of the
-                // accepted and of the band candidates gather in registers (bit j: position
-                // 2(mg + j), bit 16 + j: position 2(mg + j) + 1) and go to the candidate
-                // bits once per group; band candidates are queued for the FP64 recheck.
-                const uint4* rec = srec - (cb >> 1);
-                const int m0 = lo >> 1, mend = (hi + 1) >> 1;
-                for (int mg = m0; mg < mend; mg += kGroup) {
-                    uint32_t acc = 0, ebits = 0, gt = 0;
+            // kGroup pair records (2 kGroup positions) at a time: bit j for position
+            // 2(mg + j), bit 16 + j for position 2(mg + j) + 1
+            const int m0 = lo >> 1, mend = (hi + 1) >> 1;
+            for (int mg = m0; mg < mend; mg += kGroup) {
+                uint32_t acc = 0, ebits = 0;
+                if (MODE == 0) {
 #pragma unroll
                     for (int j = 0; j < kGroup; ++j) {
                         const uint32_t rb = r2_pair<DIM>(tg, ay, az, rec[mg + j]);
@@ -705,120 +527,22 @@ k_count16(SearchArgs a)
                         const u16x2 e = d - th.w12;
                         acc |= (u16x2_bits(d) >> (15 - j)) & (0x10001u << j);
                         ebits |= (u16x2_bits(e) >> (15 - j)) & (0x10001u << j);
-                        if (HALF) {
-                            const int2 oo = *reinterpret_cast<const int2*>(&corig[2 * (mg + j) - cb]);
-                            gt |= (oo.x > oi ? 1u << j : 0u) | (oo.y > oi ? 1u << (16 + j) : 0u);
-                        }
                     }
-                    // the group's positions inside [lo, hi)
-                    const int a0 = lo - 2 * mg, b0 = hi - 2 * mg;
-                    const uint32_t valid = span8((a0 + 1) >> 1, (b0 + 1) >> 1) |
-                                           (span8(a0 >> 1, b0 >> 1) << 16);
-                    acc &= valid;
-                    const uint32_t bnd = ebits & ~acc & valid;
-                    if (HALF) acc &= gt;  // half list: only candidates of larger original index
-                    cnt += __builtin_popcount(acc);
-                    cb_.put16(2 * mg, interleave8(acc));
-                    if (bnd) {
-                        const uint32_t where = (static_cast<uint32_t>(r) << 27) | static_cast<uint32_t>(mg);
-                        const uint32_t bits = interleave8(bnd);
-                        if (!bg.push(where, bits)) band_group(where, bits);
-                    }
+                }
+                // the group's positions inside [lo, hi)
+                const int a0 = lo - 2 * mg, b0 = hi - 2 * mg;
+                const uint32_t valid = span8((a0 + 1) >> 1, (b0 + 1) >> 1) | (span8(a0 >> 1, b0 >> 1) << 16);
+                for (uint32_t q = MODE == 0 ? ebits & ~acc & valid : valid; q; q &= q - 1u) {
+                    const int k = __builtin_ctz(q);
+                    const int posl = 2 * (mg + (k & 15)) + (k >> 4);
+                    if (posl == g.pself) continue;
+                    const uint32_t rb = r2_pair<DIM>(tg, ay, az, rec[posl >> 1]);
+                    classify<DIM, MODE>(a, g, pi, posl, (rb >> (16 * (posl & 1))) & 0xFFFFu, t);
                 }
             }
         }
-        if constexpr (MODE == 0) bg.drain(band_group);
     }
-    if constexpr (MODE == 0) {
-        // self (r2 = 0) was counted as "in" when T_lo > 0, or queued as a band pair; half
-        // lists never count it (its index is not larger than its own)
-        if (!HALF && g.active && fr.t_lo > 0) cnt -= 1;
-        bq.drain([&](int posl, uint32_t r2h) {
-            if (posl == g.pself) return;
-            const int oj = a.perm[g.global_of_any(posl)];
-            const bool truth = recheck<DIM>(spos_set, pi, oj - poff, fr.R2);
-            const bool naive = r2h <= fr.t_mid;
-            t.band++;
-            t.fpos += naive && !truth;
-            t.fneg += !naive && truth;
-            const bool keep = truth && (!HALF || oj > oi);
-            cnt += keep;
-            if (keep) cb_.set(posl);
-        });
-        // candidates: the lane's ranges minus itself
-        if (g.active) t.cand += cb_.total - 1;
-    }
-    if (g.active) {
-        a.counts[oi] = static_cast<int>(cnt);
-        a.counts_s[g.p] = static_cast<int>(cnt);
-    }
-    cb_.store(a, g.p);
-    unsigned long long v[5] = {t.cand, t.band, t.fpos, t.fneg, t.odis};
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const unsigned long long sum = wave_sum_u64(v[k]);
-        if (lane == 0) a.blk_stats[static_cast<size_t>(b) * 5 + k] = sum;
-    }
-}
-
-// Count pass, plain FP64 baseline: one lane per target, global FP64 loads.
-template <int DIM, bool HALF>
-__global__ void __launch_bounds__(64)
-k_count64(SearchArgs a)
-{
-    using CB = CandBits<DIM>;
-    __shared__ uint32_t lbits[64 * (CB::CW + 1)];
-    const int b = xcd_block(*a.nblk);
-    if (b < 0) return;
-    if (dense_block(a, b)) {
-        if ((threadIdx.x & 63) < 5) a.blk_stats[static_cast<size_t>(b) * 5 + (threadIdx.x & 63)] = 0;
-        write_desc_dense(a, b);
-        return;
-    }
-    Geom<DIM> g;
-    g.init(a, b);
-    write_desc(a, g, b);
-    const Frame& fr = g.fr;
-    CB cb_;
-    cb_.init(g, lbits);
-    int cnt = 0;
-    unsigned long long cand = 0;
-    if (g.active) {
-        const int oi = a.perm[g.p];
-        const double* pi = a.spos + static_cast<size_t>(g.p) * 4;
-        const double pix[3] = {pi[0], pi[1], DIM == 3 ? pi[2] : 0.0};
-#pragma unroll
-        for (int r = 0; r < Geom<DIM>::NSEG; ++r) {
-            const int ga = g.global_of(r, g.la[r]), gb = g.global_of(r, g.lb[r]);
-            const int pbase = g.la[r] - ga;  // union position = pbase + j
-            cand += gb - ga;
-            // four candidates per step, their loads issued together (the last index is
-            // repeated past the range end and its result dropped)
-            for (int j = ga; j < gb; j += 4) {
-                double d2[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const double* pj = a.spos + static_cast<size_t>(min(j + u, gb - 1)) * 4;
-                    d2[u] = r2_fp64<DIM>(pix, pj);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (j + u < gb && d2[u] <= fr.R2 && (!HALF || a.perm[j + u] > oi)) {
-                        ++cnt;
-                        cb_.set(pbase + j + u);
-                    }
-                }
-            }
-        }
-        if (!HALF) cnt -= 1;  // itself (r2 = 0)
-        cand -= 1;
-        a.counts[oi] = cnt;
-        a.counts_s[g.p] = cnt;
-    }
-    cb_.store(a, g.p);
-    const unsigned long long s = wave_sum_u64(cand);
-    if ((threadIdx.x & 63) < 5)
-        a.blk_stats[static_cast<size_t>(b) * 5 + (threadIdx.x & 63)] = (threadIdx.x & 63) == 0 ? s : 0ull;
+    write_stats<DIM>(a, g, b, t);
 }
 
 // FP32 r2 of Eq. 7 on twice the displacement in cell widths: per axis
@@ -840,128 +564,55 @@ __device__ __forceinline__ float r2_fp32(const float4& qi, float wi, float cy, f
     return r2;
 }
 
-constexpr int kStage32 = 256;  // candidates per staged chunk of the FP32 count (16 B each)
-
-// Count pass, FP32 relative coordinates (the paper's FP32 variant of the relative-
-// coordinate list). The block's candidate union is staged in LDS chunk by chunk as
-// {q_x, q_y, q_z, 2 x-offset} (f32); each lane tests its own ranges four candidates per
-// step and turns the four results into "in" and "band" bits with no branch; the rare band
-// pairs are decided by the FP64 predicate on the caller's positions. The lane's own entry
-// (r2 = 0) is "in" when T32_lo > 0 and is taken out at the end; otherwise it is a band
-// entry and skipped there.
-template <int DIM, bool HALF>
+// The FP32 test of the relative coordinates (the paper's FP32 variant), band pairs against
+// the FP64 predicate.
+template <int DIM>
 __global__ void __launch_bounds__(64)
-k_count32(SearchArgs a)
+k_stats32(SearchArgs a)
 {
-    using CB = CandBits<DIM>;
-    // the staged chunk, and 4 more entries that the last step of a range may read past it
-    // (their results are dropped)
-    __shared__ float4 sq[kStage32 + 4];
-    // half lists: the staged candidates' original indices (same padding)
-    __shared__ int sorig[HALF ? kStage32 + 4 : 1];
-    __shared__ uint32_t lbits[64 * (CB::CW + 1)];
-    const int b = xcd_block(*a.nblk);
+    const int b = stats_block(a);
     if (b < 0) return;
-    const int lane = threadIdx.x & 63;
-    if (dense_block(a, b)) {
-        if (lane < 5) a.blk_stats[static_cast<size_t>(b) * 5 + lane] = 0;
-        write_desc_dense(a, b);
-        return;
-    }
     Geom<DIM> g;
     g.init(a, b);
-    write_desc(a, g, b);
-    const Frame& fr = g.fr;
     const int pp = g.active ? g.p : g.p1 - 1;
-    const int oi = a.perm[pp];
-    const double* spos_set = g.sd->pos;
-    const int poff = g.sd->poff;
-    double pi[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) pi[k] = spos_set[static_cast<size_t>(oi - poff) * DIM + k];
+    const double* pi = a.spos + static_cast<size_t>(pp) * 4;
     const float4 qi = a.rq[pp];
     const float wi = static_cast<float>(2 * (g.x - g.sx0));
-    const float tlo = fr.t32_lo, thi = fr.t32_hi, tmid = fr.t32_mid;
-    CB cb_;
-    cb_.init(g, lbits);
-    int cnt = 0;
     Tally t;
-    const uint32_t sx0 = static_cast<uint32_t>(g.sx0);
-    for (int cb = 0; cb < g.U; cb += kStage32) {
-        const int ce = min(g.U, cb + kStage32);
-        __syncthreads();
-        for (int u = cb + lane; u < ce; u += 64) {
-            const float4 v = a.rq[g.global_of_any(u)];
-            // the union spans fewer than 2^10 cells in x, so the offset mod 2^10 is exact
-            const uint32_t rel = (__builtin_bit_cast(uint32_t, v.w) - sx0) & 1023u;
-            sq[u - cb] = make_float4(v.x, v.y, v.z, static_cast<float>(2 * static_cast<int>(rel)));
-            if (HALF) sorig[u - cb] = a.perm[g.global_of_any(u)];
-        }
-        __syncthreads();
-        if (!g.active) continue;
+    if (g.active) {
 #pragma unroll
         for (int r = 0; r < Geom<DIM>::NSEG; ++r) {
-            const int lo = max(g.la[r], cb), hi = min(g.lb[r], ce);
-            if (lo >= hi) continue;
             const float cy = static_cast<float>(2 - 2 * (r % 3));                 // -2 dy
             const float cz = DIM == 3 ? static_cast<float>(2 - 2 * (r / 3)) : 0.0f;  // -2 dz
-            for (int j = lo; j < hi; j += 4) {
-                uint32_t in4 = 0, band4 = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float v = r2_fp32<DIM>(qi, wi, cy, cz, sq[j - cb + u]);
-                    in4 |= static_cast<uint32_t>(v < tlo) << u;
-                    band4 |= static_cast<uint32_t>(v <= thi) << u;
-                }
-                const int left = hi - j;
-                const uint32_t valid = left >= 4 ? 0xFu : (1u << left) - 1u;
-                in4 &= valid;
-                band4 &= valid & ~in4;
-                if (band4) {
-                    uint32_t bb = band4;
-                    while (bb) {
-                        const int k = __builtin_ctz(bb);
-                        bb &= bb - 1u;
-                        const int posl = j + k;
-                        if (posl == g.pself) continue;
-                        const float v = r2_fp32<DIM>(qi, wi, cy, cz, sq[j - cb + k]);
-                        const bool truth = recheck<DIM>(spos_set, pi, a.perm[g.global_of(r, posl)] - poff, fr.R2);
-                        const bool naive = v <= tmid;
-                        t.band++;
-                        t.fpos += naive && !truth;
-                        t.fneg += !naive && truth;
-                        in4 |= static_cast<uint32_t>(truth) << k;
-                    }
-                }
-                if (HALF) {
-                    uint32_t gt = 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) gt |= static_cast<uint32_t>(sorig[j - cb + u] > oi) << u;
-                    in4 &= gt;
-                }
-                cnt += __builtin_popcount(in4);
-                cb_.put(j, in4);
+            for (int posl = g.la[r]; posl < g.lb[r]; ++posl) {
+                const int gj = g.global_of(r, posl);
+                float4 v = a.rq[gj];
+                // the union spans fewer than 2^10 cells in x, so the offset mod 2^10 is exact
+                v.w = static_cast<float>(2 * ((__builtin_bit_cast(int, v.w) - g.sx0) & 1023));
+                const float r2 = r2_fp32<DIM>(qi, wi, cy, cz, v);
+                if (posl == g.pself || r2 < g.fr.t32_lo || !(r2 <= g.fr.t32_hi)) continue;
+                const bool truth = recheck_sorted<DIM>(a.spos, pi, gj, g.fr.R2);
+                const bool naive = r2 <= g.fr.t32_mid;
+                t.band++;
+                t.fpos += naive && !truth;
+                t.fneg += !naive && truth;
             }
         }
     }
-    if (g.active) {
-        if (!HALF && tlo > 0.0f) {  // itself, taken as "in" (half lists never keep it)
-            cnt -= 1;
-            cb_.clear(g.pself);
-        }
-#pragma unroll
-        for (int r = 0; r < Geom<DIM>::NSEG; ++r) t.cand += g.lb[r] - g.la[r];
-        t.cand -= 1;  // itself
-        a.counts[oi] = cnt;
-        a.counts_s[g.p] = cnt;
-    }
-    cb_.store(a, g.p);
-    const unsigned long long v[5] = {t.cand, t.band, t.fpos, t.fneg, 0ull};
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        const unsigned long long sum = wave_sum_u64(v[k]);
-        if (lane == 0) a.blk_stats[static_cast<size_t>(b) * 5 + k] = sum;
-    }
+    write_stats<DIM>(a, g, b, t);
+}
+
+// FP64: the candidates only.
+template <int DIM>
+__global__ void __launch_bounds__(64)
+k_stats64(SearchArgs a)
+{
+    const int b = stats_block(a);
+    if (b < 0) return;
+    Geom<DIM> g;
+    g.init(a, b);
+    Tally t;
+    write_stats<DIM>(a, g, b, t);
 }
 
 // Sum of the per-block statistics and of the dense path's per-workgroup statistics
@@ -994,18 +645,13 @@ k_reduce_stats(const unsigned long long* __restrict__ blk, const int* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Fill pass. The block's whole candidate union is staged and sorted once by original
-// index (a bitonic network over the wavefront's registers); each lane then records its
-// accepted neighbours as a bitmask over those ranks, so reading the bits in order gives
-// the row in ascending original index with no per-row sort. The rows are compacted into
-// one flat list per block and written 64 entries at a time: consecutive lanes store
-// consecutive CSR slots.
+// Limits of the block path: candidates of a block's union.
 template <int DIM>
 struct FillCfg {
     static constexpr int UCAP = DIM == 3 ? kUnion3 : kUnion2;
     static constexpr int MW = UCAP / 32;    // mask words per lane
-    static constexpr int FCAP = DIM == 3 ? kFlat3 : kFlat2;
-    static constexpr int SHIFT = DIM == 3 ? 10 : 9;  // log2(UCAP): key = orig << SHIFT | pos
+    static constexpr int FLAT = DIM == 3 ? 1024 : 512;  // entries a wavefront of the fill compacts at a time
+    static constexpr int SHIFT = DIM == 3 ? 10 : 9;  // log2(UCAP)
 };
 
 // Bitonic sort of 64*EPL keys held blocked across the wavefront (element e = lane*EPL + i).
@@ -1076,14 +722,15 @@ __device__ __forceinline__ int count_below(const uint32_t* run, uint32_t key)
 
 // Ranks of the U union keys (key_of(e), e < U) across NW wavefronts: wavefront wv sorts
 // keys [wv Q, wv Q + Q) in registers and stores them padded to 64 EPL entries; a key's
-// rank is the number of keys below it in the NW sorted quarters. Writes rank_of[e] and
-// moves the original indices into rank order (sorig[rank]). Keys that carry their
-// position (packed) are ranked straight from the registers; otherwise every element
-// looks its own key up in all quarters.
+// rank is the number of keys below it in the NW sorted quarters. rk[i] receives the rank of
+// element tid + i 64 NW. Keys that carry their position (packed) are ranked straight from
+// the registers of whichever thread sorted them and handed over through rank_of; otherwise
+// every thread looks its own elements' keys up in all quarters.
 template <int UCAP, int SHIFT, int NW, int EPL, typename K>
-__device__ __forceinline__ void rank_union(int U, int Q, bool packed, int omin, K&& key_of, uint32_t* skeys,
-                                           uint16_t* rank_of, int* sorig)
+__device__ __forceinline__ void rank_union(int U, int Q, bool packed, K&& key_of, uint32_t* skeys, uint16_t* rank_of,
+                                           int (&out)[UCAP / (64 * NW)])
 {
+    constexpr int EPT = UCAP / (64 * NW);
     constexpr int QP = 64 * EPL;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int e0 = wv * Q, n = max(0, min(Q, U - e0));
@@ -1108,34 +755,22 @@ __device__ __forceinline__ void rank_union(int U, int Q, bool packed, int omin, 
             for (int i = 0; i < EPL; ++i) rk[i] += count_below<QP>(skeys + q * QP, v[i]);
         }
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) {
-            if (v[i] == 0xFFFFFFFFu) continue;
-            rank_of[v[i] & (UCAP - 1)] = static_cast<uint16_t>(rk[i]);
-            sorig[rk[i]] = static_cast<int>(v[i] >> SHIFT) + omin;
-        }
+        for (int i = 0; i < EPL; ++i)
+            if (v[i] != 0xFFFFFFFFu) rank_of[v[i] & (UCAP - 1)] = static_cast<uint16_t>(rk[i]);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) out[i] = tid + i * 64 * NW < U ? rank_of[tid + i * 64 * NW] : 0;
     } else {
-        constexpr int EPT = UCAP / (64 * NW);
-        int rk[EPT], og[EPT];
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
             const int e = tid + i * 64 * NW;
-            rk[i] = -1;
-            og[i] = 0;
             if (e < U) {
-                const uint32_t key = static_cast<uint32_t>(sorig[e]);
+                const uint32_t key = key_of(e);
                 int r = 0;
 #pragma unroll
                 for (int q = 0; q < NW; ++q) r += count_below<QP>(skeys + q * QP, key);
-                rk[i] = r;
-                og[i] = static_cast<int>(key);
+                out[i] = r;
             }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            if (rk[i] < 0) continue;
-            rank_of[tid + i * 64 * NW] = static_cast<uint16_t>(rk[i]);
-            sorig[rk[i]] = og[i];
         }
     }
 }
@@ -1143,11 +778,11 @@ __device__ __forceinline__ void rank_union(int U, int Q, bool packed, int omin, 
 // Ranks by bitmap, for unions whose original indices span at most 32 BW values (the
 // common case when particles are numbered in space): one bit per index in [omin, omin +
 // range), an exclusive scan of the word popcounts, and a key's rank is the number of set
-// bits below it. Same outputs as rank_union: rank_of[e], and the original indices moved
-// into rank order (sorig[rank]). bw (BW words) and pc (BW 16-bit prefixes) are scratch.
+// bits below it. og[i] is the original index of element tid + i 64 NW (below U), rk[i] its
+// rank. bw (BW words) and pc (BW 16-bit prefixes) are scratch.
 template <int UCAP, int NW, int BW>
-__device__ __forceinline__ void rank_bitmap(int U, int omin, int range, uint32_t* bw, uint16_t* pc, int* wsum,
-                                            uint16_t* rank_of, int* sorig)
+__device__ __forceinline__ void rank_bitmap(int U, int omin, int range, const int (&og)[UCAP / (64 * NW)], uint32_t* bw,
+                                            uint16_t* pc, int* wsum, int (&rk)[UCAP / (64 * NW)])
 {
     constexpr int NT = 64 * NW;
     constexpr int EPT = UCAP / NT;
@@ -1155,11 +790,9 @@ __device__ __forceinline__ void rank_bitmap(int U, int omin, int range, uint32_t
     const int W = (range + 31) >> 5;
     for (int w = tid; w < W; w += NT) bw[w] = 0u;
     __syncthreads();
-    int og[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
         const int e = tid + i * NT;
-        og[i] = e < U ? sorig[e] : omin;
         if (e < U) {
             const int o = og[i] - omin;
             atomicOr(&bw[o >> 5], 1u << (o & 31));
@@ -1182,20 +815,14 @@ __device__ __forceinline__ void rank_bitmap(int U, int omin, int range, uint32_t
         run += __builtin_popcount(bw[w]);
     }
     __syncthreads();
-    int rk[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
         const int e = tid + i * NT;
-        const int o = og[i] - omin;
-        const int w = o >> 5;
-        rk[i] = pc[w] + __builtin_popcount(bw[w] & ((1u << (o & 31)) - 1u));
-        if (e < U) rank_of[e] = static_cast<uint16_t>(rk[i]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * NT;
-        if (e < U) sorig[rk[i]] = og[i];
+        if (e < U) {
+            const int o = og[i] - omin;
+            const int w = o >> 5;
+            rk[i] = pc[w] + __builtin_popcount(bw[w] & ((1u << (o & 31)) - 1u));
+        }
     }
 }
 
@@ -1205,12 +832,12 @@ __device__ __forceinline__ void rank_bitmap(int U, int omin, int range, uint32_t
 // [omin, omin + 2^17) hold a union index (4096 bits); the occupied chunks are numbered in
 // order by a scan of the level-1 word popcounts; level 2 keeps one 32-bit word of index
 // bits per occupied chunk; a key's rank is the set level-2 bits before it (a block scan of
-// the level-2 word popcounts, plus the bits below it in its own word). Same outputs as
-// rank_union: rank_of[e], and the original indices moved into rank order (sorig[rank]).
-// l1 (128 words), l1pre (128), l2 (UCAP words) and l2pre (UCAP) are scratch.
+// the level-2 word popcounts, plus the bits below it in its own word). Input and output as
+// rank_bitmap. l1 (128 words), l1pre (128), l2 (UCAP words) and l2pre (UCAP) are scratch.
 template <int UCAP, int NW>
-__device__ __forceinline__ void rank_bitmap2(int U, int omin, uint32_t* l1, uint16_t* l1pre, uint32_t* l2,
-                                             uint16_t* l2pre, int* wsum, uint16_t* rank_of, int* sorig)
+__device__ __forceinline__ void rank_bitmap2(int U, int omin, const int (&og)[UCAP / (64 * NW)], uint32_t* l1,
+                                             uint16_t* l1pre, uint32_t* l2, uint16_t* l2pre, int* wsum,
+                                             int (&rk)[UCAP / (64 * NW)])
 {
     constexpr int NT = 64 * NW;
     constexpr int EPT = UCAP / NT;
@@ -1220,12 +847,11 @@ __device__ __forceinline__ void rank_bitmap2(int U, int omin, uint32_t* l1, uint
 #pragma unroll
     for (int i = 0; i < EPT; ++i) l2[tid * EPT + i] = 0u;
     __syncthreads();
-    int og[EPT], ch[EPT];
+    int ch[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
         const int e = tid + i * NT;
-        og[i] = e < U ? sorig[e] - omin : 0;
-        ch[i] = og[i] >> 5;
+        ch[i] = e < U ? (og[i] - omin) >> 5 : 0;
         if (e < U) atomicOr(&l1[ch[i] >> 5], 1u << (ch[i] & 31));
     }
     __syncthreads();
@@ -1245,7 +871,7 @@ __device__ __forceinline__ void rank_bitmap2(int U, int omin, uint32_t* l1, uint
         const int e = tid + i * NT;
         const int w1 = ch[i] >> 5;
         slot[i] = l1pre[w1] + __builtin_popcount(l1[w1] & ((1u << (ch[i] & 31)) - 1u));
-        if (e < U) atomicOr(&l2[slot[i]], 1u << (og[i] & 31));
+        if (e < U) atomicOr(&l2[slot[i]], 1u << ((og[i] - omin) & 31));
     }
     __syncthreads();
     // exclusive scan of the level-2 popcounts: thread t takes slots [t EPT, t EPT + EPT)
@@ -1268,26 +894,17 @@ __device__ __forceinline__ void rank_bitmap2(int U, int omin, uint32_t* l1, uint
         }
     }
     __syncthreads();
-    int rk[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
         const int e = tid + i * NT;
-        rk[i] = l2pre[slot[i]] + __builtin_popcount(l2[slot[i]] & ((1u << (og[i] & 31)) - 1u));
-        if (e < U) rank_of[e] = static_cast<uint16_t>(rk[i]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const int e = tid + i * NT;
-        if (e < U) sorig[rk[i]] = og[i] + omin;
+        if (e < U)
+            rk[i] = l2pre[slot[i]] + __builtin_popcount(l2[slot[i]] & ((1u << ((og[i] - omin) & 31)) - 1u));
     }
 }
 
 __device__ __forceinline__ int wave_min_i32(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
+    return __builtin_amdgcn_readlane(wave_fold_i32(v, 0x7FFFFFFF, [](int x, int y) { return min(x, y); }), 63);
 }
 
 __device__ __forceinline__ long long wave_max_i64(long long v)
@@ -1299,352 +916,847 @@ __device__ __forceinline__ long long wave_max_i64(long long v)
 
 __device__ __forceinline__ int wave_max_i32(int v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
+    return __builtin_amdgcn_readlane(wave_fold_i32(v, -0x7FFFFFFF - 1, [](int x, int y) { return max(x, y); }), 63);
 }
 
-constexpr int kFillThreads = 256;  // four wavefronts share one block's tables
+// Scratch of rank_originals (bytes): the two-level bitmap's tables (level 1 and its prefixes
+// 768, level 2 and its prefixes 6 UCAP), or the sorted quarters and the keys (8 UCAP).
+template <int UCAP>
+constexpr int kRankScratch = 8 * UCAP > 6 * UCAP + 768 ? 8 * UCAP : 6 * UCAP + 768;
 
-template <int DIM, int MODE>
-__global__ void __launch_bounds__(kFillThreads) __attribute__((amdgpu_waves_per_eu(5)))
-k_fill(SearchArgs a)
+// The rank rk[i] of union element tid + i 64 NW (below U) by original index, og[i] its index. Unions spanning few indices are ranked by a
+// bitmap, up to 2^17 by a two-level bitmap, the others (an unordered numbering) by sorting:
+// keys (orig - omin) << SHIFT | position when the range allows, else the original index
+// itself, distinct either way and below the all-ones key that pads the sorted quarters.
+// rank_of (UCAP entries) is scratch too; both are free again on return.
+template <int UCAP, int SHIFT, int NW>
+__device__ __forceinline__ void rank_originals(int U, const int (&og)[UCAP / (64 * NW)], unsigned char* scratch,
+                                               int (*sred)[NW], int* wsum, uint16_t* rank_of,
+                                               int (&rk)[UCAP / (64 * NW)])
 {
-    using C = FillCfg<DIM>;
-    using CB = CandBits<DIM>;
-    constexpr int NW = kFillThreads / 64;
-    // LDS: the rank table is dead once the rows are compacted, so the flat entry list
-    // reuses its space.
-    constexpr int kRankBytes = C::UCAP * 2;
-    constexpr int kFlatBytes = C::FCAP * 2;
-    constexpr int kShared = kRankBytes > kFlatBytes ? kRankBytes : kFlatBytes;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[kShared];
-    __shared__ int sorig[C::UCAP];
-    __shared__ uint32_t masks[64 * (C::MW + 1)];
-    __shared__ long long sbase[64];  // row start in the output minus the row's flat offset
-    __shared__ double sxi[64 * DIM];  // targets' positions: fixed point, or FP64 (baseline)
-    __shared__ int spart[NW][64];   // per-wave popcounts of each row's mask quarter
-    __shared__ int sred[2][NW];
-    __shared__ int swsum[NW];
-    uint16_t* rank_of = reinterpret_cast<uint16_t*>(smem);
-    // flat list entry: target lane << SHIFT | the candidate's rank in the union
-    uint16_t* flat = reinterpret_cast<uint16_t*>(smem);
-    static_assert(64 << C::SHIFT <= 65536 && (1 << C::SHIFT) == C::UCAP, "flat entries fit 16 bits");
-
-    const int b = xcd_block(*a.nblk);
-    if (b < 0) return;
-    // the block's geometry from the count pass's descriptor (wave-uniform), and each
-    // target's row start and length in sorted order: no chain of dependent loads
-    const int* __restrict__ dsc = a.bdesc + static_cast<size_t>(b) * kDescInts;
-    if (dsc[4]) return;  // a block of the dense-cell path
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, uniform
-    FillGeom<DIM> g;
-    g.init(a, dsc);
-    const SetView sd(*g.sd);
-    const float dist_scale = g.sd->fr.dist_scale;  // in a register: stores below cannot change it
-    const int pp = g.active ? g.p : g.p1 - 1;
-    const long long rs = a.rsort[pp];
-    const int rlen = g.active ? a.counts_s[g.p] : 0;
-    int E;
-    const int off = wave_excl_scan_i32(rlen, &E);
-    E = __builtin_amdgcn_readfirstlane(E);  // the block's entry count, wave-uniform
-    static_assert(32 * CB::CW == C::UCAP, "the count pass keeps a bit per union position");
-    if (g.U > C::UCAP || E > C::FCAP) {
-        // too big for this path: every row of the block goes to the long-row path
-        if (wv == 0 && g.active) a.heavy[atomicAdd(a.nheavy, 1)] = g.p;
-        return;
-    }
-    // the count pass's accepted-candidate bits (by union position), this wavefront's words
-    // w = wv + NW k, are loaded first: their latency is hidden behind staging and ranking
-    constexpr int KW = (CB::CW + NW - 1) / NW;
-    uint32_t wbits[KW];
-    {
-        const int nwt = g.active ? (g.U + 31) >> 5 : 0;
-#pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const int w = wv + NW * k;
-            wbits[k] = w < nwt ? a.cbits[static_cast<size_t>(w) * a.L.ntot + g.p] : 0u;
-        }
-    }
-    // 1. stage the union's original indices; clear the masks
-    const int U = g.U;
+    constexpr int NT = 64 * NW, EPT = UCAP / NT;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int omin = 0x7FFFFFFF, omax = 0;
-    {
-        // a thread's gathers are issued together, then stored
-        constexpr int EPT = C::UCAP / kFillThreads;
-        int og[EPT];
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + i * kFillThreads;
-            og[i] = e < U ? a.perm[g.global_of_any(e)] : -1;
+    for (int i = 0; i < EPT; ++i)
+        if (tid + i * NT < U) {
+            omin = min(omin, og[i]);
+            omax = max(omax, og[i]);
         }
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            const int e = tid + i * kFillThreads;
-            if (e < U) {
-                sorig[e] = og[i];
-                omin = min(omin, og[i]);
-                omax = max(omax, og[i]);
-            }
-        }
-    }
-    for (int i = tid; i < 64 * (C::MW + 1); i += kFillThreads) masks[i] = 0;
     omin = wave_min_i32(omin);
     omax = wave_max_i32(omax);
     if (lane == 0) {
         sred[0][wv] = omin;
         sred[1][wv] = omax;
     }
-    if (wv == 0) {
-        sbase[lane] = rs - off;
-        const int oi = a.perm[pp];
-        const int li = oi - sd.poff;
-#pragma unroll
-        for (int k = 0; k < DIM; ++k) {
-            // the target's own coordinates for the distance: fixed point, or FP64 bits (baseline)
-            sxi[lane * DIM + k] = MODE == 1 ? sd.pos[static_cast<size_t>(li) * DIM + k]
-                                            : a.X[static_cast<size_t>(oi) * x_stride(DIM) + k];
-        }
-    }
     __syncthreads();
-    // 2. rank the union by original index. Keys are (orig - omin) << SHIFT | position when
-    // the union's index range allows, else the original index itself: distinct either way,
-    // and below the all-ones key that pads the sorted quarters.
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         omin = min(omin, sred[0][w]);
         omax = max(omax, sred[1][w]);
     }
-    const bool packed = static_cast<uint32_t>(omax - omin) < (1u << (32 - C::SHIFT)) - 1u;
-    static_assert(C::UCAP * 2 + C::UCAP * 4 <= kShared, "sorted quarters fit beside the rank table");
-    uint32_t* skeys = reinterpret_cast<uint32_t*>(smem + C::UCAP * 2);
-    const int Q = (U + NW - 1) / NW;
-    auto key_of = [&](int e) -> uint32_t {
-        const int o = sorig[e];
-        return packed ? (static_cast<uint32_t>(o - omin) << C::SHIFT) | static_cast<uint32_t>(e)
-                      : static_cast<uint32_t>(o);
-    };
-    // unions spanning few original indices are ranked by bitmap (scratch after the rank table)
-    constexpr int BW = (kShared - C::UCAP * 2) / 6;
-    // the two-level bitmap's tables after the rank table: level 1 (512 B) and its prefixes
-    // (256 B), level 2 (4 UCAP B) and its prefixes (2 UCAP B)
-    constexpr bool kTwoLevel = C::UCAP * 2 + 768 + C::UCAP * 6 <= kShared;
-    if (static_cast<unsigned>(omax - omin) < 32u * BW)
-        rank_bitmap<C::UCAP, NW, BW>(U, omin, omax - omin + 1, reinterpret_cast<uint32_t*>(smem + C::UCAP * 2),
-                                     reinterpret_cast<uint16_t*>(smem + C::UCAP * 2 + BW * 4), swsum, rank_of, sorig);
-    else if (kTwoLevel && static_cast<unsigned>(omax - omin) < (1u << 17))
-        rank_bitmap2<C::UCAP, NW>(U, omin, reinterpret_cast<uint32_t*>(smem + C::UCAP * 2),
-                                  reinterpret_cast<uint16_t*>(smem + C::UCAP * 2 + 512),
-                                  reinterpret_cast<uint32_t*>(smem + C::UCAP * 2 + 768),
-                                  reinterpret_cast<uint16_t*>(smem + C::UCAP * 6 + 768), swsum, rank_of, sorig);
-    else if (Q <= 64) rank_union<C::UCAP, C::SHIFT, NW, 1>(U, Q, packed, omin, key_of, skeys, rank_of, sorig);
-    else if (Q <= 128) rank_union<C::UCAP, C::SHIFT, NW, 2>(U, Q, packed, omin, key_of, skeys, rank_of, sorig);
-    else rank_union<C::UCAP, C::SHIFT, NW, 4>(U, Q, packed, omin, key_of, skeys, rank_of, sorig);
+    constexpr int BW = kRankScratch<UCAP> / 6;
+    uint32_t* s32 = reinterpret_cast<uint32_t*>(scratch);
+    if (static_cast<unsigned>(omax - omin) < 32u * BW) {
+        rank_bitmap<UCAP, NW, BW>(U, omin, omax - omin + 1, og, s32, reinterpret_cast<uint16_t*>(s32 + BW), wsum, rk);
+    } else if (static_cast<unsigned>(omax - omin) < (1u << 17)) {
+        rank_bitmap2<UCAP, NW>(U, omin, og, s32, reinterpret_cast<uint16_t*>(s32 + 128), s32 + 192,
+                               reinterpret_cast<uint16_t*>(s32 + 192 + UCAP), wsum, rk);
+    } else {
+        const bool packed = static_cast<uint32_t>(omax - omin) < (1u << (32 - SHIFT)) - 1u;
+        uint32_t* keys = s32 + UCAP;
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            const int e = tid + i * NT;
+            if (e < U)
+                keys[e] = packed ? (static_cast<uint32_t>(og[i] - omin) << SHIFT) | static_cast<uint32_t>(e)
+                                 : static_cast<uint32_t>(og[i]);
+        }
+        __syncthreads();
+        auto key_of = [&](int e) { return keys[e]; };
+        const int Q = (U + NW - 1) / NW;
+        if (Q <= 64) rank_union<UCAP, SHIFT, NW, 1>(U, Q, packed, key_of, s32, rank_of, rk);
+        else if (UCAP / NW <= 128 || Q <= 128) rank_union<UCAP, SHIFT, NW, 2>(U, Q, packed, key_of, s32, rank_of, rk);
+        else rank_union<UCAP, SHIFT, NW, UCAP / NW <= 128 ? 2 : 4>(U, Q, packed, key_of, s32, rank_of, rk);
+    }
     __syncthreads();
-    // 3. accepted candidates from the count pass, re-indexed by rank into each target's
-    // mask. Wavefront wv holds the bit words w = wv (mod 4) of every target; it lists its
-    // nonzero ones (one ballot per word) in LDS and then takes one listed word per lane,
-    // so a round of bit extraction waits for the fullest of 64 nonzero words, not for the
-    // fullest lane of every word. The list lives in the ranking scratch, dead by now.
-    uint32_t* mk = masks + lane * (C::MW + 1);
+}
+
+// ---------------------------------------------------------------------------
+// Count pass, on the matrix cores. Four wavefronts per block: the block's union is ranked by
+// original index first, so the candidate bits come out in row order and the fill only has to
+// compact them.
+//
+// The test is the contraction r2 = |c|^2 - 2 c.t + |t|^2 over candidates c and targets t
+// about the block's centre, with the cutoff on the target side (|t|^2 - R^2), so the result D
+// is negative for "in"; |D| below an error bound is decided by the binary64 predicate.
+//   P = 16 (FP16 RCLL): coordinates in half cell widths (Eq. 6 plus twice the cell offset),
+//     each and the squares split into two FP16 parts, the dominant products of which take
+//     the 16 slots of one 32x32x16 FP16 MFMA with FP32 sums: 1024 pairs per 8 passes.
+//   P = 32 (FP32 RCLL): the same coordinates in FP32, three 32x32x2 FP32 MFMAs.
+//   P = 64: binary64 positions less the first target's, one 16x16x4 FP64 MFMA per 256 pairs
+//     with |t|^2 - R^2 as its accumulator.
+// One funnel shift per 64 pairs moves D's sign bits into a lane's row bits (lane = target;
+// candidates are dealt to operand rows so that a lane's 16 results are consecutive ranks),
+// and half a three-way minimum watches |D|.
+//
+// Error of D against M, the sum of the magnitudes of its terms, M <= 2 (|c|^2 + |t|^2) + R^2,
+// bounded from the block's x-span: the products are exact (P = 16) or rounded once, the sum
+// of at most 16 errs by 2^-19 M (P = 16 and 32; any order, truncating; 2^-21.9 M measured
+// for the FP16 instruction) and 2^-49 M (P = 64), the FP16 splits by 2^-21 M, the
+// coordinates by 2^-22 M (2^-51 M). The bounds taken are 2^-18 M and 2^-46 M.
+//
+// What bounds it: VALU issue, about half of it the ranking. At 1M particles in 3D (64 targets
+// against 870 candidates per block, 28 tiles) the start took 251 us per launch (packed-FP16 tests
+// of each target's own 348 candidates, bits in union order), this 162; FP64 486 -> 280 us.
+// Wavefronts per block: in 2D a union has a few hundred candidates and the work that every
+// wavefront repeats (geometry, target operands) weighs more.
+template <int DIM>
+constexpr int kCountThreads = DIM == 3 ? 256 : 128;
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+// Geometry of a block, the same in every lane (scalar registers).
+template <int DIM>
+struct BlockGeom {
+    static constexpr int NSEG = Geom<DIM>::NSEG;
+    static constexpr int SELF = Geom<DIM>::SELF;
+    int p0, p1, U, xa, xb, y0, z0;  // xa, xb: the targets' first and last cell along x
+    int seg_g0[NSEG], seg_base[NSEG];
+    const SetDesc* sd;
+    __device__ __forceinline__ void init(const SearchArgs& a, int b)
     {
-        constexpr int kListBytes = kShared - C::UCAP * 2;
-        constexpr int LCAP = (kListBytes / NW / 6) & ~63;  // entries per wavefront
-        static_assert(LCAP >= 64, "a wavefront lists at least one word per lane");
-        uint32_t* lbits = reinterpret_cast<uint32_t*>(smem + C::UCAP * 2) + wv * LCAP;
-        uint16_t* ltw = reinterpret_cast<uint16_t*>(smem + C::UCAP * 2 + NW * LCAP * 4) + wv * LCAP;
-        auto drain = [&](int n) {
-            for (int e = lane; e < n; e += 64) {
-                uint32_t bits = lbits[e];
-                const int tw = ltw[e];
-                uint32_t* mt = masks + (tw & 63) * (C::MW + 1);
-                const int w32 = (tw >> 6) * 32;
-                // four bits per round: their rank lookups are issued together, and bits past
-                // the word's last read entry 0 and OR nothing
-                while (bits) {
-                    uint32_t rk[4], on[4];
+        auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+        sd = a.L.sets + uni(a.bset[b]);
+        const int coff = sd->coff;
+        const int* cs = a.cell_start + coff;
+        p0 = uni(a.bstart[b]);
+        p1 = uni(a.bstart[b + 1]);
+        const uint32_t ncx = static_cast<uint32_t>(sd->fr.nc[0]);
+        const int ncy = sd->fr.nc[1], ncz = sd->fr.nc[2];
+        const uint32_t k0 = static_cast<uint32_t>(uni(static_cast<int>(a.skey[p0])) - coff);
+        const uint32_t k1 = static_cast<uint32_t>(uni(static_cast<int>(a.skey[p1 - 1])) - coff);
+        const uint32_t row0 = k0 / ncx;
+        xa = static_cast<int>(k0 - row0 * ncx);
+        xb = static_cast<int>(k1 - row0 * ncx);  // the block lies in one row of cells
+        y0 = static_cast<int>(row0 % static_cast<uint32_t>(ncy));
+        z0 = static_cast<int>(row0 / static_cast<uint32_t>(ncy));
+        const int sx0 = max(xa - 1, 0), sx1 = min(xb + 1, static_cast<int>(ncx) - 1);
+        U = 0;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        on[j] = bits != 0u ? 1u : 0u;
-                        const int posl = w32 + __builtin_ctz(bits | (on[j] ? 0u : 1u));
-                        bits &= bits - 1u;
-                        rk[j] = rank_of[on[j] ? posl : 0];
-                    }
+        for (int r = 0; r < NSEG; ++r) {
+            const int yy = y0 + r % 3 - 1, zz = DIM == 3 ? z0 + r / 3 - 1 : 0;
+            const bool in = yy >= 0 && yy < ncy && zz >= 0 && zz < ncz;
+            const int rb = in ? (zz * ncy + yy) * static_cast<int>(ncx) : 0;
+            const int g0 = uni(cs[rb + sx0]), g1 = uni(cs[rb + sx1 + 1]);
+            seg_g0[r] = in ? g0 : 0;
+            seg_base[r] = U;
+            U += in ? g1 - g0 : 0;
+        }
+    }
+    __device__ __forceinline__ int global_of_any(int posl) const
+    {
+        int delta = seg_g0[0] - seg_base[0];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) atomicOr(&mt[rk[j] >> 5], on[j] << (rk[j] & 31));
+        for (int k = 1; k < NSEG; ++k)
+            if (posl >= seg_base[k]) delta = seg_g0[k] - seg_base[k];
+        return posl + delta;
+    }
+};
+
+// The FP16 parts v = h + l + (a residual of 2^-22 |v|), and two halves in a word.
+struct Split16 {
+    _Float16 h, l;
+    __device__ __forceinline__ explicit Split16(float v)
+        : h(static_cast<_Float16>(v)), l(static_cast<_Float16>(v - static_cast<float>(h)))
+    {
+    }
+};
+__device__ __forceinline__ uint32_t halves(_Float16 lo, _Float16 hi) { return as_u32(h2{lo, hi}); }
+
+// MFMA operands of one item per lane: words 0-3 hold slots 0-7, words 4-7 slots 8-15.
+// Candidates: xh xh xl xl yh yh yl zh | zh zl s0 s1 0 1 1 1, with s the squared norm;
+// targets (x = -2 x and so on): xh xl xh xl yh yl yh zh | zl zh 1 1 1 u0 u1 0, with u the
+// squared norm less 4 rho^2.
+__device__ __forceinline__ void candidate_words(float x, float y, float z, uint32_t (&w)[8])
+{
+    const Split16 X(x), Y(y), Z(z), S(x * x + y * y + z * z);
+    w[0] = halves(X.h, X.h);
+    w[1] = halves(X.l, X.l);
+    w[2] = halves(Y.h, Y.h);
+    w[3] = halves(Y.l, Z.h);
+    w[4] = halves(Z.h, Z.l);
+    w[5] = halves(S.h, S.l);
+    w[6] = 0x3C000000u;
+    w[7] = 0x3C003C00u;
+}
+__device__ __forceinline__ void target_words(float x, float y, float z, float rho4, uint32_t (&w)[8])
+{
+    const Split16 X(-2.0f * x), Y(-2.0f * y), Z(-2.0f * z), Uu(x * x + y * y + z * z - rho4);
+    w[0] = halves(X.h, X.l);
+    w[1] = w[0];
+    w[2] = halves(Y.h, Y.l);
+    w[3] = halves(Y.h, Z.h);
+    w[4] = halves(Z.l, Z.h);
+    w[5] = 0x3C003C00u;
+    w[6] = halves(static_cast<_Float16>(1.0f), Uu.h);
+    w[7] = halves(Uu.l, static_cast<_Float16>(0.0f));
+}
+// 4x4 transposes over the wavefront's quarters: out[i] of quarter q = in[q] of quarter i.
+__device__ __forceinline__ void swap32(uint32_t& a, uint32_t& b)
+{
+    const u32x2 v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = v[0];
+    b = v[1];
+}
+__device__ __forceinline__ void swap16(uint32_t& a, uint32_t& b)
+{
+    const u32x2 v = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = v[0];
+    b = v[1];
+}
+__device__ __forceinline__ void quarter_transpose(uint32_t (&v)[4])
+{
+    swap32(v[0], v[2]);
+    swap32(v[1], v[3]);
+    swap16(v[0], v[1]);
+    swap16(v[2], v[3]);
+}
+
+// The MFMA operands of 64 items, one prepared per lane, and 64 x 64 tests. load: the item's
+// coordinates; words: the two row words (candidates 0-31 and 32-63 of the step) of target
+// `lane`, with `decide(bnd, acc, e, t)` settling the results bnd (bits) of a lane whose 16
+// results are the step's candidates e.. against target t.
+template <int DIM, int P>
+struct Tiles;
+
+// P = 16: words 0-3 of an item hold slots 0-7, words 4-7 slots 8-15; an operand lane l holds
+// item l mod 32, slots 8 (l / 32) onwards. Operand row rho = 8 (r / 4) + 4 h + r mod 4 gives
+// result r of the lanes 32 h ..., and holds candidate 16 h + r.
+template <int DIM>
+struct Tiles<DIM, 16> {
+    using Rec = float4;  // a union record in LDS
+    struct Coord { float x, y, z; };
+    h8 t0, t1;
+    float beta;
+    static __device__ __forceinline__ int item(int lane)
+    {
+        return 16 * ((lane >> 2) & 1) + 4 * ((lane >> 3) & 3) + (lane & 3) + (lane & 32);
+    }
+    static __device__ __forceinline__ Rec fetch(const SearchArgs& a, int j) { return a.rq[j]; }
+    // coordinates about the block's centre, in half cell widths
+    static __device__ __forceinline__ Coord coords(const Rec& rec, const BlockGeom<DIM>& g)
+    {
+        // the low ten bits as a signed number: cell indices are kept mod 2^10
+        auto sbits10 = [](int v) { return static_cast<int>(static_cast<uint32_t>(v) << 22) >> 22; };
+        const int cb = __builtin_bit_cast(int, rec.w);
+        Coord c;
+        c.x = rec.x + static_cast<float>(2 * sbits10(cb - g.xa) + g.xa - g.xb);
+        c.y = rec.y + static_cast<float>(2 * sbits10((cb >> 10) - g.y0));
+        c.z = DIM == 3 ? rec.z + static_cast<float>(2 * sbits10((cb >> 20) - g.z0)) : 0.0f;
+        return c;
+    }
+    static __device__ __forceinline__ float bound(const BlockGeom<DIM>& g)
+    {
+        const float ht = static_cast<float>(g.xb - g.xa + 1);
+        return 0x1p-18f * (2.0f * (ht * ht + 2.0f + (ht + 2.0f) * (ht + 2.0f) + 18.0f) + 4.0f);
+    }
+    static __device__ __forceinline__ void fragments(uint32_t (&w)[8], h8& f0, h8& f1)
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) swap32(w[k], w[k + 4]);
+        f0 = __builtin_bit_cast(h8, make_uint4(w[0], w[1], w[2], w[3]));
+        f1 = __builtin_bit_cast(h8, make_uint4(w[4], w[5], w[6], w[7]));
+    }
+    __device__ __forceinline__ void targets(const Rec& rec, const BlockGeom<DIM>& g)
+    {
+        const Coord c = coords(rec, g);
+        uint32_t w[8];
+        target_words(c.x, c.y, c.z, g.sd->fr.t32_mid, w);
+        fragments(w, t0, t1);
+        beta = bound(g);
+    }
+    // the sign bits of D's 16 results, result r at bit r; decide settles those with |D| below
+    // the bound, if the wavefront has any
+    template <typename F>
+    static __device__ __forceinline__ uint32_t row_bits(const f32x16& D, float beta, F&& decide)
+    {
+        uint32_t acc = 0;
+        float m = fabsf(D[15]);
+#pragma unroll
+        for (int r = 15; r >= 0; --r) {
+            const float d = D[r];
+            acc = __builtin_amdgcn_alignbit(acc, __builtin_bit_cast(uint32_t, d), 31);
+        }
+#pragma unroll
+        for (int r = 0; r < 14; r += 2) m = fminf(fminf(m, fabsf(D[r])), fabsf(D[r + 1]));
+        m = fminf(m, fabsf(D[14]));
+        if (__builtin_amdgcn_ballot_w64(m < beta)) {
+            uint32_t bnd = 0;
+#pragma unroll
+            for (int r = 15; r >= 0; --r) {
+                const float d = fabsf(D[r]) - beta;
+                bnd = __builtin_amdgcn_alignbit(bnd, __builtin_bit_cast(uint32_t, d), 31);
+            }
+            acc = decide(bnd, acc);
+        }
+        return acc;
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    {
+        const Coord x = coords(rec, g);
+        uint32_t w[8];
+        candidate_words(x.x, x.y, x.z, w);
+        if (past) {  // past the list: far away
+            w[0] = w[1] = w[2] = w[3] = w[4] = 0u;
+            w[5] = 0x7800u;  // 32768
+        }
+        h8 c[2];
+        fragments(w, c[0], c[1]);
+        const int lane = threadIdx.x & 63, e = 16 * (lane >> 5), tl = lane & 31;
+        const f32x16 zero = {};
+        u32x2 out;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[t], t0, zero, 0, 0, 0);
+            const f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[t], t1, zero, 0, 0, 0);
+            uint32_t b0 = row_bits(D0, beta, [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * t + e, tl); });
+            uint32_t b1 = row_bits(D1, beta, [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * t + e, 32 + tl); });
+            swap32(b0, b1);
+            out[t] = b0 | (b1 << 16);
+        }
+        return out;
+    }
+};
+
+// P = 32: slots x y | z s | 1 0 (targets -2x -2y | -2z 1 | u 0), two per instruction; an
+// operand lane l holds item l mod 32, slot l / 32 of each pair.
+template <int DIM>
+struct Tiles<DIM, 32> : Tiles<DIM, 16> {
+    using B = Tiles<DIM, 16>;
+    using typename B::Coord;
+    using typename B::Rec;
+    float t[2][3];
+    static __device__ __forceinline__ void pair(float a, float b, float& f0, float& f1)
+    {
+        uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+        swap32(x, y);
+        f0 = __builtin_bit_cast(float, x);
+        f1 = __builtin_bit_cast(float, y);
+    }
+    __device__ __forceinline__ void targets(const Rec& rec, const BlockGeom<DIM>& g)
+    {
+        const Coord c = B::coords(rec, g);
+        pair(-2.0f * c.x, -2.0f * c.y, t[0][0], t[1][0]);
+        pair(-2.0f * c.z, 1.0f, t[0][1], t[1][1]);
+        pair(c.x * c.x + c.y * c.y + c.z * c.z - g.sd->fr.t32_mid, 0.0f, t[0][2], t[1][2]);
+        this->beta = B::bound(g);
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    {
+        Coord x = B::coords(rec, g);
+        float s = x.x * x.x + x.y * x.y + x.z * x.z;
+        if (past) {
+            x.x = x.y = x.z = 0.0f;
+            s = 0x1p60f;
+        }
+        float c[2][2];
+        pair(x.x, x.y, c[0][0], c[1][0]);
+        pair(x.z, s, c[0][1], c[1][1]);
+        const int lane = threadIdx.x & 63, e = 16 * (lane >> 5), tl = lane & 31;
+        const float one = lane < 32 ? 1.0f : 0.0f;
+        u32x2 out;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            uint32_t b[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                f32x16 D = {};
+                D = __builtin_amdgcn_mfma_f32_32x32x2f32(one, t[h][2], D, 0, 0, 0);
+                D = __builtin_amdgcn_mfma_f32_32x32x2f32(c[k][0], t[h][0], D, 0, 0, 0);
+                D = __builtin_amdgcn_mfma_f32_32x32x2f32(c[k][1], t[h][1], D, 0, 0, 0);
+                b[h] = B::row_bits(D, this->beta,
+                                   [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * k + e, 32 * h + tl); });
+            }
+            swap32(b[0], b[1]);
+            out[k] = b[0] | (b[1] << 16);
+        }
+        return out;
+    }
+};
+
+// P = 64: slots x y z s (targets -2x -2y -2z 1, accumulator |t|^2 - R^2); an operand lane l
+// holds item l mod 16, slot l / 16. Operand row rho = 4 r + q of tile i gives result r of the
+// wavefront's quarter q, and holds candidate 16 q + 4 i + r of the step's 64.
+template <int DIM>
+struct Tiles<DIM, 64> {
+    struct Rec { double x, y, z; };  // a union record in LDS
+    double t[4], u[4], ox, oy, oz;
+    int bhi;  // the high word of the bound, rounded up
+    static __device__ __forceinline__ int item(int lane)
+    {
+        return 16 * (lane & 3) + 4 * (lane >> 4) + ((lane >> 2) & 3);
+    }
+    static __device__ __forceinline__ Rec fetch(const SearchArgs& a, int j)
+    {
+        const double2* s = reinterpret_cast<const double2*>(a.spos + static_cast<size_t>(j) * 4);
+        const double2 xy = s[0];
+        return Rec{xy.x, xy.y, DIM == 3 ? s[1].x : 0.0};
+    }
+    // out[i]: component l / 16 of item 16 i + l mod 16
+    static __device__ __forceinline__ void fragments(const double (&v)[4], double (&out)[4])
+    {
+        uint32_t lo[4], hi[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint64_t q = __builtin_bit_cast(uint64_t, v[k]);
+            lo[k] = static_cast<uint32_t>(q);
+            hi[k] = static_cast<uint32_t>(q >> 32);
+        }
+        quarter_transpose(lo);
+        quarter_transpose(hi);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            out[k] = __builtin_bit_cast(double, static_cast<uint64_t>(hi[k]) << 32 | lo[k]);
+    }
+    __device__ __forceinline__ void targets(const Rec& rec, const BlockGeom<DIM>& g)
+    {
+        // the block's first target is the origin
+        auto first = [](double v) {
+            const uint64_t q = __builtin_bit_cast(uint64_t, v);
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(q));
+            const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(q >> 32));
+            return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+        };
+        ox = first(rec.x);
+        oy = first(rec.y);
+        oz = first(rec.z);
+        const double x = rec.x - ox, y = rec.y - oy, z = rec.z - oz;
+        const double v[4] = {-2.0 * x, -2.0 * y, -2.0 * z, 1.0};
+        fragments(v, t);
+        const double uu = x * x + y * y + z * z - g.sd->fr.R2;
+        // the accumulator of target tile k: u of target 16 k + l mod 16
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k] = __shfl(uu, 16 * k + static_cast<int>(threadIdx.x & 15), 64);
+        const double xs = static_cast<double>(g.xb - g.xa + 2), w = g.sd->fr.w;
+        const double beta = 0x1p-46 * w * w * (4.0 * (xs * xs + 8.0) + 1.0);
+        bhi = static_cast<int>(__builtin_bit_cast(uint64_t, beta) >> 32) + 1;
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    {
+        const double x = past ? 0.0 : rec.x - ox, y = past ? 0.0 : rec.y - oy, z = past ? 0.0 : rec.z - oz;
+        const double v[4] = {x, y, z, past ? 0x1p200 : x * x + y * y + z * z};
+        double c[4];
+        fragments(v, c);
+        const int lane = threadIdx.x & 63, nt = g.p1 - g.p0;
+        uint32_t b[4] = {0, 0, 0, 0};
+        // non-negative doubles order like their high words read as floats
+        const float below = __builtin_bit_cast(float, bhi);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (16 * k >= nt) break;
+            const f64x4 acc0 = {u[k], u[k], u[k], u[k]};
+            float hi[16];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f64x4 D = __builtin_amdgcn_mfma_f64_16x16x4f64(c[i], t[k], acc0, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double d = D[r];
+                    hi[4 * i + r] = __builtin_bit_cast(float, static_cast<uint32_t>(__builtin_bit_cast(uint64_t, d) >> 32));
                 }
             }
-        };
-        int qn = 0;
+            uint32_t acc = 0;
+            float m = fabsf(hi[15]);
 #pragma unroll
-        for (int k = 0; k < KW; ++k) {
-            const int w = wv + NW * k;
-            const uint32_t word = g.active ? wbits[k] : 0u;
-            const uint64_t nz = __builtin_amdgcn_ballot_w64(word != 0u);
-            const int add = __builtin_popcountll(nz);
-            if (qn + add > LCAP) {  // wave-uniform
-                drain(qn);
-                qn = 0;
+            for (int r = 15; r >= 0; --r)
+                acc = __builtin_amdgcn_alignbit(acc, __builtin_bit_cast(uint32_t, hi[r]), 31);
+#pragma unroll
+            for (int r = 0; r < 14; r += 2) m = fminf(fminf(m, fabsf(hi[r])), fabsf(hi[r + 1]));
+            m = fminf(m, fabsf(hi[14]));
+            if (__builtin_amdgcn_ballot_w64(!(m >= below))) {  // also where squares overflow
+                uint32_t bnd = 0;
+#pragma unroll
+                for (int r = 15; r >= 0; --r) bnd = (bnd << 1) | (fabsf(hi[r]) >= below ? 0u : 1u);
+                acc = decide(bnd, acc, 16 * (lane >> 4), 16 * k + (lane & 15));
             }
-            if (word) {
-                const int at = qn + static_cast<int>(__builtin_amdgcn_mbcnt_hi(
-                                        static_cast<uint32_t>(nz >> 32),
-                                        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(nz), 0u)));
-                lbits[at] = word;
-                ltw[at] = static_cast<uint16_t>(lane | (w << 6));
-            }
-            qn += add;
+            b[k] = acc;
         }
-        drain(qn);
+        quarter_transpose(b);
+        return u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
     }
-    // the target's own bit (set by the count pass when it accepted the target itself) is
-    // masked out below
-    const int rself = g.active ? rank_of[g.pself] : -1;
-    __syncthreads();
-    // 4. compaction: each target's mask walked in rank order into the block's flat list;
-    // wavefront wv takes word quarter wv, after the popcounts of the quarters before it
-    const int nw = (U + 31) >> 5;
-    const int qw = (nw + NW - 1) / NW;
-    const int wa = wv * qw, wb = min(nw, wa + qw);
-    const int wself = rself >> 5;
-    const uint32_t keep_self = ~(1u << (rself & 31));
-    auto word = [&](int w) { return mk[w] & (w == wself ? keep_self : ~0u); };
-    int cnt = 0;
-    if (g.active)
-        for (int w = wa; w < wb; ++w) cnt += __builtin_popcount(word(w));
-    spart[wv][lane] = cnt;
-    __syncthreads();  // rank table dead from here on: the flat list reuses its space
-    if (g.active) {
-        int got = 0;
-        for (int q = 0; q < wv; ++q) got += spart[q][lane];
-        for (int w = wa; w < wb; ++w) {
-            uint32_t bits = word(w);
-            while (bits) {
-                const int bi = __builtin_ctz(bits);
-                bits &= bits - 1;
-                if (got < rlen) flat[off + got] = static_cast<uint16_t>((lane << C::SHIFT) | (w * 32 + bi));
-                ++got;
-            }
-        }
-        if (wv == NW - 1 && got != rlen) atomicOr(a.err, kErrLongRow);
-    }
-    __syncthreads();
-    // 5. emission, 64 entries per round, rounds dealt to the wavefronts in turn. Later
-    // rounds' gathers are issued before this round's stores, and every round issues the
-    // same memory instructions on every path. Vector-memory counters count loads and
-    // stores in issue order, so with a fixed instruction count the wait for the prefetch
-    // need not include the previous round's stores.
-    struct Ent {
-        int t, oj;
-        long long idx;
-        double xj[DIM];
-    };
-    auto gather = [&](Ent& s) {
-#pragma unroll
-        for (int c = 0; c < DIM; ++c)
-            s.xj[c] = MODE == 1 ? sd.pos[static_cast<size_t>(s.oj - sd.poff) * DIM + c]
-                                : a.X[static_cast<size_t>(s.oj) * x_stride(DIM) + c];
-    };
-    auto distance = [&](const Ent& s) -> float {
-        if constexpr (MODE == 1) {
-            double pi2[3], pj2[3];
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                pi2[c] = sxi[s.t * DIM + c];
-                pj2[c] = s.xj[c];
-            }
-            return static_cast<float>(__dsqrt_rn(r2_fp64<DIM>(pi2, pj2)));
-        } else {
-            float s2 = 0.0f;
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                const float f = static_cast<float>(s.xj[c] - sxi[s.t * DIM + c]);  // exact difference, one rounding
-                s2 = s2 + f * f;
-            }
-            return __builtin_amdgcn_sqrtf(s2) * dist_scale;  // <= 1 ulp; s2 >= 1 or 0
-        }
-    };
-    constexpr int R = 64 * NW;  // stride between a wavefront's rounds
-    const int64_t cap = sd.capacity;
-    const long long rend = g.active ? rs + rlen : 0;  // the row's end in the output
-    if (wave_max_i64(rend) <= cap) {
-        // every row fits the output: lanes past the list repeat the list's last entry (the
-        // same values to the same place), so no address is ever switched
-        auto fetch = [&](int e, Ent& s) {
-            const uint32_t f = flat[min(e, E - 1)];
-            s.t = static_cast<int>(f >> C::SHIFT);
-            s.oj = sorig[f & (C::UCAP - 1)];
-            s.idx = sbase[s.t] + min(e, E - 1);
-            gather(s);
-        };
-        auto emit = [&](const Ent& s) {
-            const float d = distance(s);
-            sd.col[s.idx] = s.oj - sd.poff;
-            sd.dist[s.idx] = d;
-        };
-        // four entry sets in rotation: the fetch three rounds ahead never waits for a copy
-        Ent A, B, Cn, D;
-        int e0 = wv * 64;
-        if (e0 < E) {
-            fetch(e0 + lane, A);
-            fetch(e0 + R + lane, B);
-            fetch(e0 + 2 * R + lane, Cn);
-            for (;;) {
-                fetch(e0 + 3 * R + lane, D);
-                emit(A);
-                if ((e0 += R) >= E) break;
-                fetch(e0 + 3 * R + lane, A);
-                emit(B);
-                if ((e0 += R) >= E) break;
-                fetch(e0 + 3 * R + lane, B);
-                emit(Cn);
-                if ((e0 += R) >= E) break;
-                fetch(e0 + 3 * R + lane, Cn);
-                emit(D);
-                if ((e0 += R) >= E) break;
-            }
-        }
+};
+
+template <int DIM, int P, bool HALF>
+__global__ void __launch_bounds__(kCountThreads<DIM>) __attribute__((amdgpu_waves_per_eu(P == 64 ? 4 : 5)))
+k_count(SearchArgs a)
+{
+    constexpr int UCAP = FillCfg<DIM>::UCAP;
+    constexpr int NW = kCountThreads<DIM> / 64;
+    constexpr int EPT = UCAP / kCountThreads<DIM>;
+    using T = Tiles<DIM, P>;
+    using Rec = typename T::Rec;
+    // the ranking's scratch, then the union's records by rank
+    constexpr int kShared = kRankScratch<UCAP> > UCAP * static_cast<int>(sizeof(Rec))
+                                ? kRankScratch<UCAP> : UCAP * static_cast<int>(sizeof(Rec));
+    __shared__ __attribute__((aligned(16))) unsigned char scratch[kShared];
+    __shared__ int slist[UCAP];  // sorted positions by rank (the ranking's ranks before)
+    __shared__ int srself[64];   // the targets' own ranks
+    __shared__ int sred[2][NW];
+    __shared__ int swsum[NW];
+    __shared__ int spart[NW][64];
+    const int b = xcd_block(*a.nblk);
+    if (b < 0) return;
+    if (dense_block(a, b)) {
+        if (threadIdx.x < 64) write_desc_dense(a, b);
         return;
     }
-    // some row ends past the output capacity: entries there (and lanes past the list)
-    // store to a per-lane sink slot, and the capacity error is raised
-    NNPS_GLOBAL int32_t* sink_col = (NNPS_GLOBAL int32_t*)a.sink + 2 * lane;
-    NNPS_GLOBAL float* sink_dist = (NNPS_GLOBAL float*)(a.sink + 2 * lane + 1);
-    auto fetch = [&](int e, Ent& s) {
-        // every read stays inside its table whatever e is, so no branch is needed: entries
-        // past the list read stale values that the selects below discard
-        const bool ok = e < E;
-        const uint32_t f = flat[min(e, C::FCAP - 1)];
-        const int t = static_cast<int>(f >> C::SHIFT) & 63;
-        const int o = sorig[f & (C::UCAP - 1)];
-        const long long base = sbase[t];
-        s.t = t;
-        s.oj = ok ? o : sd.poff;
-        s.idx = ok ? base + e : -1;
-        gather(s);
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    BlockGeom<DIM> g;
+    g.init(a, b);
+    if (wv == 0) write_desc<DIM>(a, g, b);
+    const int U = g.U, nt = g.p1 - g.p0;
+    Rec* const srec = reinterpret_cast<Rec*>(scratch);
+    const Rec trec = T::fetch(a, g.p0 + min(lane, nt - 1));
+    // blocks with a larger union keep no bits (their rows take the long-row path): counted
+    // in union order, unranked
+    const bool ranked = U <= UCAP;
+    int rself = g.seg_base[g.SELF] + (g.p0 + lane - g.seg_g0[g.SELF]);
+    if (ranked) {
+        // the union's indices and records, in union order (contiguous along x)
+        int gi[EPT], og[EPT], rk[EPT];
+        Rec rec[EPT];
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) gi[i] = g.global_of_any(min(tid + i * kCountThreads<DIM>, U - 1));
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) og[i] = a.perm[gi[i]];
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) rec[i] = T::fetch(a, gi[i]);
+        rank_originals<UCAP, FillCfg<DIM>::SHIFT, NW>(U, og, scratch, sred, swsum, reinterpret_cast<uint16_t*>(slist),
+                                                      rk);
+        const int self0 = g.seg_base[g.SELF] + (g.p0 - g.seg_g0[g.SELF]);  // the first target's union position
+        uint16_t* ranks = a.branks + static_cast<size_t>(b) * UCAP;
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            const int e = tid + i * kCountThreads<DIM>;
+            if (e < U) {
+                srec[rk[i]] = rec[i];
+                slist[rk[i]] = gi[i];
+                ranks[e] = static_cast<uint16_t>(rk[i]);
+                if (static_cast<unsigned>(e - self0) < static_cast<unsigned>(nt)) srself[e - self0] = rk[i];
+            }
+        }
+        __syncthreads();
+        rself = lane < nt ? srself[lane] : 0;
+    }
+    T tiles;
+    tiles.targets(trec, g);
+    const double R2 = g.sd->fr.R2;
+    const int mi = T::item(lane);
+    int cnt = 0;
+    for (int c0 = 0; c0 < U; c0 += UCAP) {  // one pass when ranked
+        const int m = min(UCAP, U - c0);
+        if (!ranked) {
+            __syncthreads();
+            for (int e = tid; e < m; e += kCountThreads<DIM>) {
+                slist[e] = g.global_of_any(c0 + e);
+                srec[e] = T::fetch(a, slist[e]);
+            }
+            __syncthreads();
+        }
+        // 64 list entries a step, steps dealt to the wavefronts
+#pragma unroll 1
+        for (int s = wv; 64 * s < m; s += NW) {
+            const Rec rec = srec[min(64 * s + mi, m - 1)];
+            auto decide = [&](uint32_t bnd, uint32_t acc, int e0, int t) -> uint32_t {
+                const double* pi = a.spos + static_cast<size_t>(g.p0 + min(t, nt - 1)) * 4;
+                while (bnd) {
+                    const int r = __builtin_ctz(bnd);
+                    bnd &= bnd - 1u;
+                    const int e = 64 * s + e0 + r;
+                    if (e < m) {
+                        const bool in = recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
+                        acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
+                    }
+                }
+                return acc;
+            };
+            const u32x2 ww = tiles.words(rec, g, 64 * s + mi >= m, decide);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int tile = 2 * s + k;
+                uint32_t word = ww[k];
+                // the target itself is no neighbour; half lists keep larger original indices
+                const int d = rself - c0 - 32 * tile;
+                if (HALF && ranked) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
+                else word &= (d >= 0 && d < 32) ? ~(1u << d) : ~0u;
+                if (HALF && !ranked && lane < nt) {
+                    const int oi = a.perm[g.p0 + lane];
+                    for (uint32_t q = word; q; q &= q - 1u) {
+                        const int j = __builtin_ctz(q);
+                        if (a.perm[slist[32 * tile + j]] < oi) word &= ~(1u << j);
+                    }
+                }
+                cnt += __builtin_popcount(word);
+                if (ranked && lane < nt && 32 * tile < m)
+                    a.cbits[static_cast<size_t>(tile) * a.L.ntot + g.p0 + lane] = word;
+            }
+        }
+    }
+    spart[wv][lane] = cnt;
+    __syncthreads();
+    if (tid < nt) {
+        int c = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) c += spart[q][tid];
+        a.counts[a.perm[g.p0 + tid]] = c;
+        a.counts_s[g.p0 + tid] = c;
+    }
+}
+
+constexpr int kFillThreads = 256;  // four wavefronts share one block's union
+
+// Fill pass. The union's positions and set-local indices are staged in LDS in rank order;
+// then each wavefront works alone on sixteen of the block's targets: their accepted
+// candidates (the count pass's bits, in rank order; lane = target and quarter of the row's
+// words) are compacted into its flat list of 16-bit entries (target << 10 | rank), as many
+// quarter rows at a time as the list holds, and written 64 entries per store, the entries'
+// gathers being LDS reads. One workgroup barrier per block and 26 KB of LDS, so that
+// memory, LDS and vector work overlap over six workgroups per compute unit (lists of 512 entries
+// fit seven, but walk the words twice: 222 against 213 us).
+// F64: positions in binary64, distances (float)sqrt(r2) in binary64. Otherwise the low 32 bits
+// of the positions in units of 2^-30 or so of a cell width (Frame::quantum), one 16-byte
+// record per candidate: neighbours lie fewer than 2^31 units apart, so the difference mod
+// 2^32 is exact, and is rounded once to FP32; pairs so near that the unit would show are
+// recomputed from the binary64 positions. The stores are non-temporal: the lists would
+// otherwise push the positions, bits and lists of the next blocks out of the L2s.
+// What bounds it: vector issue and HBM about evenly. At 1M particles in 3D (60 M entries, 728 MB
+// of DRAM traffic, 78 M vector instructions): 322 us with the ranking and gathers from global
+// memory here, 213 now; 2D 93 -> 60, binary64 321 -> 244 us.
+template <int DIM, bool F64>
+__global__ void __launch_bounds__(kFillThreads) __attribute__((amdgpu_waves_per_eu(F64 ? 4 : 6)))
+k_fill(SearchArgs a)
+{
+    using C = FillCfg<DIM>;
+    constexpr int NW = kFillThreads / 64;
+    constexpr int EPT = C::UCAP / kFillThreads;
+    constexpr int KW = C::MW / 4;  // bit words per lane
+    constexpr int TW = 64 / NW;    // targets per wavefront
+    static_assert(TW == 16, "a lane's target is its place in a row of 16 lanes");
+    constexpr int FW = C::FLAT;
+    static_assert(FW >= 32 * KW, "a quarter row fits the list");
+    __shared__ uint16_t sflat[NW][FW];
+    __shared__ int4 srec[F64 ? 1 : C::UCAP];          // position, set-local index, by rank
+    __shared__ double spos[F64 ? DIM * C::UCAP : 1];  // axis-major, by rank
+    __shared__ int sorig[F64 ? C::UCAP : 1];          // set-local index by rank
+    __shared__ int4 strec[F64 ? 1 : 64];              // the targets' positions
+    __shared__ double sxi[F64 ? 64 * DIM : 1];
+    __shared__ long long sbase[64];  // row start in the output minus the row's flat offset
+
+    const int b = xcd_block(*a.nblk);
+    if (b < 0) return;
+    // the block's geometry from the count pass's descriptor (wave-uniform), and each
+    // target's row start and length in sorted order: no chain of dependent loads
+    const NNPS_CONST int* dsc = (const NNPS_CONST int*)(a.bdesc + static_cast<size_t>(b) * kDescInts);
+    if (dsc[4]) return;  // a block of the dense-cell path
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wavefront index, uniform
+    const int p0 = dsc[0], nt = dsc[1] - p0, U = dsc[3];
+    if (U > C::UCAP) {
+        // too big for this path: every row of the block goes to the long-row path
+        if (tid < nt) a.heavy[atomicAdd(a.nheavy, 1)] = p0 + tid;
+        return;
+    }
+    const NNPS_CONST SetDesc& sd = ((const NNPS_CONST SetDesc*)a.L.sets)[dsc[2]];
+    // this lane's target and quarter of its row's words
+    const int tg = wv * TW + (lane & 15), quarter = lane >> 4;
+    const bool active = tg < nt;
+    const int pt = p0 + min(tg, nt - 1);
+    const int nw = (U + 31) >> 5, qw = (nw + 3) >> 2, wa = quarter * qw;
+    // union position -> sorted position, from the segments' first particles and union offsets
+    auto global_of = [&](int posl) {
+        constexpr int NSEG = Geom<DIM>::NSEG;
+        int delta = dsc[5] - dsc[5 + NSEG];
+#pragma unroll
+        for (int k = 1; k < NSEG; ++k)
+            if (posl >= dsc[5 + NSEG + k]) delta = dsc[5 + k] - dsc[5 + NSEG + k];
+        return posl + delta;
     };
-    Ent cur, n1;
-    fetch(wv * 64 + lane, cur);
-    fetch(wv * 64 + R + lane, n1);
-    for (int e0 = wv * 64; e0 < E; e0 += R) {
-        Ent n2;
-        fetch(e0 + 2 * R + lane, n2);
-        const float d = distance(cur);
-        const bool valid = cur.idx >= 0 && cur.idx < cap;
-        if (cur.idx >= cap) atomicOr(a.err, kErrCapacity);
-        NNPS_GLOBAL int32_t* pc = valid ? sd.col + cur.idx : sink_col;
-        NNPS_GLOBAL float* pd = valid ? sd.dist + cur.idx : sink_dist;
-        *pc = cur.oj - sd.poff;
-        *pd = d;
-        cur = n1;
-        n1 = n2;
+    int rank[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i)
+        rank[i] = a.branks[static_cast<size_t>(b) * C::UCAP + min(tid + i * kFillThreads, U - 1)];
+    uint32_t wbits[KW];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) wbits[k] = a.cbits[static_cast<size_t>(min(wa + k, nw - 1)) * a.L.ntot + pt];
+    const long long rs = a.rsort[pt];
+    int rlen = a.counts_s[pt];
+    struct Raw {
+        double2 lo, hi;
+    };
+    auto raw = [&](int j) {
+        const double2* s = reinterpret_cast<const double2*>(a.spos + static_cast<size_t>(j) * 4);
+        return Raw{s[0], s[1]};
+    };
+    const double inv_quantum = sd.fr.inv_quantum;
+    const double lo[3] = {sd.fr.lo[0], sd.fr.lo[1], sd.fr.lo[2]};
+    auto fixed = [&](double x, int k) { return in_quanta(x, lo[k], inv_quantum); };
+    auto packed = [&](const Raw& r, int w) {
+        return make_int4(fixed(r.lo.x, 0), fixed(r.lo.y, 1), DIM == 3 ? fixed(r.hi.x, 2) : 0, w);
+    };
+    // 1. the union and the targets to LDS, a thread's gathers issued together
+    {
+        const int poff = sd.poff;
+        Raw r[EPT];
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) r[i] = raw(global_of(min(tid + i * kFillThreads, U - 1)));
+        const Raw t = raw(p0 + min(tid, nt - 1));
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            const int e = tid + i * kFillThreads;
+            const int oj = static_cast<int>(__builtin_bit_cast(int64_t, r[i].hi.y)) - poff;
+            if (e >= U) continue;
+            if (F64) {
+                spos[rank[i]] = r[i].lo.x;
+                spos[C::UCAP + rank[i]] = r[i].lo.y;
+                if (DIM == 3) spos[2 * C::UCAP + rank[i]] = r[i].hi.x;
+                sorig[rank[i]] = oj;
+            } else {
+                srec[rank[i]] = packed(r[i], oj);
+            }
+        }
+        if (tid < 64) {
+            if (F64) {
+                sxi[tid * DIM] = t.lo.x;
+                sxi[tid * DIM + 1] = t.lo.y;
+                if (DIM == 3) sxi[tid * DIM + 2] = t.hi.x;
+            } else {
+                strec[tid] = packed(t, 0);
+            }
+        }
+    }
+    // the rows' places: off among the wavefront's sixteen rows, before among the row's quarters
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+        if (!(active && k < qw && wa + k < nw)) wbits[k] = 0u;
+        cnt += __builtin_popcount(wbits[k]);
+    }
+    if (!active) rlen = 0;
+    int incl = rlen;  // inclusive over the 16 lanes of a row
+    incl += dpp<0x111>(0, incl);
+    incl += dpp<0x112>(0, incl);
+    incl += dpp<0x114>(0, incl);
+    incl += dpp<0x118>(0, incl);
+    const int off = incl - rlen;
+    if (lane < TW) sbase[tg] = rs - off;
+    int before = 0;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int c = __shfl(cnt, 16 * q + (lane & 15), 64);
+        if (q < quarter) before += c;
+    }
+    // a row whose bits do not match its count writes nothing
+    const bool bad = __shfl(before + cnt, 48 + (lane & 15), 64) != rlen;
+    if (bad) atomicOr(a.err, kErrLongRow);
+    __syncthreads();
+    NNPS_GLOBAL int32_t* const col = (NNPS_GLOBAL int32_t*)sd.col;
+    NNPS_GLOBAL float* const dist = (NNPS_GLOBAL float*)sd.dist;
+    const int64_t cap = sd.capacity;
+    const long long rend = active ? rs + rlen : 0;  // the row's end in the output
+    const bool room = __builtin_amdgcn_ballot_w64(rend > cap || bad) == 0;
+    if (!room && rend > cap) atomicOr(a.err, kErrCapacity);
+    const float quantum = sd.fr.quantum, near2 = sd.fr.near2;
+    uint16_t* const flat = sflat[wv];
+    // the lane's quarter row among the wavefront's entries
+    const int u0 = off + before, u1 = u0 + cnt;
+    for (int o0 = 0;;) {
+        // the quarter rows from o0 up to the list's capacity
+        const bool mine = u0 >= o0 && u1 - o0 <= FW;
+        const int o1 = wave_max_i32(mine ? u1 : o0);
+        if (o1 == o0) break;
+        // 2. compaction: each row's bits walked in rank order
+        if (mine) {
+            uint16_t* f = flat + (u0 - o0);
+            const uint32_t tag0 = static_cast<uint32_t>((lane & 15) << 10);
+#pragma unroll
+            for (int k = 0; k < KW; ++k) {
+                uint32_t bits = wbits[k];
+                const uint32_t tag = tag0 | static_cast<uint32_t>((wa + k) * 32);
+                while (bits) {
+                    *f++ = static_cast<uint16_t>(tag | __builtin_ctz(bits));
+                    bits &= bits - 1u;
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        // 3. emission: consecutive lanes write consecutive entries, two entries of a lane in
+        // flight (entries past the list repeat its last one)
+        const int n = o1 - o0;
+        constexpr int Q = 2;
+        for (int e0 = lane; e0 < n; e0 += Q * 64) {
+            int t[Q], rk[Q], oj[Q];
+            long long idx[Q];
+            float d[Q];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const uint32_t f = flat[min(e0 + q * 64, n - 1)];
+                t[q] = wv * TW + static_cast<int>(f >> 10);
+                rk[q] = static_cast<int>(f & 1023u);
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                idx[q] = sbase[t[q]] + (o0 + min(e0 + q * 64, n - 1));
+                if constexpr (F64) {
+                    double xi[3], xj[3];
+#pragma unroll
+                    for (int k = 0; k < DIM; ++k) {
+                        xj[k] = spos[k * C::UCAP + rk[q]];
+                        xi[k] = sxi[t[q] * DIM + k];
+                    }
+                    oj[q] = sorig[rk[q]];
+                    d[q] = dist_fp64<DIM>(xi, xj);
+                } else {
+                    const int4 j = srec[rk[q]];
+                    oj[q] = j.w;
+                    d[q] = quanta2<DIM>(strec[t[q]], j);
+                }
+            }
+            if constexpr (!F64) {
+                float least = d[0];
+#pragma unroll
+                for (int q = 1; q < Q; ++q) least = fminf(least, d[q]);
+                const bool near = !(least >= near2);
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const float s2 = d[q];
+                    d[q] = __builtin_amdgcn_sqrtf(s2) * quantum;  // <= 1 ulp, then exact
+                    if (near && !(s2 >= near2))
+                        d[q] = dist_near<DIM>(a.spos + static_cast<size_t>(p0 + t[q]) * 4,
+                                              (const double*)sd.pos + static_cast<size_t>(oj[q]) * DIM, inv_quantum,
+                                              quantum);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (room || idx[q] < cap) {
+                    col[idx[q]] = oj[q];
+                    dist[idx[q]] = d[q];
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        o0 = o1;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Long rows (blocks whose union, entry count or candidate count exceed the fill's
-// limits): one workgroup per target. Its candidates are tested across the workgroup and
+// Long rows (blocks whose union exceeds the fill's limit): one workgroup per target. Its candidates are tested in binary64 across the workgroup and
 // the accepted original indices appended to the row in any order; the row is then sorted
 // in place (LDS bitonic network for up to lr_keys entries, in which every comparator puts
 // the smaller key first so padding at +inf never moves; longer rows are sorted in chunks
@@ -1681,8 +1793,7 @@ k_long(SearchArgs a)
         const int rlen = static_cast<int>(sd.row_ptr[li + 1] - rs);
         double pi[3] = {0, 0, 0};
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) pi[k] = sd.pos[static_cast<size_t>(li) * DIM + k];
-        const ushort4 qi = a.q4[p];
+        for (int k = 0; k < DIM; ++k) pi[k] = a.spos[static_cast<size_t>(p) * 4 + k];
         if (threadIdx.x == 0) fill = 0;
         __syncthreads();
         const bool room = rs + rlen <= sd.capacity;
@@ -1697,35 +1808,10 @@ k_long(SearchArgs a)
             if (yy < 0 || yy >= ncy || zz < 0 || zz >= ncz) continue;
             const int rb = (zz * ncy + yy) * static_cast<int>(ncx);
             const int ga = cs[rb + lx0], gb = cs[rb + lx1 + 1];
-            const _Float16 ay = as_f16(qi.y) + static_cast<_Float16>(-2 * dy);
-            const _Float16 az = as_f16(qi.z) + static_cast<_Float16>(-2 * dz);
             for (int j = ga + static_cast<int>(threadIdx.x); j < gb; j += T) {
                 if (j == p) continue;
-                bool nb;
+                const bool nb = recheck_sorted<DIM>(a.spos, pi, j, fr.R2);
                 const int oj = a.perm[j];
-                if (MODE == 1) {
-                    nb = r2_fp64<DIM>(a.spos + static_cast<size_t>(p) * 4, a.spos + static_cast<size_t>(j) * 4) <= fr.R2;
-                } else {
-                    const ushort4 v = a.q4[j];
-                    const uint32_t kj = a.skey[j] - scoff;
-                    const int cjx = static_cast<int>(kj - (kj / ncx) * ncx);
-                    const _Float16 s = as_f16(qi.x) - as_f16(v.x);
-                    const _Float16 tx = s + static_cast<_Float16>(2 * (x - cjx));
-                    const _Float16 ty = ay - as_f16(v.y);
-                    _Float16 r2;
-                    if (DIM == 3) {
-                        const _Float16 tz = az - as_f16(v.z);
-                        r2 = tz * tz;
-                        r2 = __builtin_fmaf16(ty, ty, r2);
-                    } else {
-                        r2 = ty * ty;
-                    }
-                    r2 = __builtin_fmaf16(tx, tx, r2);
-                    const uint16_t r2h = __builtin_bit_cast(uint16_t, r2);
-                    const bool in16 = r2h < fr.t_lo;
-                    const bool band = !in16 && r2h <= fr.t_hi;
-                    nb = (MODE == 2 || band) ? recheck_g<DIM>(sd.pos, pi, oj - sd.poff, fr.R2) : in16;
-                }
                 if (nb && (!a.half || oj > oi)) {
                     const int slot = atomicAdd(&fill, 1);
                     if (slot < rlen && room) col[slot] = oj - sd.poff;
@@ -1815,9 +1901,22 @@ k_long(SearchArgs a)
         }
         // 3. distances of the sorted row
         for (int e = threadIdx.x; e < L; e += T) {
-            const int lj = col[e];
-            sd.dist[rs + e] = MODE == 1 ? dist_fp64<DIM>(sdesc.pos, li, lj)
-                                        : dist_fixed<DIM>(a.X, oi, lj + sd.poff, fr.dist_scale);
+            double pj[3] = {0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < DIM; ++k) pj[k] = sd.pos[static_cast<size_t>(col[e]) * DIM + k];
+            float d;
+            if (MODE == 1) {
+                d = dist_fp64<DIM>(pi, pj);
+            } else {  // as the block path's fill: which rows come here depends on the block table
+                auto fixed = [&](const double* x) {
+                    return make_int4(in_quanta(x[0], fr.lo[0], fr.inv_quantum), in_quanta(x[1], fr.lo[1], fr.inv_quantum),
+                                     DIM == 3 ? in_quanta(x[2], fr.lo[2], fr.inv_quantum) : 0, 0);
+                };
+                const float s2 = quanta2<DIM>(fixed(pi), fixed(pj));
+                d = s2 >= fr.near2 ? __builtin_amdgcn_sqrtf(s2) * fr.quantum
+                                   : dist_near<DIM>(pi, pj, fr.inv_quantum, fr.quantum);
+            }
+            sd.dist[rs + e] = d;
         }
         __syncthreads();
     }
@@ -1828,36 +1927,47 @@ k_long(SearchArgs a)
 // every block of any count up to nblk_max.
 static dim3 block_grid(int nblk_max) { return dim3((nblk_max + kXcds - 1) / kXcds * kXcds); }
 
+template <int DIM, bool HALF>
+void launch_count_mode(const SearchArgs& a, int mode, const dim3& g, hipStream_t st)
+{
+    const dim3 b(kCountThreads<DIM>);
+    if (mode == 0) hipLaunchKernelGGL((k_count<DIM, 16, HALF>), g, b, 0, st, a);
+    else if (mode == 3) hipLaunchKernelGGL((k_count<DIM, 32, HALF>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_count<DIM, 64, HALF>), g, b, 0, st, a);
+}
+
+template <int DIM>
+void launch_block_stats(const SearchArgs& a, const dim3& g, hipStream_t st)
+{
+    const int m = a.L.mode;
+    if (m == 0) hipLaunchKernelGGL((k_stats16<DIM, 0>), g, dim3(64), 0, st, a);
+    else if (m == 1) hipLaunchKernelGGL((k_stats64<DIM>), g, dim3(64), 0, st, a);
+    else if (m == 2) hipLaunchKernelGGL((k_stats16<DIM, 2>), g, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((k_stats32<DIM>), g, dim3(64), 0, st, a);
+}
+
 hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st)
 {
     if (a.L.ntot == 0 || nblk_max == 0) return hipSuccess;
-    const dim3 g = block_grid(nblk_max), b(64);
+    const dim3 g = block_grid(nblk_max);
     const int d = a.L.dim, m = a.L.mode;
     if (a.half) {
-        if (d == 2 && m == 0) hipLaunchKernelGGL((k_count16<2, 0, true>), g, b, 0, st, a);
-        else if (d == 3 && m == 0) hipLaunchKernelGGL((k_count16<3, 0, true>), g, b, 0, st, a);
-        else if (d == 2 && m == 2) hipLaunchKernelGGL((k_count16<2, 2, true>), g, b, 0, st, a);
-        else if (d == 3 && m == 2) hipLaunchKernelGGL((k_count16<3, 2, true>), g, b, 0, st, a);
-        else if (d == 2 && m == 3) hipLaunchKernelGGL((k_count32<2, true>), g, b, 0, st, a);
-        else if (d == 3 && m == 3) hipLaunchKernelGGL((k_count32<3, true>), g, b, 0, st, a);
-        else if (d == 2) hipLaunchKernelGGL((k_count64<2, true>), g, b, 0, st, a);
-        else hipLaunchKernelGGL((k_count64<3, true>), g, b, 0, st, a);
-        return hipGetLastError();
+        if (d == 2) launch_count_mode<2, true>(a, m, g, st);
+        else launch_count_mode<3, true>(a, m, g, st);
+    } else {
+        if (d == 2) launch_count_mode<2, false>(a, m, g, st);
+        else launch_count_mode<3, false>(a, m, g, st);
     }
-    if (d == 2 && m == 0) hipLaunchKernelGGL((k_count16<2, 0, false>), g, b, 0, st, a);
-    else if (d == 3 && m == 0) hipLaunchKernelGGL((k_count16<3, 0, false>), g, b, 0, st, a);
-    else if (d == 2 && m == 2) hipLaunchKernelGGL((k_count16<2, 2, false>), g, b, 0, st, a);
-    else if (d == 3 && m == 2) hipLaunchKernelGGL((k_count16<3, 2, false>), g, b, 0, st, a);
-    else if (d == 2 && m == 3) hipLaunchKernelGGL((k_count32<2, false>), g, b, 0, st, a);
-    else if (d == 3 && m == 3) hipLaunchKernelGGL((k_count32<3, false>), g, b, 0, st, a);
-    else if (d == 2) hipLaunchKernelGGL((k_count64<2, false>), g, b, 0, st, a);
-    else hipLaunchKernelGGL((k_count64<3, false>), g, b, 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_stats(const SearchArgs& a, hipStream_t st)
+hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st)
 {
     if (a.L.ntot == 0) return hipSuccess;
+    if (nblk_max > 0) {
+        if (a.L.dim == 2) launch_block_stats<2>(a, block_grid(nblk_max), st);
+        else launch_block_stats<3>(a, block_grid(nblk_max), st);
+    }
     hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, st, a.blk_stats, a.nblk,
                        static_cast<const unsigned long long*>(a.dstats), a.dstats ? a.dgrid : 0, a.stats);
     return hipGetLastError();
@@ -1866,14 +1976,13 @@ hipError_t launch_stats(const SearchArgs& a, hipStream_t st)
 hipError_t launch_fill(const SearchArgs& a, int nblk_max, hipStream_t st)
 {
     if (a.L.ntot == 0 || nblk_max == 0) return hipSuccess;
+    const int d = a.L.dim;
+    const bool f64 = a.L.mode == 1 || a.L.mode == 3;  // FP64 and FP32 modes: binary64 distances
     const dim3 g = block_grid(nblk_max), b(kFillThreads);
-    const int d = a.L.dim, m = a.L.mode == 3 ? 1 : a.L.mode;  // FP32 mode: binary64 distances
-    if (d == 2 && m == 0) hipLaunchKernelGGL((k_fill<2, 0>), g, b, 0, st, a);
-    else if (d == 3 && m == 0) hipLaunchKernelGGL((k_fill<3, 0>), g, b, 0, st, a);
-    else if (d == 2 && m == 2) hipLaunchKernelGGL((k_fill<2, 2>), g, b, 0, st, a);
-    else if (d == 3 && m == 2) hipLaunchKernelGGL((k_fill<3, 2>), g, b, 0, st, a);
-    else if (d == 2) hipLaunchKernelGGL((k_fill<2, 1>), g, b, 0, st, a);
-    else hipLaunchKernelGGL((k_fill<3, 1>), g, b, 0, st, a);
+    if (d == 2 && !f64) hipLaunchKernelGGL((k_fill<2, false>), g, b, 0, st, a);
+    else if (d == 3 && !f64) hipLaunchKernelGGL((k_fill<3, false>), g, b, 0, st, a);
+    else if (d == 2) hipLaunchKernelGGL((k_fill<2, true>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_fill<3, true>), g, b, 0, st, a);
     return hipGetLastError();
 }
 
@@ -1883,10 +1992,8 @@ hipError_t launch_long_rows(const SearchArgs& a, int grid, hipStream_t st)
     const int d = a.L.dim, m = a.L.mode == 3 ? 1 : a.L.mode;  // FP32 mode: long rows in FP64
     const dim3 gh(grid), bh(kLongThreads);
     const size_t lds = static_cast<size_t>(a.lr_keys) * 4;
-    if (d == 2 && m == 0) hipLaunchKernelGGL((k_long<2, 0>), gh, bh, lds, st, a);
-    else if (d == 3 && m == 0) hipLaunchKernelGGL((k_long<3, 0>), gh, bh, lds, st, a);
-    else if (d == 2 && m == 2) hipLaunchKernelGGL((k_long<2, 2>), gh, bh, lds, st, a);
-    else if (d == 3 && m == 2) hipLaunchKernelGGL((k_long<3, 2>), gh, bh, lds, st, a);
+    if (d == 2 && m != 1) hipLaunchKernelGGL((k_long<2, 0>), gh, bh, lds, st, a);
+    else if (d == 3 && m != 1) hipLaunchKernelGGL((k_long<3, 0>), gh, bh, lds, st, a);
     else if (d == 2) hipLaunchKernelGGL((k_long<2, 1>), gh, bh, lds, st, a);
     else hipLaunchKernelGGL((k_long<3, 1>), gh, bh, lds, st, a);
     return hipGetLastError();
@@ -2018,7 +2125,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
 #pragma unroll
             for (int k = 0; k < DIM; ++k) pi_k[k] = sd.pos[static_cast<size_t>(li) * DIM + k];
             if (F16) {
-                const ushort4 q = a.q4[pk];
+                const ushort4 q = q16_of(a.rq[pk]);
                 q01_k = static_cast<int>(static_cast<uint32_t>(q.x) | (static_cast<uint32_t>(q.y) << 16));
                 q2_k = static_cast<int>(q.z);
             }
@@ -2050,8 +2157,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                         sorig[e] = oj;
 #pragma unroll
                         for (int k = 0; k < DIM; ++k)
-                            spj[k * K + e] = a.spos ? a.spos[static_cast<size_t>(j) * 4 + k]
-                                                    : sd.pos[static_cast<size_t>(oj - poff) * DIM + k];
+                            spj[k * K + e] = a.spos[static_cast<size_t>(j) * 4 + k];
                         if (j >= t0 && j < t1) sself[j - t0] = c0 + e;  // a target of this unit
                     } else {
                         sorig[e] = -1;
@@ -2068,7 +2174,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                         const uint32_t sh = 16u * h;
                         if (e < nc) {
                             const int j = a.ulist[ub + c0 + e];
-                            const ushort4 v = a.q4[j];
+                            const ushort4 v = q16_of(a.rq[j]);
                             const uint32_t kj = a.skey[j] - coff;
                             const int xj = static_cast<int>(kj % static_cast<uint32_t>(ncx));
                             const uint32_t rj = kj / static_cast<uint32_t>(ncx);
@@ -2088,8 +2194,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                             if (FILL) {
 #pragma unroll
                                 for (int k = 0; k < DIM; ++k)
-                                    spj[k * K + e] = a.spos ? a.spos[static_cast<size_t>(j) * 4 + k]
-                                                        : sd.pos[static_cast<size_t>(oj - poff) * DIM + k];
+                                    spj[k * K + e] = a.spos[static_cast<size_t>(j) * 4 + k];
                                 if (j >= t0 && j < t1) sself[j - t0] = c0 + e;  // a target of this unit
                             }
                         } else {
