@@ -134,9 +134,9 @@ typedef struct nnps_stats {
  *   (device scratch: 16 bytes per entry, allocated as min(3^d n, bound)). Beyond it a
  *   build falls back to the block and long-row paths. 0 = default (2^28). Valid
  *   0..2^31-1.
- * dense_bits_mib: bound (MiB) on the device scratch in which the FP16 dense count keeps
- *   every target's accepted bits per candidate chunk (16 bits per 128 candidates per
- *   lane: about one bit per candidate) so that the fill does not test again. The
+ * dense_bits_mib: bound (MiB) on the device scratch in which the dense count keeps
+ *   every target's accepted bits per candidate chunk (one bit per candidate, 1024
+ *   candidates a chunk) so that the fill does not test again. The
  *   structure sizes it at a build from what the last call that synchronised (a count
  *   with h_nnz, a search) found the dense cells need; while it is too small, or above
  *   the bound, the fill tests the candidates again (same result). 0 = default (16384);

@@ -78,7 +78,7 @@ struct DenseBuild {
     uint32_t* table;        // radix scratch
     int64_t* partial;       // scan scratch
     int* seen;              // [1] set to 1 when any cell is dense
-    int* dbn;               // [ncell_tot] (target, chunk) pairs of each dense cell (FP16 chunks)
+    int* dbn;               // [ncell_tot] (target, chunk) pairs of each dense cell
     int64_t* dboff;         // [ncell_tot + 1] exclusive scan of dbn
 };
 // Stencil sizes and the dense flag only (the path is not used by this build).
@@ -133,9 +133,10 @@ struct SearchArgs {
     int* ucount;                    // work-unit counter (zeroed before each launch)
     unsigned long long* dstats;     // [dgrid][kDenseStats] per-workgroup statistics
     int dgrid;
-    // FP16 dense passes: the count keeps each target's accepted bits per chunk (64 lanes x
-    // 16 bits) at dbits[(dboff[cell] + target_in_cell * chunks + chunk) * 64 + lane] when
-    // dboff[ncell_tot] * 64 <= dbits_cap, and the fill then reads them instead of testing
+    // the dense count keeps each target's accepted bits per chunk of kDenseChunk candidates,
+    // in candidate order (64 x 16 bits), at dbits[(dboff[cell] + target_in_cell * chunks +
+    // chunk) * 64] when dboff[ncell_tot] * 64 <= dbits_cap, and the fill then reads them
+    // instead of testing
     const int64_t* dboff;
     uint16_t* dbits;
     int64_t dbits_cap;
@@ -144,9 +145,11 @@ struct SearchArgs {
 hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st);
 hipError_t launch_fill(const SearchArgs& a, int nblk_max, hipStream_t st);
 hipError_t launch_long_rows(const SearchArgs& a, int grid, hipStream_t st);
-hipError_t launch_dense(const SearchArgs& a, bool fill, hipStream_t st);
-// The last count's statistics, summed into a.stats. The block path's count decides on the
-// matrix cores and tallies nothing: its statistics are made here.
+// The dense-cell path's passes over its work units.
+enum class DensePass { kCount, kFill, kStats };
+hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st);
+// The last count's statistics, summed into a.stats: the count passes decide on the matrix
+// cores and tally nothing, so they are made here.
 hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st);
 
 }  // namespace nnps

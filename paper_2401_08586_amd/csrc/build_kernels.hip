@@ -839,7 +839,7 @@ k_dense_units(int ncell_tot, const int* __restrict__ cell_start, const int64_t* 
     const int occ = cell_start[g + 1] - cell_start[g];
     const bool on = !over && usz[g] > 0;
     nsl[g] = on ? (occ + kDenseSlice - 1) / kDenseSlice : 0;
-    dbn[g] = on ? occ * ((usz[g] + kDenseChunkF16 - 1) / kDenseChunkF16) : 0;
+    dbn[g] = on ? occ * ((usz[g] + kDenseChunk - 1) / kDenseChunk) : 0;
 }
 
 __global__ void __launch_bounds__(256)

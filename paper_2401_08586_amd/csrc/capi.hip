@@ -293,7 +293,7 @@ struct nnps_cells {
     int64_t dcap = 0;
     int* ulist = nullptr;
     DevBuf usz, wdense, uoff, nsl, unit_off, ucell, dn, ecnt, epos, uk0, uk1, uv0, uv1, inv, ucount, dstats, dseen;
-    // FP16 dense passes: (target, chunk) offsets per cell and the count's accepted bits,
+    // dense passes: (target, chunk) offsets per cell and the count's accepted bits,
     // sized at a build from what the last synchronising call found the dense cells need
     DevBuf dbn, dboff, dbits;
     size_t dbits_want = 0;  // bytes
@@ -353,13 +353,9 @@ nnps_status upload(nnps_cells* c, bool with_offsets, hipStream_t s)
     return NNPS_OK;
 }
 
-// The FP16 dense passes (FP16 RCLL and its recheck-all mode) may keep the count's
-// accepted bits for the fill, within a bound on the scratch (tuning; -1 = never).
-bool dense_bits_on(const nnps_cells* c)
-{
-    return c->dense && (c->mode == NNPS_MODE_FP16_RCLL || c->mode == NNPS_MODE_RECHECK_ALL) &&
-           c->ctx->tuning.dense_bits_mib >= 0;
-}
+// The dense passes may keep the count's accepted bits for the fill, within a bound on the
+// scratch (tuning; -1 = never).
+bool dense_bits_on(const nnps_cells* c) { return c->dense && c->ctx->tuning.dense_bits_mib >= 0; }
 
 size_t dense_bits_bound(const nnps_cells* c)
 {
@@ -702,7 +698,7 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s)
     c->timer.end(NNPS_PHASE_COUNT, s);
     if (c->dense_active) {
         c->timer.begin(NNPS_PHASE_DCOUNT, s);
-        HIP_TRY(launch_dense(a, false, s));
+        HIP_TRY(launch_dense(a, DensePass::kCount, s));
         c->timer.end(NNPS_PHASE_DCOUNT, s);
     }
     // the per-block statistics stay in place until the next count; nnps_stats_get sums
@@ -727,7 +723,7 @@ nnps_status enqueue_fill(nnps_cells* c, hipStream_t s)
     c->timer.end(NNPS_PHASE_LONGROWS, s);
     if (c->dense_active) {
         c->timer.begin(NNPS_PHASE_DFILL, s);
-        HIP_TRY(launch_dense(a, true, s));
+        HIP_TRY(launch_dense(a, DensePass::kFill, s));
         c->timer.end(NNPS_PHASE_DFILL, s);
     }
     return NNPS_OK;

@@ -27,16 +27,16 @@ constexpr int kMfmaXWin = 48;
 // Dense-cell path: candidates staged per chunk, targets per work unit (a workgroup of
 // four wavefronts, 64 targets each) and the default thresholds.
 constexpr int kDenseChunk = 1024;
-// The FP16 passes stage fewer candidates per chunk, so that the fill's tables (records,
+// The FP16 fill that tests stages fewer candidates per chunk, so that its tables (records,
 // FP64 positions and the per-wavefront queues of accepted candidates) still fit four
-// workgroups per CU (a multiple of 128); the count uses the same chunks, so that the
-// accepted bits it keeps per target and chunk are the fill's.
+// workgroups per CU (a multiple of 128).
 constexpr int kDenseChunkF16 = 896;
-// Default bound on the device scratch for those bits (MiB).
+// Default bound on the device scratch for the count's kept bits (MiB).
 constexpr int kDenseBitsMiB = 16384;
 constexpr int kDenseQueue = 512;  // per-wavefront queue of a row's accepted candidates in a chunk
 constexpr int kDenseThreads = 256;
-constexpr int kDenseBitsThreads = 512;  // the dense fill that takes the count's kept bits
+constexpr int kDenseFillThreads = 1024;  // the dense fill that takes the count's kept bits
+constexpr int kDenseFillQueue = 448;     // and its per-wavefront queue
 constexpr int kDenseSlice = 256;
 constexpr int kDenseUnion3 = 512;
 constexpr int kDenseUnion2 = 160;

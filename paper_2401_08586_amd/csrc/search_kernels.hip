@@ -80,6 +80,20 @@ __device__ __forceinline__ float quanta2(const int4& i, const int4& j)
     return s2;
 }
 
+// The FP32 distance of the FP16 RCLL mode, the same on every path: in quanta, pairs nearer
+// than near2 from the binary64 displacement.
+template <int DIM>
+__device__ __forceinline__ float dist_quanta(const Frame& fr, const double* pi, const double* pj)
+{
+    auto fixed = [&](const double* x) {
+        return make_int4(in_quanta(x[0], fr.lo[0], fr.inv_quantum), in_quanta(x[1], fr.lo[1], fr.inv_quantum),
+                         DIM == 3 ? in_quanta(x[2], fr.lo[2], fr.inv_quantum) : 0, 0);
+    };
+    const float s2 = quanta2<DIM>(fixed(pi), fixed(pj));
+    return s2 >= fr.near2 ? __builtin_amdgcn_sqrtf(s2) * fr.quantum
+                          : dist_near<DIM>(pi, pj, fr.inv_quantum, fr.quantum);
+}
+
 template <int DIM>
 __device__ __forceinline__ float dist_fp64(const double* pi, const double* pj)
 {
@@ -1125,10 +1139,11 @@ __device__ __forceinline__ void quarter_transpose(uint32_t (&v)[4])
     swap16(v[2], v[3]);
 }
 
-// The MFMA operands of 64 items, one prepared per lane, and 64 x 64 tests. load: the item's
-// coordinates; words: the two row words (candidates 0-31 and 32-63 of the step) of target
-// `lane`, with `decide(bnd, acc, e, t)` settling the results bnd (bits) of a lane whose 16
-// results are the step's candidates e.. against target t.
+// The MFMA operands of 64 items, one prepared per lane, and 64 x 64 tests. prepare: the
+// fragments of 64 candidates (lane l prepares candidate item(l); `past`: none, far away);
+// words: the two row words (candidates 0-31 and 32-63 of the step) of target `lane`, with
+// `decide(bnd, acc, e, t)` settling the results bnd (bits) of a lane whose 16 results are the
+// step's candidates e.. against target t.
 template <int DIM, int P>
 struct Tiles;
 
@@ -1204,25 +1219,30 @@ struct Tiles<DIM, 16> {
         }
         return acc;
     }
-    template <typename F>
-    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    struct Frag { h8 c[2]; };
+    __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>& g, bool past) const
     {
         const Coord x = coords(rec, g);
         uint32_t w[8];
         candidate_words(x.x, x.y, x.z, w);
-        if (past) {  // past the list: far away
+        if (past) {
             w[0] = w[1] = w[2] = w[3] = w[4] = 0u;
             w[5] = 0x7800u;  // 32768
         }
-        h8 c[2];
-        fragments(w, c[0], c[1]);
+        Frag f;
+        fragments(w, f.c[0], f.c[1]);
+        return f;
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Frag& f, const BlockGeom<DIM>&, F&& decide) const
+    {
         const int lane = threadIdx.x & 63, e = 16 * (lane >> 5), tl = lane & 31;
         const f32x16 zero = {};
         u32x2 out;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[t], t0, zero, 0, 0, 0);
-            const f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(c[t], t1, zero, 0, 0, 0);
+            const f32x16 D0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.c[t], t0, zero, 0, 0, 0);
+            const f32x16 D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(f.c[t], t1, zero, 0, 0, 0);
             uint32_t b0 = row_bits(D0, beta, [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * t + e, tl); });
             uint32_t b1 = row_bits(D1, beta, [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * t + e, 32 + tl); });
             swap32(b0, b1);
@@ -1255,8 +1275,8 @@ struct Tiles<DIM, 32> : Tiles<DIM, 16> {
         pair(c.x * c.x + c.y * c.y + c.z * c.z - g.sd->fr.t32_mid, 0.0f, t[0][2], t[1][2]);
         this->beta = B::bound(g);
     }
-    template <typename F>
-    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    struct Frag { float c[2][2]; };
+    __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>& g, bool past) const
     {
         Coord x = B::coords(rec, g);
         float s = x.x * x.x + x.y * x.y + x.z * x.z;
@@ -1264,9 +1284,14 @@ struct Tiles<DIM, 32> : Tiles<DIM, 16> {
             x.x = x.y = x.z = 0.0f;
             s = 0x1p60f;
         }
-        float c[2][2];
-        pair(x.x, x.y, c[0][0], c[1][0]);
-        pair(x.z, s, c[0][1], c[1][1]);
+        Frag f;
+        pair(x.x, x.y, f.c[0][0], f.c[1][0]);
+        pair(x.z, s, f.c[0][1], f.c[1][1]);
+        return f;
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Frag& f, const BlockGeom<DIM>&, F&& decide) const
+    {
         const int lane = threadIdx.x & 63, e = 16 * (lane >> 5), tl = lane & 31;
         const float one = lane < 32 ? 1.0f : 0.0f;
         u32x2 out;
@@ -1277,8 +1302,8 @@ struct Tiles<DIM, 32> : Tiles<DIM, 16> {
             for (int h = 0; h < 2; ++h) {
                 f32x16 D = {};
                 D = __builtin_amdgcn_mfma_f32_32x32x2f32(one, t[h][2], D, 0, 0, 0);
-                D = __builtin_amdgcn_mfma_f32_32x32x2f32(c[k][0], t[h][0], D, 0, 0, 0);
-                D = __builtin_amdgcn_mfma_f32_32x32x2f32(c[k][1], t[h][1], D, 0, 0, 0);
+                D = __builtin_amdgcn_mfma_f32_32x32x2f32(f.c[k][0], t[h][0], D, 0, 0, 0);
+                D = __builtin_amdgcn_mfma_f32_32x32x2f32(f.c[k][1], t[h][1], D, 0, 0, 0);
                 b[h] = B::row_bits(D, this->beta,
                                    [&](uint32_t n, uint32_t q) { return decide(n, q, 32 * k + e, 32 * h + tl); });
             }
@@ -1323,18 +1348,22 @@ struct Tiles<DIM, 64> {
         for (int k = 0; k < 4; ++k)
             out[k] = __builtin_bit_cast(double, static_cast<uint64_t>(hi[k]) << 32 | lo[k]);
     }
+    // about the wavefront's first target
     __device__ __forceinline__ void targets(const Rec& rec, const BlockGeom<DIM>& g)
     {
-        // the block's first target is the origin
         auto first = [](double v) {
             const uint64_t q = __builtin_bit_cast(uint64_t, v);
             const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(q));
             const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(q >> 32));
             return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
         };
-        ox = first(rec.x);
-        oy = first(rec.y);
-        oz = first(rec.z);
+        targets_about(rec, Rec{first(rec.x), first(rec.y), first(rec.z)}, g);
+    }
+    __device__ __forceinline__ void targets_about(const Rec& rec, const Rec& origin, const BlockGeom<DIM>& g)
+    {
+        ox = origin.x;
+        oy = origin.y;
+        oz = origin.z;
         const double x = rec.x - ox, y = rec.y - oy, z = rec.z - oz;
         const double v[4] = {-2.0 * x, -2.0 * y, -2.0 * z, 1.0};
         fragments(v, t);
@@ -1346,13 +1375,18 @@ struct Tiles<DIM, 64> {
         const double beta = 0x1p-46 * w * w * (4.0 * (xs * xs + 8.0) + 1.0);
         bhi = static_cast<int>(__builtin_bit_cast(uint64_t, beta) >> 32) + 1;
     }
-    template <typename F>
-    __device__ __forceinline__ u32x2 words(const Rec& rec, const BlockGeom<DIM>& g, bool past, F&& decide) const
+    struct Frag { double c[4]; };
+    __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>&, bool past) const
     {
         const double x = past ? 0.0 : rec.x - ox, y = past ? 0.0 : rec.y - oy, z = past ? 0.0 : rec.z - oz;
         const double v[4] = {x, y, z, past ? 0x1p200 : x * x + y * y + z * z};
-        double c[4];
-        fragments(v, c);
+        Frag f;
+        fragments(v, f.c);
+        return f;
+    }
+    template <typename F>
+    __device__ __forceinline__ u32x2 words(const Frag& f, const BlockGeom<DIM>& g, F&& decide) const
+    {
         const int lane = threadIdx.x & 63, nt = g.p1 - g.p0;
         uint32_t b[4] = {0, 0, 0, 0};
         // non-negative doubles order like their high words read as floats
@@ -1364,7 +1398,7 @@ struct Tiles<DIM, 64> {
             float hi[16];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const f64x4 D = __builtin_amdgcn_mfma_f64_16x16x4f64(c[i], t[k], acc0, 0, 0, 0);
+                const f64x4 D = __builtin_amdgcn_mfma_f64_16x16x4f64(f.c[i], t[k], acc0, 0, 0, 0);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const double d = D[r];
@@ -1486,7 +1520,7 @@ k_count(SearchArgs a)
                 }
                 return acc;
             };
-            const u32x2 ww = tiles.words(rec, g, 64 * s + mi >= m, decide);
+            const u32x2 ww = tiles.words(tiles.prepare(rec, g, 64 * s + mi >= m), g, decide);
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int tile = 2 * s + k;
@@ -1908,13 +1942,7 @@ k_long(SearchArgs a)
             if (MODE == 1) {
                 d = dist_fp64<DIM>(pi, pj);
             } else {  // as the block path's fill: which rows come here depends on the block table
-                auto fixed = [&](const double* x) {
-                    return make_int4(in_quanta(x[0], fr.lo[0], fr.inv_quantum), in_quanta(x[1], fr.lo[1], fr.inv_quantum),
-                                     DIM == 3 ? in_quanta(x[2], fr.lo[2], fr.inv_quantum) : 0, 0);
-                };
-                const float s2 = quanta2<DIM>(fixed(pi), fixed(pj));
-                d = s2 >= fr.near2 ? __builtin_amdgcn_sqrtf(s2) * fr.quantum
-                                   : dist_near<DIM>(pi, pj, fr.inv_quantum, fr.quantum);
+                d = dist_quanta<DIM>(fr, pi, pj);
             }
             sd.dist[rs + e] = d;
         }
@@ -1968,6 +1996,8 @@ hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st)
         if (a.L.dim == 2) launch_block_stats<2>(a, block_grid(nblk_max), st);
         else launch_block_stats<3>(a, block_grid(nblk_max), st);
     }
+    const hipError_t e = launch_dense(a, DensePass::kStats, st);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, st, a.blk_stats, a.nblk,
                        static_cast<const unsigned long long*>(a.dstats), a.dstats ? a.dgrid : 0, a.stats);
     return hipGetLastError();
@@ -1999,24 +2029,6 @@ hipError_t launch_long_rows(const SearchArgs& a, int grid, hipStream_t st)
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Dense-cell path. A work unit is up to kDenseSlice targets of one dense cell, all with
-// the same stencil union (the cell's list, ascending original index). A workgroup of four
-// wavefronts (eight in the fill that takes the count's kept bits) takes units from a
-// counter; for each chunk of candidates (kDenseChunkF16 in the FP16 modes, kDenseChunk in
-// FP64) it stages their FP16 pair records and original indices (and, for the fill, FP64
-// positions) in LDS, then each wavefront runs its targets one at a time over the chunk.
-// Lane L tests a contiguous run of the chunk's candidates, two per packed FP16
-// instruction with the same op sequence as the block kernels, and band pairs are settled
-// by the FP64 recheck (on the staged positions in the fill). A target's accepted
-// candidates thus come out lane by lane in row order: the fill places them with one
-// wavefront prefix sum of the lanes' counts, queues them per lane and writes them 64 at a
-// time, so consecutive lanes store consecutive CSR entries and the row comes out
-// ascending. In the FP16 modes the count keeps each lane's accepted bits of every
-// (target, chunk) when the buffer holds them; the fill then reads them back instead of
-// testing again and stages only original indices and positions.
-// Wavefront w of a unit's W holds targets w, w + W, ...: lane k keeps target w + W k's data
-// in registers, read by the whole wavefront with readlane when its turn comes.
 __device__ __forceinline__ int rl32(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
 // A pointer every lane holds, marked wave-uniform (scalar registers), so that stores through
 // it can take a 32-bit per-lane offset.
@@ -2039,26 +2051,371 @@ __device__ __forceinline__ double rlf64(double v, int k)
     return __builtin_bit_cast(double, rl64(__builtin_bit_cast(long long, v), k));
 }
 
-// BITS: the FP16 fill that takes the count's kept bits. It holds no pair records, so
-// eight wavefronts share one staged chunk (about 34 KB of LDS) and six wavefronts per SIMD
-// fit, where the passes that test run four wavefronts per workgroup and four or five per
-// SIMD.
-template <int DIM, int MODE, bool FILL, bool BITS = false>
-__global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
-    __attribute__((amdgpu_waves_per_eu(BITS ? 6 : 4))) k_dense(SearchArgs a)
+// ---------------------------------------------------------------------------
+// Dense-cell path. A work unit is up to kDenseSlice targets of one dense cell, all with
+// the same stencil union (the cell's list, ascending original index); persistent workgroups
+// take units from a counter.
+//
+// Count: four wavefronts of 64 targets each against the list in chunks of kDenseChunk, whose
+// MFMA operands the wavefronts prepare once and share through LDS (see k_count: the same
+// contraction, about the cell's centre; binary64 outside the FP16 RCLL mode). The accepted
+// bits of every (target, chunk) are kept when the buffer holds them. What bounds it: vector
+// issue, 1.7 instructions per 64 pairs (the packed-FP16 count took 2.36 ms per
+// launch on 422 thousand clustered particles, 2.2 G candidates; this 0.41).
+//
+// Fill: it takes the kept bits, or (no room for them) tests again with packed FP16 (or in
+// binary64) and an FP64 recheck. For each chunk the workgroup stages the candidates' original
+// indices and FP64 positions in LDS, then each wavefront runs its targets one at a time over
+// the chunk. Lane L holds a contiguous run of the chunk's candidates, so a target's accepted
+// ones come out lane by lane in row order: one wavefront prefix sum of the lanes' counts
+// places them, they are queued per lane and written 64 at a time, so consecutive lanes store
+// consecutive CSR entries and the row comes out ascending.
+// Wavefront w of a unit's W holds targets w, w + W, ...: lane k keeps target w + W k's data
+// in registers, read by the whole wavefront with readlane when its turn comes.
+constexpr int kNotSeen = 1 << 30;  // a target whose own place in the union has not come yet
+
+__device__ __forceinline__ bool dense_bits_fit(const SearchArgs& a, int nunits)
 {
-    constexpr int NTH = BITS ? kDenseBitsThreads : kDenseThreads;  // threads per workgroup
-    constexpr int NWV = NTH / 64;                                  // wavefronts per workgroup
+    return a.dbits && nunits > 0 && a.dboff[a.L.ncell_tot] * 64 <= a.dbits_cap;
+}
+
+template <int DIM, int P, bool HALF>
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(4)))
+k_dense_count(SearchArgs a)
+{
+    using T = Tiles<DIM, P>;
+    using Rec = typename T::Rec;
+    using Frag = typename T::Frag;
+    constexpr int K = kDenseChunk, NW = kDenseThreads / 64, NS = K / 64;
+    static_assert(kDenseSlice == 64 * NW && sizeof(Frag) == 32, "a wavefront per 64 targets; operands of 32 bytes");
+    __shared__ uint4 sfrag[NS][2][64];  // the chunk's operands, 64 candidates a step
+    __shared__ int slist[K];            // its sorted positions
+    __shared__ int sself[kDenseSlice];  // the targets' own places in the union
+    __shared__ int s_unit;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nunits = *a.dn > 0 ? a.unit_off[a.L.ncell_tot] : 0;
+    const bool bits = dense_bits_fit(a, nunits);
+    const int mi = T::item(lane);
+    for (;;) {
+        __syncthreads();  // the previous unit is done with the shared tables
+        if (tid == 0) s_unit = atomicAdd(a.ucount, 1);
+        __syncthreads();
+        const int u = __builtin_amdgcn_readfirstlane(s_unit);
+        if (u >= nunits) break;
+        const int c = __builtin_amdgcn_readfirstlane(a.ucell[u]);
+        const int slice = u - __builtin_amdgcn_readfirstlane(a.unit_off[c]);
+        const SetDesc& sd = a.L.sets[__builtin_amdgcn_readfirstlane(find_set(a.L.coffs, a.L.nsets, c))];
+        const int ncx = sd.fr.nc[0], ncy = sd.fr.nc[1];
+        const int lk = c - sd.coff, row = lk / ncx;
+        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseSlice;
+        const int u1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), u0 + kDenseSlice);
+        const int U = __builtin_amdgcn_readfirstlane(a.usz[c]);
+        const int* list = a.ulist + a.uoff[c];
+        const int nchunk = (U + K - 1) / K;
+        // the wavefront's targets, tests about the cell's centre
+        BlockGeom<DIM> g;
+        g.sd = &sd;
+        g.xa = g.xb = lk - row * ncx;
+        g.y0 = row % ncy;
+        g.z0 = row / ncy;
+        g.p0 = min(u0 + 64 * wv, u1);
+        g.p1 = min(u0 + 64 * wv + 64, u1);
+        const int nt = g.p1 - g.p0;
+        const int pt = nt > 0 ? g.p0 + min(lane, nt - 1) : u0;
+        const double R2 = sd.fr.R2;
+        T tiles;
+        if constexpr (P == 64) {
+            // one origin for the workgroup, whose wavefronts share the candidates' operands
+            tiles.targets_about(T::fetch(a, pt), T::fetch(a, u0), g);
+        } else {
+            tiles.targets(T::fetch(a, pt), g);
+        }
+        for (int t = tid; t < kDenseSlice; t += kDenseThreads) sself[t] = kNotSeen;
+        int cnt = 0;
+        for (int c0 = 0; c0 < U; c0 += K) {
+            const int nc = min(K, U - c0), ns = (nc + 63) >> 6;
+            __syncthreads();
+            for (int s = wv; s < ns; s += NW) {
+                const int e = 64 * s + mi;
+                const int j = list[c0 + min(e, nc - 1)];
+                const Frag f = tiles.prepare(T::fetch(a, j), g, e >= nc);
+                uint4 q[2];
+                __builtin_memcpy(q, &f, sizeof(f));
+                sfrag[s][0][lane] = q[0];
+                sfrag[s][1][lane] = q[1];
+                if (e < nc) {
+                    slist[e] = j;
+                    if (j >= u0 && j < u1) sself[j - u0] = c0 + e;
+                }
+            }
+            __syncthreads();
+            if (nt == 0) continue;
+            const int self = sself[64 * wv + lane] - c0;
+            uint4* out = nullptr;
+            if (bits)
+                out = reinterpret_cast<uint4*>(a.dbits + (a.dboff[c] + static_cast<int64_t>(pt - a.cell_start[c]) * nchunk +
+                                                          c0 / K) * 64);
+            // four steps' words go out together (32 bytes a target)
+#pragma unroll 1
+            for (int sb = 0; sb < ns; sb += 4) {
+                uint32_t w[8];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int s = sb + k;
+                    w[2 * k] = w[2 * k + 1] = 0u;
+                    if (s >= ns) continue;
+                    auto decide = [&](uint32_t bnd, uint32_t acc, int e0, int t) -> uint32_t {
+                        const double* pi = a.spos + static_cast<size_t>(g.p0 + min(t, nt - 1)) * 4;
+                        while (bnd) {
+                            const int r = __builtin_ctz(bnd);
+                            bnd &= bnd - 1u;
+                            const int e = 64 * s + e0 + r;
+                            if (e < nc) {
+                                const bool in = recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
+                                acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
+                            }
+                        }
+                        return acc;
+                    };
+                    const uint4 q[2] = {sfrag[s][0][lane], sfrag[s][1][lane]};
+                    Frag f;
+                    __builtin_memcpy(&f, q, sizeof(f));
+                    const u32x2 ww = tiles.words(f, g, decide);
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        // the target itself is no neighbour; half lists keep larger original indices
+                        const int d = self - 64 * s - 32 * h;
+                        uint32_t word = ww[h];
+                        if (HALF) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
+                        else word &= (d >= 0 && d < 32) ? ~(1u << d) : ~0u;
+                        cnt += __builtin_popcount(word);
+                        w[2 * k + h] = word;
+                    }
+                }
+                if (bits && lane < nt) {
+                    out[sb >> 1] = make_uint4(w[0], w[1], w[2], w[3]);
+                    out[(sb >> 1) + 1] = make_uint4(w[4], w[5], w[6], w[7]);
+                }
+            }
+        }
+        if (lane < nt) a.counts[a.perm[g.p0 + lane]] = cnt;
+    }
+}
+
+// The fill that takes the count's bits. Sixteen wavefronts share the staged candidates, as many
+// as two workgroups per compute unit have room for: 4096 as 16-byte records in quanta (see
+// k_fill), 2048 in binary64. A wavefront takes a target's bits 1024 candidates at a time, one
+// after the other, so that several KB of a row go out at once: rows lie far apart in the
+// output, and with 1024 candidates staged at a time the pieces of about 0.8 KB cost DRAM
+// efficiency (2.9 ms per launch for 4.6 GB of lists, 2.2 now).
+template <int DIM, bool F64>
+__global__ void __launch_bounds__(kDenseFillThreads) __attribute__((amdgpu_waves_per_eu(8)))
+k_dense_fill(SearchArgs a)
+{
+    constexpr int NW = kDenseFillThreads / 64, QCAP = kDenseFillQueue;
+    constexpr int NSUB = F64 ? 2 : 4, K = NSUB * kDenseChunk;
+    constexpr int GT = 8 / NSUB;  // targets whose bits are loaded together
+    __shared__ int4 srec[F64 ? 1 : K];            // position, set-local index
+    __shared__ double sdbl[F64 ? K * DIM : 1];    // [K][DIM]
+    __shared__ int sorig[F64 ? K : 1];
+    __shared__ uint16_t squeue[NW * QCAP];        // per wavefront: accepted candidates, in row order
+    __shared__ int s_unit;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nunits = *a.dn > 0 ? a.unit_off[a.L.ncell_tot] : 0;
+    if (!dense_bits_fit(a, nunits)) return;
+    uint16_t* const queue = squeue + wv * QCAP;
+    for (;;) {
+        __syncthreads();  // the previous unit is done with the shared tables
+        if (tid == 0) s_unit = atomicAdd(a.ucount, 1);
+        __syncthreads();
+        const int u = __builtin_amdgcn_readfirstlane(s_unit);
+        if (u >= nunits) break;
+        const int c = __builtin_amdgcn_readfirstlane(a.ucell[u]);
+        const int slice = u - __builtin_amdgcn_readfirstlane(a.unit_off[c]);
+        const NNPS_CONST SetDesc& sd =
+            ((const NNPS_CONST SetDesc*)a.L.sets)[__builtin_amdgcn_readfirstlane(find_set(a.L.coffs, a.L.nsets, c))];
+        const int poff = sd.poff;
+        const double inv_quantum = sd.fr.inv_quantum;
+        const float quantum = sd.fr.quantum, near2 = sd.fr.near2;
+        const double lo[3] = {sd.fr.lo[0], sd.fr.lo[1], sd.fr.lo[2]};
+        const int64_t cap = sd.capacity;
+        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseSlice;
+        const int u1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), u0 + kDenseSlice);
+        const int U = __builtin_amdgcn_readfirstlane(a.usz[c]);
+        const int* list = a.ulist + a.uoff[c];
+        const int nchunk = (U + kDenseChunk - 1) / kDenseChunk;
+        const uint16_t* rows = a.dbits + (a.dboff[c] + static_cast<int64_t>(slice * kDenseSlice + wv) * nchunk) * 64 + lane;
+        auto packed = [&](const double2& xy, const double2& zw, int w) {
+            return make_int4(in_quanta(xy.x, lo[0], inv_quantum), in_quanta(xy.y, lo[1], inv_quantum),
+                             DIM == 3 ? in_quanta(zw.x, lo[2], inv_quantum) : 0, w);
+        };
+        // this lane's target (held for the wavefront): targets wv, wv + NW, ... of the unit
+        const int pk = u0 + wv + NW * lane;
+        const int nt = u1 - u0 > wv ? (u1 - u0 - wv + NW - 1) / NW : 0;
+        int rl_k = 0, acc_k = 0;
+        long long rs_k = 0;
+        int4 t_k = make_int4(0, 0, 0, 0);
+        double pi_k[3] = {0, 0, 0};
+        if (pk < u1) {
+            const double2* r = reinterpret_cast<const double2*>(a.spos + static_cast<size_t>(pk) * 4);
+            const double2 xy = r[0], zw = r[1];
+            const int li = static_cast<int>(__builtin_bit_cast(int64_t, zw.y)) - poff;
+            rs_k = sd.row_ptr[li];
+            rl_k = static_cast<int>(sd.row_ptr[li + 1] - rs_k);
+            if (F64) {
+                pi_k[0] = xy.x;
+                pi_k[1] = xy.y;
+                pi_k[2] = zw.x;
+            } else {
+                t_k = packed(xy, zw, 0);
+            }
+        }
+        for (int c0 = 0; c0 < U; c0 += K) {
+            const int nc = min(K, U - c0), nsub = (nc + kDenseChunk - 1) / kDenseChunk;
+            __syncthreads();
+            for (int e = tid; e < nc; e += kDenseFillThreads) {
+                const double2* r = reinterpret_cast<const double2*>(a.spos + static_cast<size_t>(list[c0 + e]) * 4);
+                const double2 xy = r[0], zw = r[1];
+                const int oj = static_cast<int>(__builtin_bit_cast(int64_t, zw.y)) - poff;
+                if (F64) {
+                    sdbl[e * DIM] = xy.x;
+                    sdbl[e * DIM + 1] = xy.y;
+                    if (DIM == 3) sdbl[e * DIM + 2] = zw.x;
+                    sorig[e] = oj;
+                } else {
+                    srec[e] = packed(xy, zw, oj);
+                }
+            }
+            __syncthreads();
+            for (int k0 = 0; k0 < nt; k0 += GT) {
+                // the bits of GT targets, loaded together (waiting for a load also waits for
+                // every store issued before it); lane L takes candidates 16 L ... of each 1024
+                uint32_t wb[GT * NSUB];
+#pragma unroll
+                for (int t = 0; t < GT; ++t)
+#pragma unroll
+                    for (int q = 0; q < NSUB; ++q)
+                        wb[t * NSUB + q] = rows[(static_cast<int64_t>(NW * min(k0 + t, nt - 1)) * nchunk +
+                                                 min(c0 / kDenseChunk + q, nchunk - 1)) * 64];
+#pragma unroll
+                for (int t = 0; t < GT; ++t) {
+                    const int k = k0 + t;
+                    if (k >= nt) break;
+                    const long long rs = rl64(rs_k, k);
+                    const int rl = rl32(rl_k, k);
+                    int done = rl32(acc_k, k);
+                    const bool room = rs + rl <= cap;
+                    const int4 ti = make_int4(rl32(t_k.x, k), rl32(t_k.y, k), rl32(t_k.z, k), 0);
+                    double pi[3];
+                    if (F64) {
+#pragma unroll
+                        for (int d = 0; d < 3; ++d) pi[d] = rlf64(pi_k[d], k);
+                    }
+                    // the row's output, wave-uniform: entries are addressed by a 32-bit slot
+                    NNPS_GLOBAL int32_t* const rcol = uniform_ptr((NNPS_GLOBAL int32_t*)sd.col + rs);
+                    NNPS_GLOBAL float* const rdist = uniform_ptr((NNPS_GLOBAL float*)sd.dist + rs);
+#pragma unroll
+                    for (int q = 0; q < NSUB; ++q) {
+                        if (q >= nsub) break;
+                        const int lb = q * kDenseChunk + 16 * lane;  // the lane's first candidate
+                        const uint32_t M = lb < nc ? wb[t * NSUB + q] : 0u;  // nothing was kept past the list
+                        int tot;
+                        const int base = wave_excl_scan_i32(__builtin_popcount(M), &tot);
+                        // accepted candidates queued per lane, as many as the queue holds at a
+                        // time, then written 64 at a time with all lanes active
+                        for (int w0 = 0; w0 < tot; w0 += QCAP) {
+                            int pos = base - w0;
+                            for (uint32_t mm = M; mm; mm &= mm - 1, ++pos)
+                                if (static_cast<unsigned>(pos) < static_cast<unsigned>(QCAP))
+                                    queue[pos] = static_cast<uint16_t>(lb + __builtin_ctz(mm));
+                            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                            const int n = min(QCAP, tot - w0);
+                            for (int i = lane; i < n; i += 64) {
+                                const int e = queue[i], slot = done + w0 + i;
+                                float dv;
+                                int oj;
+                                if constexpr (F64) {
+                                    oj = sorig[e];
+                                    dv = dist_fp64<DIM>(pi, sdbl + e * DIM);
+                                } else {
+                                    const int4 r = srec[e];
+                                    oj = r.w;
+                                    const float s2 = quanta2<DIM>(ti, r);
+                                    dv = __builtin_amdgcn_sqrtf(s2) * quantum;
+                                    if (!(s2 >= near2))
+                                        dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
+                                                            (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
+                                                            inv_quantum, quantum);
+                                }
+                                if (slot < rl && room) {
+                                    if (rl <= (1 << 30)) {  // byte offsets within the row fit 32 bits
+                                        const uint32_t off = static_cast<uint32_t>(slot) * 4u;
+                                        *(NNPS_GLOBAL int32_t*)((NNPS_GLOBAL char*)rcol + off) = oj;
+                                        *(NNPS_GLOBAL float*)((NNPS_GLOBAL char*)rdist + off) = dv;
+                                    } else {
+                                        rcol[slot] = oj;
+                                        rdist[slot] = dv;
+                                    }
+                                }
+                            }
+                            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                        }
+                        done += tot;
+                    }
+                    if (!room && lane == 0 && rl > 0) atomicOr(a.err, kErrCapacity);
+                    if (lane == k) acc_k = done;
+                }
+            }
+        }
+        if (pk < u1 && acc_k != rl_k) atomicOr(a.err, kErrLongRow);
+    }
+}
+
+// Statistics of the dense cells decided in binary64: candidates and rows.
+__global__ void __launch_bounds__(kDenseThreads)
+k_dense_stats64(SearchArgs a)
+{
+    __shared__ unsigned long long sh[2][kDenseThreads / 64];
+    unsigned long long cand = 0, rows = 0;
+    const bool on = *a.dn > 0;
+    for (int c = blockIdx.x * kDenseThreads + threadIdx.x; on && c < a.L.ncell_tot; c += gridDim.x * kDenseThreads) {
+        const int U = a.usz[c];
+        if (U == 0) continue;
+        const unsigned long long occ = static_cast<unsigned long long>(a.cell_start[c + 1] - a.cell_start[c]);
+        rows += occ;
+        cand += occ * static_cast<unsigned long long>(U - 1);
+    }
+    cand = wave_sum_u64(cand);
+    rows = wave_sum_u64(rows);
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = cand;
+        sh[1][threadIdx.x >> 6] = rows;
+    }
+    __syncthreads();
+    if (threadIdx.x < kDenseStats) {
+        unsigned long long v = 0;
+        if (threadIdx.x == 0 || threadIdx.x == 5)
+            for (int w = 0; w < kDenseThreads / 64; ++w) v += sh[threadIdx.x == 5 ? 1 : 0][w];
+        a.dstats[static_cast<size_t>(blockIdx.x) * kDenseStats + threadIdx.x] = v;
+    }
+}
+
+// The fill that tests the candidates itself, and the packed-FP16 statistics (FILL false:
+// nothing but dstats is written).
+template <int DIM, int MODE, bool FILL>
+__global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per_eu(4))) k_dense(SearchArgs a)
+{
+    constexpr int NTH = kDenseThreads;  // threads per workgroup
+    constexpr int NWV = NTH / 64;       // wavefronts per workgroup
     constexpr bool F16 = MODE != 1;
-    static_assert(!BITS || (FILL && F16), "only the FP16 fill takes the count's bits");
-    constexpr bool kTest = F16 && !BITS;  // the pass tests candidates in FP16
+    static_assert(FILL || F16, "the statistics are the FP16 test's");
     constexpr int K = F16 ? kDenseChunkF16 : kDenseChunk;
     constexpr int QCAP = kDenseQueue;
     static_assert(K % 128 == 0 && K <= 2048, "whole 128-candidate groups, chunk positions fit 16 bits");
     static_assert(QCAP >= 64 && K <= 65536, "a queue holds a full store; chunk positions fit 16 bits");
-    static_assert(!F16 || K / 128 <= 7, "a lane's accepted bits of a chunk fit 14 bits");
-    __shared__ uint4 recA[kTest ? K / 2 : 1];             // qx, qy, qz, 2(c_x - c_jx) pairs
-    __shared__ uint2 recB[kTest ? K / 2 : 1];             // 2(c_y - c_jy), 2(c_z - c_jz) pairs
+    static_assert(K / 64 <= 16, "a lane's accepted bits of a chunk fit 16 bits");
+    __shared__ uint4 recA[F16 ? K / 2 : 1];             // qx, qy, qz, 2(c_x - c_jx) pairs
+    __shared__ uint2 recB[F16 ? K / 2 : 1];             // 2(c_y - c_jy), 2(c_z - c_jz) pairs
     __shared__ __attribute__((aligned(16))) int sorig[K];
     // candidates' FP64 positions: [K][DIM] (baseline), axis-major [DIM][K] (FP16 fill)
     __shared__ double sdbl[(!F16 || FILL) ? K * DIM : 1];
@@ -2067,23 +2424,17 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
     // fill: per-wavefront queues of a row's accepted candidates in a chunk (chunk positions,
     // in row order)
     __shared__ uint16_t squeue[FILL ? NWV * QCAP : 1];
-    // FP16 count keeping its bits: eight targets' bit words per wavefront, stored together
-    __shared__ uint16_t sbits[(!FILL && F16) ? (kDenseThreads / 64) * 8 * 64 : 1];
     // fill: each target's position in the union (found while staging; kNotSeen before)
     __shared__ int sself[FILL ? kDenseSlice : 1];
-    constexpr int kNotSeen = 1 << 30;
     // the unit counter's broadcast slot: the first record word, free between the last use of
     // one unit's staged chunk and the staging of the next unit's first chunk
     int* const s_unit = reinterpret_cast<int*>(recA);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const int nunits = *a.dn > 0 ? a.unit_off[a.L.ncell_tot] : 0;
-    // FP16: the count keeps the accepted bits of every (target, chunk) when they fit, and
-    // the fill then takes them instead of testing again. The host launches both FP16 fills;
-    // the one that does not apply returns here.
-    const bool bits_fit = F16 && a.dbits && nunits > 0 && a.dboff[a.L.ncell_tot] * 64 <= a.dbits_cap;
-    if (FILL && F16 && bits_fit != BITS) return;
-    const bool bits = FILL ? BITS : bits_fit;
+    // the count keeps the accepted bits of every (target, chunk) when they fit, and the fill
+    // then takes them instead of testing again. The host launches both fills; the one that
+    // does not apply returns here.
+    if (FILL && dense_bits_fit(a, nunits)) return;
     unsigned long long tc[kDenseStats] = {0, 0, 0, 0, 0, 0};
     for (;;) {
         __syncthreads();  // the previous unit is done with s_unit and the staged chunk
@@ -2105,9 +2456,6 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
         const int t1 = min(a.cell_start[g + 1], t0 + kDenseSlice);
         const int U = a.usz[g];
         const int64_t ub = a.uoff[g];
-        const int nchunk = (U + K - 1) / K;
-        // this wavefront's first (target, chunk) bit row: targets wv + NWV k of the unit
-        const int64_t brow = bits ? a.dboff[g] + static_cast<int64_t>(slice * kDenseSlice + wv) * nchunk : 0;
         Thresh th;
         th.init(sdesc.fr);
         const uint16_t tmid = sdesc.fr.t_mid;
@@ -2148,22 +2496,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
             const int nit = (nc + 127) >> 7;
             __syncthreads();
             // stage the chunk (padding tests as +inf / far away: never a neighbour)
-            if constexpr (BITS) {
-                // the fill with the count's bits: original indices and FP64 positions only
-                for (int e = threadIdx.x; e < K; e += NTH) {
-                    if (e < nc) {
-                        const int j = a.ulist[ub + c0 + e];
-                        const int oj = a.perm[j];
-                        sorig[e] = oj;
-#pragma unroll
-                        for (int k = 0; k < DIM; ++k)
-                            spj[k * K + e] = a.spos[static_cast<size_t>(j) * 4 + k];
-                        if (j >= t0 && j < t1) sself[j - t0] = c0 + e;  // a target of this unit
-                    } else {
-                        sorig[e] = -1;
-                    }
-                }
-            } else if constexpr (F16) {
+            if constexpr (F16) {
                 // pair m goes to record slot (m mod nit) 64 + m / nit: the test reads slot
                 // it 64 + lane, consecutive lanes, at iteration it
                 for (int m = threadIdx.x; m < 64 * nit; m += NTH) {
@@ -2222,10 +2555,6 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                 }
             }
             __syncthreads();
-            // bit row of target k of this wavefront in this chunk
-            auto bit_index = [&](int k) {
-                return (brow + static_cast<int64_t>(NWV * k) * nchunk + c0 / K) * 64 + lane;
-            };
             // the fill's emission of target k's accepted candidates in this chunk: bit j of
             // M is the lane's candidate 2 lane nit + j
             auto fill_row = [&](int k, uint32_t M, const double* pi) {
@@ -2248,14 +2577,8 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                     if (slot < rl && room) {
                         float dv;
                         if (F16) {
-                            // the FP64 displacement rounded once to FP32 per axis
-                            float s2 = 0.0f;
-#pragma unroll
-                            for (int d = 0; d < DIM; ++d) {
-                                const float f = static_cast<float>(spj[d * K + e] - pi[d]);
-                                s2 = s2 + f * f;
-                            }
-                            dv = __builtin_amdgcn_sqrtf(s2);
+                            double pj[3] = {spj[e], spj[K + e], DIM == 3 ? spj[(DIM - 1) * K + e] : 0.0};
+                            dv = dist_quanta<DIM>(sdesc.fr, pi, pj);
                         } else {
                             dv = static_cast<float>(__dsqrt_rn(r2_fp64<DIM>(pis, spj + e * DIM)));
                         }
@@ -2269,11 +2592,11 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                         }
                     }
                 };
+                const int lb = 2 * lane * nit;  // the lane's first candidate
                 // the target itself is never its own neighbour and half lists keep only
                 // larger original indices: the union is in original-index order, so both
                 // are a condition on the chunk position against the target's own, p
                 const int p = sself[wv + NWV * k] - c0;
-                const int lb = 2 * lane * nit;  // the lane's first candidate
                 const int d = p - lb;
                 if (a.half) M &= d < 0 ? 0xFFFFu : (d >= 15 ? 0u : (0xFFFEu << d) & 0xFFFFu);
                 else if (p >= 0 && p < nc && d >= 0 && d < 2 * nit) M &= ~(1u << d);
@@ -2304,33 +2627,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                 if (!room && lane == 0 && w > done) atomicOr(a.err, kErrCapacity);
                 if (lane == k) acc_k = w;
             };
-            if constexpr (BITS) {
-                // the count's bits, loaded for eight targets at a time and packed two to a
-                // register at once (waiting for a load also waits for every store issued
-                // before it, so that wait is paid once per eight rows); each row takes the
-                // low half and the rest shift down
-                uint32_t wp0 = 0, wp1 = 0, wp2 = 0, wp3 = 0;
-                for (int k = 0; k < nt; ++k) {
-                    if ((k & 7) == 0) {
-                        uint32_t wb[8];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) wb[t] = a.dbits[bit_index(min(k + t, nt - 1))];
-                        wp0 = wb[0] | (wb[1] << 16);
-                        wp1 = wb[2] | (wb[3] << 16);
-                        wp2 = wb[4] | (wb[5] << 16);
-                        wp3 = wb[6] | (wb[7] << 16);
-                    }
-                    const uint32_t w16 = wp0 & 0xFFFFu;
-                    wp0 = (wp0 >> 16) | (wp1 << 16);
-                    wp1 = (wp1 >> 16) | (wp2 << 16);
-                    wp2 = (wp2 >> 16) | (wp3 << 16);
-                    wp3 >>= 16;
-                    double pi[3];
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) pi[d] = rlf64(pi_k[d], k);
-                    fill_row(k, w16, pi);
-                }
-            } else {
+            {
                 for (int k = 0; k < nt; ++k) {
                     const int oi = rl32(oi_k, k);
                     double pi[3] = {0.0, 0.0, 0.0};
@@ -2339,7 +2636,7 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
 #pragma unroll
                         for (int d = 0; d < 3; ++d) pi[d] = rlf64(pi_k[d], k);
                     }
-                    uint32_t inb = 0, bnd = 0, gt = 0;
+                    uint32_t inb = 0, bnd = 0;
                     {
                         h2 qix2, qiy2, qiz2;
                         if (F16) {
@@ -2358,10 +2655,6 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                             if (it >= nit) break;
                             const int m = it * 64 + lane;  // record slot of pair lane nit + it
                             const int e0 = 2 * (lane * nit + it);
-                            if (!FILL && a.half) {  // half lists: candidates of larger original index
-                                const int2 oo = *reinterpret_cast<const int2*>(&sorig[e0]);
-                                gt |= (oo.x > oi ? 1u << it : 0u) | (oo.y > oi ? 1u << (16 + it) : 0u);
-                            }
                             if (F16) {
                                 const uint4 A = recA[m];
                                 const uint2 B = recB[m];
@@ -2482,37 +2775,12 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
                                 }
                             }
                         }
-                        if (!FILL && bits) {
-                            // the decided bits, before the half-list mask; stored eight targets at
-                            // a time, so the band recheck's loads seldom wait for a store
-                            uint16_t* const cb = sbits + wv * 8 * 64;
-                            cb[(k & 7) * 64 + lane] = static_cast<uint16_t>(interleave8(inb & 0x007F007Fu));
-                            if ((k & 7) == 7 || k == nt - 1) {
-                                const int k0 = k & ~7;
-                                for (int t = 0; t <= (k & 7); ++t) a.dbits[bit_index(k0 + t)] = cb[t * 64 + lane];
-                            }
-                        }
                     }
-                    if constexpr (!FILL) {
-                        if (a.half) inb &= gt;
-                        const int tot = wave_sum_i32(__builtin_popcount(inb));
-                        if (lane == k) acc_k += tot;
-                    } else {
-                        fill_row(k, interleave8(inb), pi);
-                    }
+                    if constexpr (FILL) fill_row(k, interleave8(inb), pi);
                 }
             }
         }
-        if (vk) {
-            if (!FILL) {
-                // itself: "in" in FP16 when T_lo > 0, always in the FP64 baseline; never
-                // counted when every candidate is decided in FP64 (it is skipped there)
-                const int self = a.half ? 0 : (MODE == 1 ? 1 : (MODE == 2 ? 0 : (tlo > 0 ? 1 : 0)));
-                a.counts[oi_k] = acc_k - self;
-            } else if (acc_k != rl_k) {
-                atomicOr(a.err, kErrLongRow);
-            }
-        }
+        if (FILL && vk && acc_k != rl_k) atomicOr(a.err, kErrLongRow);
     }
     if (!FILL) {
 #pragma unroll
@@ -2529,32 +2797,56 @@ __global__ void __launch_bounds__(BITS ? kDenseBitsThreads : kDenseThreads)
     }
 }
 
-template <int D, int M>
-void launch_dense_pass(const SearchArgs& a, bool fill, hipStream_t st)
+template <int D>
+void launch_dense_count(const SearchArgs& a, hipStream_t st)
 {
     const dim3 g(a.dgrid), b(kDenseThreads);
-    if (!fill) {
-        hipLaunchKernelGGL((k_dense<D, M, false>), g, b, 0, st, a);
-        return;
-    }
-    // FP16 fills: both kernels run, and the one that does not match whether the count kept
-    // its bits returns at once
-    if constexpr (M != 1) hipLaunchKernelGGL((k_dense<D, M, true, true>), g, dim3(kDenseBitsThreads), 0, st, a);
-    hipLaunchKernelGGL((k_dense<D, M, true, false>), g, b, 0, st, a);
+    const bool f16 = a.L.mode == 0;  // the others decide dense cells in binary64
+    if (f16 && a.half) hipLaunchKernelGGL((k_dense_count<D, 16, true>), g, b, 0, st, a);
+    else if (f16) hipLaunchKernelGGL((k_dense_count<D, 16, false>), g, b, 0, st, a);
+    else if (a.half) hipLaunchKernelGGL((k_dense_count<D, 64, true>), g, b, 0, st, a);
+    else hipLaunchKernelGGL((k_dense_count<D, 64, false>), g, b, 0, st, a);
 }
 
-hipError_t launch_dense(const SearchArgs& a, bool fill, hipStream_t st)
+// Both fills run, and the one that does not match whether the count kept its bits returns at
+// once.
+template <int D>
+void launch_dense_fill(const SearchArgs& a, hipStream_t st)
+{
+    const dim3 g(a.dgrid), b(kDenseThreads), bb(kDenseFillThreads);
+    if (a.L.mode == 0) {
+        if (a.dbits) hipLaunchKernelGGL((k_dense_fill<D, false>), g, bb, 0, st, a);
+        hipLaunchKernelGGL((k_dense<D, 0, true>), g, b, 0, st, a);
+    } else {
+        if (a.dbits) hipLaunchKernelGGL((k_dense_fill<D, true>), g, bb, 0, st, a);
+        hipLaunchKernelGGL((k_dense<D, 1, true>), g, b, 0, st, a);
+    }
+}
+
+template <int D>
+void launch_dense_stats(const SearchArgs& a, hipStream_t st)
+{
+    const dim3 g(a.dgrid), b(kDenseThreads);
+    if (a.L.mode == 0) hipLaunchKernelGGL((k_dense<D, 0, false>), g, b, 0, st, a);
+    else if (a.L.mode == 2) hipLaunchKernelGGL((k_dense<D, 2, false>), g, b, 0, st, a);
+    else hipLaunchKernelGGL(k_dense_stats64, g, b, 0, st, a);
+}
+
+hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st)
 {
     if (a.L.ntot == 0 || !a.wdense) return hipSuccess;
     hipError_t e = launch_fill_i32(a.ucount, 1, 0, st);
     if (e != hipSuccess) return e;
-    const int d = a.L.dim, m = a.L.mode == 3 ? 1 : a.L.mode;  // FP32 mode: dense cells in FP64
-    if (d == 2 && m == 0) launch_dense_pass<2, 0>(a, fill, st);
-    else if (d == 3 && m == 0) launch_dense_pass<3, 0>(a, fill, st);
-    else if (d == 2 && m == 1) launch_dense_pass<2, 1>(a, fill, st);
-    else if (d == 3 && m == 1) launch_dense_pass<3, 1>(a, fill, st);
-    else if (d == 2) launch_dense_pass<2, 2>(a, fill, st);
-    else launch_dense_pass<3, 2>(a, fill, st);
+    if (pass == DensePass::kCount) {
+        if (a.L.dim == 2) launch_dense_count<2>(a, st);
+        else launch_dense_count<3>(a, st);
+    } else if (pass == DensePass::kFill) {
+        if (a.L.dim == 2) launch_dense_fill<2>(a, st);
+        else launch_dense_fill<3>(a, st);
+    } else {
+        if (a.L.dim == 2) launch_dense_stats<2>(a, st);
+        else launch_dense_stats<3>(a, st);
+    }
     return hipGetLastError();
 }
 

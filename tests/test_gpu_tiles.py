@@ -99,3 +99,45 @@ def test_tiles_against_the_oracle(mode, half):
     finally:
         ctx.set_tuning()
         ctx.close()
+
+
+@pytest.mark.parametrize("half", [False, True], ids=["full", "half"])
+@pytest.mark.parametrize("mode", MODES)
+def test_dense_tiles_against_the_oracle(mode, half):
+    """Every cell through the dense-cell path: lists at the edges of a step (64 candidates), a
+    kept-bits row (1024) and a staged chunk (2048, 4096), units at the edges of a wavefront
+    and a slice (256 targets). The first search tests in the fill, the later ones take the
+    count's bits; both give the oracle's rows, and the same distances bit for bit."""
+    ctx = nnps.Context(0)
+    try:
+        ctx.set_tuning(dense_min_union=1)
+        pss = [blob(n, dim, 100 + n) for dim in (2, 3) for n in (2, 63, 64, 65, 255, 256, 257, 1024, 1025, 2049, 4097)]
+        pss += [p for p in cases() if p.name.startswith("near") or "_1e-30" in p.name or "_1000000" in p.name]
+        for ps in pss:
+            print(f"[gpu] dense tiles {ps.name} n={ps.n} {mode} half={half}", flush=True)
+            want = oracle.search_ps(ps)
+            if half:
+                want = half_of(*want)
+            pos = torch.from_numpy(np.ascontiguousarray(ps.pos)).cuda()
+            cells = ctx.cells()
+            cells.set_half(half)
+            first = None
+            for rep in range(2):
+                rp, col, dist, _ = nnps.search(pos, ps.lo, ps.hi, ps.cell_size, ps.radius, mode=MODES[mode], ctx=ctx,
+                                               cells=cells)
+                assert cells.stats()["dense_rows"] > 0
+                np.testing.assert_array_equal(rp.cpu().numpy(), want[0], err_msg=ps.name)
+                np.testing.assert_array_equal(col.cpu().numpy(), want[1], err_msg=ps.name)
+                d = dist.cpu().numpy()
+                if mode in ("fp64", "fp32"):
+                    np.testing.assert_array_equal(d.view(np.uint32), want[2].view(np.uint32), err_msg=ps.name)
+                else:
+                    w = want[2].astype(np.float64)
+                    assert np.all(np.abs(d - w) <= 1e-6 * w), ps.name
+                if rep:
+                    np.testing.assert_array_equal(d, first, err_msg=ps.name)
+                first = d
+            cells.close()
+    finally:
+        ctx.set_tuning()
+        ctx.close()
