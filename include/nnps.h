@@ -384,7 +384,7 @@ nnps_status nnps_probe_valu_rate(int32_t device, int32_t kind, double *rate, int
 enum {
     NNPS_PHASE_ASSIGN = 0,   /* FP64 cell assignment + cell histogram */
     NNPS_PHASE_CELLSCAN,     /* exclusive scan of the histogram -> cell starts */
-    NNPS_PHASE_SORT,         /* radix sort of (cell key, index) */
+    NNPS_PHASE_SORT,         /* counting sort by cell */
     NNPS_PHASE_PACK,         /* FP16 relative-coordinate pack (or sorted FP64 copy) */
     NNPS_PHASE_BLOCKS,       /* work-block table */
     NNPS_PHASE_UNIONS,       /* dense cells: stencil-union lists sorted by original index */
@@ -399,7 +399,9 @@ enum {
 
 /* Turn per-phase HIP-event timing on (on != 0) or off for a cell structure, and forget
  * what was recorded. Events are recorded on the stream of each call; no extra
- * synchronisation is added. */
+ * synchronisation is added. While it is on, the phases run in launches of their own;
+ * otherwise the block table and the dense cells' sizes share launches with the sort and
+ * the pack, and a step is shorter than the sum of its phases. */
 nnps_status nnps_cells_set_profiling(nnps_cells *cells, int on);
 
 /* Waits for the stream, then writes for each phase the summed device time in

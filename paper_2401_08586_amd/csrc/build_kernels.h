@@ -19,27 +19,22 @@ struct Launch {
 };
 
 hipError_t launch_fill_i32(int* p, int64_t m, int v, hipStream_t st);
-hipError_t launch_fill2_i32(int* p, int64_t m, int* q, int64_t k, int v, hipStream_t st);
 int row_segments(int ncx);  // pieces a row of ncx cells is walked in
 hipError_t launch_assign(const Launch& L, uint32_t* key, int* slot, int* cell_count, int* err,
                          hipStream_t st);
-hipError_t launch_place(int ntot, const uint32_t* key, const int* slot, const int* cell_start, uint32_t* skey,
-                        int* perm, hipStream_t st);
-hipError_t launch_scan_i32_i32(const int* in, int64_t m, int* out, int64_t* partial, hipStream_t st);
-hipError_t launch_scan_i32_i64(const int* in, int64_t m, int64_t* out, int64_t* partial, hipStream_t st);
+// Cell starts from the cells' counts; also starts the structure's flags for this build.
+hipError_t launch_cell_scan(const Launch& L, const int* cell_count, int* cell_start, int64_t* partial, int* flags,
+                            hipStream_t st);
 int64_t scan_partials_needed(int64_t m);
 int radix_tiles(int n);
 size_t radix_table_entries(int n);
-hipError_t launch_pack(const Launch& L, const uint32_t* skey, const int* perm, double* spos, float4* rq, int* inv,
-                       hipStream_t st, uint32_t* skey_out = nullptr, int* perm_out = nullptr);
-
 // Incremental update of a built structure (see k_upd_move): device tables of one update.
 struct Update {
     uint32_t* knew;           // [ntot] new cell key by particle
     uint32_t* mig;            // [ceil(ntot / 32)] bit s: the particle at old position s changed cell
     int* leave;               // [ncell_tot + 1] migrants out of each cell
     int* arrive;              // [ncell_tot + 1] migrants into each cell
-                              // (leave, arrive and mig are one zeroed block: see update_of)
+                              // (leave, arrive and mig are one block, zero between updates: see update_of)
     int* aslot;               // [ntot] by particle: a migrant's arrival slot in its new cell
     int* cs_old;              // [ncell_tot + 1] cell starts before the update
     uint32_t* skey2;          // [ntot] new order: cell keys
@@ -50,13 +45,7 @@ hipError_t launch_update_move(const Launch& L, const uint32_t* skey, const int* 
                               hipStream_t st);
 // U2: new cell occupancies and starts (cell_start is rewritten; the old one goes to cs_old).
 hipError_t launch_update_cells(const Launch& L, int* cell_start, int* cnt, const Update& u, int64_t* partial,
-                               hipStream_t st);
-// U3: every particle's new sorted position (into skey2 / perm2).
-hipError_t launch_update_place(const Launch& L, const uint32_t* skey, const int* perm, const int* cell_start,
-                               const Update& u, hipStream_t st);
-hipError_t launch_blocks(const Launch& L, const int* cell_start, const int* wdense, int* boff, int* bstart, int* bset,
-                         int64_t* partial, hipStream_t st);
-
+                               int* flags, hipStream_t st);
 // Dense-cell path: device tables of one build. A cell is "dense" when its stencil holds
 // more than `thresh` particles; runs of dense cells get no work blocks. Each dense cell g owns the list ulist[uoff[g] ..
 // uoff[g] + usz[g]) of the sorted positions of the particles in its 3^d stencil, in
@@ -81,17 +70,62 @@ struct DenseBuild {
     int* dbn;               // [ncell_tot] (target, chunk) pairs of each dense cell
     int64_t* dboff;         // [ncell_tot + 1] exclusive scan of dbn
 };
-// Stencil sizes and the dense flag only (the path is not used by this build).
-hipError_t launch_dense_detect(const Launch& L, const int* cell_start, const DenseBuild& d, hipStream_t st);
-// Before the block table: stencil sizes, dense windows, union offsets and work units.
+
+// The sort by cell: of a build (key and slot of every particle), or of an update (moved: the
+// old order skey / perm and u, every particle's new sorted position going to u.skey2, u.perm2).
+struct PlaceArgs {
+    bool moved;
+    const uint32_t* key;
+    const int* slot;
+    uint32_t* skey_out;
+    int* perm_out;
+    const uint32_t* skey;
+    const int* perm;
+    Update u;
+};
+
+// The pack of the sorted particles (see pack_particle); skey_out / perm_out: a copy of the
+// order, or null; clear0, clear1: counters to leave zero for the next build or update.
+struct PackArgs {
+    const uint32_t* skey;
+    const int* perm;
+    double* spos;
+    float4* rq;
+    int* inv;
+    uint32_t* skey_out;
+    int* perm_out;
+    int* clear0;
+    int64_t nclear0;
+    int* clear1;
+    int64_t nclear1;
+};
+
+// The work-block table (see row_blocks).
+struct BlockTable {
+    const int* wdense;      // null: no dense cells
+    int* boff;              // [nrows_tot + 1] blocks of each segment, then the total
+    int* bstart;            // [total + 1]
+    int* bset;              // [total]
+    const int* cell_start;  // set by the launchers
+    int fold;
+};
+
+// After the cell starts: the sort (place), the stencil sizes with the dense flag (dense) and
+// the segments' block counts (blocks), each if given.
+hipError_t launch_sort(const Launch& L, const PlaceArgs* place, const DenseBuild* dense, const BlockTable* blocks,
+                       const int* cell_start, hipStream_t st);
+// After that: the pack and the block table, each if given.
+hipError_t launch_pack(const Launch& L, const PackArgs* pack, const BlockTable* blocks, const int* cell_start,
+                       int64_t* partial, hipStream_t st);
+// After the stencil sizes, before the block table: dense windows, union offsets, work units.
 hipError_t launch_dense_cells(const Launch& L, const int* cell_start, const DenseBuild& d, hipStream_t st);
 // After the sort and pack: the union lists. *ulist receives the sorted list array.
 hipError_t launch_dense_unions(const Launch& L, const uint32_t* skey, const int* inv, const DenseBuild& d,
                                hipStream_t st, int** ulist);
 // Row pointers of every set from the counts; also each particle's row start by sorted
 // position (rsort[inv[i]]).
-hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* rowg, int64_t* partial, int64_t* nnz,
-                         const int* inv, int64_t* rsort, hipStream_t st);
+hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* partial, int64_t* nnz, const int* inv,
+                         int64_t* rsort, hipStream_t st);
 
 // Search passes over every block of every set. `nblk_max` bounds the number of blocks
 // (the exact count is on the device).
@@ -112,14 +146,13 @@ struct SearchArgs {
     uint16_t* branks;         // [nblk_max][union limit] ranks of each block's union by original index
                               // (the order of its candidate bits)
     int* heavy;               // sorted positions of long rows
-    int* nheavy;
+    int* flags;               // the structure's flags and counters (kFlag*)
     unsigned long long* stats;      // [kStCount] totals
     unsigned long long* blk_stats;  // [nblk_max][5] per-block partial statistics
     uint32_t* cbits;                // accepted-candidate bits, word-major [words][ntot]
     uint32_t* lrscratch;            // long-row path merge scratch, per workgroup
     int64_t lrscratch_words;        // its size per workgroup (32-bit words)
     int lr_keys;                    // keys a long-row workgroup sorts in LDS
-    int* err;
     int* sink;                      // [2 * 64] per-lane dummy output slots
     int half;                       // 1: rows keep only neighbours of larger original index
     // dense-cell path (wdense == nullptr: off)
@@ -130,7 +163,6 @@ struct SearchArgs {
     const int* unit_off;
     const int* ucell;
     const int* dn;
-    int* ucount;                    // work-unit counter (zeroed before each launch)
     unsigned long long* dstats;     // [dgrid][kDenseStats] per-workgroup statistics
     int dgrid;
     // the dense count keeps each target's accepted bits per chunk of kDenseChunk candidates,

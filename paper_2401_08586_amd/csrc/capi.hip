@@ -262,6 +262,7 @@ struct nnps_cells {
     GraphCache graph;
     bool use_graphs = false;
     bool half = false;                    // rows keep only neighbours of larger original index
+    bool counters_clear = false;          // see clear_counters
     bool built = false, counted = false;
     int nsets = 0, dim = 0, mode = 0, ntot = 0, ncell_tot = 0, nblk_max = 0;
     std::vector<Frame> frames;
@@ -276,7 +277,7 @@ struct nnps_cells {
     std::vector<unsigned char> up_sets, up_offs;
     uint64_t up_gen = ~0ull;
     int64_t* h_report = nullptr;          // pinned: nnz per set, then error and dense words
-    int h_report_cap = 0;
+    size_t h_report_cap = 0;
     hipEvent_t report_done = nullptr;     // the last enqueued report's copies
     bool report_pending = false;
     uint64_t buf_gen = 0;                 // bumps whenever a device buffer moves
@@ -284,7 +285,7 @@ struct nnps_cells {
     int* perm = nullptr;
     DevBuf counts_s, rsort, bdesc, branks;
     DevBuf d_sets, d_offs, k0, k1, v0, v1, cell_count, cell_start, spos, rq, boff, bstart, bset,
-        counts, table, partial, stats, blk_stats, cbits, err, heavy, nheavy, rowg, nnz, sink;
+        counts, table, partial, stats, blk_stats, cbits, report, heavy, sink;
     // dense-cell path (see DenseBuild)
     bool dense = false;         // the tuning allows the dense-cell path
     bool dense_active = false;  // the last build uses it
@@ -292,7 +293,7 @@ struct nnps_cells {
     int dthresh = 0, dgrid = 0;
     int64_t dcap = 0;
     int* ulist = nullptr;
-    DevBuf usz, wdense, uoff, nsl, unit_off, ucell, dn, ecnt, epos, uk0, uk1, uv0, uv1, inv, ucount, dstats, dseen;
+    DevBuf usz, wdense, uoff, nsl, unit_off, ucell, dn, ecnt, epos, uk0, uk1, uv0, uv1, inv, dstats;
     // dense passes: (target, chunk) offsets per cell and the count's accepted bits,
     // sized at a build from what the last synchronising call found the dense cells need
     DevBuf dbn, dboff, dbits;
@@ -308,6 +309,9 @@ struct nnps_cells {
     } while (0)
 
 namespace {
+
+// Each set's neighbour count, after the flags (one copy brings both to the host).
+int64_t* nnz_of(const nnps_cells* c) { return reinterpret_cast<int64_t*>(c->report.as<int>() + kFlags); }
 
 nnps_status err_status(int err)
 {
@@ -340,10 +344,15 @@ nnps_status upload(nnps_cells* c, bool with_offsets, hipStream_t s)
     const bool sets_ok = gen_ok && c->up_sets.size() == ns && memcmp(c->up_sets.data(), hs, ns) == 0;
     const bool offs_ok = !with_offsets || (gen_ok && c->up_offs.size() == no && memcmp(c->up_offs.data(), ho, no) == 0);
     if (sets_ok && offs_ok) return NNPS_OK;
-    if (!gen_ok) c->up_offs.clear();  // the offsets buffer moved too: not known to hold anything
-    HIP_TRY(hipMemcpyAsync(c->d_sets.p, c->h_sets, ns, hipMemcpyHostToDevice, s));
-    c->up_sets.assign(hs, hs + ns);
-    if (with_offsets) {
+    if (!gen_ok) {  // the buffers moved: not known to hold anything
+        c->up_sets.clear();
+        c->up_offs.clear();
+    }
+    if (!sets_ok) {
+        HIP_TRY(hipMemcpyAsync(c->d_sets.p, c->h_sets, ns, hipMemcpyHostToDevice, s));
+        c->up_sets.assign(hs, hs + ns);
+    }
+    if (!offs_ok) {
         HIP_TRY(hipMemcpyAsync(c->d_offs.p, c->h_offs, no, hipMemcpyHostToDevice, s));
         c->up_offs.assign(ho, ho + no);
     }
@@ -397,14 +406,13 @@ SearchArgs args_of(const nnps_cells* c)
     a.bdesc = c->bdesc.as<int>();
     a.branks = c->branks.as<uint16_t>();
     a.heavy = c->heavy.as<int>();
-    a.nheavy = c->nheavy.as<int>();
+    a.flags = c->report.as<int>();
     a.stats = c->stats.as<unsigned long long>();
     a.blk_stats = c->blk_stats.as<unsigned long long>();
     a.cbits = c->cbits.as<uint32_t>();
     int keys = 1;
     while (keys * 2 <= std::min(c->ctx->max_lds - 1024, 64 * 1024) / 4) keys *= 2;
     a.lr_keys = c->ctx->tuning.long_rows_keys > 0 ? std::min(c->ctx->tuning.long_rows_keys, keys) : keys;
-    a.err = c->err.as<int>();
     a.sink = c->sink.as<int>();
     a.half = c->half ? 1 : 0;
     if (c->dense_active) {
@@ -415,7 +423,6 @@ SearchArgs args_of(const nnps_cells* c)
         a.unit_off = c->unit_off.as<int>();
         a.ucell = c->ucell.as<int>();
         a.dn = c->dn.as<int>();
-        a.ucount = c->ucount.as<int>();
         a.dstats = c->dstats.as<unsigned long long>();
         a.dgrid = c->dgrid;
         a.dboff = c->dboff.as<int64_t>();
@@ -447,14 +454,14 @@ DenseBuild dense_of(nnps_cells* c)
     d.uv1 = c->uv1.as<int>();
     d.table = c->table.as<uint32_t>();
     d.partial = c->partial.as<int64_t>();
-    d.seen = c->dseen.as<int>();
+    d.seen = c->report.as<int>() + kFlagSeen;
     d.dbn = c->dbn.as<int>();
     d.dboff = c->dboff.as<int64_t>();
     return d;
 }
 
 // Validate a batch, lay out its grids and index spaces, size the device buffers and fill
-// the pinned set table (output pointers cleared). No device work is queued.
+// the pinned set table (its output pointers untouched). No device work is queued.
 nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem* probs, const double* const* d_pos)
 {
     if (nsets < 1 || !probs || !d_pos) return NNPS_EINVAL;
@@ -483,6 +490,7 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
             hipHostMalloc(reinterpret_cast<void**>(&c->h_offs), sizeof(int) * 3 * (nsets + 1),
                           hipHostMallocDefault) != hipSuccess)
             return NNPS_ENOMEM;
+        memset(c->h_sets, 0, sizeof(SetDesc) * nsets);
         c->h_cap = nsets;
     }
     if (!c->upload_done && hipEventCreateWithFlags(&c->upload_done, hipEventDisableTiming) != hipSuccess)
@@ -502,7 +510,15 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     int64_t nblk_bound = 0;
     for (int s = 0; s < nsets; ++s) {
         SetDesc& sd = c->h_sets[s];
+        // the output pointers of the call before stay: nothing reads them before the count or
+        // fill that sets its own, and a search into the same outputs then finds its table
+        // already on the device
+        const SetDesc was = sd;
         memset(&sd, 0, sizeof(sd));
+        sd.row_ptr = was.row_ptr;
+        sd.col = was.col;
+        sd.dist = was.dist;
+        sd.capacity = was.capacity;
         sd.fr = frames[s];
         sd.poff = poff;
         sd.coff = coff;
@@ -562,17 +578,15 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         {&c->stats, kStCount * 8},
         {&c->blk_stats, static_cast<size_t>(std::max(c->nblk_max, 1)) * 5 * 8},
         {&c->cbits, nn * cw * 4},
-        {&c->err, 4}, {&c->heavy, nn * 4}, {&c->nheavy, 4}, {&c->sink, 2 * 64 * 4},
-        {&c->rowg, (nn + 1) * 8},
-        {&c->nnz, sizeof(int64_t) * nsets},
+        {&c->heavy, nn * 4}, {&c->sink, 2 * 64 * 4},
+        {&c->report, sizeof(int) * kFlags + sizeof(int64_t) * nsets},
         {&c->usz, c->dense ? (nc + 1) * 4 : 0}, {&c->wdense, c->dense ? (nc + 1) * 4 : 0},
         {&c->uoff, c->dense ? (nc + 1) * 8 : 0}, {&c->nsl, c->dense ? (nc + 1) * 4 : 0},
         {&c->unit_off, c->dense ? (nc + 1) * 4 : 0}, {&c->ucell, c->dense ? (nn + 1) * 4 : 0},
         {&c->dn, c->dense ? size_t(4) : size_t(0)}, {&c->ecnt, c->dense ? nn * 4 : 0}, {&c->epos, c->dense ? (nn + 1) * 4 : 0},
         {&c->uk0, dcap * 4}, {&c->uk1, dcap * 4}, {&c->uv0, dcap * 4}, {&c->uv1, dcap * 4},
-        {&c->inv, nn * 4}, {&c->ucount, c->dense ? size_t(4) : size_t(0)},
+        {&c->inv, nn * 4},
         {&c->dstats, c->dense ? static_cast<size_t>(c->dgrid) * kDenseStats * 8 : 0},
-        {&c->dseen, c->dense ? size_t(4) : size_t(0)},
         {&c->dbn, c->dense ? (nc + 1) * 4 : 0}, {&c->dboff, c->dense ? (nc + 1) * 8 : 0},
         {&c->dbits, dense_bits_on(c) ? c->dbits_want : 0},
         // leave, arrive (ncell + 1 each) and the migrant bits (ceil(n / 32) words), one block
@@ -582,16 +596,17 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     for (auto& q : need) {
         if (q.bytes == 0) continue;
         void* before = q.b->p;
+        const size_t cap = q.b->cap;
         hipError_t e = q.b->ensure(q.bytes);
         if (e != hipSuccess) return e == hipErrorOutOfMemory ? NNPS_ENOMEM : NNPS_EDEVICE;
         if (q.b->p != before) ++c->buf_gen;
+        // (new memory may have the old address)
+        if (q.b->cap != cap && (q.b == &c->cell_count || q.b == &c->uleave || q.b == &c->report)) c->counters_clear = false;
     }
     c->built = false;
     c->counted = false;
     return NNPS_OK;
 }
-
-nnps_status enqueue_build_tail(nnps_cells* c, hipStream_t s);
 
 Update update_of(nnps_cells* c)
 {
@@ -607,6 +622,67 @@ Update update_of(nnps_cells* c)
     return u;
 }
 
+// The counters that a build or an update adds to are zero between calls: each leaves them so
+// (in its pack), and this clears them, whole buffers, where none has: new buffers, and after
+// a sequence that an error cut short.
+nnps_status clear_counters(nnps_cells* c, hipStream_t s)
+{
+    if (c->counters_clear) return NNPS_OK;
+    for (const DevBuf* b : {&c->cell_count, &c->uleave})
+        HIP_TRY(launch_fill_i32(b->as<int>(), static_cast<int64_t>(b->cap / 4), 0, s));
+    HIP_TRY(launch_fill_i32(c->report.as<int>(), kFlags, 0, s));
+    c->counters_clear = true;
+    return NNPS_OK;
+}
+
+// After the new cell starts (build or update): the sorted order, the sorted arrays, the
+// dense-cell tables and the work blocks. The block counts and the stencil sizes go with the
+// sort and the block table with the pack, in one launch each, except where the blocks have to
+// wait for the dense cells and where the phases are timed apart.
+nnps_status enqueue_sorted(nnps_cells* c, const PlaceArgs& place, const PackArgs& pack, hipStream_t s)
+{
+    const Launch L = launch_of(c);
+    PhaseTimer& tm = c->timer;
+    const int* cell_start = c->cell_start.as<int>();
+    int64_t* partial = c->partial.as<int64_t>();
+    // The dense-cell path runs unless the last synchronising call saw no dense cell; the
+    // stencil sizes are computed either way, so a change is seen at the next such call.
+    c->dense_active = c->dense && c->dense_seen != 0;
+    const DenseBuild d = dense_of(c);
+    BlockTable t{};
+    t.wdense = c->dense_active ? c->wdense.as<int>() : nullptr;
+    t.boff = c->boff.as<int>();
+    t.bstart = c->bstart.as<int>();
+    t.bset = c->bset.as<int>();
+    const DenseBuild* sizes = c->dense && !tm.on ? &d : nullptr;
+    const BlockTable* blocks = !c->dense_active && !tm.on ? &t : nullptr;
+    tm.begin(NNPS_PHASE_SORT, s);
+    HIP_TRY(launch_sort(L, &place, sizes, blocks, cell_start, s));
+    tm.end(NNPS_PHASE_SORT, s);
+    tm.begin(NNPS_PHASE_PACK, s);
+    HIP_TRY(launch_pack(L, &pack, blocks, cell_start, partial, s));
+    tm.end(NNPS_PHASE_PACK, s);
+    if (c->dense && (c->dense_active || !sizes)) {
+        tm.begin(NNPS_PHASE_UNIONS, s);
+        if (!sizes) HIP_TRY(launch_sort(L, nullptr, &d, nullptr, cell_start, s));
+        if (c->dense_active) {
+            HIP_TRY(launch_dense_cells(L, cell_start, d, s));
+            HIP_TRY(launch_dense_unions(L, c->skey, c->inv.as<int>(), d, s, &c->ulist));
+        }
+        tm.end(NNPS_PHASE_UNIONS, s);
+    }
+    if (!blocks) {
+        tm.begin(NNPS_PHASE_BLOCKS, s);
+        HIP_TRY(launch_sort(L, nullptr, nullptr, &t, cell_start, s));
+        HIP_TRY(launch_pack(L, nullptr, &t, cell_start, partial, s));
+        tm.end(NNPS_PHASE_BLOCKS, s);
+    }
+    c->counters_clear = true;
+    c->built = true;
+    c->counted = false;
+    return NNPS_OK;
+}
+
 // The stream-ordered incremental update: move and re-bin (the assignment phase), new
 // cell starts (cell scan), new sorted positions (sort), pack (and copy the new order
 // back), then the same dense tables and blocks as a build.
@@ -615,22 +691,26 @@ nnps_status enqueue_update(nnps_cells* c, hipStream_t s)
     const Launch L = launch_of(c);
     PhaseTimer& tm = c->timer;
     const Update u = update_of(c);
-    const int64_t zero = 2 * (static_cast<int64_t>(c->ncell_tot) + 1) + (c->ntot + 31) / 32;
-    HIP_TRY(launch_fill2_i32(u.leave, zero, c->err.as<int>(), 1, 0, s));
+    int* flags = c->report.as<int>();
+    nnps_status st = clear_counters(c, s);
+    if (st != NNPS_OK) return st;
+    c->counters_clear = false;
     tm.begin(NNPS_PHASE_ASSIGN, s);
-    HIP_TRY(launch_update_move(L, c->skey, c->inv.as<int>(), u, c->err.as<int>(), s));
+    HIP_TRY(launch_update_move(L, c->skey, c->inv.as<int>(), u, flags + kFlagBad, s));
     tm.end(NNPS_PHASE_ASSIGN, s);
     tm.begin(NNPS_PHASE_CELLSCAN, s);
-    HIP_TRY(launch_update_cells(L, c->cell_start.as<int>(), c->cell_count.as<int>(), u, c->partial.as<int64_t>(), s));
+    HIP_TRY(launch_update_cells(L, c->cell_start.as<int>(), c->cell_count.as<int>(), u, c->partial.as<int64_t>(),
+                                flags, s));
     tm.end(NNPS_PHASE_CELLSCAN, s);
-    tm.begin(NNPS_PHASE_SORT, s);
-    HIP_TRY(launch_update_place(L, c->skey, c->perm, c->cell_start.as<int>(), u, s));
-    tm.end(NNPS_PHASE_SORT, s);
-    tm.begin(NNPS_PHASE_PACK, s);
-    HIP_TRY(launch_pack(L, u.skey2, u.perm2, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), s, c->skey,
-                        c->perm));
-    tm.end(NNPS_PHASE_PACK, s);
-    return enqueue_build_tail(c, s);
+    PlaceArgs place{};
+    place.moved = true;
+    place.skey = c->skey;
+    place.perm = c->perm;
+    place.u = u;
+    const PackArgs pack{u.skey2, u.perm2, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), c->skey, c->perm,
+                        c->cell_count.as<int>(), static_cast<int64_t>(c->ncell_tot) + 1,
+                        u.leave, 2 * (static_cast<int64_t>(c->ncell_tot) + 1) + (c->ntot + 31) / 32};
+    return enqueue_sorted(c, place, pack, s);
 }
 
 // The stream-ordered build: assign, cell starts, sort, pack, blocks.
@@ -638,55 +718,26 @@ nnps_status enqueue_build(nnps_cells* c, hipStream_t s)
 {
     const Launch L = launch_of(c);
     PhaseTimer& tm = c->timer;
-    HIP_TRY(launch_fill2_i32(c->cell_count.as<int>(), static_cast<int64_t>(c->ncell_tot) + 1, c->err.as<int>(), 1, 0, s));
+    int* flags = c->report.as<int>();
+    nnps_status st = clear_counters(c, s);
+    if (st != NNPS_OK) return st;
+    c->counters_clear = false;
     tm.begin(NNPS_PHASE_ASSIGN, s);
-    HIP_TRY(launch_assign(L, c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_count.as<int>(), c->err.as<int>(), s));
+    HIP_TRY(launch_assign(L, c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_count.as<int>(), flags + kFlagBad, s));
     tm.end(NNPS_PHASE_ASSIGN, s);
     tm.begin(NNPS_PHASE_CELLSCAN, s);
-    HIP_TRY(launch_scan_i32_i32(c->cell_count.as<int>(), c->ncell_tot, c->cell_start.as<int>(),
-                                c->partial.as<int64_t>(), s));
+    HIP_TRY(launch_cell_scan(L, c->cell_count.as<int>(), c->cell_start.as<int>(), c->partial.as<int64_t>(), flags, s));
     tm.end(NNPS_PHASE_CELLSCAN, s);
-    tm.begin(NNPS_PHASE_SORT, s);
-    HIP_TRY(launch_place(c->ntot, c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_start.as<int>(),
-                         c->k1.as<uint32_t>(), c->v0.as<int>(), s));
-    tm.end(NNPS_PHASE_SORT, s);
-    uint32_t* kf = c->k1.as<uint32_t>();
-    int* vf = c->v0.as<int>();
-    c->skey = kf;
-    c->perm = vf;
-    tm.begin(NNPS_PHASE_PACK, s);
-    HIP_TRY(launch_pack(L, c->skey, c->perm, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), s));
-    tm.end(NNPS_PHASE_PACK, s);
-    return enqueue_build_tail(c, s);
-}
-
-// After the cells and the sorted arrays are in place (build or update): the dense-cell
-// tables and the work blocks.
-nnps_status enqueue_build_tail(nnps_cells* c, hipStream_t s)
-{
-    const Launch L = launch_of(c);
-    PhaseTimer& tm = c->timer;
-    // The dense-cell path runs unless the last synchronising call saw no dense cell; the
-    // stencil sizes are computed either way, so a change is seen at the next such call.
-    c->dense_active = c->dense && c->dense_seen != 0;
-    if (c->dense) {
-        tm.begin(NNPS_PHASE_UNIONS, s);
-        const DenseBuild d = dense_of(c);
-        if (c->dense_active) {
-            HIP_TRY(launch_dense_cells(L, c->cell_start.as<int>(), d, s));
-            HIP_TRY(launch_dense_unions(L, c->skey, c->inv.as<int>(), d, s, &c->ulist));
-        } else {
-            HIP_TRY(launch_dense_detect(L, c->cell_start.as<int>(), d, s));
-        }
-        tm.end(NNPS_PHASE_UNIONS, s);
-    }
-    tm.begin(NNPS_PHASE_BLOCKS, s);
-    HIP_TRY(launch_blocks(L, c->cell_start.as<int>(), c->dense_active ? c->wdense.as<int>() : nullptr,
-                          c->boff.as<int>(), c->bstart.as<int>(), c->bset.as<int>(), c->partial.as<int64_t>(), s));
-    tm.end(NNPS_PHASE_BLOCKS, s);
-    c->built = true;
-    c->counted = false;
-    return NNPS_OK;
+    c->skey = c->k1.as<uint32_t>();
+    c->perm = c->v0.as<int>();
+    PlaceArgs place{};
+    place.key = c->k0.as<uint32_t>();
+    place.slot = c->v1.as<int>();
+    place.skey_out = c->skey;
+    place.perm_out = c->perm;
+    const PackArgs pack{c->skey, c->perm, c->spos.as<double>(), c->rq.as<float4>(), c->inv.as<int>(), nullptr, nullptr,
+                        c->cell_count.as<int>(), static_cast<int64_t>(c->ncell_tot) + 1, nullptr, 0};
+    return enqueue_sorted(c, place, pack, s);
 }
 
 // Count pass and row pointers (written into the row_ptr arrays of the set table).
@@ -704,8 +755,8 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s)
     // the per-block statistics stay in place until the next count; nnps_stats_get sums
     // them when asked, so a step does not pay for the reduction
     c->timer.begin(NNPS_PHASE_ROWSCAN, s);
-    HIP_TRY(launch_rowptr(a.L, c->counts.as<int>(), c->rowg.as<int64_t>(), c->partial.as<int64_t>(),
-                          c->nnz.as<int64_t>(), c->inv.as<int>(), c->rsort.as<int64_t>(), s));
+    HIP_TRY(launch_rowptr(a.L, c->counts.as<int>(), c->partial.as<int64_t>(), nnz_of(c), c->inv.as<int>(),
+                          c->rsort.as<int64_t>(), s));
     c->timer.end(NNPS_PHASE_ROWSCAN, s);
     c->counted = true;
     return NNPS_OK;
@@ -714,7 +765,6 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s)
 nnps_status enqueue_fill(nnps_cells* c, hipStream_t s)
 {
     SearchArgs a = args_of(c);
-    HIP_TRY(launch_fill_i32(c->nheavy.as<int>(), 1, 0, s));
     c->timer.begin(NNPS_PHASE_FILL, s);
     HIP_TRY(launch_fill(a, c->nblk_max, s));
     c->timer.end(NNPS_PHASE_FILL, s);
@@ -745,23 +795,26 @@ nnps_status read_nnz(nnps_cells* c, int64_t* h_nnz, hipStream_t s)
 {
     int64_t* hp = c->ctx->h_pinned;
     nnps_status st = NNPS_OK;
-    // the pinned staging holds 64 values: up to 62 counts per piece, the dense cells'
-    // (target, chunk) pairs, the error word and the dense flag
+    // the pinned staging holds 64 values: the flags with up to 60 counts, a copy a piece, and
+    // the dense cells' (target, chunk) pairs
     const bool bits = c->dense_active && dense_bits_on(c);
-    for (int s0 = 0; s0 < c->nsets; s0 += 62) {
-        const int k = std::min(62, c->nsets - s0);
-        HIP_TRY(hipMemcpyAsync(hp, c->nnz.as<int64_t>() + s0, 8 * k, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(hp + 63, c->err.p, 4, hipMemcpyDeviceToHost, s));
-        if (c->dense) HIP_TRY(hipMemcpyAsync(reinterpret_cast<int*>(hp + 63) + 1, c->dseen.p, 4, hipMemcpyDeviceToHost, s));
+    constexpr int kFlagWords = kFlags / 2, kPiece = 63 - kFlagWords;
+    const int64_t* rep = c->report.as<int64_t>();
+    for (int s0 = 0; s0 < c->nsets; s0 += kPiece) {
+        const int k = std::min(kPiece, c->nsets - s0);
+        const int skip = s0 == 0 ? 0 : kFlagWords;  // the flags come with the first piece
+        HIP_TRY(hipMemcpyAsync(hp + skip, rep + s0 + skip, 8 * (kFlagWords - skip + k), hipMemcpyDeviceToHost, s));
         if (bits && s0 == 0)
-            HIP_TRY(hipMemcpyAsync(hp + 62, c->dboff.as<int64_t>() + launch_of(c).ncell_tot, 8, hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipMemcpyAsync(hp + 63, c->dboff.as<int64_t>() + launch_of(c).ncell_tot, 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
-        for (int i = 0; i < k; ++i) h_nnz[s0 + i] = hp[i];
-        st = err_status(static_cast<int>(hp[63] & 0xFFFFFFFF));
-        if (c->dense) c->dense_seen = reinterpret_cast<int*>(hp + 63)[1] != 0 ? 1 : 0;
-        if (bits && s0 == 0) {
+        for (int i = 0; i < k; ++i) h_nnz[s0 + i] = hp[kFlagWords + i];
+        if (s0) continue;
+        const int* flags = reinterpret_cast<const int*>(hp);
+        st = err_status(flags[kFlagErr]);
+        if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+        if (bits) {
             // the next build keeps room for the count's bits if they fit the bound
-            const size_t want = static_cast<size_t>(hp[62]) * 64 * sizeof(uint16_t);
+            const size_t want = static_cast<size_t>(hp[63]) * 64 * sizeof(uint16_t);
             if (want <= dense_bits_bound(c)) c->dbits_want = std::max(c->dbits_want, want);
         }
     }
@@ -917,10 +970,10 @@ void nnps_cells_destroy(nnps_cells* c)
     if (c->upload_pending) (void)hipEventSynchronize(c->upload_done);
     DevBuf* all[] = {&c->d_sets, &c->d_offs, &c->k0, &c->k1, &c->v0, &c->v1, &c->cell_count,
                      &c->cell_start, &c->spos, &c->rq, &c->boff, &c->bstart, &c->bset, &c->counts,
-                     &c->table, &c->partial, &c->stats, &c->blk_stats, &c->cbits, &c->err, &c->heavy,
-                     &c->nheavy, &c->rowg, &c->nnz, &c->sink, &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
+                     &c->table, &c->partial, &c->stats, &c->blk_stats, &c->cbits, &c->report, &c->heavy,
+                     &c->sink, &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
                      &c->ucell, &c->dn, &c->ecnt, &c->epos, &c->uk0, &c->uk1, &c->uv0, &c->uv1, &c->inv,
-                     &c->ucount, &c->dstats, &c->dseen, &c->uleave, &c->ucs_old,
+                     &c->dstats, &c->uleave, &c->ucs_old,
                      &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc, &c->branks, &c->dbn, &c->dboff, &c->dbits};
     for (DevBuf* b : all) b->release();
     c->timer.release();
@@ -1242,6 +1295,7 @@ nnps_status nnps_batch_step(nnps_ctx* ctx, nnps_cells* c, int32_t nsets, const n
     const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0);
     memcpy(q, &plan, 4);
     (void)gen0;
+    if ((st = clear_counters(c, s)) != NNPS_OK) return st;  // outside the graph
     if (!c->graph.exec || c->graph.sig != sig) {
         c->graph.reset();
         hipGraph_t graph = nullptr;
@@ -1263,7 +1317,9 @@ nnps_status nnps_batch_step(nnps_ctx* ctx, nnps_cells* c, int32_t nsets, const n
         }
         c->graph.sig = sig;
     }
+    c->counters_clear = false;
     HIP_TRY(hipGraphLaunch(c->graph.exec, s));
+    c->counters_clear = true;
     c->built = true;
     c->counted = true;
     return NNPS_OK;
@@ -1331,6 +1387,7 @@ nnps_status nnps_batch_update_step(nnps_ctx* ctx, nnps_cells* c, const double* c
     q += 4;
     const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0);
     memcpy(q, &plan, 4);
+    if ((st = clear_counters(c, s)) != NNPS_OK) return st;  // outside the graph
     if (!c->ugraph.exec || c->ugraph.sig != sig) {
         c->ugraph.reset();
         hipGraph_t graph = nullptr;
@@ -1352,7 +1409,9 @@ nnps_status nnps_batch_update_step(nnps_ctx* ctx, nnps_cells* c, const double* c
         }
         c->ugraph.sig = sig;
     }
+    c->counters_clear = false;
     HIP_TRY(hipGraphLaunch(c->ugraph.exec, s));
+    c->counters_clear = true;
     c->built = true;
     c->counted = true;
     return NNPS_OK;
@@ -1376,23 +1435,18 @@ nnps_status nnps_batch_nnz_enqueue(nnps_cells* c, void* stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (c->report_pending) HIP_TRY(hipEventSynchronize(c->report_done));  // the buffer is reused
     c->report_pending = false;
-    if (c->h_report_cap < c->nsets + 2) {
+    const size_t bytes = sizeof(int) * kFlags + sizeof(int64_t) * c->nsets;
+    if (c->h_report_cap < bytes) {
         if (c->h_report) (void)hipHostFree(c->h_report);
         c->h_report = nullptr;
         c->h_report_cap = 0;
-        if (hipHostMalloc(reinterpret_cast<void**>(&c->h_report), sizeof(int64_t) * (c->nsets + 2),
-                          hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(reinterpret_cast<void**>(&c->h_report), bytes, hipHostMallocDefault) != hipSuccess)
             return NNPS_ENOMEM;
-        c->h_report_cap = c->nsets + 2;
+        c->h_report_cap = bytes;
     }
     if (!c->report_done && hipEventCreateWithFlags(&c->report_done, hipEventDisableTiming) != hipSuccess)
         return NNPS_EDEVICE;
-    int64_t* hp = c->h_report;
-    hp[c->nsets] = 0;
-    hp[c->nsets + 1] = 0;
-    HIP_TRY(hipMemcpyAsync(hp, c->nnz.p, 8 * c->nsets, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hp + c->nsets, c->err.p, 4, hipMemcpyDeviceToHost, s));
-    if (c->dense) HIP_TRY(hipMemcpyAsync(hp + c->nsets + 1, c->dseen.p, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(c->h_report, c->report.p, bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipEventRecord(c->report_done, s));
     c->report_pending = true;
     return NNPS_OK;
@@ -1405,10 +1459,10 @@ nnps_status nnps_batch_nnz_fetch(nnps_cells* c, int64_t* h_nnz)
     DeviceGuard g(c->ctx->device);
     if (!g.ok) return NNPS_EDEVICE;
     HIP_TRY(hipEventSynchronize(c->report_done));
-    const int64_t* hp = c->h_report;
-    for (int i = 0; i < c->nsets; ++i) h_nnz[i] = hp[i];
-    if (c->dense) c->dense_seen = static_cast<int>(hp[c->nsets + 1] & 0xFFFFFFFF) != 0 ? 1 : 0;
-    return err_status(static_cast<int>(hp[c->nsets] & 0xFFFFFFFF));
+    const int* flags = reinterpret_cast<const int*>(c->h_report);
+    for (int i = 0; i < c->nsets; ++i) h_nnz[i] = c->h_report[kFlags / 2 + i];
+    if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+    return err_status(flags[kFlagErr]);
 }
 
 nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
@@ -1420,19 +1474,18 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
     if (!g.ok) return NNPS_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
     unsigned long long st[kStCount];
-    int err = 0, nh = 0;
+    int flags[kFlags];
     // the sums of the last count pass's per-block (and dense-path) statistics; none
     // before a count
     HIP_TRY(launch_fill_i32(c->stats.as<int>(), 2 * kStCount, 0, s));
     if (c->counted) HIP_TRY(launch_stats(args_of(c), c->nblk_max, s));
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(st, c->stats.p, sizeof(st), hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&err, c->err.p, 4, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(&nh, c->nheavy.p, 4, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(flags, c->report.p, sizeof(flags), hipMemcpyDeviceToHost));
     out->n = c->ntot;
     if (c->counted) {
         std::vector<int64_t> nz(c->nsets);
-        HIP_TRY(hipMemcpy(nz.data(), c->nnz.p, 8 * c->nsets, hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(nz.data(), nnz_of(c), 8 * c->nsets, hipMemcpyDeviceToHost));
         for (int64_t v : nz) out->nnz += v;
     }
     out->candidates = static_cast<int64_t>(st[kStCandidates]);
@@ -1440,12 +1493,11 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
     out->fp16_false_pos = static_cast<int64_t>(st[kStFalsePos]);
     out->fp16_false_neg = static_cast<int64_t>(st[kStFalseNeg]);
     out->outside_band_disagree = static_cast<int64_t>(st[kStOutsideDisagree]);
-    out->heavy_rows = nh;
+    out->heavy_rows = flags[kFlagLong];
     out->dense_rows = static_cast<int64_t>(st[kStDenseRows]);
     if (c->dense) {
-        int dn = 0, seen = 0;
-        HIP_TRY(hipMemcpy(&seen, c->dseen.p, 4, hipMemcpyDeviceToHost));
-        c->dense_seen = seen != 0 ? 1 : 0;
+        int dn = 0;
+        c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
         if (c->dense_active) HIP_TRY(hipMemcpy(&dn, c->dn.p, 4, hipMemcpyDeviceToHost));
         out->dense_entries = dn;
     }
@@ -1457,7 +1509,7 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
         out->cell_width = c->frames[0].w;
     }
     out->band = ldexp(1.0, -7);
-    return err_status(err);
+    return err_status(flags[kFlagErr]);
 }
 
 nnps_status nnps_cells_set_profiling(nnps_cells* c, int on)

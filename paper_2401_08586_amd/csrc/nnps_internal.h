@@ -54,6 +54,22 @@ constexpr int kErrDomain = 1;
 constexpr int kErrCapacity = 2;
 constexpr int kErrLongRow = 4;
 
+// A structure's flags and counters (int32 on the device). A build or an update starts
+// them at zero; a pass leaves the counters it used as it found them, so a count or a
+// fill may follow another, or be replayed, without a launch that clears them.
+enum Flag {
+    kFlagErr = 0,    // device error flags
+    kFlagSeen,       // 1: some cell is dense
+    kFlagHeavy,      // long rows listed by the running fill
+    kFlagLong,       // long rows of the last fill
+    kFlagLongDone,   // workgroups of the long-row kernel that are through with the list
+    kFlagUnit,       // next work unit of the running dense pass
+    kFlagBad,        // the assignment's error flags (the cell starts' scan moves them on)
+    kFlagPad,
+    kFlags           // an even number: 64-bit counts follow
+};
+static_assert(kFlags % 2 == 0, "64-bit counts follow the flags");
+
 // Statistic slots (int64 on the device).
 enum StatSlot {
     kStCandidates = 0,

@@ -1444,6 +1444,7 @@ k_count(SearchArgs a)
     __shared__ int sred[2][NW];
     __shared__ int swsum[NW];
     __shared__ int spart[NW][64];
+    if (a.wdense && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense count behind this
     const int b = xcd_block(*a.nblk);
     if (b < 0) return;
     if (dense_block(a, b)) {
@@ -1603,7 +1604,7 @@ k_fill(SearchArgs a)
     const int p0 = dsc[0], nt = dsc[1] - p0, U = dsc[3];
     if (U > C::UCAP) {
         // too big for this path: every row of the block goes to the long-row path
-        if (tid < nt) a.heavy[atomicAdd(a.nheavy, 1)] = p0 + tid;
+        if (tid < nt) a.heavy[atomicAdd(a.flags + kFlagHeavy, 1)] = p0 + tid;
         return;
     }
     const NNPS_CONST SetDesc& sd = ((const NNPS_CONST SetDesc*)a.L.sets)[dsc[2]];
@@ -1697,14 +1698,14 @@ k_fill(SearchArgs a)
     }
     // a row whose bits do not match its count writes nothing
     const bool bad = __shfl(before + cnt, 48 + (lane & 15), 64) != rlen;
-    if (bad) atomicOr(a.err, kErrLongRow);
+    if (bad) atomicOr(a.flags + kFlagErr, kErrLongRow);
     __syncthreads();
     NNPS_GLOBAL int32_t* const col = (NNPS_GLOBAL int32_t*)sd.col;
     NNPS_GLOBAL float* const dist = (NNPS_GLOBAL float*)sd.dist;
     const int64_t cap = sd.capacity;
     const long long rend = active ? rs + rlen : 0;  // the row's end in the output
     const bool room = __builtin_amdgcn_ballot_w64(rend > cap || bad) == 0;
-    if (!room && rend > cap) atomicOr(a.err, kErrCapacity);
+    if (!room && rend > cap) atomicOr(a.flags + kFlagErr, kErrCapacity);
     const float quantum = sd.fr.quantum, near2 = sd.fr.near2;
     uint16_t* const flat = sflat[wv];
     // the lane's quarter row among the wavefront's entries
@@ -1804,7 +1805,12 @@ k_long(SearchArgs a)
 {
     extern __shared__ uint32_t keys[];  // a.lr_keys entries
     __shared__ int fill;
-    const int nh = *a.nheavy;
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense fill behind this
+    const int nh = a.flags[kFlagHeavy];
+    if (nh == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagLong] = 0;
+        return;
+    }
     const int T = kLongThreads;
     for (int h = blockIdx.x; h < nh; h += gridDim.x) {
         const int p = a.heavy[h];
@@ -1855,7 +1861,7 @@ k_long(SearchArgs a)
         __syncthreads();
         const int L = fill;
         if (L != rlen || !room) {
-            if (threadIdx.x == 0) atomicOr(a.err, !room ? kErrCapacity : kErrLongRow);
+            if (threadIdx.x == 0) atomicOr(a.flags + kFlagErr, !room ? kErrCapacity : kErrLongRow);
             __syncthreads();
             continue;
         }
@@ -1947,6 +1953,13 @@ k_long(SearchArgs a)
             sd.dist[rs + e] = d;
         }
         __syncthreads();
+    }
+    // the last workgroup hands the list back empty, once every thread has read its length
+    __syncthreads();
+    if (threadIdx.x == 0 && atomicAdd(a.flags + kFlagLongDone, 1) == static_cast<int>(gridDim.x) - 1) {
+        a.flags[kFlagLong] = nh;
+        a.flags[kFlagLongDone] = 0;
+        a.flags[kFlagHeavy] = 0;
     }
 }
 
@@ -2098,7 +2111,7 @@ k_dense_count(SearchArgs a)
     const int mi = T::item(lane);
     for (;;) {
         __syncthreads();  // the previous unit is done with the shared tables
-        if (tid == 0) s_unit = atomicAdd(a.ucount, 1);
+        if (tid == 0) s_unit = atomicAdd(a.flags + kFlagUnit, 1);
         __syncthreads();
         const int u = __builtin_amdgcn_readfirstlane(s_unit);
         if (u >= nunits) break;
@@ -2226,7 +2239,7 @@ k_dense_fill(SearchArgs a)
     uint16_t* const queue = squeue + wv * QCAP;
     for (;;) {
         __syncthreads();  // the previous unit is done with the shared tables
-        if (tid == 0) s_unit = atomicAdd(a.ucount, 1);
+        if (tid == 0) s_unit = atomicAdd(a.flags + kFlagUnit, 1);
         __syncthreads();
         const int u = __builtin_amdgcn_readfirstlane(s_unit);
         if (u >= nunits) break;
@@ -2362,12 +2375,12 @@ k_dense_fill(SearchArgs a)
                         }
                         done += tot;
                     }
-                    if (!room && lane == 0 && rl > 0) atomicOr(a.err, kErrCapacity);
+                    if (!room && lane == 0 && rl > 0) atomicOr(a.flags + kFlagErr, kErrCapacity);
                     if (lane == k) acc_k = done;
                 }
             }
         }
-        if (pk < u1 && acc_k != rl_k) atomicOr(a.err, kErrLongRow);
+        if (pk < u1 && acc_k != rl_k) atomicOr(a.flags + kFlagErr, kErrLongRow);
     }
 }
 
@@ -2438,7 +2451,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     unsigned long long tc[kDenseStats] = {0, 0, 0, 0, 0, 0};
     for (;;) {
         __syncthreads();  // the previous unit is done with s_unit and the staged chunk
-        if (threadIdx.x == 0) *s_unit = atomicAdd(a.ucount, 1);
+        if (threadIdx.x == 0) *s_unit = atomicAdd(a.flags + kFlagUnit, 1);
         __syncthreads();
         const int u = *s_unit;
         if (u >= nunits) break;
@@ -2624,7 +2637,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                     }
                 }
                 const int w = done + tot;
-                if (!room && lane == 0 && w > done) atomicOr(a.err, kErrCapacity);
+                if (!room && lane == 0 && w > done) atomicOr(a.flags + kFlagErr, kErrCapacity);
                 if (lane == k) acc_k = w;
             };
             {
@@ -2780,7 +2793,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                 }
             }
         }
-        if (FILL && vk && acc_k != rl_k) atomicOr(a.err, kErrLongRow);
+        if (FILL && vk && acc_k != rl_k) atomicOr(a.flags + kFlagErr, kErrLongRow);
     }
     if (!FILL) {
 #pragma unroll
@@ -2835,8 +2848,6 @@ void launch_dense_stats(const SearchArgs& a, hipStream_t st)
 hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st)
 {
     if (a.L.ntot == 0 || !a.wdense) return hipSuccess;
-    hipError_t e = launch_fill_i32(a.ucount, 1, 0, st);
-    if (e != hipSuccess) return e;
     if (pass == DensePass::kCount) {
         if (a.L.dim == 2) launch_dense_count<2>(a, st);
         else launch_dense_count<3>(a, st);
@@ -2844,6 +2855,8 @@ hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st)
         if (a.L.dim == 2) launch_dense_fill<2>(a, st);
         else launch_dense_fill<3>(a, st);
     } else {
+        const hipError_t e = launch_fill_i32(a.flags + kFlagUnit, 1, 0, st);
+        if (e != hipSuccess) return e;
         if (a.L.dim == 2) launch_dense_stats<2>(a, st);
         else launch_dense_stats<3>(a, st);
     }
