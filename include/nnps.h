@@ -304,16 +304,14 @@ nnps_status nnps_batch_update_step(nnps_ctx *ctx, nnps_cells *cells, const doubl
  *
  * nnps_allpairs_count writes d_row_ptr [n+1] and waits for the stream once to return nnz
  * (*nnz_out); NNPS_EDOMAIN if a position lies outside [lo, hi] or is not finite. The
- * context keeps per-slice row counts (device memory it owns) for the fill that follows.
+ * context keeps no device memory for the fill that follows.
  * nnps_allpairs_fill queues the fill of d_col/d_dist [nnz] (asynchronous); it must follow
  * a successful count on the same context with the same problem, d_pos and d_row_ptr
  * (else NNPS_EORDER), and needs capacity >= nnz (else NNPS_ECAPACITY, nothing written).
  * The contents of d_pos and d_row_ptr must also be unchanged since the count; the fill
  * cannot tell a change from here, but it writes each row only inside [row_ptr[i],
  * min(row_ptr[i+1], capacity)), and a row whose pairs no longer match its count is
- * reported as NNPS_EORDER by the next nnps_ctx_check. A later count on the context
- * replaces the kept counts: a fill still queued on another stream must have finished by
- * then.
+ * reported as NNPS_EORDER by the next nnps_ctx_check.
  * nnps_allpairs_search is count then, if capacity >= nnz, fill: NNPS_OK, or
  * NNPS_ECAPACITY with *nnz_out = nnz and only row_ptr written. */
 nnps_status nnps_allpairs_count(nnps_ctx *ctx, const nnps_problem *prob, const double *d_pos, int64_t *d_row_ptr,
@@ -327,17 +325,12 @@ nnps_status nnps_allpairs_search(nnps_ctx *ctx, const nnps_problem *prob, const 
 
 /* The same search for callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): count and fill as in
- * nnps_allpairs_search, with the per-slice row counts and the error word kept in a
- * static device array of the library (2.25 MiB per device, held until the process ends;
- * its address is looked up when a context is created on the device) instead of memory
- * the context allocates. Makes no hipMalloc, hipFree or other allocating call. The same
- * limits: prob->n <= 65536 (NNPS_EINVAL above; the array is sized for that maximum);
- * waits for the stream once (after the count) to return *nnz_out; NNPS_EDOMAIN,
- * NNPS_ECAPACITY (with *nnz_out = nnz and only row_ptr written) as there; NNPS_EDEVICE
- * if the array's address could not be found. Every call on a device shares that
- * device's array, so calls that overlap on one device (other host threads or streams)
- * race and must be serialised by the caller; the array keeps the last call's contents
- * (each call clears what it needs). Leaves the context's all-list count state alone. */
+ * nnps_allpairs_search. Makes no hipMalloc, hipFree or other allocating call and needs no
+ * device memory beside its arguments and a few words of the context. The same limits:
+ * prob->n <= 65536 (NNPS_EINVAL above); waits for the stream once (after the count) to
+ * return *nnz_out; NNPS_EDOMAIN, NNPS_ECAPACITY (with *nnz_out = nnz and only row_ptr
+ * written) as there. Calls on one context must not overlap. Leaves the context's all-list
+ * count state alone. */
 nnps_status nnps_allpairs_search_noalloc(nnps_ctx *ctx, const nnps_problem *prob, const double *d_pos,
                                          int64_t *d_row_ptr, int32_t *d_col, float *d_dist, int64_t capacity,
                                          int64_t *nnz_out, void *stream);

@@ -175,19 +175,16 @@ nnps_status frame_of(const nnps_problem* p, Frame* fr, int block_target)
 struct nnps_ctx {
     int device = 0;
     int64_t* h_pinned = nullptr;  // pinned staging for synchronous read-backs
-    // device error words: [0] the all-list count's domain flag; [1] errors of the
-    // asynchronous calls (all-list fill, SPH gradient), kept until nnps_ctx_check reads them
+    // device words: [1] errors of the asynchronous calls (all-list fill, SPH gradient), kept
+    // until nnps_ctx_check reads them; [2] the all-list count's error word, zero between counts
     int* d_flag = nullptr;
-    int* d_apcnt = nullptr;       // all-list per-slice row counts
-    size_t apcnt_cap = 0;         // ints in d_apcnt
     struct {                      // the last successful all-list count (what a fill may follow)
         bool valid = false;
-        int dim = 0;
+        int dim = 0, n = 0;
         const double* pos = nullptr;
         const int64_t* row_ptr = nullptr;
         double R2 = 0.0;
         int64_t nnz = 0;
-        ApPlan plan;
     } ap;
     int max_lds = 65536;          // LDS bytes a workgroup may use on this device
     nnps_tuning tuning{80, 1024, 0, 0, 0, 0, 0};
@@ -885,10 +882,6 @@ nnps_status nnps_ctx_create(int device, nnps_ctx** out)
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         c->max_lds = lds;
-    // the allocation-free all-list search finds this device's static scratch here, once
-    // per device (with the device current); a failed lookup makes that call return
-    // NNPS_EDEVICE and leaves every other call unaffected
-    (void)allpairs_static_scratch_init(device);
     if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), 64 * sizeof(int64_t), hipHostMallocDefault) !=
         hipSuccess) {
         delete c;
@@ -927,7 +920,6 @@ void nnps_ctx_destroy(nnps_ctx* c)
     DeviceGuard g(c->device);
     if (c->h_pinned) (void)hipHostFree(c->h_pinned);
     if (c->d_flag) (void)hipFree(c->d_flag);
-    if (c->d_apcnt) (void)hipFree(c->d_apcnt);
     delete c;
 }
 
@@ -1036,6 +1028,33 @@ nnps_status nnps_count(nnps_ctx* ctx, nnps_cells* c, int64_t* d_row_ptr, int64_t
     return nnps_batch_count(ctx, c, rp, h_nnz, stream);
 }
 
+namespace {
+
+// The all-list count of a checked problem: row pointers, then nnz, after a wait for the stream.
+nnps_status allpairs_count(nnps_ctx* ctx, const nnps_problem* prob, const double* d_pos, int64_t* d_row_ptr,
+                           int64_t* nnz_out, hipStream_t s)
+{
+    *nnz_out = 0;
+    if (prob->n == 0) {
+        HIP_TRY(launch_fill_i32(reinterpret_cast<int*>(d_row_ptr), 2, 0, s));  // row_ptr[0] = 0
+        return NNPS_OK;
+    }
+    ApBox box{};
+    for (int k = 0; k < prob->dim; ++k) {
+        box.lo[k] = prob->lo[k];
+        box.hi[k] = prob->hi[k];
+    }
+    volatile int64_t* hp = ctx->h_pinned;
+    HIP_TRY(launch_allpairs_count(prob->dim, static_cast<int>(prob->n), d_pos, prob->radius * prob->radius, box, d_row_ptr,
+                                  ctx->d_flag + 2, ctx->h_pinned, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    if (hp[1] != 0) return NNPS_EDOMAIN;
+    *nnz_out = hp[0];
+    return NNPS_OK;
+}
+
+}  // namespace
+
 nnps_status nnps_allpairs_count(nnps_ctx* ctx, const nnps_problem* prob, const double* d_pos, int64_t* d_row_ptr,
                                 int64_t* nnz_out, void* stream)
 {
@@ -1045,49 +1064,16 @@ nnps_status nnps_allpairs_count(nnps_ctx* ctx, const nnps_problem* prob, const d
     if (prob->n > kAllPairsMaxN || (prob->n > 0 && !d_pos)) return NNPS_EINVAL;
     DeviceGuard g(ctx->device);
     if (!g.ok) return NNPS_EDEVICE;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const int n = static_cast<int>(prob->n);
     ctx->ap.valid = false;
-    *nnz_out = 0;
-    const double R2 = prob->radius * prob->radius;
-    const ApPlan plan = allpairs_plan(n);
-    if (n == 0) {
-        HIP_TRY(launch_fill_i32(reinterpret_cast<int*>(d_row_ptr), 2, 0, s));  // row_ptr[0] = 0
-    } else {
-        const size_t need = static_cast<size_t>(plan.nslice) * static_cast<size_t>(n);
-        if (need > ctx->apcnt_cap) {
-            if (ctx->d_apcnt) {
-                HIP_TRY(hipStreamSynchronize(s));  // a queued fill of this context may still read it
-                (void)hipFree(ctx->d_apcnt);
-                ctx->d_apcnt = nullptr;
-                ctx->apcnt_cap = 0;
-            }
-            if (hipMalloc(reinterpret_cast<void**>(&ctx->d_apcnt), need * sizeof(int)) != hipSuccess) return NNPS_ENOMEM;
-            ctx->apcnt_cap = need;
-        }
-        ApBox box{};
-        for (int k = 0; k < prob->dim; ++k) {
-            box.lo[k] = prob->lo[k];
-            box.hi[k] = prob->hi[k];
-        }
-        HIP_TRY(launch_fill_i32(ctx->d_flag, 1, 0, s));
-        HIP_TRY(launch_allpairs_count(prob->dim, plan, d_pos, R2, box, ctx->d_apcnt, d_row_ptr, ctx->d_flag, s));
-        int64_t* hp = ctx->h_pinned;
-        hp[0] = 0;
-        hp[1] = 0;
-        HIP_TRY(hipMemcpyAsync(hp, d_row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(hp + 1, ctx->d_flag, sizeof(int), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (static_cast<int>(hp[1] & 0xFFFFFFFF) != 0) return NNPS_EDOMAIN;
-        *nnz_out = hp[0];
-    }
+    const nnps_status st = allpairs_count(ctx, prob, d_pos, d_row_ptr, nnz_out, static_cast<hipStream_t>(stream));
+    if (st != NNPS_OK) return st;
     ctx->ap.valid = true;
     ctx->ap.dim = prob->dim;
+    ctx->ap.n = static_cast<int>(prob->n);
     ctx->ap.pos = d_pos;
     ctx->ap.row_ptr = d_row_ptr;
-    ctx->ap.R2 = R2;
+    ctx->ap.R2 = prob->radius * prob->radius;
     ctx->ap.nnz = *nnz_out;
-    ctx->ap.plan = plan;
     return NNPS_OK;
 }
 
@@ -1100,14 +1086,14 @@ nnps_status nnps_allpairs_fill(nnps_ctx* ctx, const nnps_problem* prob, const do
     const nnps_status v = nnps_validate(prob);
     if (v != NNPS_OK) return v;
     const auto& ap = ctx->ap;
-    if (!ap.valid || ap.plan.n != prob->n || ap.dim != prob->dim || ap.pos != d_pos || ap.row_ptr != d_row_ptr ||
+    if (!ap.valid || ap.n != prob->n || ap.dim != prob->dim || ap.pos != d_pos || ap.row_ptr != d_row_ptr ||
         ap.R2 != prob->radius * prob->radius)
         return NNPS_EORDER;
     if (ap.nnz > capacity) return NNPS_ECAPACITY;
     DeviceGuard g(ctx->device);
     if (!g.ok) return NNPS_EDEVICE;
-    HIP_TRY(launch_allpairs_fill(ap.dim, ap.plan, d_pos, ap.R2, ctx->d_apcnt, d_row_ptr, d_col, d_dist, capacity,
-                                 ctx->d_flag + 1, static_cast<hipStream_t>(stream)));
+    HIP_TRY(launch_allpairs_fill(ap.dim, ap.n, d_pos, ap.R2, d_row_ptr, d_col, d_dist, capacity, ctx->d_flag + 1,
+                                 static_cast<hipStream_t>(stream)));
     return NNPS_OK;
 }
 
@@ -1131,40 +1117,14 @@ nnps_status nnps_allpairs_search_noalloc(nnps_ctx* ctx, const nnps_problem* prob
     const nnps_status v = nnps_validate(prob);
     if (v != NNPS_OK) return v;
     if (prob->n > kAllPairsMaxN || (prob->n > 0 && !d_pos)) return NNPS_EINVAL;
-    const int n = static_cast<int>(prob->n);
-    const ApPlan plan = allpairs_plan(n);
-    if (static_cast<int64_t>(plan.nslice) * n > kApStaticCounts) return NNPS_EUNSUPPORTED;
     DeviceGuard g(ctx->device);
     if (!g.ok) return NNPS_EDEVICE;
-    int* scr = allpairs_static_scratch(ctx->device);
-    if (!scr) return NNPS_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    *nnz_out = 0;
-    if (n == 0) {
-        HIP_TRY(launch_fill_i32(reinterpret_cast<int*>(d_row_ptr), 2, 0, s));  // row_ptr[0] = 0
-        return NNPS_OK;
-    }
-    int* cnt = scr;
-    int* flag = scr + kApStaticCounts;
-    const double R2 = prob->radius * prob->radius;
-    ApBox box{};
-    for (int k = 0; k < prob->dim; ++k) {
-        box.lo[k] = prob->lo[k];
-        box.hi[k] = prob->hi[k];
-    }
-    HIP_TRY(launch_fill_i32(flag, 1, 0, s));
-    HIP_TRY(launch_allpairs_count(prob->dim, plan, d_pos, R2, box, cnt, d_row_ptr, flag, s));
-    int64_t* hp = ctx->h_pinned;
-    hp[0] = 0;
-    hp[1] = 0;
-    HIP_TRY(hipMemcpyAsync(hp, d_row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(hp + 1, flag, sizeof(int), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (static_cast<int>(hp[1] & 0xFFFFFFFF) != 0) return NNPS_EDOMAIN;
-    *nnz_out = hp[0];
-    if (hp[0] > capacity) return NNPS_ECAPACITY;
-    HIP_TRY(launch_allpairs_fill(prob->dim, plan, d_pos, R2, cnt, d_row_ptr, d_col, d_dist, capacity,
-                                 ctx->d_flag + 1, s));
+    const nnps_status st = allpairs_count(ctx, prob, d_pos, d_row_ptr, nnz_out, s);
+    if (st != NNPS_OK) return st;
+    if (*nnz_out > capacity) return NNPS_ECAPACITY;
+    HIP_TRY(launch_allpairs_fill(prob->dim, static_cast<int>(prob->n), d_pos, prob->radius * prob->radius, d_row_ptr, d_col,
+                                 d_dist, capacity, ctx->d_flag + 1, s));
     return NNPS_OK;
 }
 

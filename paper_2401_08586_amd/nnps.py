@@ -469,7 +469,7 @@ def allpairs_search(pos, lo, hi, radius, ctx: Context | None = None, stream=None
 def allpairs_search_noalloc(pos, lo, hi, radius, row_ptr, col, dist, ctx: Context, stream=None):
     """nnps_allpairs_search_noalloc into caller-sized outputs (row_ptr [n+1] int64, col
     int32 and dist float32 of equal length, the capacity): returns (status, nnz). The
-    library allocates nothing for it; its scratch is a static device array."""
+    library allocates nothing for it."""
     import torch
     n, dim = pos.shape
     assert pos.is_cuda and pos.dtype == torch.float64 and pos.is_contiguous()
