@@ -124,8 +124,17 @@ hipError_t launch_dense_unions(const Launch& L, const uint32_t* skey, const int*
                                hipStream_t st, int** ulist);
 // Row pointers of every set from the counts; also each particle's row start by sorted
 // position (rsort[inv[i]]).
+// What a caller that waits for the count wants on the host, written there by the row pointer
+// kernel: the structure's flags, then each set's nnz, and `pairs` (if given) in the last word.
+struct HostReport {
+    int64_t* host = nullptr;  // kHostWords words that the host reads after the stream; null: none
+    const int* flags = nullptr;
+    const int64_t* pairs = nullptr;
+};
+constexpr int kHostWords = 64;
+constexpr int kHostSets = kHostWords - 1 - kFlags / 2;  // sets that fit
 hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* partial, int64_t* nnz, const int* inv,
-                         int64_t* rsort, hipStream_t st);
+                         int64_t* rsort, const HostReport& rep, hipStream_t st);
 
 // Search passes over every block of every set. `nblk_max` bounds the number of blocks
 // (the exact count is on the device).

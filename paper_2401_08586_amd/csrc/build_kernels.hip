@@ -722,8 +722,16 @@ template <int OFF>
 __global__ void __launch_bounds__(kScanThreads)
 k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int nsets, const int* __restrict__ counts,
          int64_t m, const int64_t* __restrict__ partial, int64_t* __restrict__ nnz, const int* __restrict__ inv,
-         int64_t* __restrict__ rsort)
+         int64_t* __restrict__ rsort, HostReport rep)
 {
+    if (rep.host && blockIdx.x == 0) {
+        if (threadIdx.x < kFlags) reinterpret_cast<int*>(rep.host)[threadIdx.x] = rep.flags[threadIdx.x];
+        if (threadIdx.x == kFlags) rep.host[kHostWords - 1] = rep.pairs ? *rep.pairs : 0;
+    }
+    auto total = [&](int s, int64_t v) {
+        nnz[s] = v;
+        if (rep.host) rep.host[kFlags / 2 + s] = v;
+    };
     __shared__ int64_t sh[kScanThreads / 64];
     __shared__ int64_t local[kScanTile + kScanTile / 16];  // the tile's prefixes, one pad per 16
     const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * kScanTile;
@@ -762,7 +770,7 @@ k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
         rsort[inv[i]] = val;
         if (i + 1 == start + sd.fr.n) {
             rp[sd.fr.n] = val + counts[i];
-            nnz[s] = val + counts[i];
+            total(s, val + counts[i]);
         }
     };
     const int len = static_cast<int>(min(m - tile0, static_cast<int64_t>(kScanTile)));
@@ -785,7 +793,7 @@ k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
         for (int s = threadIdx.x; s < nsets; s += kScanThreads)
             if (sets[s].fr.n == 0) {
                 sets[s].row_ptr[0] = 0;
-                nnz[s] = 0;
+                total(s, 0);
             }
 }
 
@@ -1146,20 +1154,20 @@ hipError_t launch_dense_unions(const Launch& L, const uint32_t* skey, const int*
 }
 
 hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* partial, int64_t* nnz, const int* inv,
-                         int64_t* rsort, hipStream_t st)
+                         int64_t* rsort, const HostReport& rep, hipStream_t st)
 {
     const int64_t m = L.ntot, nt = std::max<int64_t>(1, (m + kScanTile - 1) / kScanTile);
     const dim3 g(nt), b(kScanThreads);
     switch (scan_sums(counts, m, nt, true, partial, st, nullptr)) {
     case kScanSelf:
-        hipLaunchKernelGGL(k_rowptr<kScanSelf>, g, b, 0, st, L.sets, L.poffs, L.nsets, counts, m, partial, nnz, inv, rsort);
+        hipLaunchKernelGGL(k_rowptr<kScanSelf>, g, b, 0, st, L.sets, L.poffs, L.nsets, counts, m, partial, nnz, inv, rsort, rep);
         break;
     case kScanFold:
-        hipLaunchKernelGGL(k_rowptr<kScanFold>, g, b, 0, st, L.sets, L.poffs, L.nsets, counts, m, partial, nnz, inv, rsort);
+        hipLaunchKernelGGL(k_rowptr<kScanFold>, g, b, 0, st, L.sets, L.poffs, L.nsets, counts, m, partial, nnz, inv, rsort, rep);
         break;
     default:
         hipLaunchKernelGGL(k_rowptr<kScanScanned>, g, b, 0, st, L.sets, L.poffs, L.nsets, counts, m, partial, nnz, inv,
-                           rsort);
+                           rsort, rep);
     }
     return hipGetLastError();
 }

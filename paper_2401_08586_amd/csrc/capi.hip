@@ -738,7 +738,8 @@ nnps_status enqueue_build(nnps_cells* c, hipStream_t s)
 }
 
 // Count pass and row pointers (written into the row_ptr arrays of the set table).
-nnps_status enqueue_count(nnps_cells* c, hipStream_t s)
+// `host`: where the row pointer kernel leaves a report for the host, or null.
+nnps_status enqueue_count(nnps_cells* c, hipStream_t s, int64_t* host = nullptr)
 {
     SearchArgs a = args_of(c);
     c->timer.begin(NNPS_PHASE_COUNT, s);
@@ -751,9 +752,13 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s)
     }
     // the per-block statistics stay in place until the next count; nnps_stats_get sums
     // them when asked, so a step does not pay for the reduction
+    HostReport rep;
+    rep.host = host;
+    rep.flags = c->report.as<int>();
+    rep.pairs = c->dense_active && dense_bits_on(c) ? c->dboff.as<int64_t>() + c->ncell_tot : nullptr;
     c->timer.begin(NNPS_PHASE_ROWSCAN, s);
     HIP_TRY(launch_rowptr(a.L, c->counts.as<int>(), c->partial.as<int64_t>(), nnz_of(c), c->inv.as<int>(),
-                          c->rsort.as<int64_t>(), s));
+                          c->rsort.as<int64_t>(), rep, s));
     c->timer.end(NNPS_PHASE_ROWSCAN, s);
     c->counted = true;
     return NNPS_OK;
@@ -788,32 +793,47 @@ void set_outputs(nnps_cells* c, int64_t* const* row_ptr, int32_t* const* col, fl
     }
 }
 
+// What a report on the host says of a structure: its error, whether it has dense cells, and
+// the room its next build keeps for the dense count's bits.
+nnps_status take_report(nnps_cells* c, const int64_t* hp)
+{
+    const int* flags = reinterpret_cast<const int*>(hp);
+    if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+    if (c->dense_active && dense_bits_on(c)) {
+        const size_t want = static_cast<size_t>(hp[kHostWords - 1]) * 64 * sizeof(uint16_t);
+        if (want <= dense_bits_bound(c)) c->dbits_want = std::max(c->dbits_want, want);
+    }
+    return err_status(flags[kFlagErr]);
+}
+
+// Count, wait, and read the sets' nnz from what the row pointer kernel left on the host (up to
+// kHostSets sets; a copy instead of it costs a search of 10,000 particles 6 us).
+nnps_status count_and_wait(nnps_cells* c, int64_t* h_nnz, hipStream_t s)
+{
+    int64_t* hp = c->ctx->h_pinned;
+    const nnps_status st = enqueue_count(c, s, hp);
+    if (st != NNPS_OK) return st;
+    HIP_TRY(hipStreamSynchronize(s));
+    for (int i = 0; i < c->nsets; ++i) h_nnz[i] = hp[kFlags / 2 + i];
+    return take_report(c, hp);
+}
+
+// The same from the device's copy, at any time after a count.
 nnps_status read_nnz(nnps_cells* c, int64_t* h_nnz, hipStream_t s)
 {
     int64_t* hp = c->ctx->h_pinned;
     nnps_status st = NNPS_OK;
-    // the pinned staging holds 64 values: the flags with up to 60 counts, a copy a piece, and
-    // the dense cells' (target, chunk) pairs
-    const bool bits = c->dense_active && dense_bits_on(c);
-    constexpr int kFlagWords = kFlags / 2, kPiece = 63 - kFlagWords;
+    constexpr int kFlagWords = kFlags / 2;
     const int64_t* rep = c->report.as<int64_t>();
-    for (int s0 = 0; s0 < c->nsets; s0 += kPiece) {
-        const int k = std::min(kPiece, c->nsets - s0);
+    for (int s0 = 0; s0 < c->nsets; s0 += kHostSets) {
+        const int k = std::min(kHostSets, c->nsets - s0);
         const int skip = s0 == 0 ? 0 : kFlagWords;  // the flags come with the first piece
         HIP_TRY(hipMemcpyAsync(hp + skip, rep + s0 + skip, 8 * (kFlagWords - skip + k), hipMemcpyDeviceToHost, s));
-        if (bits && s0 == 0)
-            HIP_TRY(hipMemcpyAsync(hp + 63, c->dboff.as<int64_t>() + launch_of(c).ncell_tot, 8, hipMemcpyDeviceToHost, s));
+        if (s0 == 0 && c->dense_active && dense_bits_on(c))
+            HIP_TRY(hipMemcpyAsync(hp + kHostWords - 1, c->dboff.as<int64_t>() + c->ncell_tot, 8, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         for (int i = 0; i < k; ++i) h_nnz[s0 + i] = hp[kFlagWords + i];
-        if (s0) continue;
-        const int* flags = reinterpret_cast<const int*>(hp);
-        st = err_status(flags[kFlagErr]);
-        if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
-        if (bits) {
-            // the next build keeps room for the count's bits if they fit the bound
-            const size_t want = static_cast<size_t>(hp[63]) * 64 * sizeof(uint16_t);
-            if (want <= dense_bits_bound(c)) c->dbits_want = std::max(c->dbits_want, want);
-        }
+        if (s0 == 0) st = take_report(c, hp);
     }
     return st;
 }
@@ -882,7 +902,7 @@ nnps_status nnps_ctx_create(int device, nnps_ctx** out)
     int lds = 0;
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
         c->max_lds = lds;
-    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), 64 * sizeof(int64_t), hipHostMallocDefault) !=
+    if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), kHostWords * sizeof(int64_t), hipHostMallocDefault) !=
         hipSuccess) {
         delete c;
         return NNPS_ENOMEM;
@@ -1016,6 +1036,7 @@ nnps_status nnps_batch_count(nnps_ctx* ctx, nnps_cells* c, int64_t* const* d_row
     set_outputs(c, d_row_ptr, nullptr, nullptr, nullptr);
     st = upload(c, false, s);
     if (st != NNPS_OK) return st;
+    if (h_nnz && c->nsets <= kHostSets) return count_and_wait(c, h_nnz, s);
     st = enqueue_count(c, s);
     if (st != NNPS_OK) return st;
     return h_nnz ? read_nnz(c, h_nnz, s) : NNPS_OK;

@@ -49,6 +49,7 @@ def args_of(pss):
 
 
 SETS = {
+    "fifty_nine": list(range(1, 60)), "sixty": list(range(0, 60)),
     "tiles_inside": [0, 1, 4095, 0, 4096, 4097, 3, 0],
     "many_tiles": [5, 70001, 0, 4096, 1],
     "one_4095": [4095], "one_4096": [4096], "one_65536": [65536], "one_65537": [65537], "none": [0], "none_twice": [0, 0],
