@@ -119,9 +119,12 @@ hipError_t launch_pack(const Launch& L, const PackArgs* pack, const BlockTable* 
                        int64_t* partial, hipStream_t st);
 // After the stencil sizes, before the block table: dense windows, union offsets, work units.
 hipError_t launch_dense_cells(const Launch& L, const int* cell_start, const DenseBuild& d, hipStream_t st);
-// After the sort and pack: the union lists. *ulist receives the sorted list array.
-hipError_t launch_dense_unions(const Launch& L, const uint32_t* skey, const int* inv, const DenseBuild& d,
-                               hipStream_t st, int** ulist);
+// After the sort and pack: the union lists. *ulist receives the list array. `nmax` is the
+// largest set's size; above a bound (dense_unions_sorted) the lists are made by a sort, which
+// needs ecnt, epos, uk0, uk1, uv1 and table, else they are ranked in place.
+bool dense_unions_sorted(int64_t nmax);
+hipError_t launch_dense_unions(const Launch& L, int64_t nmax, const int* cell_start, const uint32_t* skey, const int* perm,
+                               const int* inv, const DenseBuild& d, hipStream_t st, int** ulist);
 // Row pointers of every set from the counts; also each particle's row start by sorted
 // position (rsort[inv[i]]).
 // What a caller that waits for the count wants on the host, written there by the row pointer

@@ -264,6 +264,7 @@ struct nnps_cells {
     int nsets = 0, dim = 0, mode = 0, ntot = 0, ncell_tot = 0, nblk_max = 0;
     std::vector<Frame> frames;
     int nrows_tot = 0;                    // row segments of all sets
+    int64_t nmax = 0;                     // the largest set's particles
     std::vector<const double*> pos;
     SetDesc* h_sets = nullptr;            // pinned mirror of the set table
     int* h_offs = nullptr;                // pinned mirror of the offsets
@@ -463,13 +464,14 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
 {
     if (nsets < 1 || !probs || !d_pos) return NNPS_EINVAL;
     std::vector<Frame> frames(nsets);
-    int64_t ntot = 0, ncell = 0;
+    int64_t ntot = 0, ncell = 0, nmax = 0;
     for (int s = 0; s < nsets; ++s) {
         nnps_status st = frame_of(&probs[s], &frames[s], ctx->tuning.block_target);
         if (st != NNPS_OK) return st;
         if (probs[s].dim != probs[0].dim || probs[s].mode != probs[0].mode) return NNPS_EINVAL;
         if (probs[s].n > 0 && !d_pos[s]) return NNPS_EINVAL;
         ntot += probs[s].n;
+        nmax = std::max<int64_t>(nmax, probs[s].n);
         ncell += frames[s].ncell;
     }
     if (ntot >= (int64_t(1) << 31)) return NNPS_EINVAL;
@@ -496,6 +498,7 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     c->dim = probs[0].dim;
     c->mode = probs[0].mode;
     c->ntot = static_cast<int>(ntot);
+    c->nmax = nmax;
     c->ncell_tot = static_cast<int>(ncell);
     c->frames = frames;
     c->pos.assign(d_pos, d_pos + nsets);
@@ -551,7 +554,9 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
     c->dcap = c->dense ? std::max<int64_t>(1, std::min<int64_t>((c->dim == 3 ? 27 : 9) * static_cast<int64_t>(nn), dmax))
                        : 0;
     const size_t dcap = static_cast<size_t>(c->dcap);
-    const size_t table_n = (c->dense ? radix_table_entries(static_cast<int>(dcap)) : size_t(0)) + 1;
+    const bool dsort = c->dense && dense_unions_sorted(nmax);
+    const size_t scap = dsort ? dcap : 0;  // the sort's second buffers
+    const size_t table_n = (dsort ? radix_table_entries(static_cast<int>(dcap)) : size_t(0)) + 1;
     const int64_t scan_m = std::max<int64_t>({static_cast<int64_t>(nn) + 1, static_cast<int64_t>(nc) + 1,
                                               static_cast<int64_t>(table_n),
                                               static_cast<int64_t>(c->nrows_tot) + 1});
@@ -580,8 +585,8 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         {&c->usz, c->dense ? (nc + 1) * 4 : 0}, {&c->wdense, c->dense ? (nc + 1) * 4 : 0},
         {&c->uoff, c->dense ? (nc + 1) * 8 : 0}, {&c->nsl, c->dense ? (nc + 1) * 4 : 0},
         {&c->unit_off, c->dense ? (nc + 1) * 4 : 0}, {&c->ucell, c->dense ? (nn + 1) * 4 : 0},
-        {&c->dn, c->dense ? size_t(4) : size_t(0)}, {&c->ecnt, c->dense ? nn * 4 : 0}, {&c->epos, c->dense ? (nn + 1) * 4 : 0},
-        {&c->uk0, dcap * 4}, {&c->uk1, dcap * 4}, {&c->uv0, dcap * 4}, {&c->uv1, dcap * 4},
+        {&c->dn, c->dense ? size_t(4) : size_t(0)}, {&c->ecnt, dsort ? nn * 4 : 0}, {&c->epos, dsort ? (nn + 1) * 4 : 0},
+        {&c->uk0, scap * 4}, {&c->uk1, scap * 4}, {&c->uv0, dcap * 4}, {&c->uv1, scap * 4},
         {&c->inv, nn * 4},
         {&c->dstats, c->dense ? static_cast<size_t>(c->dgrid) * kDenseStats * 8 : 0},
         {&c->dbn, c->dense ? (nc + 1) * 4 : 0}, {&c->dboff, c->dense ? (nc + 1) * 8 : 0},
@@ -664,7 +669,7 @@ nnps_status enqueue_sorted(nnps_cells* c, const PlaceArgs& place, const PackArgs
         if (!sizes) HIP_TRY(launch_sort(L, nullptr, &d, nullptr, cell_start, s));
         if (c->dense_active) {
             HIP_TRY(launch_dense_cells(L, cell_start, d, s));
-            HIP_TRY(launch_dense_unions(L, c->skey, c->inv.as<int>(), d, s, &c->ulist));
+            HIP_TRY(launch_dense_unions(L, c->nmax, cell_start, c->skey, c->perm, c->inv.as<int>(), d, s, &c->ulist));
         }
         tm.end(NNPS_PHASE_UNIONS, s);
     }
