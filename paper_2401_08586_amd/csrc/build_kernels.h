@@ -49,7 +49,7 @@ hipError_t launch_update_cells(const Launch& L, int* cell_start, int* cnt, const
 // Dense-cell path: device tables of one build. A cell is "dense" when its stencil holds
 // more than `thresh` particles; runs of dense cells get no work blocks. Each dense cell g owns the list ulist[uoff[g] ..
 // uoff[g] + usz[g]) of the sorted positions of the particles in its 3^d stencil, in
-// ascending original index, and ceil(occupancy / kDenseSlice) work units.
+// ascending original index, and ceil(occupancy / kDenseUnit) work units.
 struct DenseBuild {
     int thresh;             // stencil size above which a window is dense
     int64_t cap;            // capacity of the union lists (entries)

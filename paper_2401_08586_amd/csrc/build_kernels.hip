@@ -914,7 +914,7 @@ k_dense_units(int ncell_tot, const int* __restrict__ cell_start, const int64_t* 
     }
     const int occ = cell_start[g + 1] - cell_start[g];
     const bool on = !over && usz[g] > 0;
-    nsl[g] = on ? (occ + kDenseSlice - 1) / kDenseSlice : 0;
+    nsl[g] = on ? (occ + kDenseUnit - 1) / kDenseUnit : 0;
     dbn[g] = on ? occ * ((usz[g] + kDenseChunk - 1) / kDenseChunk) : 0;
 }
 

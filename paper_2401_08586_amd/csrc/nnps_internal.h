@@ -37,7 +37,13 @@ constexpr int kDenseQueue = 512;  // per-wavefront queue of a row's accepted can
 constexpr int kDenseThreads = 256;
 constexpr int kDenseFillThreads = 1024;  // the dense fill that takes the count's kept bits
 constexpr int kDenseFillQueue = 448;     // and its per-wavefront queue
+// Targets of one dense cell that share staged candidates: 256 in the count and the testing
+// fill, 64, a work unit, in the fill that takes the kept bits, whose output decides the time
+// (a core cell's 256 rows can be 18 MB, as much as a workgroup's share of a whole batch: units
+// of 256 left half of the chip idle at the end, 3000 us for a clustered batch alone against
+// 2260 with 64 and 2200 with 32; several batches in flight 1956, 1945 and 1956).
 constexpr int kDenseSlice = 256;
+constexpr int kDenseUnit = 64;
 constexpr int kDenseUnion3 = 512;
 constexpr int kDenseUnion2 = 160;
 constexpr int kDenseGrid = 1280;  // five workgroups on each of the 256 compute units

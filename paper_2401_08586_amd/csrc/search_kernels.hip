@@ -1568,8 +1568,8 @@ constexpr int kFillThreads = 256;  // four wavefronts share one block's union
 // of the positions in units of 2^-30 or so of a cell width (Frame::quantum), one 16-byte
 // record per candidate: neighbours lie fewer than 2^31 units apart, so the difference mod
 // 2^32 is exact, and is rounded once to FP32; pairs so near that the unit would show are
-// recomputed from the binary64 positions. The stores are non-temporal: the lists would
-// otherwise push the positions, bits and lists of the next blocks out of the L2s.
+// recomputed from the binary64 positions. (Non-temporal stores were slower in 2D and at 64,000
+// points, two entries a store no faster: 412 against 414 us for the step in 3D, 172 against 169 in 2D.)
 // What bounds it: vector issue and HBM about evenly. At 1M particles in 3D (60 M entries, 728 MB
 // of DRAM traffic, 78 M vector instructions): 322 us with the ranking and gathers from global
 // memory here, 213 now; 2D 93 -> 60, binary64 321 -> 244 us.
@@ -2065,7 +2065,8 @@ __device__ __forceinline__ double rlf64(double v, int k)
 }
 
 // ---------------------------------------------------------------------------
-// Dense-cell path. A work unit is up to kDenseSlice targets of one dense cell, all with
+// Dense-cell path. A work unit is up to kDenseUnit targets of one dense cell (the count and
+// the testing fill take kDenseSlice at a time, with the first of their units), all with
 // the same stencil union (the cell's list, ascending original index); persistent workgroups
 // take units from a counter.
 //
@@ -2117,10 +2118,11 @@ k_dense_count(SearchArgs a)
         if (u >= nunits) break;
         const int c = __builtin_amdgcn_readfirstlane(a.ucell[u]);
         const int slice = u - __builtin_amdgcn_readfirstlane(a.unit_off[c]);
+        if (slice % (kDenseSlice / kDenseUnit)) continue;  // with the unit that starts its 256 targets
         const SetDesc& sd = a.L.sets[__builtin_amdgcn_readfirstlane(find_set(a.L.coffs, a.L.nsets, c))];
         const int ncx = sd.fr.nc[0], ncy = sd.fr.nc[1];
         const int lk = c - sd.coff, row = lk / ncx;
-        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseSlice;
+        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseUnit;
         const int u1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), u0 + kDenseSlice);
         const int U = __builtin_amdgcn_readfirstlane(a.usz[c]);
         const int* list = a.ulist + a.uoff[c];
@@ -2252,12 +2254,12 @@ k_dense_fill(SearchArgs a)
         const float quantum = sd.fr.quantum, near2 = sd.fr.near2;
         const double lo[3] = {sd.fr.lo[0], sd.fr.lo[1], sd.fr.lo[2]};
         const int64_t cap = sd.capacity;
-        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseSlice;
-        const int u1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), u0 + kDenseSlice);
+        const int u0 = __builtin_amdgcn_readfirstlane(a.cell_start[c]) + slice * kDenseUnit;
+        const int u1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), u0 + kDenseUnit);
         const int U = __builtin_amdgcn_readfirstlane(a.usz[c]);
         const int* list = a.ulist + a.uoff[c];
         const int nchunk = (U + kDenseChunk - 1) / kDenseChunk;
-        const uint16_t* rows = a.dbits + (a.dboff[c] + static_cast<int64_t>(slice * kDenseSlice + wv) * nchunk) * 64 + lane;
+        const uint16_t* rows = a.dbits + (a.dboff[c] + static_cast<int64_t>(slice * kDenseUnit + wv) * nchunk) * 64 + lane;
         auto packed = [&](const double2& xy, const double2& zw, int w) {
             return make_int4(in_quanta(xy.x, lo[0], inv_quantum), in_quanta(xy.y, lo[1], inv_quantum),
                              DIM == 3 ? in_quanta(zw.x, lo[2], inv_quantum) : 0, w);
@@ -2457,6 +2459,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
         if (u >= nunits) break;
         const int g = a.ucell[u];
         const int slice = u - a.unit_off[g];
+        if (slice % (kDenseSlice / kDenseUnit)) continue;  // with the unit that starts its 256 targets
         const SetDesc& sdesc = a.L.sets[find_set(a.L.coffs, a.L.nsets, g)];
         const SetView sd(sdesc);
         const int poff = sd.poff;
@@ -2465,7 +2468,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
         const uint32_t coff = static_cast<uint32_t>(sdesc.coff);
         const int lk = g - sdesc.coff;
         const int cx = lk % ncx, crow = lk / ncx, cy = crow % ncy, cz = crow / ncy;
-        const int t0 = a.cell_start[g] + slice * kDenseSlice;
+        const int t0 = a.cell_start[g] + slice * kDenseUnit;
         const int t1 = min(a.cell_start[g + 1], t0 + kDenseSlice);
         const int U = a.usz[g];
         const int64_t ub = a.uoff[g];
