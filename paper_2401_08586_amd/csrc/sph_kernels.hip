@@ -60,11 +60,12 @@ __device__ __forceinline__ void root_and_inverse(double r2, double& r, double& i
     const double g = __dmul_rn(r2, y1);
     r = __fma_rn(__fma_rn(-g, g, r2), __dmul_rn(0.5, y1), g);
     inv_r = __fma_rn(y1, __fma_rn(-r, y1, 1.0), y1);
+}
+
+__device__ __forceinline__ bool root_in_range(double r2)  // false for 0, infinity and NaN too
+{
     const uint32_t hi = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, r2) >> 32);
-    if (hi - ((1023u - 900u) << 20) >= (1800u << 20)) {  // also 0, infinity, NaN
-        r = __dsqrt_rn(r2);
-        inv_r = r > 0.0 ? __ddiv_rn(1.0, r) : 0.0;
-    }
+    return hi - ((1023u - 900u) << 20) < (1800u << 20);
 }
 
 // dW/dq of the cubic B-spline without alpha_d (Eq. 3 differentiated in q = r / h), as a
@@ -103,12 +104,13 @@ k_sph_gradient(int n, double inv_h, double alpha_h, const double* __restrict__ p
     for (int a = 0; a < DIM; ++a) s[a] = num[a] = den[a] = 0.0;
     struct Entry {
         double x[DIM], f, v;
+        bool in;
     };
-    // an index outside [0, n) reads particle i itself, which adds nothing
+    // an index outside [0, n) reads particle i itself, and is skipped (its r2 is out of range)
     auto fetch = [&](int j, Entry& e) {
-        const bool in = static_cast<uint32_t>(j) < static_cast<uint32_t>(n);
-        bad |= !in;
-        const OFF o = in ? static_cast<OFF>(j) : static_cast<OFF>(i);
+        e.in = static_cast<uint32_t>(j) < static_cast<uint32_t>(n);
+        bad |= !e.in;
+        const OFF o = e.in ? static_cast<OFF>(j) : static_cast<OFF>(i);
         typedef double pair __attribute__((ext_vector_type(2), aligned(8)));
         const char* p = reinterpret_cast<const char*>(pos) + (DIM == 3 ? (o + (o << 1)) << 3 : o << 4);
         const pair xy = *reinterpret_cast<const pair*>(p);
@@ -127,6 +129,11 @@ k_sph_gradient(int n, double inv_h, double alpha_h, const double* __restrict__ p
         for (int a = 1; a < DIM; ++a) r2 = __dadd_rn(r2, __dmul_rn(dx[a], dx[a]));
         double r, inv_r;
         root_and_inverse(r2, r, inv_r);
+        if (!root_in_range(r2)) {
+            if (!e.in) return;
+            r = __dsqrt_rn(r2);
+            inv_r = r > 0.0 ? __ddiv_rn(1.0, r) : 0.0;
+        }
         const double g = __dmul_rn(bspline_dwdq(__dmul_rn(r, inv_h)), inv_r);
         const double vfj = VOL ? __dmul_rn(e.v, e.f) : e.f;
         const double df = __dsub_rn(e.f, fi);

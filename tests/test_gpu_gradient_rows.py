@@ -69,3 +69,21 @@ def test_pair_distances(scale):
         # (dx / r first: dW/dr / r alone underflows for the largest)
         want = np.zeros(2) if r == 0 or not np.isfinite(r) else -f[j] * G.kernel_dwdr(r, 2, h) * (dx / r)
         assert np.all(np.abs(got[i] - want) <= 16 * 2.0 ** -52 * np.abs(want) + 16 * 5e-324), (i, got[i], want)
+
+
+def test_indices_outside_the_set_are_skipped():
+    """An index outside [0, n) adds nothing, not even where the row's own field is infinite, and is reported."""
+    ctx = nnps.Context(0)
+    up = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    pos = np.array([[0.1, 0.1, 0.1], [0.2, 0.1, 0.1], [0.1, 0.25, 0.1]])
+    f = np.array([np.inf, 2.0, 3.0])
+    rp = np.array([0, 4, 6, 8], dtype=np.int64)
+    col = np.array([1, 7, -1, 2, 2, 3, 1, -2147483648], dtype=np.int32)
+    print("[gpu] gradient indices outside the set", flush=True)
+    grad, _ = nnps.sph_gradient(up(pos), up(f), 0.2, up(rp), up(col), ctx=ctx)
+    keep = (col >= 0) & (col < 3)
+    crp = np.concatenate([[0], np.cumsum([keep[:4].sum(), keep[4:6].sum(), keep[6:].sum()])]).astype(np.int64)
+    s, _, (abs_s, *_) = G.gradient(pos, np.where(np.isinf(f), 1.0, f), 0.2, crp, col[keep])
+    assert np.all(np.abs(grad.cpu().numpy() - s) <= G.sum_bound(abs_s, np.full(3, 42)))
+    assert ctx.check() == nnps.NNPS_EINVAL
+    ctx.close()
