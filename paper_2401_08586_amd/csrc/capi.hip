@@ -22,14 +22,24 @@ namespace {
 struct DevBuf {
     void* p = nullptr;
     size_t cap = 0;
-    hipError_t ensure(size_t bytes)
+    // A buffer that has to grow again takes a quarter more than it had: freeing waits for the
+    // device, so batches of ever new sizes would stall every stream each time (exact: no spare
+    // room, also where there is none).
+    hipError_t ensure(size_t bytes, bool exact = false)
     {
         if (bytes <= cap && p) return hipSuccess;
+        const size_t spare = exact ? 0 : cap + cap / 4;
         if (p) (void)hipFree(p);
         p = nullptr;
         cap = 0;
-        const size_t want = std::max<size_t>(bytes, 256);
+        size_t want = std::max({bytes, spare, size_t(256)});
         hipError_t e = hipMalloc(&p, want);
+        if (e != hipSuccess && want > bytes) {
+            (void)hipGetLastError();
+            p = nullptr;
+            want = std::max<size_t>(bytes, 256);
+            e = hipMalloc(&p, want);
+        }
         if (e == hipSuccess) cap = want;
         return e;
     }
@@ -599,7 +609,7 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         if (q.bytes == 0) continue;
         void* before = q.b->p;
         const size_t cap = q.b->cap;
-        hipError_t e = q.b->ensure(q.bytes);
+        hipError_t e = q.b->ensure(q.bytes, q.b == &c->dbits);  // the kept bits have a bound
         if (e != hipSuccess) return e == hipErrorOutOfMemory ? NNPS_ENOMEM : NNPS_EDEVICE;
         if (q.b->p != before) ++c->buf_gen;
         // (new memory may have the old address)
