@@ -31,13 +31,13 @@ HBM_PEAK_GBS = 8000.0
 #   FETCH_SIZE / WRITE_SIZE (KiB): the copy reads 262,144 KiB fetched and 524,288 KiB
 #     written for 524,288 KiB moved each way, so they scale by 2.000 and 1.000.
 # Reported only while the source is unchanged (the counters belong to that code).
-FILL_TRAFFIC = {"source_sha256_16": "9cf6101d64cef744", "dram_read_bytes": 220.2e6, "dram_write_bytes": 487.3e6,
-                "fetch_kib": 108373, "write_kib": 475898, "fetch_scale": 2.0, "write_scale": 1.0}
+FILL_TRAFFIC = {"source_sha256_16": "d9266bf0cedff440", "dram_read_bytes": 237.3e6, "dram_write_bytes": 491.4e6,
+                "fetch_kib": 116736, "write_kib": 479923, "fetch_scale": 2.0, "write_scale": 1.0}
 
 
 # VALU wave-instructions per launch (SQ_INSTS_VALU) of the C2 search kernels, from the
 # profile of the same source; like the traffic, reported only while the source is unchanged
-VALU_INSTS = {"source_sha256_16": "9cf6101d64cef744", "k_fill<3,0>": 136435229, "k_count16<3,0,false>": 129009217}
+VALU_INSTS = {"source_sha256_16": "d9266bf0cedff440", "k_fill<3,false>": 77699923, "k_count<3,16,false>": 77693658}
 
 
 def valu_ceilings():
@@ -62,10 +62,10 @@ def issue_rates(ph, ceilings):
         if hashlib.sha256(f.read()).hexdigest()[:16] != VALU_INSTS["source_sha256_16"]:
             return None
     out = {}
-    # the kernels' instructions are 32-bit integer and bit work plus packed FP16 (the count's
-    # FP16 share is about a quarter); FP32's dual issue does not apply to them
+    # the kernels' vector instructions are 32-bit integer and bit work for the most part (the
+    # distance tests are matrix instructions); FP32's dual issue does not apply to them
     peak = ceilings["int32"]
-    for k, phase in (("k_fill<3,0>", "fill"), ("k_count16<3,0,false>", "count")):
+    for k, phase in (("k_fill<3,false>", "fill"), ("k_count<3,16,false>", "count")):
         rate = VALU_INSTS[k] / (ph[phase] * 1e-3)
         out[k] = {"valu_insts_per_launch": VALU_INSTS[k], "avg_launch_ms": ph[phase], "achieved": rate,
                   "peak": peak, "peak_kind": "measured 32-bit integer issue rate (nnps_probe_valu_rate)",
@@ -181,12 +181,11 @@ def time_batch(ctx, pss, mode, steps, warmup, graphs=True, pos=None, phase_steps
             {k: (v[0] / v[1] if v[1] else None) for k, v in ph.items()})
 
 
-def fill_bytes(ps, nnz, band_pairs):
+def fill_bytes(ps, nnz):
     """Algorithmic bytes of one fill launch: 8 per neighbour pair written (int32 col +
-    float32 dist), per particle its FP16 record (8), original index (4), fixed-point
-    position (8 d), cell key (4) and row bounds (8), and 8 d per FP64 recheck gather."""
-    d = ps.dim
-    return 8 * nnz + ps.n * (24 + 8 * d) + 8 * d * band_pairs
+    float32 dist) and per particle its position and index (8 d + 4), row start (8) and
+    length (4). The count pass decides the pairs near the cutoff: the fill rechecks none."""
+    return 8 * nnz + ps.n * (16 + 8 * ps.dim)
 
 
 def cpu_model():
@@ -307,7 +306,7 @@ def main():
         del src, dst
 
     fill_ms = ph16["fill"]
-    fb = fill_bytes(ps, nnz, st16["band_pairs"])
+    fb = fill_bytes(ps, nnz)
     traffic, traffic_detail = fill_traffic() if args.workload == "c2" else (None, None)
     achieved = fb / (fill_ms * 1e-3) / 1e9
     out = {
@@ -324,7 +323,7 @@ def main():
         "dtype": "f16",
         "data": "synthetic",
         "config": describe(ps),
-        "roofline": {"bound": "hbm", "kernel": "k_fill<3,0> (fill pass)", "achieved": achieved,
+        "roofline": {"bound": "hbm", "kernel": "k_fill<3,false> (fill pass)", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
                      "traffic_detail": traffic_detail,
@@ -389,7 +388,7 @@ def bench_config(name, args):
     ms64, nnz64, _, ph64 = time_mode(ctx, pos, ps, nnps.MODE_FP64_BASELINE, steps, args.warmup)
     ctx.close()
     assert nnz64 == nnz
-    fb = fill_bytes(ps, nnz, st16["band_pairs"])
+    fb = fill_bytes(ps, nnz)
     gbs = fb / (ph16["fill"] * 1e-3) / 1e9
     log(f"[bench] {name}: fp16 {ms16:.3f} ms/step, fp64 {ms64:.3f} ms/step, nnz={nnz}")
     del pos
@@ -399,7 +398,7 @@ def bench_config(name, args):
             "fp64_baseline": {"value": nnz / (ms64 * 1e-3) / 1e9, "ms_per_step": ms64, "phases_ms": ph64,
                               "speedup_fp16_over_fp64": ms64 / ms16},
             "fp16_stats": {k: st16[k] for k in ("candidates", "band_pairs", "fp16_false_pos", "fp16_false_neg")},
-            "roofline": {"bound": "hbm", "kernel": "k_fill<2,0> (fill pass)", "achieved": gbs, "peak": HBM_PEAK_GBS,
+            "roofline": {"bound": "hbm", "kernel": "k_fill<2,false> (fill pass)", "achieved": gbs, "peak": HBM_PEAK_GBS,
                          "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": fb,
                          "avg_launch_ms": ph16["fill"], "traffic": None}}
 
@@ -659,7 +658,7 @@ def bench_batch(args, steps=None, warmup=None, sweeps=2, space=None):
                                           "heavy_rows", "dense_rows", "dense_entries")},
         "autotune": tuned,
         "roofline": {
-            "bound": "hbm", "kernel": "fill passes (k_fill<3,0>, k_long, k_dense<3,0,true,*>)",
+            "bound": "hbm", "kernel": "fill passes (k_fill<3,false>, k_long, k_dense_fill<3,false>)",
             "achieved": fb / (fill_ms * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": fb / (fill_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": fb,
             "avg_launch_ms": fill_ms, "traffic": None},
