@@ -457,7 +457,6 @@ __device__ __forceinline__ uint32_t span8(int a, int b)
     return ((1u << b) - 1u) & ~((1u << a) - 1u);
 }
 
-constexpr uint32_t kInvLo = 0x7C00u, kInvHi = 0x7C000000u;
 constexpr int kGroup = 8;  // pair records per group in the FP16 count loop
 
 // ---------------------------------------------------------------------------
@@ -2098,7 +2097,6 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
 k_dense_count(SearchArgs a)
 {
     using T = Tiles<DIM, P>;
-    using Rec = typename T::Rec;
     using Frag = typename T::Frag;
     constexpr int K = kDenseChunk, NW = kDenseThreads / 64, NS = K / 64;
     static_assert(kDenseSlice == 64 * NW && sizeof(Frag) == 32, "a wavefront per 64 targets; operands of 32 bytes");
@@ -2475,7 +2473,6 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
         Thresh th;
         th.init(sdesc.fr);
         const uint16_t tmid = sdesc.fr.t_mid;
-        const uint16_t tlo = sdesc.fr.t_lo;
         // this lane's target (held for the wavefront)
         const int pk = t0 + wv + NWV * lane;
         const bool vk = pk < t1;
