@@ -1020,8 +1020,10 @@ __device__ __forceinline__ void rank_originals(int U, const int (&og)[UCAP / (64
 // coordinates by 2^-22 M (2^-51 M). The bounds taken are 2^-18 M and 2^-46 M.
 //
 // What bounds it: VALU issue, about half of it the ranking. At 1M particles in 3D (64 targets
-// against 870 candidates per block, 28 tiles) the start took 251 us per launch (packed-FP16 tests
-// of each target's own 348 candidates, bits in union order), this 162; FP64 486 -> 280 us.
+// against 870 candidates per block, 28 tiles) packed-FP16 tests of each target's own 348
+// candidates, with bits in union order, took 251 us per launch, this 162; FP64 486 -> 280 us.
+// (Skipping the rounds of a thread's candidates that lie past a small union spoils the loads
+// that are issued together: 53 us in 2D either way, the 3D step 437 instead of 414.)
 // Wavefronts per block: in 2D a union has a few hundred candidates and the work that every
 // wavefront repeats (geometry, target operands) weighs more.
 template <int DIM>
