@@ -20,8 +20,8 @@ struct Launch {
 
 hipError_t launch_fill_i32(int* p, int64_t m, int v, hipStream_t st);
 int row_segments(int ncx);  // pieces a row of ncx cells is walked in
-hipError_t launch_assign(const Launch& L, uint32_t* key, int* slot, int* cell_count, int* err,
-                         hipStream_t st);
+// hot: cells of thousands of particles are expected.
+hipError_t launch_assign(const Launch& L, bool hot, uint32_t* key, int* slot, int* cell_count, int* err, hipStream_t st);
 // Cell starts from the cells' counts; also starts the structure's flags for this build.
 hipError_t launch_cell_scan(const Launch& L, const int* cell_count, int* cell_start, int64_t* partial, int* flags,
                             hipStream_t st);

@@ -735,7 +735,8 @@ nnps_status enqueue_build(nnps_cells* c, hipStream_t s)
     if (st != NNPS_OK) return st;
     c->counters_clear = false;
     tm.begin(NNPS_PHASE_ASSIGN, s);
-    HIP_TRY(launch_assign(L, c->k0.as<uint32_t>(), c->v1.as<int>(), c->cell_count.as<int>(), flags + kFlagBad, s));
+    HIP_TRY(launch_assign(L, c->dense && c->dense_seen != 0, c->k0.as<uint32_t>(), c->v1.as<int>(),
+                          c->cell_count.as<int>(), flags + kFlagBad, s));
     tm.end(NNPS_PHASE_ASSIGN, s);
     tm.begin(NNPS_PHASE_CELLSCAN, s);
     HIP_TRY(launch_cell_scan(L, c->cell_count.as<int>(), c->cell_start.as<int>(), c->partial.as<int64_t>(), flags, s));

@@ -147,3 +147,30 @@ def test_counts_and_fills_repeat(ctx, thresh):
             assert (st["heavy_rows"] > 0) == (thresh < 0)
     cells.close()
     ctx.set_tuning()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 2049, 5000])
+@pytest.mark.parametrize("shape", ["one_cell", "own_cells", "shuffled_runs"])
+def test_assignment_with_and_without_the_table(ctx, shape, n):
+    """Slots taken through a workgroup's table (a first build, which expects dense cells) and run by
+    run (the builds after a count that saw none): all particles in one cell, each in its own
+    (more cells than half a table holds of one workgroup's), and short runs in random order."""
+    rng = np.random.default_rng(n)
+    side = 71
+    if shape == "one_cell":
+        cell = np.full(n, side * 30 + 40)
+    elif shape == "own_cells":
+        cell = rng.permutation(side * side)[:n]
+    else:
+        cell = rng.permutation(np.repeat(rng.integers(0, side * side, size=n // 3 + 1), 3)[:n].reshape(-1, 1)).ravel()
+    pos = np.stack([cell % side, cell // side], 1) + rng.uniform(0.05, 0.95, size=(n, 2))
+    ps = W.ParticleSet(pos, (0.0, 0.0), (side - 0.001,) * 2, 1.0, 0.05, f"{shape}_{n}")
+    print(f"[gpu] assignment {shape} n={n}", flush=True)
+    ctx.set_tuning(dense_min_union=100000)  # looked for, never seen
+    cells = ctx.cells()
+    for rep in range(2):
+        rp, col, _, _ = nnps.search(torch.from_numpy(ps.pos).cuda(), ps.lo, ps.hi, ps.cell_size, ps.radius, ctx=ctx, cells=cells)
+        check([ps], [rp], [col])
+        assert cells.stats()["dense_rows"] == 0
+    cells.close()
+    ctx.set_tuning()
