@@ -1140,8 +1140,15 @@ __device__ __forceinline__ void quarter_transpose(uint32_t (&v)[4])
     swap16(v[2], v[3]);
 }
 
+// The lowest n bits of a word: a row word's candidates, where the union ends inside or before it.
+__device__ __forceinline__ uint32_t first_bits(int n)
+{
+    return n >= 32 ? ~0u : (n <= 0 ? 0u : (1u << n) - 1u);
+}
+
 // The MFMA operands of 64 items, one prepared per lane, and 64 x 64 tests. prepare: the
-// fragments of 64 candidates (lane l prepares candidate item(l); `past`: none, far away);
+// fragments of 64 candidates (lane l prepares candidate item(l); `past`: none, put far away so
+// that its results need no recheck; the callers mask them off, whatever they are);
 // words: the two row words (candidates 0-31 and 32-63 of the step) of target `lane`, with
 // `decide(bnd, acc, e, t)` settling the results bnd (bits) of a lane whose 16 results are the
 // step's candidates e.. against target t.
@@ -1380,7 +1387,7 @@ struct Tiles<DIM, 64> {
     __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>&, bool past) const
     {
         const double x = past ? 0.0 : rec.x - ox, y = past ? 0.0 : rec.y - oy, z = past ? 0.0 : rec.z - oz;
-        const double v[4] = {x, y, z, past ? 0x1p200 : x * x + y * y + z * z};
+        const double v[4] = {x, y, z, past ? 0x1p1000 : x * x + y * y + z * z};
         Frag f;
         fragments(v, f.c);
         return f;
@@ -1515,10 +1522,8 @@ k_count(SearchArgs a)
                     const int r = __builtin_ctz(bnd);
                     bnd &= bnd - 1u;
                     const int e = 64 * s + e0 + r;
-                    if (e < m) {
-                        const bool in = recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
-                        acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
-                    }
+                    const bool in = e < m && recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
+                    acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
                 }
                 return acc;
             };
@@ -1526,7 +1531,7 @@ k_count(SearchArgs a)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int tile = 2 * s + k;
-                uint32_t word = ww[k];
+                uint32_t word = ww[k] & first_bits(m - 32 * tile);
                 // the target itself is no neighbour; half lists keep larger original indices
                 const int d = rself - c0 - 32 * tile;
                 if (HALF && ranked) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
@@ -2185,10 +2190,8 @@ k_dense_count(SearchArgs a)
                             const int r = __builtin_ctz(bnd);
                             bnd &= bnd - 1u;
                             const int e = 64 * s + e0 + r;
-                            if (e < nc) {
-                                const bool in = recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
-                                acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
-                            }
+                            const bool in = e < nc && recheck_sorted<DIM>(a.spos, pi, slist[e], R2);
+                            acc = (acc & ~(1u << r)) | (static_cast<uint32_t>(in) << r);
                         }
                         return acc;
                     };
@@ -2200,7 +2203,7 @@ k_dense_count(SearchArgs a)
                     for (int h = 0; h < 2; ++h) {
                         // the target itself is no neighbour; half lists keep larger original indices
                         const int d = self - 64 * s - 32 * h;
-                        uint32_t word = ww[h];
+                        uint32_t word = ww[h] & first_bits(nc - 64 * s - 32 * h);
                         if (HALF) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
                         else word &= (d >= 0 && d < 32) ? ~(1u << d) : ~0u;
                         cnt += __builtin_popcount(word);

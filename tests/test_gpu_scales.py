@@ -1,0 +1,59 @@
+"""Cells far from unit size: every mode finds the oracle's neighbours whatever the units, in
+work blocks and in dense cells. (Radii above 2^100: the slots past a union's last candidate
+were once put at a fixed squared distance of 2^200, which the binary64 tiles then took for
+neighbours.)"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2401_08586_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_2401_08586_amd import nnps  # noqa: E402
+
+MODES = {"fp16": nnps.MODE_FP16_RCLL, "fp64": nnps.MODE_FP64_BASELINE, "fp32": nnps.MODE_FP32_RCLL,
+         "recheck_all": nnps.MODE_RECHECK_ALL}
+
+
+def blob(n, dim, seed, scale):
+    """n points in the middle cell of a 5^dim grid, radius 0.7 cells."""
+    pos = scale * (2.0 + np.random.default_rng(seed).uniform(0.02, 0.98, size=(n, dim)))
+    return W.ParticleSet(pos, (0.0,) * dim, (5.0 * scale,) * dim, scale, 0.7 * scale, f"blob{dim}d_{n}_{scale:g}")
+
+
+def check(ps, mode, dense):
+    print(f"[gpu] scales {ps.name} n={ps.n} {mode} dense={dense}", flush=True)
+    wrp, wcol, wdist = oracle.search_ps(ps)
+    ctx = nnps.Context(0)
+    try:
+        ctx.set_tuning(dense_min_union=1 if dense else -1)
+        cells = ctx.cells()
+        for _ in range(2):  # dense cells: tested in the fill, then taken from the count's bits
+            rp, col, dist, _ = nnps.search(torch.from_numpy(ps.pos).cuda(), ps.lo, ps.hi, ps.cell_size, ps.radius,
+                                           mode=MODES[mode], ctx=ctx, cells=cells)
+            np.testing.assert_array_equal(rp.cpu().numpy(), wrp, err_msg=ps.name)
+            np.testing.assert_array_equal(col.cpu().numpy(), wcol, err_msg=ps.name)
+            d = dist.cpu().numpy()
+            if mode in ("fp64", "fp32"):
+                np.testing.assert_array_equal(d.view(np.uint32), wdist.view(np.uint32), err_msg=ps.name)
+            else:
+                # 1e-6 where FP32 has the distance (as a normal number), else the nearest it has
+                w = wdist.astype(np.float64)
+                normal = np.isfinite(wdist) & (w >= 2.0 ** -126)
+                assert np.all(np.abs(d[normal].astype(np.float64) - w[normal]) <= 1e-6 * w[normal]), ps.name
+                assert np.all(np.isinf(d[np.isinf(wdist)])), ps.name
+        cells.close()
+    finally:
+        ctx.set_tuning()
+        ctx.close()
+
+
+@pytest.mark.parametrize("dense", [False, True], ids=["blocks", "dense"])
+@pytest.mark.parametrize("mode", MODES)
+def test_radius_above_2_to_100(mode, dense):
+    for scale in (2e30, 1e36):
+        for dim in (2, 3):
+            for n in (2, 33, 200, 1025):
+                check(blob(n, dim, n, scale), mode, dense)
