@@ -1381,7 +1381,9 @@ struct Tiles<DIM, 64> {
         for (int k = 0; k < 4; ++k) u[k] = __shfl(uu, 16 * k + static_cast<int>(threadIdx.x & 15), 64);
         const double xs = static_cast<double>(g.xb - g.xa + 2), w = g.sd->fr.w;
         const double beta = 0x1p-46 * w * w * (4.0 * (xs * xs + 8.0) + 1.0);
-        bhi = static_cast<int>(__builtin_bit_cast(uint64_t, beta) >> 32) + 1;
+        // cells so wide or so narrow that a square or the bound could leave the exponent range
+        // (and a NaN pass the minimum below unseen): no result is below a NaN, all are decided
+        bhi = w > 0x1p-450 && w < 0x1p450 ? static_cast<int>(__builtin_bit_cast(uint64_t, beta) >> 32) + 1 : 0x7FFFFFFF;
     }
     struct Frag { double c[4]; };
     __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>&, bool past) const
@@ -1421,7 +1423,7 @@ struct Tiles<DIM, 64> {
 #pragma unroll
             for (int r = 0; r < 14; r += 2) m = fminf(fminf(m, fabsf(hi[r])), fabsf(hi[r + 1]));
             m = fminf(m, fabsf(hi[14]));
-            if (__builtin_amdgcn_ballot_w64(!(m >= below))) {  // also where squares overflow
+            if (__builtin_amdgcn_ballot_w64(!(m >= below))) {
                 uint32_t bnd = 0;
 #pragma unroll
                 for (int r = 15; r >= 0; --r) bnd = (bnd << 1) | (fabsf(hi[r]) >= below ? 0u : 1u);

@@ -23,6 +23,13 @@ def blob(n, dim, seed, scale):
     return W.ParticleSet(pos, (0.0,) * dim, (5.0 * scale,) * dim, scale, 0.7 * scale, f"blob{dim}d_{n}_{scale:g}")
 
 
+def sparse(dim, seed, scale):
+    """About one point in eight cells of a grid of 64 cells along an axis: blocks span many cells."""
+    n = 512 if dim == 2 else 32768
+    pos = scale * 64.0 * np.random.default_rng(seed).uniform(0, 1, size=(n, dim))
+    return W.ParticleSet(pos, (0.0,) * dim, (64.0 * scale,) * dim, scale, scale, f"sparse{dim}d_{scale:g}")
+
+
 def check(ps, mode, dense):
     print(f"[gpu] scales {ps.name} n={ps.n} {mode} dense={dense}", flush=True)
     wrp, wcol, wdist = oracle.search_ps(ps)
@@ -57,3 +64,15 @@ def test_radius_above_2_to_100(mode, dense):
         for dim in (2, 3):
             for n in (2, 33, 200, 1025):
                 check(blob(n, dim, n, scale), mode, dense)
+
+
+@pytest.mark.parametrize("dense", [False, True], ids=["blocks", "dense"])
+@pytest.mark.parametrize("mode", MODES)
+def test_squares_at_the_ends_of_the_exponent_range(mode, dense):
+    """Cells whose squared extent over a block overflows although every neighbour's squared
+    distance is finite (2^506: a block's span of up to 64 cells is squared past 2^1024), and cells
+    whose squares are subnormal or zero."""
+    for e in (449, 451, 506, 510, -449, -451, -510, -520):
+        check(sparse(3, e & 1023, 2.0 ** e), mode, dense)
+        check(sparse(2, e & 1023, 2.0 ** e), mode, dense)
+        check(blob(200, 3, e & 1023, 2.0 ** e), mode, dense)
