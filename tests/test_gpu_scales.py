@@ -30,6 +30,21 @@ def sparse(dim, seed, scale):
     return W.ParticleSet(pos, (0.0,) * dim, (64.0 * scale,) * dim, scale, scale, f"sparse{dim}d_{scale:g}")
 
 
+def straddle(dim, scale):
+    """Row A: two targets 15.9 cells apart. Row B above it: 31 points near each of them in turn, those
+    near the second its neighbours or just not, two of them 16.1 cells from the first target (their
+    squares about it overflow at scale 2^508, the others' do not). 64 candidates: every sixteen of
+    them hold some that are near either target."""
+    near = np.stack([np.linspace(0.5, 0.9, 31), np.full(31, 1.2)], axis=1)
+    far = np.stack([np.linspace(15.8, 16.0, 31), np.where(np.arange(31) % 2, 1.1, 1.48)], axis=1)
+    far[20:22] = (16.6, 1.1), (16.6, 1.49)
+    one = np.concatenate([[[0.5, 0.5], [16.4, 0.5]], np.stack([near, far], axis=1).reshape(-1, 2)])
+    pos = (one[None] + np.array([0.0, 4.0]) * np.arange(5)[:, None, None]).reshape(-1, 2)
+    if dim == 3:
+        pos = np.concatenate([pos, np.full((len(pos), 1), 0.5)], axis=1)
+    return W.ParticleSet(scale * pos, (0.0,) * dim, (64.0 * scale,) * dim, scale, scale, f"straddle{dim}d_{scale:g}")
+
+
 def check(ps, mode, dense):
     print(f"[gpu] scales {ps.name} n={ps.n} {mode} dense={dense}", flush=True)
     wrp, wcol, wdist = oracle.search_ps(ps)
@@ -70,9 +85,11 @@ def test_radius_above_2_to_100(mode, dense):
 @pytest.mark.parametrize("mode", MODES)
 def test_squares_at_the_ends_of_the_exponent_range(mode, dense):
     """Cells whose squared extent over a block overflows although every neighbour's squared
-    distance is finite (2^506: a block's span of up to 64 cells is squared past 2^1024), and cells
+    distance is finite (from 2^506 on: a block's span of up to 64 cells is squared past 2^1024), and cells
     whose squares are subnormal or zero."""
-    for e in (449, 451, 506, 510, -449, -451, -510, -520):
+    for e in (449, 451, 506, 507, 508, 510, -449, -451, -510, -520):
         check(sparse(3, e & 1023, 2.0 ** e), mode, dense)
         check(sparse(2, e & 1023, 2.0 ** e), mode, dense)
         check(blob(200, 3, e & 1023, 2.0 ** e), mode, dense)
+        check(straddle(2, 2.0 ** e), mode, dense)
+        check(straddle(3, 2.0 ** e), mode, dense)
