@@ -1691,6 +1691,20 @@ k_fill(SearchArgs a)
         cnt += __builtin_popcount(wbits[k]);
     }
     if (!active) rlen = 0;
+    int before = 0, have = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int c = __shfl(cnt, 16 * q + (lane & 15), 64);
+        if (q < quarter) before += c;
+        have += c;
+    }
+    // a row whose bits do not match its count writes nothing: it takes no place in the list
+    if (have != rlen) {
+        atomicOr(a.flags + kFlagErr, kErrLongRow);
+        cnt = before = rlen = 0;
+#pragma unroll
+        for (int k = 0; k < KW; ++k) wbits[k] = 0u;
+    }
     int incl = rlen;  // inclusive over the 16 lanes of a row
     incl += dpp<0x111>(0, incl);
     incl += dpp<0x112>(0, incl);
@@ -1698,21 +1712,12 @@ k_fill(SearchArgs a)
     incl += dpp<0x118>(0, incl);
     const int off = incl - rlen;
     if (lane < TW) sbase[tg] = rs - off;
-    int before = 0;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        const int c = __shfl(cnt, 16 * q + (lane & 15), 64);
-        if (q < quarter) before += c;
-    }
-    // a row whose bits do not match its count writes nothing
-    const bool bad = __shfl(before + cnt, 48 + (lane & 15), 64) != rlen;
-    if (bad) atomicOr(a.flags + kFlagErr, kErrLongRow);
     __syncthreads();
     NNPS_GLOBAL int32_t* const col = (NNPS_GLOBAL int32_t*)sd.col;
     NNPS_GLOBAL float* const dist = (NNPS_GLOBAL float*)sd.dist;
     const int64_t cap = sd.capacity;
     const long long rend = active ? rs + rlen : 0;  // the row's end in the output
-    const bool room = __builtin_amdgcn_ballot_w64(rend > cap || bad) == 0;
+    const bool room = __builtin_amdgcn_ballot_w64(rend > cap) == 0;
     if (!room && rend > cap) atomicOr(a.flags + kFlagErr, kErrCapacity);
     const float quantum = sd.fr.quantum, near2 = sd.fr.near2;
     uint16_t* const flat = sflat[wv];

@@ -1,0 +1,97 @@
+"""The fills on arrays that do not match each other: a row whose accepted bits and count differ
+is left out and reported, every other row comes out right, and nothing is written outside the
+rows (the outputs are surrounded by guard words). The library's own passes never leave such
+arrays, so a harness makes them. n particles of one cell, all pairs within the radius."""
+import ctypes
+
+import native_harness as native
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+ERR, LONG_ROW = 0, 4  # index of the error word, its bit for a row that does not match
+GUARD = 4096
+
+
+class Rows:
+    """Wanted rows of n particles, and the device arrays a fill of one block or dense cell takes."""
+
+    def __init__(self, dim, n, seed, f64):
+        self.dim, self.n, self.f64 = dim, n, f64
+        self.rng = np.random.default_rng(seed)
+        self.pos = self.rng.uniform(0.05, 0.95, size=(n, dim))
+        self.keep = self.rng.random((n, n)) < 0.5  # which candidates a row accepts
+        np.fill_diagonal(self.keep, False)
+        self.len = self.keep.sum(1).astype(np.int64)
+        self.dev = {}
+
+    def put(self, **arrays):
+        for k, v in arrays.items():
+            self.dev[k] = torch.from_numpy(np.ascontiguousarray(v)).cuda()
+
+    def common(self, mode):
+        n = self.n
+        rec = np.zeros((n, 4))
+        rec[:, :self.dim] = self.pos
+        rec[:, 3] = np.arange(n, dtype=np.int64).view(np.float64)
+        self.start = np.concatenate([[0], np.cumsum(self.len)])
+        self.total = int(self.start[-1])
+        self.put(pos=self.pos, row_ptr=self.start, col=np.full(self.total + 2 * GUARD, -7, np.int32),
+                 dist=np.full(self.total + 2 * GUARD, -7, np.float32),
+                 set_room=np.zeros(native.load().harness_set_bytes(), np.uint8), offs=np.array([0, n], np.int32),
+                 cell_offs=np.array([0, 1], np.int32), skey=np.zeros(n, np.uint32), perm=np.arange(n, dtype=np.int32),
+                 cell_start=np.array([0, n], np.int32), spos=rec, rq=np.zeros((n, 4), np.float32),
+                 flags=np.zeros(8, np.int32))
+        self.args = native.Args(dim=self.dim, mode=mode, n=n, half=0, capacity=self.total)
+
+    def fill(self, dense):
+        for k, t in self.dev.items():
+            at = t.data_ptr() + (GUARD * 4 if k in ("col", "dist") else 0)
+            setattr(self.args, k, at)
+        torch.cuda.synchronize()
+        assert native.load().harness_fill(ctypes.byref(self.args), dense) == 0
+        return self.dev["flags"].cpu().numpy()
+
+    def check(self, out):
+        """Rows in `out` untouched, the others as wanted, the guards untouched."""
+        col, dist = self.dev["col"].cpu().numpy(), self.dev["dist"].cpu().numpy()
+        wcol, wdist = np.full(col.shape, -7, np.int32), np.full(dist.shape, -7, np.float64)
+        for i in range(self.n):
+            if i in out:
+                continue
+            at = GUARD + self.start[i]
+            j = np.nonzero(self.keep[i])[0]
+            wcol[at:at + len(j)] = j
+            wdist[at:at + len(j)] = np.sqrt(((self.pos[j] - self.pos[i]) ** 2).sum(1))
+        np.testing.assert_array_equal(col, wcol)
+        assert np.all(np.abs(dist - wdist) <= 1e-6 * np.abs(wdist))
+
+
+@pytest.mark.parametrize("mode", [0, 1], ids=["fp16", "fp64"])
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n", [1, 17, 64])
+def test_block_row_that_does_not_match_its_count(dim, n, mode):
+    for wrong in ([], [0], [n - 1], list(range(0, n, 3)), list(range(n))):
+        for delta in (-1, 1, 40):
+            r = Rows(dim, n, 7, mode == 1)
+            bits = r.keep.copy()
+            off = [i for i in wrong if r.len[i] + delta >= 0]
+            for i in off:  # the count says otherwise than the bits
+                r.len[i] += delta
+            r.common(mode)
+            words = np.zeros((1024 // 32 if dim == 3 else 512 // 32, n), np.uint32)
+            for i in range(n):
+                for j in np.nonzero(bits[i])[0]:
+                    words[j >> 5, i] |= np.uint32(1 << (j & 31))
+            nseg = 9 if dim == 3 else 3
+            self_seg = nseg // 2
+            desc = np.zeros(24, np.int32)
+            desc[:4] = [0, n, 0, n]
+            desc[5 + nseg + self_seg + 1:5 + 2 * nseg] = n  # the segments after the targets' own start at the end
+            r.put(cbits=words, bdesc=desc, branks=np.arange(1024, dtype=np.uint16), nblk=np.array([1], np.int32),
+                  counts_s=r.len.astype(np.int32), rsort=r.start[:n], heavy=np.zeros(n, np.int32))
+            flags = r.fill(0)
+            assert flags[ERR] == (LONG_ROW if off else 0)
+            r.check(off)
