@@ -2343,7 +2343,7 @@ k_dense_fill(SearchArgs a)
                     for (int q = 0; q < NSUB; ++q) {
                         if (q >= nsub) break;
                         const int lb = q * kDenseChunk + 16 * lane;  // the lane's first candidate
-                        const uint32_t M = lb < nc ? wb[t * NSUB + q] : 0u;  // nothing was kept past the list
+                        const uint32_t M = wb[t * NSUB + q] & first_bits(nc - lb);  // none past the list
                         int tot;
                         const int base = wave_excl_scan_i32(__builtin_popcount(M), &tot);
                         // accepted candidates queued per lane, as many as the queue holds at a
@@ -2357,22 +2357,22 @@ k_dense_fill(SearchArgs a)
                             const int n = min(QCAP, tot - w0);
                             for (int i = lane; i < n; i += 64) {
                                 const int e = queue[i], slot = done + w0 + i;
-                                float dv;
-                                int oj;
-                                if constexpr (F64) {
-                                    oj = sorig[e];
-                                    dv = dist_fp64<DIM>(pi, sdbl + e * DIM);
-                                } else {
-                                    const int4 r = srec[e];
-                                    oj = r.w;
-                                    const float s2 = quanta2<DIM>(ti, r);
-                                    dv = __builtin_amdgcn_sqrtf(s2) * quantum;
-                                    if (!(s2 >= near2))
-                                        dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
-                                                            (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
-                                                            inv_quantum, quantum);
-                                }
                                 if (slot < rl && room) {
+                                    float dv;
+                                    int oj;
+                                    if constexpr (F64) {
+                                        oj = sorig[e];
+                                        dv = dist_fp64<DIM>(pi, sdbl + e * DIM);
+                                    } else {
+                                        const int4 r = srec[e];
+                                        oj = r.w;
+                                        const float s2 = quanta2<DIM>(ti, r);
+                                        dv = __builtin_amdgcn_sqrtf(s2) * quantum;
+                                        if (!(s2 >= near2))
+                                            dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
+                                                                (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
+                                                                inv_quantum, quantum);
+                                    }
                                     if (rl <= (1 << 30)) {  // byte offsets within the row fit 32 bits
                                         const uint32_t off = static_cast<uint32_t>(slot) * 4u;
                                         *(NNPS_GLOBAL int32_t*)((NNPS_GLOBAL char*)rcol + off) = oj;

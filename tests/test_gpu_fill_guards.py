@@ -95,3 +95,51 @@ def test_block_row_that_does_not_match_its_count(dim, n, mode):
             flags = r.fill(0)
             assert flags[ERR] == (LONG_ROW if off else 0)
             r.check(off)
+
+
+def kept_bits(keep):
+    """The dense count's bits: per (target, 1024-candidate chunk) 64 words of 16 bits."""
+    n = keep.shape[0]
+    nchunk = (n + 1023) // 1024
+    b = np.zeros((n, nchunk * 1024), bool)
+    b[:, :n] = keep
+    return (b.reshape(n, nchunk, 64, 16) << np.arange(16)).sum(-1).astype(np.uint16)
+
+
+@pytest.mark.parametrize("mode", [0, 1], ids=["fp16", "fp64"])
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n", [1, 17, 63, 1000, 1030])
+def test_dense_bits_past_the_list_and_rows_of_another_length(dim, n, mode):
+    """Bits past the union's last candidate are no candidates. A row with more accepted bits than
+    its length in the row pointers writes that many (the list's first), one with fewer what it has;
+    both are reported."""
+    for case in ("clean", "past", "short", "long"):
+        r = Rows(dim, n, 11, mode == 1)
+        bits = kept_bits(r.keep)
+        if case == "past":
+            nchunk = bits.shape[1]
+            lane, bit = (n % 1024) >> 4, n & 15
+            if n % 1024:
+                bits[:, nchunk - 1, lane] |= np.uint16((0xFFFF << bit) & 0xFFFF)
+                bits[:, nchunk - 1, lane + 1:] = 0xFFFF
+        off = list(range(0, n, 5)) if case in ("short", "long") else []
+        off = [i for i in off if case == "long" or r.len[i] > 0]
+        for i in off:
+            r.len[i] += 1 if case == "long" else -1
+        r.common(mode)
+        nchunk = bits.shape[1]
+        nu = (n + 63) // 64
+        r.put(dbits=bits, wdense=np.ones(1, np.int32), usz=np.array([n], np.int32), uoff=np.array([0, n], np.int64),
+              ulist=np.arange(n, dtype=np.int32), unit_off=np.array([0, nu], np.int32), ucell=np.zeros(nu, np.int32),
+              dn=np.array([n], np.int32), dboff=np.array([0, n * nchunk], np.int64))
+        r.args.dbits_cap = bits.size
+        flags = r.fill(1)
+        assert flags[ERR] == (LONG_ROW if off else 0), case
+        for i in off:  # the reported rows: as far as they go
+            j = np.nonzero(r.keep[i])[0]
+            at = GUARD + r.start[i]
+            m = min(len(j), int(r.len[i]))
+            np.testing.assert_array_equal(r.dev["col"][at:at + m].cpu().numpy(), j[:m])
+            r.dev["col"][at:at + m] = -7
+            r.dev["dist"][at:at + m] = -7
+        r.check(off)
