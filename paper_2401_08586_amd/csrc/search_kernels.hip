@@ -41,6 +41,16 @@ __device__ __forceinline__ bool recheck_sorted(const double* __restrict__ spos, 
     return r2_fp64<DIM>(pi, spos + static_cast<size_t>(j) * 4) <= R2;
 }
 
+// Square root, within 0.51 units in the last place (the hardware's own is off by up to one, and
+// low on average): its reciprocal root (relative error below 2^-22) and one Heron step. For
+// normal numbers whose square root's square does not overflow.
+__device__ __forceinline__ float root(float s2)
+{
+    const float r = __builtin_amdgcn_rsqf(s2);
+    const float y = s2 * r;
+    return __builtin_fmaf(__builtin_fmaf(-y, y, s2), 0.5f * r, y);
+}
+
 // FP32 distance from binary64 positions: the displacement in quanta (a power of two, so no
 // rounding, and no overflow of the squares), rounded once to FP32 per axis.
 template <int DIM>
@@ -50,9 +60,9 @@ __device__ __forceinline__ float dist_near(const double* pi, const double* pj, d
 #pragma unroll
     for (int k = 0; k < DIM; ++k) {
         const float f = static_cast<float>((pj[k] - pi[k]) * inv_quantum);
-        s2 = s2 + f * f;
+        s2 = __builtin_fmaf(f, f, s2);
     }
-    return __builtin_amdgcn_sqrtf(s2) * quantum;  // <= 1 ulp, then exact
+    return __fsqrt_rn(s2) * quantum;  // rare: any s2, 0 and infinity among them
 }
 
 // A coordinate in quanta (Frame::quantum), the low 32 bits: rounded to an integer in the low
@@ -72,10 +82,10 @@ __device__ __forceinline__ float quanta2(const int4& i, const int4& j)
         return static_cast<float>(static_cast<int>(static_cast<uint32_t>(x) - static_cast<uint32_t>(y)));
     };
     const float dx = diff(j.x, i.x), dy = diff(j.y, i.y);
-    float s2 = dx * dx + dy * dy;
+    float s2 = __builtin_fmaf(dy, dy, dx * dx);
     if (DIM == 3) {
         const float dz = diff(j.z, i.z);
-        s2 = s2 + dz * dz;
+        s2 = __builtin_fmaf(dz, dz, s2);
     }
     return s2;
 }
@@ -90,7 +100,7 @@ __device__ __forceinline__ float dist_quanta(const Frame& fr, const double* pi, 
                          DIM == 3 ? in_quanta(x[2], fr.lo[2], fr.inv_quantum) : 0, 0);
     };
     const float s2 = quanta2<DIM>(fixed(pi), fixed(pj));
-    return s2 >= fr.near2 ? __builtin_amdgcn_sqrtf(s2) * fr.quantum
+    return s2 >= fr.near2 ? root(s2) * fr.quantum  // exact: a power of two
                           : dist_near<DIM>(pi, pj, fr.inv_quantum, fr.quantum);
 }
 
@@ -1783,7 +1793,7 @@ k_fill(SearchArgs a)
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
                     const float s2 = d[q];
-                    d[q] = __builtin_amdgcn_sqrtf(s2) * quantum;  // <= 1 ulp, then exact
+                    d[q] = root(s2) * quantum;  // exact: a power of two
                     if (near && !(s2 >= near2))
                         d[q] = dist_near<DIM>(a.spos + static_cast<size_t>(p0 + t[q]) * 4,
                                               (const double*)sd.pos + static_cast<size_t>(oj[q]) * DIM, inv_quantum,
@@ -2367,7 +2377,7 @@ k_dense_fill(SearchArgs a)
                                         const int4 r = srec[e];
                                         oj = r.w;
                                         const float s2 = quanta2<DIM>(ti, r);
-                                        dv = __builtin_amdgcn_sqrtf(s2) * quantum;
+                                        dv = root(s2) * quantum;
                                         if (!(s2 >= near2))
                                             dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
                                                                 (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
