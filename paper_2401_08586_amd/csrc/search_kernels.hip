@@ -284,16 +284,6 @@ struct SetView {
     }
 };
 
-template <int DIM>
-__device__ __forceinline__ bool recheck_g(const NNPS_GLOBAL double* __restrict__ pos, const double* pi, int oj,
-                                          double R2)
-{
-    double pj[3];
-#pragma unroll
-    for (int k = 0; k < DIM; ++k) pj[k] = pos[static_cast<size_t>(oj) * DIM + k];
-    return r2_fp64<DIM>(pi, pj) <= R2;
-}
-
 // The work block a workgroup takes. Workgroups are dealt to the eight XCDs in turn (the
 // i-th to XCD i mod 8), each XCD with its own L2, while neighbouring blocks share most of
 // their candidate unions. So XCD k is given the k-th contiguous eighth of the blocks,
@@ -2506,7 +2496,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
             oi_k = a.perm[pk];
             const int li = oi_k - poff;
 #pragma unroll
-            for (int k = 0; k < DIM; ++k) pi_k[k] = sd.pos[static_cast<size_t>(li) * DIM + k];
+            for (int k = 0; k < DIM; ++k) pi_k[k] = a.spos[static_cast<size_t>(pk) * 4 + k];
             if (F16) {
                 const ushort4 q = q16_of(a.rq[pk]);
                 q01_k = static_cast<int>(static_cast<uint32_t>(q.x) | (static_cast<uint32_t>(q.y) << 16));
@@ -2719,19 +2709,17 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                         }
                         bnd = ebits & ~inb;
                         // the FP64 recheck of candidate e: from its staged position in the fill
-                        auto recheck = [&](int e, int oj) -> bool {
-                            if constexpr (FILL && F16) {
+                        auto recheck = [&](int e) -> bool {
+                            if constexpr (FILL) {
                                 double pj[3];
 #pragma unroll
                                 for (int d = 0; d < DIM; ++d) pj[d] = spj[d * K + e];
                                 return r2_fp64<DIM>(pi, pj) <= R2;
-                            } else if constexpr (F16) {
+                            } else {
                                 double pt[3];
 #pragma unroll
                                 for (int d = 0; d < 3; ++d) pt[d] = rlf64(pi_k[d], k);
-                                return recheck_g<DIM>(sd.pos, pt, oj - poff, R2);
-                            } else {
-                                return recheck_g<DIM>(sd.pos, pi, oj - poff, R2);
+                                return recheck_sorted<DIM>(a.spos, pt, a.ulist[ub + c0 + e], R2);
                             }
                         };
                         if (MODE == 2) {
@@ -2748,7 +2736,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                                 const int e = 2 * (lane * nit + (bb & 15)) + (bb >> 4);
                                 const int oj = sorig[e];
                                 if (oj == oi) continue;
-                                const bool truth = recheck(e, oj);
+                                const bool truth = recheck(e);
                                 if (truth) dec |= 1u << bb;
                                 if (!FILL) {
                                     const bool band = (bnd >> bb) & 1u;
@@ -2785,7 +2773,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                                 const int e = 2 * (lane * nit + (bb & 15)) + (bb >> 4);
                                 const int oj = sorig[e];
                                 if (oj == oi) continue;  // itself (a band pair only when T_lo = 0)
-                                const bool truth = recheck(e, oj);
+                                const bool truth = recheck(e);
                                 if (truth) inb |= 1u << bb;
                                 if (!FILL) {
                                     const uint4 A = recA[(bb & 15) * 64 + lane];
