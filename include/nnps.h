@@ -70,9 +70,10 @@ typedef enum nnps_mode {
                                      error of the cutoff by the predicate itself), with the same
                                      cell build, work blocks, dense and long-row paths and fill
                                      as the FP16 mode; distances (float)sqrt(r2) in binary64 */
-    NNPS_MODE_RECHECK_ALL = 2,    /* debug: decided in FP64; the statistics test every candidate
-                                     in packed FP16 as well and count the disagreements outside
-                                     the band (must be 0) */
+    NNPS_MODE_RECHECK_ALL = 2,    /* debug: decided in FP64; the statistics decide every candidate
+                                     as the FP16 mode does, on the matrix cores, and in packed
+                                     FP16 as well and count the disagreements outside either
+                                     band (must be 0) */
     NNPS_MODE_FP32_RCLL = 3       /* FP32 relative coordinates (Eq. 6-7 in single precision) +
                                      FP64 recheck in a guard band of 2^-15 squared cell widths;
                                      dense cells and long rows are decided in FP64; distances
@@ -104,7 +105,8 @@ typedef struct nnps_stats {
     int64_t fp16_false_neg;         /* naive FP16 test says out, FP64 says in */
                                     /* (NNPS_MODE_FP32_RCLL: the three above count the FP32
                                        test of the block path; dense cells add none) */
-    int64_t outside_band_disagree;  /* RECHECK_ALL only: FP16 decided outside the band but wrong */
+    int64_t outside_band_disagree;  /* RECHECK_ALL only: decided outside the band but wrong, by the
+                                       packed FP16 test or by the FP16 mode's matrix test */
     int64_t heavy_rows;             /* rows handled by the long-row path */
     int64_t dense_rows;             /* rows handled by the dense-cell path */
     int64_t dense_entries;          /* summed stencil-union sizes of the dense cells */

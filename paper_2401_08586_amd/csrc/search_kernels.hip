@@ -1990,16 +1990,6 @@ void launch_count_mode(const SearchArgs& a, int mode, const dim3& g, hipStream_t
     else hipLaunchKernelGGL((k_count<DIM, 64, HALF>), g, b, 0, st, a);
 }
 
-template <int DIM>
-void launch_block_stats(const SearchArgs& a, const dim3& g, hipStream_t st)
-{
-    const int m = a.L.mode;
-    if (m == 0) hipLaunchKernelGGL((k_stats16<DIM, 0>), g, dim3(64), 0, st, a);
-    else if (m == 1) hipLaunchKernelGGL((k_stats64<DIM>), g, dim3(64), 0, st, a);
-    else if (m == 2) hipLaunchKernelGGL((k_stats16<DIM, 2>), g, dim3(64), 0, st, a);
-    else hipLaunchKernelGGL((k_stats32<DIM>), g, dim3(64), 0, st, a);
-}
-
 hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st)
 {
     if (a.L.ntot == 0 || nblk_max == 0) return hipSuccess;
@@ -2012,20 +2002,6 @@ hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st)
         if (d == 2) launch_count_mode<2, false>(a, m, g, st);
         else launch_count_mode<3, false>(a, m, g, st);
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st)
-{
-    if (a.L.ntot == 0) return hipSuccess;
-    if (nblk_max > 0) {
-        if (a.L.dim == 2) launch_block_stats<2>(a, block_grid(nblk_max), st);
-        else launch_block_stats<3>(a, block_grid(nblk_max), st);
-    }
-    const hipError_t e = launch_dense(a, DensePass::kStats, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, st, a.blk_stats, a.nblk,
-                       static_cast<const unsigned long long*>(a.dstats), a.dstats ? a.dgrid : 0, a.stats);
     return hipGetLastError();
 }
 
@@ -2820,6 +2796,74 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     }
 }
 
+// Recheck-all: the decisions of the FP16 mode's matrix tiles, made over the counted structure and
+// each compared with the binary64 predicate. A result within the bound is decided by the predicate
+// itself; one outside it that is wrong counts as a disagreement. One wavefront per 64 targets, every
+// pair of a target and a candidate (at(e) its sorted position) of the union's U.
+template <int DIM, typename At>
+__device__ __forceinline__ unsigned long long tile_disagreements(const SearchArgs& a, const BlockGeom<DIM>& g, int U,
+                                                                 At&& at)
+{
+    using T = Tiles<DIM, 16>;
+    const int lane = threadIdx.x & 63, nt = g.p1 - g.p0, p = g.p0 + min(lane, nt - 1);
+    const double R2 = g.sd->fr.R2;
+    const double* pi = a.spos + static_cast<size_t>(p) * 4;
+    T tiles;
+    tiles.targets(T::fetch(a, p), g);
+    unsigned long long wrong = 0;
+    for (int c0 = 0; c0 < U; c0 += 64) {
+        const int e = c0 + T::item(lane);
+        const typename T::Frag f = tiles.prepare(T::fetch(a, at(min(e, U - 1))), g, e >= U);
+        // the row words with every result within the bound taken as out, and as in
+        const u32x2 low = tiles.words(f, g, [](uint32_t bnd, uint32_t acc, int, int) { return acc & ~bnd; });
+        const u32x2 high = tiles.words(f, g, [](uint32_t bnd, uint32_t acc, int, int) { return acc | bnd; });
+        for (int j = 0; lane < nt && j < min(64, U - c0); ++j) {
+            const int q = at(c0 + j);
+            if (q == p) continue;
+            const bool in = recheck_sorted<DIM>(a.spos, pi, q, R2);
+            wrong += in ? !(high[j >> 5] >> (j & 31) & 1) : low[j >> 5] >> (j & 31) & 1;
+        }
+    }
+    return wave_sum_u64(wrong);
+}
+
+// Added to the blocks' sums (after k_stats16).
+template <int DIM>
+__global__ void __launch_bounds__(64)
+k_check_tiles(SearchArgs a)
+{
+    const int b = xcd_block(*a.nblk);
+    if (b < 0 || dense_block(a, b)) return;
+    BlockGeom<DIM> g;
+    g.init(a, b);
+    const unsigned long long wrong = tile_disagreements<DIM>(a, g, g.U, [&](int e) { return g.global_of_any(e); });
+    if (threadIdx.x == 0) a.blk_stats[static_cast<size_t>(b) * 5 + 4] += wrong;
+}
+
+// Added to the dense path's sums (after k_dense).
+template <int DIM>
+__global__ void __launch_bounds__(64)
+k_check_dense_tiles(SearchArgs a)
+{
+    const int nunits = *a.dn > 0 ? a.unit_off[a.L.ncell_tot] : 0;
+    unsigned long long wrong = 0;
+    for (int u = blockIdx.x; u < nunits; u += gridDim.x) {
+        const int c = __builtin_amdgcn_readfirstlane(a.ucell[u]);
+        const SetDesc& sd = a.L.sets[__builtin_amdgcn_readfirstlane(find_set(a.L.coffs, a.L.nsets, c))];
+        const int ncx = sd.fr.nc[0], ncy = sd.fr.nc[1], lk = c - sd.coff, row = lk / ncx;
+        BlockGeom<DIM> g;
+        g.sd = &sd;
+        g.xa = g.xb = lk - row * ncx;
+        g.y0 = row % ncy;
+        g.z0 = row / ncy;
+        g.p0 = __builtin_amdgcn_readfirstlane(a.cell_start[c] + (u - a.unit_off[c]) * kDenseUnit);
+        g.p1 = min(__builtin_amdgcn_readfirstlane(a.cell_start[c + 1]), g.p0 + kDenseUnit);
+        const int* list = a.ulist + a.uoff[c];
+        wrong += tile_disagreements<DIM>(a, g, __builtin_amdgcn_readfirstlane(a.usz[c]), [&](int e) { return list[e]; });
+    }
+    if (threadIdx.x == 0) a.dstats[static_cast<size_t>(blockIdx.x) * kDenseStats + 4] += wrong;
+}
+
 template <int D>
 void launch_dense_count(const SearchArgs& a, hipStream_t st)
 {
@@ -2853,6 +2897,7 @@ void launch_dense_stats(const SearchArgs& a, hipStream_t st)
     if (a.L.mode == 0) hipLaunchKernelGGL((k_dense<D, 0, false>), g, b, 0, st, a);
     else if (a.L.mode == 2) hipLaunchKernelGGL((k_dense<D, 2, false>), g, b, 0, st, a);
     else hipLaunchKernelGGL(k_dense_stats64, g, b, 0, st, a);
+    if (a.L.mode == 2) hipLaunchKernelGGL(k_check_dense_tiles<D>, g, dim3(64), 0, st, a);
 }
 
 hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st)
@@ -2870,6 +2915,31 @@ hipError_t launch_dense(const SearchArgs& a, DensePass pass, hipStream_t st)
         if (a.L.dim == 2) launch_dense_stats<2>(a, st);
         else launch_dense_stats<3>(a, st);
     }
+    return hipGetLastError();
+}
+
+template <int DIM>
+void launch_block_stats(const SearchArgs& a, const dim3& g, hipStream_t st)
+{
+    const int m = a.L.mode;
+    if (m == 0) hipLaunchKernelGGL((k_stats16<DIM, 0>), g, dim3(64), 0, st, a);
+    else if (m == 1) hipLaunchKernelGGL((k_stats64<DIM>), g, dim3(64), 0, st, a);
+    else if (m == 2) hipLaunchKernelGGL((k_stats16<DIM, 2>), g, dim3(64), 0, st, a);
+    else hipLaunchKernelGGL((k_stats32<DIM>), g, dim3(64), 0, st, a);
+    if (m == 2) hipLaunchKernelGGL(k_check_tiles<DIM>, g, dim3(64), 0, st, a);
+}
+
+hipError_t launch_stats(const SearchArgs& a, int nblk_max, hipStream_t st)
+{
+    if (a.L.ntot == 0) return hipSuccess;
+    if (nblk_max > 0) {
+        if (a.L.dim == 2) launch_block_stats<2>(a, block_grid(nblk_max), st);
+        else launch_block_stats<3>(a, block_grid(nblk_max), st);
+    }
+    const hipError_t e = launch_dense(a, DensePass::kStats, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_reduce_stats, dim3(1), dim3(1024), 0, st, a.blk_stats, a.nblk,
+                       static_cast<const unsigned long long*>(a.dstats), a.dstats ? a.dgrid : 0, a.stats);
     return hipGetLastError();
 }
 

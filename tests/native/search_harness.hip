@@ -1,6 +1,6 @@
-// Launches the fill kernels on arrays that a test makes, so that their behaviour on bits,
-// counts and row pointers that do not match each other can be tested: the library's own
-// count never leaves such arrays. One set, one grid cell, one work block or dense cell.
+// Launches the fill and statistics kernels on arrays that a test makes, so that their behaviour
+// on bits, counts, row pointers and coordinates that do not match each other can be tested: the
+// library's own passes never leave such arrays. One set, one grid cell of width 1.
 #include <cstdint>
 
 #include "build_kernels.h"
@@ -33,12 +33,14 @@ struct HarnessArgs {
     int32_t *ulist, *unit_off, *ucell, *dn;
     int64_t* dboff;
     uint16_t* dbits;
+    uint64_t *blk_stats, *dstats, *stats;
+    double radius;
+    int32_t t_lo, t_hi, t_mid, nblk_max;  // FP16 thresholds as bits
 };
 
 int harness_set_bytes() { return static_cast<int>(sizeof(nnps::SetDesc)); }
 
-// dense 0: the block fill; 1: the dense fills. Waits for the device; returns a hipError_t.
-int harness_fill(const HarnessArgs* h, int dense)
+static hipError_t search_args(const HarnessArgs* h, int dense, nnps::SearchArgs& a)
 {
     using namespace nnps;
     SetDesc sd{};
@@ -54,21 +56,21 @@ int harness_fill(const HarnessArgs* h, int dense)
     }
     fr.w = 1.0;
     fr.s = 0x1p40;
-    fr.R2 = 4.0;
+    fr.R2 = h->radius * h->radius;
     fr.xwin = 1;
     fr.inv_quantum = 0x1p30;
     fr.quantum = 0x1p-30f;
     fr.near2 = 3.0f * 0x1p46f;
-    fr.t_lo = fr.t_hi = fr.t_mid = 0x7BFF;
-    fr.t32_lo = fr.t32_hi = fr.t32_mid = 16.0f;
+    fr.t_lo = static_cast<uint16_t>(h->t_lo);
+    fr.t_hi = static_cast<uint16_t>(h->t_hi);
+    fr.t_mid = static_cast<uint16_t>(h->t_mid);
+    fr.t32_mid = static_cast<float>(4.0 * fr.R2);
     sd.pos = h->pos;
     sd.row_ptr = h->row_ptr;
     sd.col = h->col;
     sd.dist = h->dist;
     sd.capacity = h->capacity;
-    hipError_t e = hipMemcpy(h->set_room, &sd, sizeof(sd), hipMemcpyHostToDevice);
-    if (e != hipSuccess) return e;
-    SearchArgs a{};
+    a = SearchArgs{};
     a.L.dim = h->dim;
     a.L.mode = h->mode;
     a.L.nsets = 1;
@@ -107,8 +109,30 @@ int harness_fill(const HarnessArgs* h, int dense)
         a.dboff = h->dboff;
         a.dbits = h->dbits;
         a.dbits_cap = h->dbits_cap;
+        a.dstats = reinterpret_cast<unsigned long long*>(h->dstats);
     }
-    e = dense ? launch_dense(a, DensePass::kFill, nullptr) : launch_fill(a, 1, nullptr);
+    a.blk_stats = reinterpret_cast<unsigned long long*>(h->blk_stats);
+    a.stats = reinterpret_cast<unsigned long long*>(h->stats);
+    return hipMemcpy(h->set_room, &sd, sizeof(sd), hipMemcpyHostToDevice);
+}
+
+// dense 0: the block fill; 1: the dense fills. Waits for the device; returns a hipError_t.
+int harness_fill(const HarnessArgs* h, int dense)
+{
+    using namespace nnps;
+    SearchArgs a;
+    hipError_t e = search_args(h, dense, a);
+    if (e == hipSuccess) e = dense ? launch_dense(a, DensePass::kFill, nullptr) : launch_fill(a, h->nblk_max, nullptr);
+    return e != hipSuccess ? e : hipDeviceSynchronize();
+}
+
+// The statistics of blocks (and dense cells). Waits for the device.
+int harness_stats(const HarnessArgs* h, int dense)
+{
+    using namespace nnps;
+    SearchArgs a;
+    hipError_t e = search_args(h, dense, a);
+    if (e == hipSuccess) e = launch_stats(a, h->nblk_max, nullptr);
     return e != hipSuccess ? e : hipDeviceSynchronize();
 }
 

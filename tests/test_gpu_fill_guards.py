@@ -44,7 +44,8 @@ class Rows:
                  cell_offs=np.array([0, 1], np.int32), skey=np.zeros(n, np.uint32), perm=np.arange(n, dtype=np.int32),
                  cell_start=np.array([0, n], np.int32), spos=rec, rq=np.zeros((n, 4), np.float32),
                  flags=np.zeros(8, np.int32))
-        self.args = native.Args(dim=self.dim, mode=mode, n=n, half=0, capacity=self.total)
+        self.args = native.Args(dim=self.dim, mode=mode, n=n, half=0, capacity=self.total, radius=2.0, nblk_max=1,
+                                t_lo=0x7BFF, t_hi=0x7BFF, t_mid=0x7BFF)
 
     def fill(self, dense):
         for k, t in self.dev.items():
