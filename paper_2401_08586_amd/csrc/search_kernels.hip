@@ -2881,9 +2881,10 @@ template <int D>
 void launch_dense_fill(const SearchArgs& a, hipStream_t st)
 {
     const dim3 g(a.dgrid), b(kDenseThreads), bb(kDenseFillThreads);
-    if (a.L.mode == 0) {
+    if (a.L.mode == 0 || a.L.mode == 2) {
         if (a.dbits) hipLaunchKernelGGL((k_dense_fill<D, false>), g, bb, 0, st, a);
-        hipLaunchKernelGGL((k_dense<D, 0, true>), g, b, 0, st, a);
+        if (a.L.mode == 0) hipLaunchKernelGGL((k_dense<D, 0, true>), g, b, 0, st, a);
+        else hipLaunchKernelGGL((k_dense<D, 2, true>), g, b, 0, st, a);
     } else {
         if (a.dbits) hipLaunchKernelGGL((k_dense_fill<D, true>), g, bb, 0, st, a);
         hipLaunchKernelGGL((k_dense<D, 1, true>), g, b, 0, st, a);

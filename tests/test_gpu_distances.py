@@ -46,3 +46,29 @@ def test_distances_are_unbiased(name, dense):
     finally:
         ctx.set_tuning()
         ctx.close()
+
+
+@pytest.mark.parametrize("mode", [nnps.MODE_FP16_RCLL, nnps.MODE_RECHECK_ALL])
+@pytest.mark.parametrize("name", SETS)
+def test_distances_are_the_same_on_every_path(name, mode):
+    """Bit for bit in blocks, in dense cells tested by the fill, in dense cells from the count's bits
+    and (unions past the block limit) in long rows; recheck-all's are the FP16 mode's."""
+    ps = SETS[name]()
+    far = W.ParticleSet(ps.pos, ps.lo, ps.hi, 4 * ps.cell_size, ps.radius)  # wide cells: large unions
+    pos = torch.from_numpy(ps.pos).cuda()
+    ctx = nnps.Context(0)
+    try:
+        for p in (ps, far):
+            first = None
+            for m, dense in ((nnps.MODE_FP16_RCLL, -1), (mode, -1), (mode, 1)):
+                print(f"[gpu] paths {name} cell={p.cell_size} mode={m} dense={dense}", flush=True)
+                ctx.set_tuning(dense_min_union=dense)
+                cells = ctx.cells()
+                for _ in range(2):
+                    dist = nnps.search(pos, p.lo, p.hi, p.cell_size, p.radius, mode=m, ctx=ctx, cells=cells)[2]
+                    first = dist if first is None else first
+                    assert torch.equal(dist.view(torch.int32), first.view(torch.int32))
+                cells.close()
+    finally:
+        ctx.set_tuning()
+        ctx.close()
