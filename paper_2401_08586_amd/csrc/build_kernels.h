@@ -125,19 +125,21 @@ hipError_t launch_dense_cells(const Launch& L, const int* cell_start, const Dens
 bool dense_unions_sorted(int64_t nmax);
 hipError_t launch_dense_unions(const Launch& L, int64_t nmax, const int* cell_start, const uint32_t* skey, const int* perm,
                                const int* inv, const DenseBuild& d, hipStream_t st, int** ulist);
-// Row pointers of every set from the counts; also each particle's row start by sorted
-// position (rsort[inv[i]]).
-// What a caller that waits for the count wants on the host, written there by the row pointer
-// kernel: the structure's flags, then each set's nnz, and `pairs` (if given) in the last word.
-struct HostReport {
+// What the row pointer kernel does beside them: what a caller that waits for the count wants on
+// the host, written there (the structure's flags, then each set's nnz, and `pairs`, if given, in
+// the last word), and the count's own counters cleared.
+struct RowptrExtras {
     int64_t* host = nullptr;  // kHostWords words that the host reads after the stream; null: none
     const int* flags = nullptr;
     const int64_t* pairs = nullptr;
+    int* rpool = nullptr;     // the rank pools' counters, to leave zero for the next count; or null
 };
 constexpr int kHostWords = 64;
 constexpr int kHostSets = kHostWords - 1 - kFlags / 2;  // sets that fit
+// Row pointers of every set from the counts; also each particle's row start by sorted
+// position (rsort[inv[i]]).
 hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* partial, int64_t* nnz, const int* inv,
-                         int64_t* rsort, const HostReport& rep, hipStream_t st);
+                         int64_t* rsort, const RowptrExtras& rep, hipStream_t st);
 
 // Search passes over every block of every set. `nblk_max` bounds the number of blocks
 // (the exact count is on the device).
@@ -155,8 +157,10 @@ struct SearchArgs {
     int* counts_s;            // the same by sorted position (the fill reads them in block order)
     int64_t* rsort;           // each particle's row start in its set's output, by sorted position
     int* bdesc;               // [nblk_max][24] per-block descriptors the count pass leaves for the fill
-    uint16_t* branks;         // [nblk_max][union limit] ranks of each block's union by original index
-                              // (the order of its candidate bits)
+    uint16_t* branks;         // ranks of each block's union by original index (the order of its
+                              // candidate bits), a place per block or, with rpool, taken from pools
+    int* rpool;               // [kRankPools] entries taken of each pool, zero between counts; or null
+    int rpool_cap;            // entries of a pool (a multiple of kRankPiece)
     int* heavy;               // sorted positions of long rows
     int* flags;               // the structure's flags and counters (kFlag*)
     unsigned long long* stats;      // [kStCount] totals

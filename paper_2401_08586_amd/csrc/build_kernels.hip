@@ -762,12 +762,13 @@ template <int OFF>
 __global__ void __launch_bounds__(kScanThreads)
 k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int nsets, const int* __restrict__ counts,
          int64_t m, const int64_t* __restrict__ partial, int64_t* __restrict__ nnz, const int* __restrict__ inv,
-         int64_t* __restrict__ rsort, HostReport rep)
+         int64_t* __restrict__ rsort, RowptrExtras rep)
 {
     if (rep.host && blockIdx.x == 0) {
         if (threadIdx.x < kFlags) reinterpret_cast<int*>(rep.host)[threadIdx.x] = rep.flags[threadIdx.x];
         if (threadIdx.x == kFlags) rep.host[kHostWords - 1] = rep.pairs ? *rep.pairs : 0;
     }
+    if (rep.rpool && blockIdx.x == 0 && threadIdx.x < kRankPools) rep.rpool[threadIdx.x * kRankPoolStride] = 0;
     auto total = [&](int s, int64_t v) {
         nnz[s] = v;
         if (rep.host) rep.host[kFlags / 2 + s] = v;
@@ -1313,7 +1314,7 @@ hipError_t launch_dense_unions(const Launch& L, int64_t nmax, const int* cell_st
 }
 
 hipError_t launch_rowptr(const Launch& L, const int* counts, int64_t* partial, int64_t* nnz, const int* inv,
-                         int64_t* rsort, const HostReport& rep, hipStream_t st)
+                         int64_t* rsort, const RowptrExtras& rep, hipStream_t st)
 {
     const int64_t m = L.ntot, nt = std::max<int64_t>(1, (m + kScanTile - 1) / kScanTile);
     const dim3 g(nt), b(kScanThreads);

@@ -291,7 +291,8 @@ struct nnps_cells {
     uint64_t buf_gen = 0;                 // bumps whenever a device buffer moves
     uint32_t* skey = nullptr;
     int* perm = nullptr;
-    DevBuf counts_s, rsort, bdesc, branks;
+    DevBuf counts_s, rsort, bdesc, branks, rpool;
+    int rpool_cap = 0;                    // entries of a rank pool; 0: a place per block
     DevBuf d_sets, d_offs, k0, k1, v0, v1, cell_count, cell_start, spos, rq, boff, bstart, bset,
         counts, table, partial, stats, blk_stats, cbits, report, heavy, sink;
     // dense-cell path (see DenseBuild)
@@ -413,6 +414,8 @@ SearchArgs args_of(const nnps_cells* c)
     a.rsort = c->rsort.as<int64_t>();
     a.bdesc = c->bdesc.as<int>();
     a.branks = c->branks.as<uint16_t>();
+    a.rpool = c->rpool_cap > 0 ? c->rpool.as<int>() : nullptr;
+    a.rpool_cap = c->rpool_cap;
     a.heavy = c->heavy.as<int>();
     a.flags = c->report.as<int>();
     a.stats = c->stats.as<unsigned long long>();
@@ -571,6 +574,15 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
                                               static_cast<int64_t>(table_n),
                                               static_cast<int64_t>(c->nrows_tot) + 1});
     const int cw = c->dim == 3 ? kCandWords3 : kCandWords2;
+    // the union ranks: a place per block, or pools (see kRankRoom)
+    const int64_t ucap = c->dim == 3 ? kUnion3 : kUnion2;
+    int64_t ranks = std::max(c->nblk_max, 1) * ucap;
+    c->rpool_cap = 0;
+    if (ranks > std::max(kRankRoom * static_cast<int64_t>(nn), kRankSmall)) {
+        const int64_t each = (kRankPool * static_cast<int64_t>(nn) / kRankPools + ucap) / kRankPiece * kRankPiece;
+        c->rpool_cap = static_cast<int>(each);
+        ranks = each * kRankPools;
+    }
     struct Need {
         DevBuf* b;
         size_t bytes;
@@ -584,7 +596,8 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         {&c->boff, (static_cast<size_t>(c->nrows_tot) + 1) * 4}, {&c->bstart, (nn + 2) * 4}, {&c->bset, (nn + 1) * 4},
         {&c->counts, nn * 4}, {&c->counts_s, nn * 4}, {&c->rsort, nn * 8},
         {&c->bdesc, static_cast<size_t>(std::max(c->nblk_max, 1) + kXcdPad) * kBlockDescInts * 4},
-        {&c->branks, static_cast<size_t>(std::max(c->nblk_max, 1)) * (c->dim == 3 ? kUnion3 : kUnion2) * 2},
+        {&c->branks, static_cast<size_t>(ranks) * 2},
+        {&c->rpool, c->rpool_cap > 0 ? kRankPools * kRankPoolStride * sizeof(int) : 0},
         {&c->table, table_n * 4},
         {&c->partial, static_cast<size_t>(scan_partials_needed(scan_m) + 1) * 8},
         {&c->stats, kStCount * 8},
@@ -613,7 +626,8 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         if (e != hipSuccess) return e == hipErrorOutOfMemory ? NNPS_ENOMEM : NNPS_EDEVICE;
         if (q.b->p != before) ++c->buf_gen;
         // (new memory may have the old address)
-        if (q.b->cap != cap && (q.b == &c->cell_count || q.b == &c->uleave || q.b == &c->report)) c->counters_clear = false;
+        if (q.b->cap != cap && (q.b == &c->cell_count || q.b == &c->uleave || q.b == &c->report || q.b == &c->rpool))
+            c->counters_clear = false;
     }
     c->built = false;
     c->counted = false;
@@ -640,7 +654,7 @@ Update update_of(nnps_cells* c)
 nnps_status clear_counters(nnps_cells* c, hipStream_t s)
 {
     if (c->counters_clear) return NNPS_OK;
-    for (const DevBuf* b : {&c->cell_count, &c->uleave})
+    for (const DevBuf* b : {&c->cell_count, &c->uleave, &c->rpool})
         HIP_TRY(launch_fill_i32(b->as<int>(), static_cast<int64_t>(b->cap / 4), 0, s));
     HIP_TRY(launch_fill_i32(c->report.as<int>(), kFlags, 0, s));
     c->counters_clear = true;
@@ -768,9 +782,10 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s, int64_t* host = nullptr)
     }
     // the per-block statistics stay in place until the next count; nnps_stats_get sums
     // them when asked, so a step does not pay for the reduction
-    HostReport rep;
+    RowptrExtras rep;
     rep.host = host;
     rep.flags = c->report.as<int>();
+    rep.rpool = c->rpool_cap > 0 ? c->rpool.as<int>() : nullptr;
     rep.pairs = c->dense_active && dense_bits_on(c) ? c->dboff.as<int64_t>() + c->ncell_tot : nullptr;
     c->timer.begin(NNPS_PHASE_ROWSCAN, s);
     HIP_TRY(launch_rowptr(a.L, c->counts.as<int>(), c->partial.as<int64_t>(), nnz_of(c), c->inv.as<int>(),
@@ -1002,7 +1017,8 @@ void nnps_cells_destroy(nnps_cells* c)
                      &c->sink, &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
                      &c->ucell, &c->dn, &c->ecnt, &c->epos, &c->uk0, &c->uk1, &c->uv0, &c->uv1, &c->inv,
                      &c->dstats, &c->uleave, &c->ucs_old,
-                     &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc, &c->branks, &c->dbn, &c->dboff, &c->dbits};
+                     &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc, &c->branks, &c->rpool, &c->dbn, &c->dboff,
+                     &c->dbits};
     for (DevBuf* b : all) b->release();
     c->timer.release();
     c->graph.reset();

@@ -54,6 +54,19 @@ constexpr int kDenseStats = 6;  // candidates, band, false pos, false neg, outsi
 // spare descriptors of the last round over the XCDs.
 constexpr int kBlockDescInts = 24;
 constexpr int kXcdPad = 8;
+// Where the count pass leaves the ranks of the blocks' unions, in pieces of kRankPiece entries. A
+// place for a full union per block while that is at most kRankRoom entries a particle (a million
+// lattice points in 3D: 34) or kRankSmall in all; else, where many blocks are expected to be small
+// (a grid of few particles: up to a block, so 2 KB, per particle), kRankPool entries a particle and
+// a full union more in each of kRankPools pools from which the blocks take what they need (a
+// particle is in the unions of the blocks of 27 cells, 14 of them in a lattice). A block that finds
+// its pool empty sends its rows to the long-row path.
+constexpr int kRankPiece = 16;
+constexpr int64_t kRankRoom = 64;
+constexpr int64_t kRankSmall = int64_t(1) << 24;
+constexpr int64_t kRankPool = 48;
+constexpr int kRankPools = 256;
+constexpr int kRankPoolStride = 16;  // ints between two pools' counters: a cache line each
 
 // Device error flags.
 constexpr int kErrDomain = 1;

@@ -231,25 +231,42 @@ struct Geom {
 // Per-block descriptor the count pass leaves for the fill, so the fill's set-up reads the
 // block's geometry with one load instead of re-deriving it through the block table, the
 // sorted cell keys and the cell starts: [0] first particle, [1] end, [2] set, [3] union
-// size, [4] 1 for a block of the dense-cell path, then the NSEG segment first-particle
-// indices and the NSEG segment union offsets.
+// size (above the union limit for a block without ranks), [4] 1 for a block of the dense-cell
+// path, then the NSEG segment first-particle indices and the NSEG segment union offsets, and
+// last the place of its ranks in pieces of kRankPiece.
 constexpr int kDescInts = kBlockDescInts;
+constexpr int kDescRanks = kDescInts - 1;
+static_assert(5 + 2 * 9 <= kDescRanks, "the segments of 3D fit");
 
 template <int DIM, typename G>
-__device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int b)
+__device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int b, int U, uint32_t ranks)
 {
     const int lane = threadIdx.x & 63;
     int v = 0;
     if (lane == 0) v = g.p0;
     if (lane == 1) v = g.p1;
     if (lane == 2) v = a.bset[b];
-    if (lane == 3) v = g.U;
+    if (lane == 3) v = U;
+    if (lane == kDescRanks) v = static_cast<int>(ranks);
 #pragma unroll
     for (int r = 0; r < Geom<DIM>::NSEG; ++r) {
         if (lane == 5 + r) v = g.seg_g0[r];
         if (lane == 5 + Geom<DIM>::NSEG + r) v = g.seg_base[r];
     }
     if (lane < kDescInts) a.bdesc[static_cast<size_t>(b) * kDescInts + lane] = v;
+}
+
+// The place of block b's ranks (U of them), in pieces; kNoRanks where its pool has no room.
+constexpr uint32_t kNoRanks = ~0u;
+template <int UCAP>
+__device__ __forceinline__ uint32_t take_ranks(const SearchArgs& a, int b, int U)
+{
+    static_assert(UCAP % kRankPiece == 0, "whole pieces");
+    if (!a.rpool) return static_cast<uint32_t>(b) * (UCAP / kRankPiece);
+    const int pool = b % kRankPools, need = (U + kRankPiece - 1) / kRankPiece * kRankPiece;
+    const int at = atomicAdd(a.rpool + pool * kRankPoolStride, need);
+    if (at + need > a.rpool_cap) return kNoRanks;
+    return static_cast<uint32_t>((static_cast<int64_t>(pool) * a.rpool_cap + at) / kRankPiece);
 }
 
 // A dense-cell block: only its flag is written.
@@ -1454,6 +1471,7 @@ k_count(SearchArgs a)
     __shared__ int sred[2][NW];
     __shared__ int swsum[NW];
     __shared__ int spart[NW][64];
+    __shared__ uint32_t splace;
     if (a.wdense && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense count behind this
     const int b = xcd_block(*a.nblk);
     if (b < 0) return;
@@ -1464,13 +1482,23 @@ k_count(SearchArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     BlockGeom<DIM> g;
     g.init(a, b);
-    if (wv == 0) write_desc<DIM>(a, g, b);
     const int U = g.U, nt = g.p1 - g.p0;
-    Rec* const srec = reinterpret_cast<Rec*>(scratch);
-    const Rec trec = T::fetch(a, g.p0 + min(lane, nt - 1));
     // blocks with a larger union keep no bits (their rows take the long-row path): counted
     // in union order, unranked
-    const bool ranked = U <= UCAP;
+    uint32_t place = kNoRanks;
+    if (U <= UCAP) {
+        if (a.rpool) {
+            if (tid == 0) splace = take_ranks<UCAP>(a, b, U);
+            __syncthreads();
+            place = __builtin_amdgcn_readfirstlane(splace);
+        } else {
+            place = take_ranks<UCAP>(a, b, U);
+        }
+    }
+    const bool ranked = place != kNoRanks;
+    if (wv == 0) write_desc<DIM>(a, g, b, ranked ? U : max(U, UCAP + 1), place);
+    Rec* const srec = reinterpret_cast<Rec*>(scratch);
+    const Rec trec = T::fetch(a, g.p0 + min(lane, nt - 1));
     int rself = g.seg_base[g.SELF] + (g.p0 + lane - g.seg_g0[g.SELF]);
     if (ranked) {
         // the union's indices and records, in union order (contiguous along x)
@@ -1485,7 +1513,7 @@ k_count(SearchArgs a)
         rank_originals<UCAP, FillCfg<DIM>::SHIFT, NW>(U, og, scratch, sred, swsum, reinterpret_cast<uint16_t*>(slist),
                                                       rk);
         const int self0 = g.seg_base[g.SELF] + (g.p0 - g.seg_g0[g.SELF]);  // the first target's union position
-        uint16_t* ranks = a.branks + static_cast<size_t>(b) * UCAP;
+        uint16_t* ranks = a.branks + static_cast<size_t>(place) * kRankPiece;
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
             const int e = tid + i * kCountThreads<DIM>;
@@ -1633,7 +1661,8 @@ k_fill(SearchArgs a)
     int rank[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i)
-        rank[i] = a.branks[static_cast<size_t>(b) * C::UCAP + min(tid + i * kFillThreads, U - 1)];
+        rank[i] = a.branks[static_cast<size_t>(static_cast<uint32_t>(dsc[kDescRanks])) * kRankPiece +
+                           min(tid + i * kFillThreads, U - 1)];
     uint32_t wbits[KW];
 #pragma unroll
     for (int k = 0; k < KW; ++k) wbits[k] = a.cbits[static_cast<size_t>(min(wa + k, nw - 1)) * a.L.ntot + pt];

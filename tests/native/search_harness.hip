@@ -1,4 +1,4 @@
-// Launches the fill and statistics kernels on arrays that a test makes, so that their behaviour
+// Launches the count, fill and statistics kernels on arrays that a test makes, so that their behaviour
 // on bits, counts, row pointers and coordinates that do not match each other can be tested: the
 // library's own passes never leave such arrays. One set, one grid cell of width 1.
 #include <cstdint>
@@ -34,8 +34,10 @@ struct HarnessArgs {
     int64_t* dboff;
     uint16_t* dbits;
     uint64_t *blk_stats, *dstats, *stats;
+    int32_t* rpool;
     double radius;
     int32_t t_lo, t_hi, t_mid, nblk_max;  // FP16 thresholds as bits
+    int32_t rpool_cap;
 };
 
 int harness_set_bytes() { return static_cast<int>(sizeof(nnps::SetDesc)); }
@@ -113,6 +115,8 @@ static hipError_t search_args(const HarnessArgs* h, int dense, nnps::SearchArgs&
     }
     a.blk_stats = reinterpret_cast<unsigned long long*>(h->blk_stats);
     a.stats = reinterpret_cast<unsigned long long*>(h->stats);
+    a.rpool = h->rpool;
+    a.rpool_cap = h->rpool_cap;
     return hipMemcpy(h->set_room, &sd, sizeof(sd), hipMemcpyHostToDevice);
 }
 
@@ -123,6 +127,16 @@ int harness_fill(const HarnessArgs* h, int dense)
     SearchArgs a;
     hipError_t e = search_args(h, dense, a);
     if (e == hipSuccess) e = dense ? launch_dense(a, DensePass::kFill, nullptr) : launch_fill(a, h->nblk_max, nullptr);
+    return e != hipSuccess ? e : hipDeviceSynchronize();
+}
+
+// The block count. Waits for the device.
+int harness_count(const HarnessArgs* h)
+{
+    using namespace nnps;
+    SearchArgs a;
+    hipError_t e = search_args(h, 0, a);
+    if (e == hipSuccess) e = launch_count(a, h->nblk_max, nullptr);
     return e != hipSuccess ? e : hipDeviceSynchronize();
 }
 
