@@ -1157,15 +1157,15 @@ __device__ __forceinline__ void quarter_transpose(uint32_t (&v)[4])
     swap16(v[2], v[3]);
 }
 
-// The lowest n bits of a word: a row word's candidates, where the union ends inside or before it.
+// The lowest n bits of a word.
 __device__ __forceinline__ uint32_t first_bits(int n)
 {
     return n >= 32 ? ~0u : (n <= 0 ? 0u : (1u << n) - 1u);
 }
 
 // The MFMA operands of 64 items, one prepared per lane, and 64 x 64 tests. prepare: the
-// fragments of 64 candidates (lane l prepares candidate item(l); `past`: none, put far away so
-// that its results need no recheck; the callers mask them off, whatever they are);
+// fragments of 64 candidates (lane l prepares candidate item(l); `past`: none, so far away that
+// every result is out, or, where the bound sends all results to decide, decided there as out);
 // words: the two row words (candidates 0-31 and 32-63 of the step) of target `lane`, with
 // `decide(bnd, acc, e, t)` settling the results bnd (bits) of a lane whose 16 results are the
 // step's candidates e.. against target t.
@@ -1406,6 +1406,7 @@ struct Tiles<DIM, 64> {
     __device__ __forceinline__ Frag prepare(const Rec& rec, const BlockGeom<DIM>&, bool past) const
     {
         const double x = past ? 0.0 : rec.x - ox, y = past ? 0.0 : rec.y - oy, z = past ? 0.0 : rec.z - oz;
+        // past: |t|^2 - R^2 stays below 2^917 in the range where signs decide (see targets_about)
         const double v[4] = {x, y, z, past ? 0x1p1000 : x * x + y * y + z * z};
         Frag f;
         fragments(v, f.c);
@@ -1561,7 +1562,7 @@ k_count(SearchArgs a)
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int tile = 2 * s + k;
-                uint32_t word = ww[k] & first_bits(m - 32 * tile);
+                uint32_t word = ww[k];
                 // the target itself is no neighbour; half lists keep larger original indices
                 const int d = rself - c0 - 32 * tile;
                 if (HALF && ranked) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
@@ -2215,7 +2216,7 @@ k_dense_count(SearchArgs a)
                     for (int h = 0; h < 2; ++h) {
                         // the target itself is no neighbour; half lists keep larger original indices
                         const int d = self - 64 * s - 32 * h;
-                        uint32_t word = ww[h] & first_bits(nc - 64 * s - 32 * h);
+                        uint32_t word = ww[h];
                         if (HALF) word &= d < 0 ? ~0u : (d >= 31 ? 0u : 0xFFFFFFFEu << d);
                         else word &= (d >= 0 && d < 32) ? ~(1u << d) : ~0u;
                         cnt += __builtin_popcount(word);
@@ -2302,6 +2303,9 @@ k_dense_fill(SearchArgs a)
         }
         for (int c0 = 0; c0 < U; c0 += K) {
             const int nc = min(K, U - c0), nsub = (nc + kDenseChunk - 1) / kDenseChunk;
+            uint32_t inside[NSUB];  // this lane's candidates of each 1024 that the list has
+#pragma unroll
+            for (int q = 0; q < NSUB; ++q) inside[q] = first_bits(nc - q * kDenseChunk - 16 * lane);
             __syncthreads();
             for (int e = tid; e < nc; e += kDenseFillThreads) {
                 const double2* r = reinterpret_cast<const double2*>(a.spos + static_cast<size_t>(list[c0 + e]) * 4);
@@ -2348,7 +2352,7 @@ k_dense_fill(SearchArgs a)
                     for (int q = 0; q < NSUB; ++q) {
                         if (q >= nsub) break;
                         const int lb = q * kDenseChunk + 16 * lane;  // the lane's first candidate
-                        const uint32_t M = wb[t * NSUB + q] & first_bits(nc - lb);  // none past the list
+                        const uint32_t M = wb[t * NSUB + q] & inside[q];
                         int tot;
                         const int base = wave_excl_scan_i32(__builtin_popcount(M), &tot);
                         // accepted candidates queued per lane, as many as the queue holds at a
@@ -2361,23 +2365,23 @@ k_dense_fill(SearchArgs a)
                             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                             const int n = min(QCAP, tot - w0);
                             for (int i = lane; i < n; i += 64) {
-                                const int e = queue[i], slot = done + w0 + i;
+                                const int e = queue[i], slot = done + w0 + i;  // a staged candidate (see inside)
+                                float dv;
+                                int oj;
+                                if constexpr (F64) {
+                                    oj = sorig[e];
+                                    dv = dist_fp64<DIM>(pi, sdbl + e * DIM);
+                                } else {
+                                    const int4 r = srec[e];
+                                    oj = r.w;
+                                    const float s2 = quanta2<DIM>(ti, r);
+                                    dv = root(s2) * quantum;
+                                    if (!(s2 >= near2))
+                                        dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
+                                                            (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
+                                                            inv_quantum, quantum);
+                                }
                                 if (slot < rl && room) {
-                                    float dv;
-                                    int oj;
-                                    if constexpr (F64) {
-                                        oj = sorig[e];
-                                        dv = dist_fp64<DIM>(pi, sdbl + e * DIM);
-                                    } else {
-                                        const int4 r = srec[e];
-                                        oj = r.w;
-                                        const float s2 = quanta2<DIM>(ti, r);
-                                        dv = root(s2) * quantum;
-                                        if (!(s2 >= near2))
-                                            dv = dist_near<DIM>(a.spos + static_cast<size_t>(u0 + wv + NW * k) * 4,
-                                                                (const double*)sd.pos + static_cast<size_t>(oj) * DIM,
-                                                                inv_quantum, quantum);
-                                    }
                                     if (rl <= (1 << 30)) {  // byte offsets within the row fit 32 bits
                                         const uint32_t off = static_cast<uint32_t>(slot) * 4u;
                                         *(NNPS_GLOBAL int32_t*)((NNPS_GLOBAL char*)rcol + off) = oj;
