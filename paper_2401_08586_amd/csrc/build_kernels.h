@@ -130,8 +130,9 @@ hipError_t launch_dense_unions(const Launch& L, int64_t nmax, const int* cell_st
 // the last word), and the count's own counters cleared.
 struct RowptrExtras {
     int64_t* host = nullptr;  // kHostWords words that the host reads after the stream; null: none
-    const int* flags = nullptr;
+    int* flags = nullptr;
     const int64_t* pairs = nullptr;
+    const int* nblk = nullptr;  // the number of blocks, to go with the flags
     int* rpool = nullptr;     // the rank pools' counters, to leave zero for the next count; or null
 };
 constexpr int kHostWords = 64;
@@ -168,6 +169,7 @@ struct SearchArgs {
     uint32_t* cbits;                // accepted-candidate bits, word-major [words][ntot]
     uint32_t* lrscratch;            // long-row path merge scratch, per workgroup
     int64_t lrscratch_words;        // its size per workgroup (32-bit words)
+    int sparse;                     // 1: the count by small blocks (3D, see kSparseUnion)
     int lr_keys;                    // keys a long-row workgroup sorts in LDS
     int* sink;                      // [2 * 64] per-lane dummy output slots
     int half;                       // 1: rows keep only neighbours of larger original index

@@ -667,7 +667,6 @@ __device__ __forceinline__ void update_place(const Launch& L, const PlaceArgs& a
 //
 // For up to kRowFold segments the second walk's workgroups sum the counts before theirs
 // themselves, and no scan is launched (8192 counts are 32 KB read by each of 2048 workgroups).
-constexpr int kRowSegment = 64;
 constexpr int kRowsPerGroup = 4;
 constexpr int kRowFold = 8192;
 
@@ -764,11 +763,6 @@ k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
          int64_t m, const int64_t* __restrict__ partial, int64_t* __restrict__ nnz, const int* __restrict__ inv,
          int64_t* __restrict__ rsort, RowptrExtras rep)
 {
-    if (rep.host && blockIdx.x == 0) {
-        if (threadIdx.x < kFlags) reinterpret_cast<int*>(rep.host)[threadIdx.x] = rep.flags[threadIdx.x];
-        if (threadIdx.x == kFlags) rep.host[kHostWords - 1] = rep.pairs ? *rep.pairs : 0;
-    }
-    if (rep.rpool && blockIdx.x == 0 && threadIdx.x < kRankPools) rep.rpool[threadIdx.x * kRankPoolStride] = 0;
     auto total = [&](int s, int64_t v) {
         nnz[s] = v;
         if (rep.host) rep.host[kFlags / 2 + s] = v;
@@ -829,13 +823,21 @@ k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
             put(sets[s], s, start <= tile0 ? (s == s0 ? offset : 0) : -local[b + (b >> 4)], e, start);
         }
     }
+    if (blockIdx.x) return;
     // sets without particles own no element of the scan
-    if (blockIdx.x == 0)
-        for (int s = threadIdx.x; s < nsets; s += kScanThreads)
-            if (sets[s].fr.n == 0) {
-                sets[s].row_ptr[0] = 0;
-                total(s, 0);
-            }
+    for (int s = threadIdx.x; s < nsets; s += kScanThreads)
+        if (sets[s].fr.n == 0) {
+            sets[s].row_ptr[0] = 0;
+            total(s, 0);
+        }
+    // what goes with the row pointers
+    const int t = threadIdx.x;
+    if (t == kFlagBlocks) rep.flags[t] = *rep.nblk;
+    if (rep.host) {
+        if (t < kFlags) reinterpret_cast<int*>(rep.host)[t] = t == kFlagBlocks ? *rep.nblk : rep.flags[t];
+        if (t == kFlags) rep.host[kHostWords - 1] = rep.pairs ? *rep.pairs : 0;
+    }
+    if (rep.rpool && t < kRankPools) rep.rpool[t * kRankPoolStride] = 0;
 }
 
 // ---------------------------------------------------------------------------

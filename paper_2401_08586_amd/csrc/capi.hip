@@ -157,13 +157,13 @@ nnps_status frame_of(const nnps_problem* p, Frame* fr, int block_target)
     // fill one wavefront and the candidate union stays small; and at most what keeps the
     // union of 3^(d-1) rows of xwin + 2 cells at 85 % of the fill's union limit on average
     const double occ = static_cast<double>(p->n) / static_cast<double>(ncell);
-    int xwin = occ > 0.0 ? static_cast<int>(block_target / occ) : kMaxXWin;
+    int xwin = occ > 0.0 ? static_cast<int>(std::min(block_target / occ, double(kRowSegment))) : kRowSegment;
     if (occ > 0.0) {
         const double rows = p->dim == 3 ? 9.0 : 3.0;
         const double ucap = p->dim == 3 ? kUnion3 : kUnion2;
-        xwin = std::min(xwin, static_cast<int>(0.85 * ucap / (rows * occ)) - 2);
+        xwin = static_cast<int>(std::min(double(xwin), 0.85 * ucap / (rows * occ) - 2.0));
     }
-    fr->xwin = std::max(1, std::min(p->mode == NNPS_MODE_FP16_RCLL || p->mode == NNPS_MODE_FP32_RCLL ? kMfmaXWin : kMaxXWin, xwin));
+    fr->xwin = std::max(1, xwin);
     // the fill's positions in quanta 2^-kq: neighbours (at most w apart) differ by fewer than
     // 2^31 of them, and the whole box by fewer than 2^51. A difference of two then errs by at
     // most one quantum per axis, 2^-23 of a distance of sqrt(3) 2^23 quanta (0.03 w at most
@@ -292,6 +292,8 @@ struct nnps_cells {
     uint32_t* skey = nullptr;
     int* perm = nullptr;
     DevBuf counts_s, rsort, bdesc, branks, rpool;
+    bool sparse = false;                  // counted by small blocks (see kSparseUnion)
+    int small_blocks = -1;                // at the last synchronising call: -1 unknown, 0, 1
     int rpool_cap = 0;                    // entries of a rank pool; 0: a place per block
     DevBuf d_sets, d_offs, k0, k1, v0, v1, cell_count, cell_start, spos, rq, boff, bstart, bset,
         counts, table, partial, stats, blk_stats, cbits, report, heavy, sink;
@@ -426,6 +428,7 @@ SearchArgs args_of(const nnps_cells* c)
     a.lr_keys = c->ctx->tuning.long_rows_keys > 0 ? std::min(c->ctx->tuning.long_rows_keys, keys) : keys;
     a.sink = c->sink.as<int>();
     a.half = c->half ? 1 : 0;
+    a.sparse = c->sparse ? 1 : 0;
     if (c->dense_active) {
         a.wdense = c->wdense.as<int>();
         a.usz = c->usz.as<int>();
@@ -542,9 +545,11 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         const Frame& fr = frames[s];
         const int64_t nrows = static_cast<int64_t>(fr.nc[1]) * fr.nc[2];
         const int64_t nseg = nrows * row_segments(fr.nc[0]);
-        // blocks: full ones, at most one per span of xwin cells and one per row segment
-        // ending early, and around each run of dense cells one marker plus one cut short
-        int64_t b = fr.n / kWave + nrows * ((fr.nc[0] + fr.xwin - 1) / fr.xwin) + nseg;
+        // blocks: full ones, in each row segment at most one per span of xwin cells (the
+        // others start that far apart), and around each run of dense cells one marker plus
+        // one cut short
+        const int full = fr.nc[0] / kRowSegment, rest = fr.nc[0] % kRowSegment;
+        int64_t b = fr.n / kWave + nrows * (full * ((kRowSegment + fr.xwin - 1) / fr.xwin) + (rest + fr.xwin - 1) / fr.xwin);
         if (c->dense && c->dense_seen != 0)  // the build will use the dense-cell path
             b += 2 * std::min<int64_t>(fr.ncell, stencil * fr.n / (static_cast<int64_t>(c->dthresh) + 1));
         nblk_bound += std::min<int64_t>(fr.n, b);
@@ -574,11 +579,16 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
                                               static_cast<int64_t>(table_n),
                                               static_cast<int64_t>(c->nrows_tot) + 1});
     const int cw = c->dim == 3 ? kCandWords3 : kCandWords2;
+    // counted by small blocks: where they hold most particles' expected unions
+    int64_t nsparse = 0;
+    for (const Frame& fr : frames)
+        if (9.0 * fr.n / fr.ncell * std::min(fr.nc[0], fr.xwin + 2) < kSparseUnion) nsparse += fr.n;
+    c->sparse = c->dim == 3 && 2 * nsparse > ntot && c->small_blocks != 0;
     // the union ranks: a place per block, or pools (see kRankRoom)
     const int64_t ucap = c->dim == 3 ? kUnion3 : kUnion2;
     int64_t ranks = std::max(c->nblk_max, 1) * ucap;
     c->rpool_cap = 0;
-    if (ranks > std::max(kRankRoom * static_cast<int64_t>(nn), kRankSmall)) {
+    if (c->sparse || ranks > std::max(kRankRoom * static_cast<int64_t>(nn), kRankSmall)) {
         const int64_t each = (kRankPool * static_cast<int64_t>(nn) / kRankPools + ucap) / kRankPiece * kRankPiece;
         c->rpool_cap = static_cast<int>(each);
         ranks = each * kRankPools;
@@ -785,6 +795,7 @@ nnps_status enqueue_count(nnps_cells* c, hipStream_t s, int64_t* host = nullptr)
     RowptrExtras rep;
     rep.host = host;
     rep.flags = c->report.as<int>();
+    rep.nblk = c->boff.as<int>() + c->nrows_tot;
     rep.rpool = c->rpool_cap > 0 ? c->rpool.as<int>() : nullptr;
     rep.pairs = c->dense_active && dense_bits_on(c) ? c->dboff.as<int64_t>() + c->ncell_tot : nullptr;
     c->timer.begin(NNPS_PHASE_ROWSCAN, s);
@@ -824,12 +835,20 @@ void set_outputs(nnps_cells* c, int64_t* const* row_ptr, int32_t* const* col, fl
     }
 }
 
+// What the flags on the host say for a structure's next build: whether it has dense cells, and
+// whether its blocks are small.
+void see_flags(nnps_cells* c, const int* flags)
+{
+    if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+    if (flags[kFlagBlocks] > 0) c->small_blocks = c->ntot < int64_t(kSparseTargets) * flags[kFlagBlocks] ? 1 : 0;
+}
+
 // What a report on the host says of a structure: its error, whether it has dense cells, and
 // the room its next build keeps for the dense count's bits.
 nnps_status take_report(nnps_cells* c, const int64_t* hp)
 {
     const int* flags = reinterpret_cast<const int*>(hp);
-    if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+    see_flags(c, flags);
     if (c->dense_active && dense_bits_on(c)) {
         const size_t want = static_cast<size_t>(hp[kHostWords - 1]) * 64 * sizeof(uint16_t);
         if (want <= dense_bits_bound(c)) c->dbits_want = std::max(c->dbits_want, want);
@@ -1305,7 +1324,7 @@ nnps_status nnps_batch_step(nnps_ctx* ctx, nnps_cells* c, int32_t nsets, const n
     q += sizeof(nnps_tuning);
     memcpy(q, &nsets, 4);
     q += 4;
-    const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0);
+    const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0) | (c->sparse ? 4 : 0);
     memcpy(q, &plan, 4);
     (void)gen0;
     if ((st = clear_counters(c, s)) != NNPS_OK) return st;  // outside the graph
@@ -1398,7 +1417,7 @@ nnps_status nnps_batch_update_step(nnps_ctx* ctx, nnps_cells* c, const double* c
     q += sizeof(nnps_tuning);
     memcpy(q, &c->nsets, 4);
     q += 4;
-    const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0);
+    const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0) | (c->sparse ? 4 : 0);
     memcpy(q, &plan, 4);
     if ((st = clear_counters(c, s)) != NNPS_OK) return st;  // outside the graph
     if (!c->ugraph.exec || c->ugraph.sig != sig) {
@@ -1474,7 +1493,7 @@ nnps_status nnps_batch_nnz_fetch(nnps_cells* c, int64_t* h_nnz)
     HIP_TRY(hipEventSynchronize(c->report_done));
     const int* flags = reinterpret_cast<const int*>(c->h_report);
     for (int i = 0; i < c->nsets; ++i) h_nnz[i] = c->h_report[kFlags / 2 + i];
-    if (c->dense) c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
+    see_flags(c, flags);
     return err_status(flags[kFlagErr]);
 }
 
@@ -1495,6 +1514,7 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
     HIP_TRY(hipStreamSynchronize(s));
     HIP_TRY(hipMemcpy(st, c->stats.p, sizeof(st), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(flags, c->report.p, sizeof(flags), hipMemcpyDeviceToHost));
+    see_flags(c, flags);
     out->n = c->ntot;
     if (c->counted) {
         std::vector<int64_t> nz(c->nsets);
@@ -1510,7 +1530,6 @@ nnps_status nnps_stats_get(nnps_cells* c, nnps_stats* out, void* stream)
     out->dense_rows = static_cast<int64_t>(st[kStDenseRows]);
     if (c->dense) {
         int dn = 0;
-        c->dense_seen = flags[kFlagSeen] != 0 ? 1 : 0;
         if (c->dense_active) HIP_TRY(hipMemcpy(&dn, c->dn.p, 4, hipMemcpyDeviceToHost));
         out->dense_entries = dn;
     }

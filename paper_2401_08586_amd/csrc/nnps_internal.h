@@ -19,11 +19,21 @@ constexpr int kUnion3 = 1024;
 // wavefront's stores coalesce. Blocks with a larger union take the long-row path.
 constexpr int kCandWords2 = kUnion2 / 32;
 constexpr int kCandWords3 = kUnion3 / 32;
-// Largest x-span (cells) of a work block; keeps staged cell offsets exact in FP16.
-constexpr int kMaxXWin = 256;
-// The same where the matrix cores test in FP16 or FP32: the recheck band there grows with the square of the
-// span (2^-18 of twice the squared half widths), to about 0.01 squared cell widths at 48.
-constexpr int kMfmaXWin = 48;
+// Rows of cells are walked in segments of this many cells, so that is also a work block's
+// largest x-span. (Where the matrix cores test in FP16 or FP32 the recheck band grows with the
+// square of the span, 2^-18 of twice the squared half widths, to 0.016 squared cell widths there.)
+constexpr int kRowSegment = 64;
+// 3D sets are counted by small blocks, a wavefront each for unions up to kSmallUnion (k_count_small),
+// where a block's union is expected to be below kSparseUnion candidates, unless the last
+// synchronising call found more than kSparseTargets targets in the average block: a clump in a large
+// box is sparse by the first measure only. Steps of a million uniform points in 3D (random numbering,
+// FP16 / FP64, us): 0.1 points a cell 1156 / 1486 against 1850 / 2578 with four wavefronts a block,
+// 0.25 (a union of 148, 16 targets) 640 / 787 and 905 / 1215, 0.5 (297, 32) 565 / 700 and 527 / 684,
+// 1.0 548 / 683 and 504 / 644. (Before the unions were ranked in the count: 2090 / 1945, 1080 / 1025,
+// 650 / 660, 589 / 625.)
+constexpr int kSmallUnion = 256;
+constexpr double kSparseUnion = 220.0;
+constexpr int kSparseTargets = 20;
 // Dense-cell path: candidates staged per chunk, targets per work unit (a workgroup of
 // four wavefronts, 64 targets each) and the default thresholds.
 constexpr int kDenseChunk = 1024;
@@ -56,13 +66,14 @@ constexpr int kBlockDescInts = 24;
 constexpr int kXcdPad = 8;
 // Where the count pass leaves the ranks of the blocks' unions, in pieces of kRankPiece entries. A
 // place for a full union per block while that is at most kRankRoom entries a particle (a million
-// lattice points in 3D: 34) or kRankSmall in all; else, where many blocks are expected to be small
+// lattice points in 3D: 34, and 142 while it isn't known whether there are dense cells) or
+// kRankSmall in all; else, and where many blocks are expected to be small
 // (a grid of few particles: up to a block, so 2 KB, per particle), kRankPool entries a particle and
 // a full union more in each of kRankPools pools from which the blocks take what they need (a
 // particle is in the unions of the blocks of 27 cells, 14 of them in a lattice). A block that finds
 // its pool empty sends its rows to the long-row path.
 constexpr int kRankPiece = 16;
-constexpr int64_t kRankRoom = 64;
+constexpr int64_t kRankRoom = 160;
 constexpr int64_t kRankSmall = int64_t(1) << 24;
 constexpr int64_t kRankPool = 48;
 constexpr int kRankPools = 256;
@@ -84,7 +95,7 @@ enum Flag {
     kFlagLongDone,   // workgroups of the long-row kernel that are through with the list
     kFlagUnit,       // next work unit of the running dense pass
     kFlagBad,        // the assignment's error flags (the cell starts' scan moves them on)
-    kFlagPad,
+    kFlagBlocks,     // work blocks of the last count
     kFlags           // an even number: 64-bit counts follow
 };
 static_assert(kFlags % 2 == 0, "64-bit counts follow the flags");

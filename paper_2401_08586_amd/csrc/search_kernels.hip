@@ -7,6 +7,7 @@
 // cells. Cells along x are contiguous in sorted order, so a block's candidates are 3^(d-1)
 // contiguous runs ("row segments"), one per (dy, dz): its union.
 #include <algorithm>
+#include <type_traits>
 
 #include "build_kernels.h"
 
@@ -232,14 +233,14 @@ struct Geom {
 // block's geometry with one load instead of re-deriving it through the block table, the
 // sorted cell keys and the cell starts: [0] first particle, [1] end, [2] set, [3] union
 // size (above the union limit for a block without ranks), [4] 1 for a block of the dense-cell
-// path, then the NSEG segment first-particle indices and the NSEG segment union offsets, and
+// path (2: not counted yet), then the NSEG segment first-particle indices and the NSEG segment union offsets, and
 // last the place of its ranks in pieces of kRankPiece.
 constexpr int kDescInts = kBlockDescInts;
 constexpr int kDescRanks = kDescInts - 1;
 static_assert(5 + 2 * 9 <= kDescRanks, "the segments of 3D fit");
 
 template <int DIM, typename G>
-__device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int b, int U, uint32_t ranks)
+__device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int b, int U, uint32_t ranks, int state = 0)
 {
     const int lane = threadIdx.x & 63;
     int v = 0;
@@ -247,6 +248,7 @@ __device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int 
     if (lane == 1) v = g.p1;
     if (lane == 2) v = a.bset[b];
     if (lane == 3) v = U;
+    if (lane == 4) v = state;
     if (lane == kDescRanks) v = static_cast<int>(ranks);
 #pragma unroll
     for (int r = 0; r < Geom<DIM>::NSEG; ++r) {
@@ -256,13 +258,18 @@ __device__ __forceinline__ void write_desc(const SearchArgs& a, const G& g, int 
     if (lane < kDescInts) a.bdesc[static_cast<size_t>(b) * kDescInts + lane] = v;
 }
 
-// The place of block b's ranks (U of them), in pieces; kNoRanks where its pool has no room.
+// The place of block b's ranks, in pieces: its own, or for U of them from the pools (kNoRanks
+// where its pool has no room).
 constexpr uint32_t kNoRanks = ~0u;
-template <int UCAP>
+template <int DIM>
+__device__ __forceinline__ uint32_t block_ranks(int b)
+{
+    constexpr int UCAP = DIM == 3 ? kUnion3 : kUnion2;
+    static_assert(UCAP % kRankPiece == 0, "whole pieces");
+    return static_cast<uint32_t>(b) * (UCAP / kRankPiece);
+}
 __device__ __forceinline__ uint32_t take_ranks(const SearchArgs& a, int b, int U)
 {
-    static_assert(UCAP % kRankPiece == 0, "whole pieces");
-    if (!a.rpool) return static_cast<uint32_t>(b) * (UCAP / kRankPiece);
     const int pool = b % kRankPools, need = (U + kRankPiece - 1) / kRankPiece * kRankPiece;
     const int at = atomicAdd(a.rpool + pool * kRankPoolStride, need);
     if (at + need > a.rpool_cap) return kNoRanks;
@@ -1012,6 +1019,61 @@ __device__ __forceinline__ void rank_originals(int U, const int (&og)[UCAP / (64
     __syncthreads();
 }
 
+// The same by one wavefront, for up to 256 candidates: og[i] is element lane + 64 i. Sorted in
+// registers with the position in the key where the index range allows (24 bits), else the indices
+// alone and looked up. scratch: 256 words.
+template <int EPL>
+__device__ __forceinline__ void rank_wave_of(int U, const int (&og)[4], int omin, bool packed, uint32_t* scratch,
+                                             uint16_t* rank_of, int (&rk)[4])
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t v[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+        const int e = lane + 64 * i;
+        const uint32_t key = packed ? (static_cast<uint32_t>(og[i] - omin) << 8) | static_cast<uint32_t>(e)
+                                    : static_cast<uint32_t>(og[i]);
+        v[i] = e < U ? key : 0xFFFFFFFFu;
+    }
+    wave_bitonic<EPL>(v);
+    if (packed) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+            if (v[i] != 0xFFFFFFFFu) rank_of[v[i] & 255u] = static_cast<uint16_t>(lane * EPL + i);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) rk[i] = lane + 64 * i < U ? rank_of[lane + 64 * i] : 0;
+    } else {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) scratch[lane * EPL + i] = v[i];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) rk[i] = count_below<64 * EPL>(scratch, static_cast<uint32_t>(og[i]));
+    }
+}
+
+template <int UC>
+__device__ __forceinline__ void rank_wave(int U, const int (&og)[UC / 64], uint32_t* scratch, uint16_t* rank_of,
+                                          int (&rk)[UC / 64])
+{
+    static_assert(UC == 256, "positions take 8 bits of a key");
+    const int lane = threadIdx.x & 63;
+    int omin = 0x7FFFFFFF, omax = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (lane + 64 * i < U) {
+            omin = min(omin, og[i]);
+            omax = max(omax, og[i]);
+        }
+    omin = wave_min_i32(omin);
+    omax = wave_max_i32(omax);
+    const bool packed = omax - omin < (1 << 24) - 1;
+    if (U <= 64) rank_wave_of<1>(U, og, omin, packed, scratch, rank_of, rk);
+    else if (U <= 128) rank_wave_of<2>(U, og, omin, packed, scratch, rank_of, rk);
+    else rank_wave_of<4>(U, og, omin, packed, scratch, rank_of, rk);
+    __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // Count pass, on the matrix cores. Four wavefronts per block: the block's union is ranked by
 // original index first, so the candidate bits come out in row order and the fill only has to
@@ -1454,90 +1516,91 @@ struct Tiles<DIM, 64> {
     }
 };
 
-template <int DIM, int P, bool HALF>
-__global__ void __launch_bounds__(kCountThreads<DIM>) __attribute__((amdgpu_waves_per_eu(P == 64 ? 4 : 5)))
-k_count(SearchArgs a)
+// LDS of a block's count by NW wavefronts, unions of up to UC candidates ranked.
+template <int DIM, int P, int NW, int UC>
+struct CountShared {
+    using Rec = typename Tiles<DIM, P>::Rec;
+    // the ranking's scratch, then the union's records by rank
+    static constexpr int kRecs = UC * static_cast<int>(sizeof(Rec));
+    static constexpr int kBytes = NW > 1 && kRankScratch<UC> > kRecs ? kRankScratch<UC> : kRecs;
+    alignas(16) unsigned char scratch[kBytes];
+    int slist[UC];  // sorted positions by rank (the ranking's ranks before)
+    int srself[64];  // the targets' own ranks
+    int sred[2][NW];
+    int swsum[NW];
+    int spart[NW][64];
+    uint32_t splace;
+};
+
+// Counts block b and writes its descriptor. Unions above UC are counted in union order, unranked;
+// they, and blocks whose pool is empty, keep no bits (their rows take the long-row path).
+// POOL: the ranks' places come from the pools.
+template <int DIM, int P, bool HALF, bool POOL, int NW, int UC>
+__device__ __forceinline__ void count_block(const SearchArgs& a, const BlockGeom<DIM>& g, int b,
+                                            CountShared<DIM, P, NW, UC>& sh)
 {
-    constexpr int UCAP = FillCfg<DIM>::UCAP;
-    constexpr int NW = kCountThreads<DIM> / 64;
-    constexpr int EPT = UCAP / kCountThreads<DIM>;
+    constexpr int NT = 64 * NW, EPT = UC / NT;
     using T = Tiles<DIM, P>;
     using Rec = typename T::Rec;
-    // the ranking's scratch, then the union's records by rank
-    constexpr int kShared = kRankScratch<UCAP> > UCAP * static_cast<int>(sizeof(Rec))
-                                ? kRankScratch<UCAP> : UCAP * static_cast<int>(sizeof(Rec));
-    __shared__ __attribute__((aligned(16))) unsigned char scratch[kShared];
-    __shared__ int slist[UCAP];  // sorted positions by rank (the ranking's ranks before)
-    __shared__ int srself[64];   // the targets' own ranks
-    __shared__ int sred[2][NW];
-    __shared__ int swsum[NW];
-    __shared__ int spart[NW][64];
-    __shared__ uint32_t splace;
-    if (a.wdense && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense count behind this
-    const int b = xcd_block(*a.nblk);
-    if (b < 0) return;
-    if (dense_block(a, b)) {
-        if (threadIdx.x < 64) write_desc_dense(a, b);
-        return;
-    }
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    BlockGeom<DIM> g;
-    g.init(a, b);
     const int U = g.U, nt = g.p1 - g.p0;
-    // blocks with a larger union keep no bits (their rows take the long-row path): counted
-    // in union order, unranked
-    uint32_t place = kNoRanks;
-    if (U <= UCAP) {
-        if (a.rpool) {
-            if (tid == 0) splace = take_ranks<UCAP>(a, b, U);
-            __syncthreads();
-            place = __builtin_amdgcn_readfirstlane(splace);
-        } else {
-            place = take_ranks<UCAP>(a, b, U);
-        }
-    }
-    const bool ranked = place != kNoRanks;
-    if (wv == 0) write_desc<DIM>(a, g, b, ranked ? U : max(U, UCAP + 1), place);
-    Rec* const srec = reinterpret_cast<Rec*>(scratch);
+    const bool ranked = NW == 1 || U <= UC;
+    Rec* const srec = reinterpret_cast<Rec*>(sh.scratch);
+    int* const slist = sh.slist;
     const Rec trec = T::fetch(a, g.p0 + min(lane, nt - 1));
     int rself = g.seg_base[g.SELF] + (g.p0 + lane - g.seg_g0[g.SELF]);
+    uint32_t place = !POOL && ranked ? block_ranks<DIM>(b) : kNoRanks;
+    if (!POOL && wv == 0) write_desc<DIM>(a, g, b, U, place);
     if (ranked) {
-        // the union's indices and records, in union order (contiguous along x)
-        int gi[EPT], og[EPT], rk[EPT];
+        // a pool's counter is asked before the loads and read after the ranking
+        uint32_t mine = 0;
+        if (POOL && tid == 0) mine = take_ranks(a, b, U);
+        // the union's indices and records, in union order (contiguous along x); one wavefront
+        // loads no more than the union has, several issue their loads together
+        int gi[EPT], og[EPT] = {}, rk[EPT];
         Rec rec[EPT];
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) gi[i] = g.global_of_any(min(tid + i * kCountThreads<DIM>, U - 1));
+        for (int i = 0; i < EPT; ++i) gi[i] = g.global_of_any(min(tid + i * NT, U - 1));
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) og[i] = a.perm[gi[i]];
+        for (int i = 0; i < EPT; ++i)
+            if (NW > 1 || i * NT < U) og[i] = a.perm[gi[i]];
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) rec[i] = T::fetch(a, gi[i]);
-        rank_originals<UCAP, FillCfg<DIM>::SHIFT, NW>(U, og, scratch, sred, swsum, reinterpret_cast<uint16_t*>(slist),
-                                                      rk);
+        for (int i = 0; i < EPT; ++i)
+            if (NW > 1 || i * NT < U) rec[i] = T::fetch(a, gi[i]);
+        if (POOL && tid == 0) sh.splace = mine;
+        if constexpr (NW == 1)
+            rank_wave<UC>(U, og, reinterpret_cast<uint32_t*>(sh.scratch), reinterpret_cast<uint16_t*>(slist), rk);
+        else
+            rank_originals<UC, FillCfg<DIM>::SHIFT, NW>(U, og, sh.scratch, sh.sred, sh.swsum,
+                                                        reinterpret_cast<uint16_t*>(slist), rk);
         const int self0 = g.seg_base[g.SELF] + (g.p0 - g.seg_g0[g.SELF]);  // the first target's union position
+        if (POOL) place = __builtin_amdgcn_readfirstlane(sh.splace);
         uint16_t* ranks = a.branks + static_cast<size_t>(place) * kRankPiece;
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
-            const int e = tid + i * kCountThreads<DIM>;
+            const int e = tid + i * NT;
             if (e < U) {
                 srec[rk[i]] = rec[i];
                 slist[rk[i]] = gi[i];
-                ranks[e] = static_cast<uint16_t>(rk[i]);
-                if (static_cast<unsigned>(e - self0) < static_cast<unsigned>(nt)) srself[e - self0] = rk[i];
+                if (!POOL || place != kNoRanks) ranks[e] = static_cast<uint16_t>(rk[i]);
+                if (static_cast<unsigned>(e - self0) < static_cast<unsigned>(nt)) sh.srself[e - self0] = rk[i];
             }
         }
         __syncthreads();
-        rself = lane < nt ? srself[lane] : 0;
+        rself = lane < nt ? sh.srself[lane] : 0;
     }
+    const bool kept = POOL ? place != kNoRanks : ranked;
+    if (POOL && wv == 0) write_desc<DIM>(a, g, b, kept ? U : max(U, FillCfg<DIM>::UCAP + 1), place);
     T tiles;
     tiles.targets(trec, g);
     const double R2 = g.sd->fr.R2;
     const int mi = T::item(lane);
     int cnt = 0;
-    for (int c0 = 0; c0 < U; c0 += UCAP) {  // one pass when ranked
-        const int m = min(UCAP, U - c0);
+    for (int c0 = 0; c0 < U; c0 += UC) {  // one pass when ranked
+        const int m = min(UC, U - c0);
         if (!ranked) {
             __syncthreads();
-            for (int e = tid; e < m; e += kCountThreads<DIM>) {
+            for (int e = tid; e < m; e += NT) {
                 slist[e] = g.global_of_any(c0 + e);
                 srec[e] = T::fetch(a, slist[e]);
             }
@@ -1575,19 +1638,91 @@ k_count(SearchArgs a)
                     }
                 }
                 cnt += __builtin_popcount(word);
-                if (ranked && lane < nt && 32 * tile < m)
+                if (kept && lane < nt && 32 * tile < m)
                     a.cbits[static_cast<size_t>(tile) * a.L.ntot + g.p0 + lane] = word;
             }
         }
     }
-    spart[wv][lane] = cnt;
-    __syncthreads();
+    if (NW > 1) {
+        sh.spart[wv][lane] = cnt;
+        __syncthreads();
+    }
     if (tid < nt) {
-        int c = 0;
+        int c = NW > 1 ? 0 : cnt;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) c += spart[q][tid];
+        for (int q = 0; NW > 1 && q < NW; ++q) c += sh.spart[q][tid];
         a.counts[a.perm[g.p0 + tid]] = c;
         a.counts_s[g.p0 + tid] = c;
+    }
+}
+
+template <int DIM, int P, bool HALF, bool POOL>
+__global__ void __launch_bounds__(kCountThreads<DIM>) __attribute__((amdgpu_waves_per_eu(P == 64 ? 4 : 5)))
+k_count(SearchArgs a)
+{
+    constexpr int UCAP = FillCfg<DIM>::UCAP;
+    __shared__ CountShared<DIM, P, kCountThreads<DIM> / 64, UCAP> sh;
+    if (a.wdense && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense count behind this
+    const int b = xcd_block(*a.nblk);
+    if (b < 0) return;
+    if (dense_block(a, b)) {
+        if (threadIdx.x < 64) write_desc_dense(a, b);
+        return;
+    }
+    BlockGeom<DIM> g;
+    g.init(a, b);
+    count_block<DIM, P, HALF, POOL>(a, g, b, sh);
+}
+
+// Sparse sets in 3D (see kSparseUnion): most blocks have a few targets and unions of tens of
+// candidates, and what bounds the count is the chain of dependent loads and the ranking per block, so
+// one wavefront takes a block and the chip holds four times as many at once. Unions above
+// kSmallUnion are left to k_count_rest, marked in their descriptor.
+template <int P, bool HALF>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+k_count_small(SearchArgs a)
+{
+    __shared__ CountShared<3, P, 1, kSmallUnion> sh;
+    if (a.wdense && blockIdx.x == 0 && threadIdx.x == 0) a.flags[kFlagUnit] = 0;  // for the dense count behind this
+    const int b = xcd_block(*a.nblk);
+    if (b < 0) return;
+    if (dense_block(a, b)) {
+        write_desc_dense(a, b);
+        return;
+    }
+    BlockGeom<3> g;
+    g.init(a, b);
+    if (g.U <= kSmallUnion) count_block<3, P, HALF, true>(a, g, b, sh);
+    else write_desc<3>(a, g, b, g.U, kNoRanks, 2);
+}
+
+// The blocks that k_count_small left, found by their descriptors: workgroup i takes those of the
+// blocks i, i + gridDim, ... (dealt out one by one, as they may all lie in a small part of the box).
+template <int P, bool HALF>
+__global__ void __launch_bounds__(kCountThreads<3>) __attribute__((amdgpu_waves_per_eu(P == 64 ? 4 : 5)))
+k_count_rest(SearchArgs a)
+{
+    constexpr int NT = kCountThreads<3>;
+    __shared__ CountShared<3, P, NT / 64, kUnion3> sh;
+    __shared__ int sfound[NT];
+    __shared__ int snfound;
+    const int nblk = *a.nblk, step = gridDim.x;
+    for (int64_t i0 = blockIdx.x; i0 < nblk; i0 += static_cast<int64_t>(NT) * step) {
+        if (threadIdx.x == 0) snfound = 0;
+        __syncthreads();
+        const int64_t i = i0 + static_cast<int64_t>(threadIdx.x) * step;
+        if (i < nblk && a.bdesc[static_cast<size_t>(i) * kDescInts + 4] == 2)
+            sfound[atomicAdd(&snfound, 1)] = static_cast<int>(i);
+        __syncthreads();
+        const int nfound = __builtin_amdgcn_readfirstlane(snfound);
+        for (int k = 0; k < nfound; ++k) {
+            const int b = __builtin_amdgcn_readfirstlane(sfound[k]);
+            BlockGeom<3> g;
+            g.init(a, b);
+            count_block<3, P, HALF, true>(a, g, b, sh);
+            __syncthreads();  // the next block writes the shared tables
+        }
+        __syncthreads();
     }
 }
 
@@ -1610,7 +1745,8 @@ constexpr int kFillThreads = 256;  // four wavefronts share one block's union
 // What bounds it: vector issue and HBM about evenly. At 1M particles in 3D (60 M entries, 728 MB
 // of DRAM traffic, 78 M vector instructions): 322 us with the ranking and gathers from global
 // memory here, 213 now; 2D 93 -> 60, binary64 321 -> 244 us.
-template <int DIM, bool F64>
+// POOL: the ranks' places come from the pools (else a block's is known without its descriptor).
+template <int DIM, bool F64, bool POOL>
 __global__ void __launch_bounds__(kFillThreads) __attribute__((amdgpu_waves_per_eu(F64 ? 4 : 6)))
 k_fill(SearchArgs a)
 {
@@ -1662,8 +1798,8 @@ k_fill(SearchArgs a)
     int rank[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i)
-        rank[i] = a.branks[static_cast<size_t>(static_cast<uint32_t>(dsc[kDescRanks])) * kRankPiece +
-                           min(tid + i * kFillThreads, U - 1)];
+        rank[i] = a.branks[static_cast<size_t>(POOL ? static_cast<uint32_t>(dsc[kDescRanks]) : block_ranks<DIM>(b)) *
+                               kRankPiece + min(tid + i * kFillThreads, U - 1)];
     uint32_t wbits[KW];
 #pragma unroll
     for (int k = 0; k < KW; ++k) wbits[k] = a.cbits[static_cast<size_t>(min(wa + k, nw - 1)) * a.L.ntot + pt];
@@ -2011,13 +2147,30 @@ k_long(SearchArgs a)
 // every block of any count up to nblk_max.
 static dim3 block_grid(int nblk_max) { return dim3((nblk_max + kXcds - 1) / kXcds * kXcds); }
 
+// Workgroups of k_count_rest: as many as the 256 compute units can hold.
+constexpr int kRestGrid = 2048;
+
+template <int P, bool HALF>
+void launch_count_sparse(const SearchArgs& a, const dim3& g, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_count_small<P, HALF>), g, dim3(64), 0, st, a);
+    hipLaunchKernelGGL((k_count_rest<P, HALF>), dim3(kRestGrid), dim3(kCountThreads<3>), 0, st, a);
+}
+
+template <int DIM, int P, bool HALF>
+void launch_count_of(const SearchArgs& a, const dim3& g, hipStream_t st)
+{
+    if (DIM == 3 && a.sparse && a.rpool) launch_count_sparse<P, HALF>(a, g, st);
+    else if (a.rpool) hipLaunchKernelGGL((k_count<DIM, P, HALF, true>), g, dim3(kCountThreads<DIM>), 0, st, a);
+    else hipLaunchKernelGGL((k_count<DIM, P, HALF, false>), g, dim3(kCountThreads<DIM>), 0, st, a);
+}
+
 template <int DIM, bool HALF>
 void launch_count_mode(const SearchArgs& a, int mode, const dim3& g, hipStream_t st)
 {
-    const dim3 b(kCountThreads<DIM>);
-    if (mode == 0) hipLaunchKernelGGL((k_count<DIM, 16, HALF>), g, b, 0, st, a);
-    else if (mode == 3) hipLaunchKernelGGL((k_count<DIM, 32, HALF>), g, b, 0, st, a);
-    else hipLaunchKernelGGL((k_count<DIM, 64, HALF>), g, b, 0, st, a);
+    if (mode == 0) launch_count_of<DIM, 16, HALF>(a, g, st);
+    else if (mode == 3) launch_count_of<DIM, 32, HALF>(a, g, st);
+    else launch_count_of<DIM, 64, HALF>(a, g, st);
 }
 
 hipError_t launch_count(const SearchArgs& a, int nblk_max, hipStream_t st)
@@ -2041,10 +2194,12 @@ hipError_t launch_fill(const SearchArgs& a, int nblk_max, hipStream_t st)
     const int d = a.L.dim;
     const bool f64 = a.L.mode == 1 || a.L.mode == 3;  // FP64 and FP32 modes: binary64 distances
     const dim3 g = block_grid(nblk_max), b(kFillThreads);
-    if (d == 2 && !f64) hipLaunchKernelGGL((k_fill<2, false>), g, b, 0, st, a);
-    else if (d == 3 && !f64) hipLaunchKernelGGL((k_fill<3, false>), g, b, 0, st, a);
-    else if (d == 2) hipLaunchKernelGGL((k_fill<2, true>), g, b, 0, st, a);
-    else hipLaunchKernelGGL((k_fill<3, true>), g, b, 0, st, a);
+    auto k = [&](auto pool) {
+        constexpr bool POOL = decltype(pool)::value;
+        return d == 2 ? (f64 ? k_fill<2, true, POOL> : k_fill<2, false, POOL>)
+                      : (f64 ? k_fill<3, true, POOL> : k_fill<3, false, POOL>);
+    };
+    hipLaunchKernelGGL(a.rpool ? k(std::true_type{}) : k(std::false_type{}), g, b, 0, st, a);
     return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ struct HarnessArgs {
     int32_t* rpool;
     double radius;
     int32_t t_lo, t_hi, t_mid, nblk_max;  // FP16 thresholds as bits
-    int32_t rpool_cap;
+    int32_t rpool_cap, sparse;
 };
 
 int harness_set_bytes() { return static_cast<int>(sizeof(nnps::SetDesc)); }
@@ -117,6 +117,7 @@ static hipError_t search_args(const HarnessArgs* h, int dense, nnps::SearchArgs&
     a.stats = reinterpret_cast<unsigned long long*>(h->stats);
     a.rpool = h->rpool;
     a.rpool_cap = h->rpool_cap;
+    a.sparse = h->sparse;
     return hipMemcpy(h->set_room, &sd, sizeof(sd), hipMemcpyHostToDevice);
 }
 

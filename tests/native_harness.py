@@ -27,7 +27,7 @@ class Args(ctypes.Structure):
     """HarnessArgs of search_harness.hip."""
     _fields_ = ([(k, ctypes.c_int32) for k in ("dim", "mode", "n", "half")] +
                 [(k, ctypes.c_int64) for k in ("capacity", "dbits_cap")] + [(k, ctypes.c_void_p) for k in _POINTERS] +
-                [("radius", ctypes.c_double)] + [(k, ctypes.c_int32) for k in ("t_lo", "t_hi", "t_mid", "nblk_max", "rpool_cap")])
+                [("radius", ctypes.c_double)] + [(k, ctypes.c_int32) for k in ("t_lo", "t_hi", "t_mid", "nblk_max", "rpool_cap", "sparse")])
 
 
 def load():

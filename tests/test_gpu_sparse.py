@@ -1,5 +1,6 @@
 """Sets with far fewer particles than cells: their many small blocks take the union ranks' room from
-pools, so that the structure's memory follows the particles; rows are the oracle's on every path."""
+pools, so that the structure's memory follows the particles, and are counted by a wavefront each in
+3D, larger unions among them by a workgroup; rows are the oracle's on every path."""
 import ctypes
 
 import native_harness as native
@@ -17,13 +18,13 @@ from paper_2401_08586_amd import nnps  # noqa: E402
 MODES = {"fp16": nnps.MODE_FP16_RCLL, "fp64": nnps.MODE_FP64_BASELINE, "fp32": nnps.MODE_FP32_RCLL}
 
 
-def scattered(dim, n, nc, seed, clump=0):
-    """n points over nc^dim cells, the last `clump` of them in a few cells in the middle."""
+def scattered(dim, n, nc, seed, clump=0, wide=2.0):
+    """n points over nc^dim cells, the last `clump` of them in the middle, `wide` cells to either side."""
     rng = np.random.default_rng(seed)
     pos = rng.uniform(0, 1, size=(n, dim))
-    pos[n - clump:] = 0.5 + rng.uniform(-2.0, 2.0, size=(clump, dim)) / nc
+    pos[n - clump:] = 0.5 + rng.uniform(-wide, wide, size=(clump, dim)) / nc
     return W.ParticleSet(np.ascontiguousarray(pos[rng.permutation(n)]), (0.0,) * dim, (1.0,) * dim, 1.0 / nc, 1.0 / nc,
-                         f"scattered{dim}d_{n}_in_{nc}_{clump}")
+                         f"scattered{dim}d_{n}_in_{nc}_{clump}_{wide}")
 
 
 def free_bytes():
@@ -63,6 +64,7 @@ def test_memory_follows_the_particles(mode):
 @pytest.mark.parametrize("dim", [2, 3])
 def test_sparse_sets_against_the_oracle(dim, mode, half):
     for ps in (scattered(dim, 40000, 128 if dim == 3 else 2000, 3), scattered(dim, 60000, 128 if dim == 3 else 2000, 4, 9000),
+               scattered(dim, 60000, 128 if dim == 3 else 2000, 6, 25000, 9.0),  # unions of 500 to 900 in 3D
                scattered(dim, 100, 128 if dim == 3 else 2000, 5)):
         print(f"[gpu] sparse {ps.name} {mode} half={half}", flush=True)
         wrp, wcol, wdist = oracle.search_ps(ps)
@@ -152,3 +154,61 @@ def test_block_whose_pool_is_empty(dim, mode):
         np.testing.assert_array_equal(ranks[at:at + n], np.arange(n))  # one cell, numbered in order
         left[at:at + n] = 0xABCD
     assert np.all(left == 0xABCD)
+
+
+@pytest.mark.parametrize("half", [0, 1], ids=["full", "half"])
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("sparse", [0, 1], ids=["workgroup", "wavefront"])
+@pytest.mark.parametrize("span", [1 << 10, 1 << 17, 18_000_000])
+def test_ranks_and_bits_of_a_count(span, sparse, mode, half):
+    """One cell in 3D, numbered at random in `span` values (sorting keys hold a position beside the
+    index up to 2^24): every block's union ranks, kept bits and counts, at the edges of what a
+    wavefront ranks (64, 128, 256 candidates) and past it."""
+    radius = 0.5
+    for n in (1, 2, 63, 64, 65, 127, 129, 192, 255, 256, 257, 600, 1024):
+        if n > span:
+            continue
+        rng = np.random.default_rng(n)
+        pos = rng.uniform(0.02, 0.98, size=(n, 3))
+        near = ((pos[:, None] - pos[None]) ** 2).sum(-1) <= radius * radius
+        perm = rng.permutation(np.concatenate([[0, span - 1], 1 + rng.choice(span - 2, n - 2, replace=False)]) if n > 1
+                               else [span - 1]).astype(np.int32)  # distinct, the ends among them
+        rank = np.empty(n, np.int64)
+        rank[np.argsort(perm)] = np.arange(n)
+        spos = np.zeros((n, 4))
+        spos[:, :3] = pos
+        spos[:, 3] = perm.astype(np.int64).view(np.float64)
+        rq = np.zeros((n, 4), np.float32)
+        rq[:, :3] = 2 * pos - 1
+        nb, cap = (n + 63) // 64, 1024
+        arrays = dict(pos=pos, set_room=np.zeros(native.load().harness_set_bytes(), np.uint8),
+                      offs=np.array([0, n], np.int32), cell_offs=np.array([0, 1], np.int32), skey=np.zeros(n, np.uint32),
+                      perm=perm, cell_start=np.array([0, n], np.int32), spos=spos, rq=rq, flags=np.zeros(8, np.int32),
+                      bstart=np.minimum(64 * np.arange(nb + 1), n).astype(np.int32), bset=np.zeros(nb, np.int32),
+                      nblk=np.array([nb], np.int32), counts=np.full(span, -1, np.int32), counts_s=np.full(n, -1, np.int32),
+                      cbits=np.zeros((32, n), np.uint32), bdesc=np.zeros((nb + 8, 24), np.int32),
+                      rpool=np.zeros((256, 16), np.int32), branks=np.full(256 * cap, 0xABCD, np.uint16))
+        dev = {k: torch.from_numpy(np.ascontiguousarray(v)).cuda() for k, v in arrays.items()}
+        args = native.Args(dim=3, mode=MODES[mode], n=n, half=half, radius=radius, nblk_max=nb, rpool_cap=cap, sparse=sparse)
+        for k, v in dev.items():
+            setattr(args, k, v.data_ptr())
+        torch.cuda.synchronize()
+        print(f"[gpu] ranks n={n} span={span} sparse={sparse} {mode} half={half}", flush=True)
+        assert native.load().harness_count(ctypes.byref(args)) == 0
+        keep = near & ~np.eye(n, dtype=bool)
+        if half:
+            keep &= perm[None] > perm[:, None]
+        counts = np.full(span, -1, np.int32)
+        counts[perm] = keep.sum(1)
+        np.testing.assert_array_equal(dev["counts"].cpu().numpy(), counts)
+        np.testing.assert_array_equal(dev["counts_s"].cpu().numpy(), keep.sum(1))
+        desc, ranks = dev["bdesc"].cpu().numpy(), dev["branks"].cpu().numpy()
+        bits = dev["cbits"].cpu().numpy()
+        want = np.zeros((1024, n), bool)
+        want[rank] = keep.T
+        got = (bits[:, None, :] >> np.arange(32, dtype=np.uint32)[None, :, None] & 1).reshape(1024, n).astype(bool)
+        np.testing.assert_array_equal(got, want)
+        for b in range(nb):
+            assert desc[b, 3] == n and desc[b, 4] == 0
+            at = 16 * int(desc[b, 23])
+            np.testing.assert_array_equal(ranks[at:at + n], rank)
