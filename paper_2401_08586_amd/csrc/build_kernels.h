@@ -67,7 +67,7 @@ struct DenseBuild {
     uint32_t* table;        // radix scratch
     int64_t* partial;       // scan scratch
     int* seen;              // [1] set to 1 when any cell is dense
-    int* dbn;               // [ncell_tot] (target, chunk) pairs of each dense cell
+    uint32_t* dbn;          // [ncell_tot] (target, chunk) pairs of each dense cell (saturated)
     int64_t* dboff;         // [ncell_tot + 1] exclusive scan of dbn
 };
 

@@ -944,7 +944,7 @@ k_pack(Launch L, PackArgs a, BlockTable t, int nrows)
 __global__ void __launch_bounds__(256)
 k_dense_units(int ncell_tot, const int* __restrict__ cell_start, const int64_t* __restrict__ uoff, int64_t cap,
               int* __restrict__ usz, int* __restrict__ wdense, int* __restrict__ nsl, int* __restrict__ dn,
-              int* __restrict__ dbn)
+              uint32_t* __restrict__ dbn)
 {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t ue = uoff[ncell_tot];
@@ -958,7 +958,9 @@ k_dense_units(int ncell_tot, const int* __restrict__ cell_start, const int64_t* 
     const int occ = cell_start[g + 1] - cell_start[g];
     const bool on = !over && usz[g] > 0;
     nsl[g] = on ? (occ + kDenseUnit - 1) / kDenseUnit : 0;
-    dbn[g] = on ? occ * ((usz[g] + kDenseChunk - 1) / kDenseChunk) : 0;
+    // 2^32 - 1 pairs would be 512 GiB of kept bits: more than any buffer holds, so none are kept
+    const int64_t pairs = on ? static_cast<int64_t>(occ) * ((usz[g] + kDenseChunk - 1) / kDenseChunk) : 0;
+    dbn[g] = static_cast<uint32_t>(min(pairs, static_cast<int64_t>(0xFFFFFFFFu)));
 }
 
 __global__ void __launch_bounds__(256)
@@ -1272,7 +1274,7 @@ hipError_t launch_dense_cells(const Launch& L, const int* cell_start, const Dens
                        d.wdense, d.nsl, d.dn, d.dbn);
     e = scan_exclusive<int, int>(d.nsl, nc, d.unit_off, d.partial, st);
     if (e != hipSuccess) return e;
-    e = scan_exclusive<int, int64_t>(d.dbn, nc, d.dboff, d.partial, st);
+    e = scan_exclusive<uint32_t, int64_t>(d.dbn, nc, d.dboff, d.partial, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_dense_unit_cells, g, b, 0, st, nc, d.nsl, d.unit_off, d.dn, d.ucell);
     return hipGetLastError();

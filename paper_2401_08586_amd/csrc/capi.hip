@@ -469,7 +469,7 @@ DenseBuild dense_of(nnps_cells* c)
     d.table = c->table.as<uint32_t>();
     d.partial = c->partial.as<int64_t>();
     d.seen = c->report.as<int>() + kFlagSeen;
-    d.dbn = c->dbn.as<int>();
+    d.dbn = c->dbn.as<uint32_t>();
     d.dboff = c->dboff.as<int64_t>();
     return d;
 }
