@@ -308,7 +308,8 @@ struct nnps_cells {
     // dense passes: (target, chunk) offsets per cell and the count's accepted bits,
     // sized at a build from what the last synchronising call found the dense cells need
     DevBuf dbn, dboff, dbits;
-    size_t dbits_want = 0;  // bytes
+    size_t dbits_want = 0;                 // bytes
+    size_t dbits_denied = ~size_t(0);      // no memory was found for so many: none is asked for again
     // incremental update (nnps_cells_update): see Update
     DevBuf uleave, ucs_old, uskey2, uperm2;
     GraphCache ugraph;  // a captured update + count + fill sequence
@@ -633,6 +634,12 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         void* before = q.b->p;
         const size_t cap = q.b->cap;
         hipError_t e = q.b->ensure(q.bytes, q.b == &c->dbits);  // the kept bits have a bound
+        if (e == hipErrorOutOfMemory && q.b == &c->dbits) {  // the fill tests again without them
+            (void)hipGetLastError();
+            c->dbits_denied = q.bytes;
+            c->dbits_want = 0;
+            e = hipSuccess;
+        }
         if (e != hipSuccess) return e == hipErrorOutOfMemory ? NNPS_ENOMEM : NNPS_EDEVICE;
         if (q.b->p != before) ++c->buf_gen;
         // (new memory may have the old address)
@@ -851,7 +858,7 @@ nnps_status take_report(nnps_cells* c, const int64_t* hp)
     see_flags(c, flags);
     if (c->dense_active && dense_bits_on(c)) {
         const size_t want = static_cast<size_t>(hp[kHostWords - 1]) * 64 * sizeof(uint16_t);
-        if (want <= dense_bits_bound(c)) c->dbits_want = std::max(c->dbits_want, want);
+        if (want <= dense_bits_bound(c) && want < c->dbits_denied) c->dbits_want = std::max(c->dbits_want, want);
     }
     return err_status(flags[kFlagErr]);
 }
