@@ -185,10 +185,9 @@ k_sph_gradient(int n, double inv_h, double alpha_h, const double* __restrict__ p
             no = sub == a ? num[a] : no;
             de = sub == a ? den[a] : de;
         }
-        if (grad) grad[i * DIM + sub] = -__dmul_rn(alpha_h, so);
-        no = __dmul_rn(alpha_h, no);  // both lack the sign of x_i - x_j as well
-        de = __dmul_rn(alpha_h, de);
-        if (grad_norm) grad_norm[i * DIM + sub] = de != 0.0 ? __ddiv_rn(no, de) : 0.0;
+        // a row that adds nothing gives +0, also where alpha_d / h overflows
+        if (grad) grad[i * DIM + sub] = so != 0.0 ? -__dmul_rn(alpha_h, so) : 0.0;
+        if (grad_norm) grad_norm[i * DIM + sub] = de != 0.0 ? __ddiv_rn(no, de) : 0.0;  // the factor cancels
     }
 }
 
