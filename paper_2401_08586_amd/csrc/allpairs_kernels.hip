@@ -91,16 +91,18 @@ k_allpairs_count(int n, const double* __restrict__ pos, double R2, ApBox box, in
     for (int r = 0; r < R; ++r) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) c[r] += __shfl_xor(c[r], o, 64);
-        mine = lane == r ? c[r] - 1 : mine;  // less the row itself
+        mine = lane == r ? c[r] : mine;
     }
     if (lane < R && i0 + lane < n) {
-        row_ptr[i0 + lane + 1] = mine;
-        bool bad = false;
+        bool bad = false, self = true;
 #pragma unroll
         for (int k = 0; k < DIM; ++k) {
             const double x = pos[static_cast<size_t>(i0 + lane) * DIM + k];
             bad |= !(x >= box.lo[k] && x <= box.hi[k]);
+            self &= __dsub_rn(x, x) == 0.0;
         }
+        // less the row itself, which is among those counted if its position is finite
+        row_ptr[i0 + lane + 1] = mine - (self ? 1 : 0);
         if (bad) atomicOr(flag, 1);
     }
 }
