@@ -167,11 +167,8 @@ struct SearchArgs {
     unsigned long long* stats;      // [kStCount] totals
     unsigned long long* blk_stats;  // [nblk_max][5] per-block partial statistics
     uint32_t* cbits;                // accepted-candidate bits, word-major [words][ntot]
-    uint32_t* lrscratch;            // long-row path merge scratch, per workgroup
-    int64_t lrscratch_words;        // its size per workgroup (32-bit words)
     int sparse;                     // 1: the count by small blocks (3D, see kSparseUnion)
     int lr_keys;                    // keys a long-row workgroup sorts in LDS
-    int* sink;                      // [2 * 64] per-lane dummy output slots
     int half;                       // 1: rows keep only neighbours of larger original index
     // dense-cell path (wdense == nullptr: off)
     const int* wdense;

@@ -544,8 +544,8 @@ __device__ __forceinline__ void pack_particle(const Launch& L, const PackArgs& a
 template <int DIM>
 __global__ void __launch_bounds__(256)
 k_upd_move(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int nsets, int ntot,
-           const uint32_t* __restrict__ skey, const int* __restrict__ inv, uint32_t* __restrict__ knew, uint32_t* __restrict__ mig, int* __restrict__ leave,
-           int* __restrict__ arrive, int* __restrict__ aslot, int* __restrict__ err)
+           const uint32_t* __restrict__ skey, const int* __restrict__ inv, uint32_t* __restrict__ knew,
+           uint32_t* __restrict__ mig, int* __restrict__ leave, int* __restrict__ arrive, int* __restrict__ aslot, int* __restrict__ err)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= ntot) return;
@@ -843,9 +843,10 @@ k_rowptr(const SetDesc* __restrict__ sets, const int* __restrict__ poffs, int ns
 // ---------------------------------------------------------------------------
 // Dense-cell path tables. Where clustering piles hundreds or thousands of particles
 // into a cell, every target of the cell tests the same stencil union, and its rows are
-// long. A cell is dense when its stencil holds more than a threshold of particles. For such cells the search stages the union once per chunk for all the cell's
-// targets, in ascending original index, so each row comes out sorted with no per-row
-// sort. The union lists come from one stable sort: every particle, visited in original
+// long. A cell is dense when its stencil holds more than a threshold of particles. For such
+// cells the search stages the union once per chunk for all the cell's targets, in ascending
+// original index, so each row comes out sorted with no per-row sort. The union lists are ranked
+// in a bitmap (k_union_rank), or come from one stable sort: every particle, visited in original
 // order, emits (dense cell, sorted position) for each dense cell whose stencil holds it.
 
 // Global cell index -> local coordinates of its set.

@@ -296,7 +296,7 @@ struct nnps_cells {
     int small_blocks = -1;                // at the last synchronising call: -1 unknown, 0, 1
     int rpool_cap = 0;                    // entries of a rank pool; 0: a place per block
     DevBuf d_sets, d_offs, k0, k1, v0, v1, cell_count, cell_start, spos, rq, boff, bstart, bset,
-        counts, table, partial, stats, blk_stats, cbits, report, heavy, sink;
+        counts, table, partial, stats, blk_stats, cbits, report, heavy;
     // dense-cell path (see DenseBuild)
     bool dense = false;         // the tuning allows the dense-cell path
     bool dense_active = false;  // the last build uses it
@@ -427,7 +427,6 @@ SearchArgs args_of(const nnps_cells* c)
     int keys = 1;
     while (keys * 2 <= std::min(c->ctx->max_lds - 1024, 64 * 1024) / 4) keys *= 2;
     a.lr_keys = c->ctx->tuning.long_rows_keys > 0 ? std::min(c->ctx->tuning.long_rows_keys, keys) : keys;
-    a.sink = c->sink.as<int>();
     a.half = c->half ? 1 : 0;
     a.sparse = c->sparse ? 1 : 0;
     if (c->dense_active) {
@@ -550,7 +549,8 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         // others start that far apart), and around each run of dense cells one marker plus
         // one cut short
         const int full = fr.nc[0] / kRowSegment, rest = fr.nc[0] % kRowSegment;
-        int64_t b = fr.n / kWave + nrows * (full * ((kRowSegment + fr.xwin - 1) / fr.xwin) + (rest + fr.xwin - 1) / fr.xwin);
+        int64_t b = full * ((kRowSegment + fr.xwin - 1) / fr.xwin) + (rest + fr.xwin - 1) / fr.xwin;
+        b = fr.n / kWave + nrows * b;
         if (c->dense && c->dense_seen != 0)  // the build will use the dense-cell path
             b += 2 * std::min<int64_t>(fr.ncell, stencil * fr.n / (static_cast<int64_t>(c->dthresh) + 1));
         nblk_bound += std::min<int64_t>(fr.n, b);
@@ -614,7 +614,7 @@ nnps_status prepare(nnps_ctx* ctx, nnps_cells* c, int nsets, const nnps_problem*
         {&c->stats, kStCount * 8},
         {&c->blk_stats, static_cast<size_t>(std::max(c->nblk_max, 1)) * 5 * 8},
         {&c->cbits, nn * cw * 4},
-        {&c->heavy, nn * 4}, {&c->sink, 2 * 64 * 4},
+        {&c->heavy, nn * 4},
         {&c->report, sizeof(int) * kFlags + sizeof(int64_t) * nsets},
         {&c->usz, c->dense ? (nc + 1) * 4 : 0}, {&c->wdense, c->dense ? (nc + 1) * 4 : 0},
         {&c->uoff, c->dense ? (nc + 1) * 8 : 0}, {&c->nsl, c->dense ? (nc + 1) * 4 : 0},
@@ -1040,7 +1040,7 @@ void nnps_cells_destroy(nnps_cells* c)
     DevBuf* all[] = {&c->d_sets, &c->d_offs, &c->k0, &c->k1, &c->v0, &c->v1, &c->cell_count,
                      &c->cell_start, &c->spos, &c->rq, &c->boff, &c->bstart, &c->bset, &c->counts,
                      &c->table, &c->partial, &c->stats, &c->blk_stats, &c->cbits, &c->report, &c->heavy,
-                     &c->sink, &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
+                     &c->usz, &c->wdense, &c->uoff, &c->nsl, &c->unit_off,
                      &c->ucell, &c->dn, &c->ecnt, &c->epos, &c->uk0, &c->uk1, &c->uv0, &c->uv1, &c->inv,
                      &c->dstats, &c->uleave, &c->ucs_old,
                      &c->uskey2, &c->uperm2, &c->counts_s, &c->rsort, &c->bdesc, &c->branks, &c->rpool, &c->dbn, &c->dboff,
@@ -1307,7 +1307,6 @@ nnps_status nnps_batch_step(nnps_ctx* ctx, nnps_cells* c, int32_t nsets, const n
     DeviceGuard g(ctx->device);
     if (!g.ok) return NNPS_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const uint64_t gen0 = c->buf_gen;
     nnps_status st = prepare(ctx, c, nsets, probs, d_pos);
     if (st != NNPS_OK) return st;
     set_outputs(c, d_row_ptr, d_col, d_dist, capacity);
@@ -1333,7 +1332,6 @@ nnps_status nnps_batch_step(nnps_ctx* ctx, nnps_cells* c, int32_t nsets, const n
     q += 4;
     const int plan = (c->dense && c->dense_seen != 0 ? 1 : 0) | (c->half ? 2 : 0) | (c->sparse ? 4 : 0);
     memcpy(q, &plan, 4);
-    (void)gen0;
     if ((st = clear_counters(c, s)) != NNPS_OK) return st;  // outside the graph
     if (!c->graph.exec || c->graph.sig != sig) {
         c->graph.reset();

@@ -944,13 +944,6 @@ __device__ __forceinline__ int wave_min_i32(int v)
     return __builtin_amdgcn_readlane(wave_fold_i32(v, 0x7FFFFFFF, [](int x, int y) { return min(x, y); }), 63);
 }
 
-__device__ __forceinline__ long long wave_max_i64(long long v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, static_cast<long long>(__shfl_xor(v, o, 64)));
-    return v;
-}
-
 __device__ __forceinline__ int wave_max_i32(int v)
 {
     return __builtin_amdgcn_readlane(wave_fold_i32(v, -0x7FFFFFFF - 1, [](int x, int y) { return max(x, y); }), 63);
@@ -961,10 +954,11 @@ __device__ __forceinline__ int wave_max_i32(int v)
 template <int UCAP>
 constexpr int kRankScratch = 8 * UCAP > 6 * UCAP + 768 ? 8 * UCAP : 6 * UCAP + 768;
 
-// The rank rk[i] of union element tid + i 64 NW (below U) by original index, og[i] its index. Unions spanning few indices are ranked by a
-// bitmap, up to 2^17 by a two-level bitmap, the others (an unordered numbering) by sorting:
-// keys (orig - omin) << SHIFT | position when the range allows, else the original index
-// itself, distinct either way and below the all-ones key that pads the sorted quarters.
+// The rank rk[i] of union element tid + i 64 NW (below U) by original index, og[i] its index.
+// Unions spanning few indices are ranked by a bitmap, up to 2^17 by a two-level bitmap, the
+// others (an unordered numbering) by sorting: keys (orig - omin) << SHIFT | position when the
+// range allows, else the original index itself, distinct either way and below the all-ones key
+// that pads the sorted quarters.
 // rank_of (UCAP entries) is scratch too; both are free again on return.
 template <int UCAP, int SHIFT, int NW>
 __device__ __forceinline__ void rank_originals(int U, const int (&og)[UCAP / (64 * NW)], unsigned char* scratch,
@@ -1492,7 +1486,8 @@ struct Tiles<DIM, 64> {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const double d = D[r];
-                    hi[4 * i + r] = __builtin_bit_cast(float, static_cast<uint32_t>(__builtin_bit_cast(uint64_t, d) >> 32));
+                    const uint32_t top = static_cast<uint32_t>(__builtin_bit_cast(uint64_t, d) >> 32);
+                    hi[4 * i + r] = __builtin_bit_cast(float, top);
                 }
             }
             uint32_t acc = 0;
@@ -1970,8 +1965,9 @@ k_fill(SearchArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Long rows (blocks whose union exceeds the fill's limit): one workgroup per target. Its candidates are tested in binary64 across the workgroup and
-// the accepted original indices appended to the row in any order; the row is then sorted
+// Long rows (blocks whose union exceeds the fill's limit or that have no ranks): one workgroup per
+// target. Its candidates are tested in binary64 across the workgroup and the accepted original
+// indices appended to the row in any order; the row is then sorted
 // in place (LDS bitonic network for up to lr_keys entries, in which every comparator puts
 // the smaller key first so padding at +inf never moves; longer rows are sorted in chunks
 // and merged pairwise by rank, using the row's distance slots as scratch), and finally
