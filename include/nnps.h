@@ -133,15 +133,15 @@ typedef struct nnps_stats {
  * dense_grid: workgroups of the dense-cell kernels (persistent). 0 = default (1280).
  *   Valid 0..2^20.
  * dense_max_entries: bound on the summed stencil-union sizes of dense cells per build
- *   (device scratch: 16 bytes per entry, allocated as min(3^d n, bound)). Beyond it a
- *   build falls back to the block and long-row paths. 0 = default (2^28). Valid
+ *   (device scratch: 4 bytes per entry, 16 where a set has more than 1,048,576 particles,
+ *   allocated as min(3^d n, bound)). Beyond it a build falls back to the block and long-row paths. 0 = default (2^28). Valid
  *   0..2^31-1.
  * dense_bits_mib: bound (MiB) on the device scratch in which the dense count keeps
  *   every target's accepted bits per candidate chunk (one bit per candidate, 1024
  *   candidates a chunk) so that the fill does not test again. The
  *   structure sizes it at a build from what the last call that synchronised (a count
- *   with h_nnz, a search) found the dense cells need; while it is too small, or above
- *   the bound, the fill tests the candidates again (same result). 0 = default (16384);
+ *   with h_nnz, a search) found the dense cells need; while it is too small, above the
+ *   bound or not to be had, the fill tests the candidates again (same result). 0 = default (16384);
  *   -1 = never. Valid -1..2^20. */
 typedef struct nnps_tuning {
     int32_t block_target;

@@ -1235,8 +1235,12 @@ hipError_t launch_pack(const Launch& L, const PackArgs* pack, const BlockTable* 
         if (e != hipSuccess) return e;
     }
     const int nrows = blocks ? (L.nrows_tot + kRowsPerGroup - 1) / kRowsPerGroup : 0;
-    const dim3 g(static_cast<unsigned>(nrows) + (pack ? (L.ntot + 255) / 256 : 0)), b(256);
+    // workgroups for the particles, and for the counters where a grid has far more cells than
+    // particles (16 of them a thread, as many as keep the chip busy)
     const PackArgs a = pack ? *pack : PackArgs{};
+    const int64_t clear = std::min<int64_t>((a.nclear0 + a.nclear1) / (256 * 16), 2048);
+    const int npack = pack ? static_cast<int>(std::max<int64_t>((static_cast<int64_t>(L.ntot) + 255) / 256, clear)) : 0;
+    const dim3 g(static_cast<unsigned>(nrows) + npack), b(256);
     if (L.dim == 2) hipLaunchKernelGGL(k_pack<2>, g, b, 0, st, L, a, t, nrows);
     else hipLaunchKernelGGL(k_pack<3>, g, b, 0, st, L, a, t, nrows);
     return hipGetLastError();

@@ -212,3 +212,43 @@ def test_ranks_and_bits_of_a_count(span, sparse, mode, half):
             assert desc[b, 3] == n and desc[b, 4] == 0
             at = 16 * int(desc[b, 23])
             np.testing.assert_array_equal(ranks[at:at + n], rank)
+
+
+@pytest.mark.parametrize("graphs", [False, True], ids=["eager", "graph"])
+@pytest.mark.parametrize("n", [1, 100, 3000])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_updates_in_a_grid_of_few_particles(dim, n, graphs):
+    """Builds and updates leave their per-cell counters clear for the next one also where the cells
+    are thousands of times the particles: rows after every one of them."""
+    nc = 128 if dim == 3 else 1448
+    ps = scattered(dim, n, nc, 7)
+    ps = W.ParticleSet(np.ascontiguousarray(ps.pos), ps.lo, ps.hi, 3.0 / nc, 3.0 / nc)  # some pairs
+    rng = np.random.default_rng(n)
+    pos = torch.from_numpy(ps.pos.copy()).cuda()
+    print(f"[gpu] sparse updates {dim}d n={n} graphs={graphs}", flush=True)
+    ctx = nnps.Context(0)
+    try:
+        cells = ctx.cells()
+        cells.set_graphs(graphs)
+        stream = torch.cuda.Stream()
+        cells.build(pos, ps.lo, ps.hi, ps.cell_size, ps.radius)
+        rp = torch.empty(n + 1, dtype=torch.int64, device="cuda")
+        cells.count(rp)
+        for step in range(6):
+            d = torch.from_numpy(rng.uniform(-0.3, 0.3, size=(n, dim))).cuda()  # far jumps, reflected at the faces
+            col = torch.full((64 * n + 64,), -1, dtype=torch.int32, device="cuda")
+            dist = torch.empty(col.shape, dtype=torch.float32, device="cuda")
+            torch.cuda.synchronize()
+            if step == 3:  # a fresh build in between
+                cells.batch_step([(pos, ps.lo, ps.hi, ps.cell_size, ps.radius)], [rp], [col], [dist],
+                                 nnps.MODE_FP16_RCLL, stream=stream)
+            else:
+                cells.batch_update_step([rp], [col], [dist], disp=[d], stream=stream)
+            torch.cuda.synchronize()
+            now = W.ParticleSet(pos.cpu().numpy(), ps.lo, ps.hi, ps.cell_size, ps.radius)
+            wrp, wcol, _ = oracle.search_ps(now)
+            np.testing.assert_array_equal(rp.cpu().numpy(), wrp)
+            np.testing.assert_array_equal(col.cpu().numpy()[:len(wcol)], wcol)
+        cells.close()
+    finally:
+        ctx.close()
