@@ -37,9 +37,9 @@ constexpr int kSparseTargets = 20;
 // Dense-cell path: candidates staged per chunk, targets per work unit (a workgroup of
 // four wavefronts, 64 targets each) and the default thresholds.
 constexpr int kDenseChunk = 1024;
-// The FP16 fill that tests stages fewer candidates per chunk, so that its tables (records,
-// FP64 positions and the per-wavefront queues of accepted candidates) still fit four
-// workgroups per CU (a multiple of 128).
+// The FP16 fill that tests stages fewer candidates per chunk, so that its tables (test records,
+// positions and the per-wavefront queues of accepted candidates) fit five workgroups per CU (a
+// multiple of 128).
 constexpr int kDenseChunkF16 = 896;
 // Default bound on the device scratch for the count's kept bits (MiB).
 constexpr int kDenseBitsMiB = 16384;

@@ -2605,10 +2605,10 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
     static_assert(K / 64 <= 16, "a lane's accepted bits of a chunk fit 16 bits");
     __shared__ uint4 recA[F16 ? K / 2 : 1];             // qx, qy, qz, 2(c_x - c_jx) pairs
     __shared__ uint2 recB[F16 ? K / 2 : 1];             // 2(c_y - c_jy), 2(c_z - c_jz) pairs
-    __shared__ __attribute__((aligned(16))) int sorig[K];
-    // candidates' FP64 positions: [K][DIM] (baseline), axis-major [DIM][K] (FP16 fill)
-    __shared__ double sdbl[(!F16 || FILL) ? K * DIM : 1];
-    double* const spj = sdbl;
+    constexpr bool QUANTA = F16 && FILL;  // candidates as k_dense_fill stages them
+    __shared__ int4 srec[QUANTA ? K : 1];               // position in quanta, set-local index
+    __shared__ __attribute__((aligned(16))) int sorig[QUANTA ? 1 : K];
+    __shared__ double spj[F16 ? 1 : K * DIM];           // FP64 positions, [K][DIM]
     __shared__ unsigned long long s_red[FILL ? 1 : kDenseThreads / 64][kDenseStats];  // count pass only
     // fill: per-wavefront queues of a row's accepted candidates in a chunk (chunk positions,
     // in row order)
@@ -2656,11 +2656,20 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
         int oi_k = 0, q01_k = 0, q2_k = 0, acc_k = 0, rl_k = 0;
         long long rs_k = 0;
         double pi_k[3] = {0, 0, 0};
+        int4 t_k = make_int4(0, 0, 0, 0);
+        const double inv_quantum = sdesc.fr.inv_quantum;
+        const float quantum = sdesc.fr.quantum, near2 = sdesc.fr.near2;
+        const double lo[3] = {sdesc.fr.lo[0], sdesc.fr.lo[1], sdesc.fr.lo[2]};
+        auto packed = [&](const double* x, int w) {
+            return make_int4(in_quanta(x[0], lo[0], inv_quantum), in_quanta(x[1], lo[1], inv_quantum),
+                             DIM == 3 ? in_quanta(x[2], lo[2], inv_quantum) : 0, w);
+        };
         if (vk) {
             oi_k = a.perm[pk];
             const int li = oi_k - poff;
 #pragma unroll
             for (int k = 0; k < DIM; ++k) pi_k[k] = a.spos[static_cast<size_t>(pk) * 4 + k];
+            if (QUANTA) t_k = packed(pi_k, 0);
             if (F16) {
                 const ushort4 q = q16_of(a.rq[pk]);
                 q01_k = static_cast<int>(static_cast<uint32_t>(q.x) | (static_cast<uint32_t>(q.y) << 16));
@@ -2712,16 +2721,16 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                             w4 |= static_cast<uint32_t>(__builtin_bit_cast(uint16_t, c2y)) << sh;
                             w5 |= static_cast<uint32_t>(__builtin_bit_cast(uint16_t, c2z)) << sh;
                             const int oj = a.perm[j];
-                            sorig[e] = oj;
-                            if (FILL) {
-#pragma unroll
-                                for (int k = 0; k < DIM; ++k)
-                                    spj[k * K + e] = a.spos[static_cast<size_t>(j) * 4 + k];
+                            if constexpr (QUANTA) {
+                                srec[e] = packed(a.spos + static_cast<size_t>(j) * 4, oj - poff);
                                 if (j >= t0 && j < t1) sself[j - t0] = c0 + e;  // a target of this unit
+                            } else {
+                                sorig[e] = oj;
                             }
                         } else {
                             w0 |= 0x7C00u << sh;  // qx = +inf: r2 = +inf
-                            sorig[e] = -1;
+                            if (QUANTA) srec[e].w = -1 - poff;
+                            else sorig[e] = -1;
                         }
                     }
                     const int slot = (m % nit) * 64 + m / nit;
@@ -2739,11 +2748,13 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                     } else {
                         sorig[e] = -1;
 #pragma unroll
-                        for (int k = 0; k < DIM; ++k) spj[e * DIM + k] = 1e300;  // r2 = +inf
+                        for (int k = 0; k < DIM; ++k) spj[e * DIM + k] = __builtin_nan("");  // never a neighbour
                     }
                 }
             }
             __syncthreads();
+            // original index of candidate e
+            auto orig_of = [&](int e) { return QUANTA ? srec[e].w + poff : sorig[e]; };
             // the fill's emission of target k's accepted candidates in this chunk: bit j of
             // M is the lane's candidate 2 lane nit + j
             auto fill_row = [&](int k, uint32_t M, const double* pi) {
@@ -2758,25 +2769,32 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                 const int rl = rl32(rl_k, k);
                 const int done = rl32(acc_k, k);
                 const bool room = rs + rl <= sd.capacity;
-                const double* pis = pi;
+                const int4 ti = make_int4(rl32(t_k.x, k), rl32(t_k.y, k), rl32(t_k.z, k), 0);
                 // the row's output, wave-uniform: entries are addressed by a 32-bit slot
                 NNPS_GLOBAL int32_t* const rcol = uniform_ptr(sd.col + rs);
                 NNPS_GLOBAL float* const rdist = uniform_ptr(sd.dist + rs);
-                auto emit = [&](int e, int slot, int oj) {
+                auto emit = [&](int e, int slot) {
+                    int lj;
+                    float dv;
+                    if constexpr (QUANTA) {  // as k_dense_fill
+                        const int4 r = srec[e];
+                        lj = r.w;
+                        const float s2 = quanta2<DIM>(ti, r);
+                        dv = root(s2) * quantum;
+                        if (!(s2 >= near2))
+                            dv = dist_near<DIM>(a.spos + static_cast<size_t>(t0 + wv + NWV * k) * 4,
+                                                a.spos + static_cast<size_t>(a.ulist[ub + c0 + e]) * 4, inv_quantum, quantum);
+                    } else {
+                        lj = sorig[e] - poff;
+                        dv = dist_fp64<DIM>(pi, spj + e * DIM);
+                    }
                     if (slot < rl && room) {
-                        float dv;
-                        if (F16) {
-                            double pj[3] = {spj[e], spj[K + e], DIM == 3 ? spj[(DIM - 1) * K + e] : 0.0};
-                            dv = dist_quanta<DIM>(sdesc.fr, pi, pj);
-                        } else {
-                            dv = static_cast<float>(__dsqrt_rn(r2_fp64<DIM>(pis, spj + e * DIM)));
-                        }
                         if (rl <= (1 << 30)) {  // byte offsets within the row fit 32 bits
                             const uint32_t off = static_cast<uint32_t>(slot) * 4u;
-                            *(NNPS_GLOBAL int32_t*)((NNPS_GLOBAL char*)rcol + off) = oj - poff;
+                            *(NNPS_GLOBAL int32_t*)((NNPS_GLOBAL char*)rcol + off) = lj;
                             *(NNPS_GLOBAL float*)((NNPS_GLOBAL char*)rdist + off) = dv;
                         } else {
-                            rcol[slot] = oj - poff;
+                            rcol[slot] = lj;
                             rdist[slot] = dv;
                         }
                     }
@@ -2797,20 +2815,14 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                     for (uint32_t mm = M; mm; mm &= mm - 1) q[pos++] = static_cast<uint16_t>(lb + __builtin_ctz(mm));
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                     for (int q0 = 0; q0 < tot; q0 += 64) {
-                        if (q0 + lane < tot) {
-                            const int e = q[q0 + lane];
-                            emit(e, done + q0 + lane, sorig[e]);
-                        }
+                        if (q0 + lane < tot) emit(q[q0 + lane], done + q0 + lane);
                     }
                     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 } else {
                     // more than the queue holds (a chunk with most candidates accepted): each
                     // lane writes its own entries
                     int pos = done + base;
-                    for (uint32_t mm = M; mm; mm &= mm - 1) {
-                        const int e = lb + __builtin_ctz(mm);
-                        emit(e, pos++, sorig[e]);
-                    }
+                    for (uint32_t mm = M; mm; mm &= mm - 1) emit(lb + __builtin_ctz(mm), pos++);
                 }
                 const int w = done + tot;
                 if (!room && lane == 0 && w > done) atomicOr(a.flags + kFlagErr, kErrCapacity);
@@ -2820,8 +2832,8 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                 for (int k = 0; k < nt; ++k) {
                     const int oi = rl32(oi_k, k);
                     double pi[3] = {0.0, 0.0, 0.0};
-                    // the FP16 count needs the target's FP64 position only for a band recheck
-                    if (!F16 || FILL) {
+                    // the FP16 test needs the target's FP64 position only for a band recheck
+                    if (!F16) {
 #pragma unroll
                         for (int d = 0; d < 3; ++d) pi[d] = rlf64(pi_k[d], k);
                     }
@@ -2872,19 +2884,12 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                             }
                         }
                         bnd = ebits & ~inb;
-                        // the FP64 recheck of candidate e: from its staged position in the fill
+                        // the FP64 recheck of candidate e
                         auto recheck = [&](int e) -> bool {
-                            if constexpr (FILL) {
-                                double pj[3];
+                            double pt[3];
 #pragma unroll
-                                for (int d = 0; d < DIM; ++d) pj[d] = spj[d * K + e];
-                                return r2_fp64<DIM>(pi, pj) <= R2;
-                            } else {
-                                double pt[3];
-#pragma unroll
-                                for (int d = 0; d < 3; ++d) pt[d] = rlf64(pi_k[d], k);
-                                return recheck_sorted<DIM>(a.spos, pt, a.ulist[ub + c0 + e], R2);
-                            }
+                            for (int d = 0; d < 3; ++d) pt[d] = rlf64(pi_k[d], k);
+                            return recheck_sorted<DIM>(a.spos, pt, a.ulist[ub + c0 + e], R2);
                         };
                         if (MODE == 2) {
                             // every candidate decided in FP64; the FP16 classes are only compared
@@ -2898,7 +2903,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                                 const int bb = __builtin_ctz(all);
                                 all &= all - 1;
                                 const int e = 2 * (lane * nit + (bb & 15)) + (bb >> 4);
-                                const int oj = sorig[e];
+                                const int oj = orig_of(e);
                                 if (oj == oi) continue;
                                 const bool truth = recheck(e);
                                 if (truth) dec |= 1u << bb;
@@ -2935,7 +2940,7 @@ __global__ void __launch_bounds__(kDenseThreads) __attribute__((amdgpu_waves_per
                                 const int bb = __builtin_ctz(bb_all);
                                 bb_all &= bb_all - 1;
                                 const int e = 2 * (lane * nit + (bb & 15)) + (bb >> 4);
-                                const int oj = sorig[e];
+                                const int oj = orig_of(e);
                                 if (oj == oi) continue;  // itself (a band pair only when T_lo = 0)
                                 const bool truth = recheck(e);
                                 if (truth) inb |= 1u << bb;
