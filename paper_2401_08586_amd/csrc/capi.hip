@@ -857,8 +857,14 @@ nnps_status take_report(nnps_cells* c, const int64_t* hp)
     const int* flags = reinterpret_cast<const int*>(hp);
     see_flags(c, flags);
     if (c->dense_active && dense_bits_on(c)) {
-        const size_t want = static_cast<size_t>(hp[kHostWords - 1]) * 64 * sizeof(uint16_t);
-        if (want <= dense_bits_bound(c) && want < c->dbits_denied) c->dbits_want = std::max(c->dbits_want, want);
+        // an eighth more than that, as far as the bound goes: steps that nobody waits for move the
+        // particles on, and a fill without room for its bits takes several times as long
+        const size_t bound = dense_bits_bound(c);
+        size_t want = static_cast<size_t>(hp[kHostWords - 1]) * 64 * sizeof(uint16_t);
+        if (want <= bound) {
+            want = std::min(want + want / 8, bound);
+            if (want < c->dbits_denied) c->dbits_want = std::max(c->dbits_want, want);
+        }
     }
     return err_status(flags[kFlagErr]);
 }

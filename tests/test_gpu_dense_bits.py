@@ -1,8 +1,10 @@
 """The dense count's kept bits where they cannot be kept: a cell with more than 2^31 (target, chunk)
 pairs, on a structure that holds bits of an earlier search. Under the default bound they are not
 asked for; under one above the device's memory the allocation fails and the search does without."""
+import numpy as np
 import pytest
 
+import oracle
 from paper_2401_08586_amd import workloads as W
 
 torch = pytest.importorskip("torch")
@@ -38,4 +40,38 @@ def test_more_pairs_than_32_bits(bits_mib):
         cells.close()
     finally:
         ctx.set_tuning()
+        ctx.close()
+
+
+@pytest.mark.parametrize("mode", [nnps.MODE_FP16_RCLL, nnps.MODE_FP64_BASELINE])
+@pytest.mark.parametrize("dim", [2, 3])
+def test_lists_that_outgrow_the_kept_bits(dim, mode):
+    """Updates contract a clustered set step by step, with no call that waits in between: the bits of
+    the first steps fit the buffer, those of the last do not. Rows as the oracle's after every step."""
+    ps = W.clustered(6000, 4, dim=dim)
+    pos = torch.from_numpy(ps.pos.copy()).cuda()
+    print(f"[gpu] outgrown bits {dim}d mode={mode}", flush=True)
+    ctx = nnps.Context(0)
+    try:
+        cells = ctx.cells()
+        rp = torch.empty(ps.n + 1, dtype=torch.int64, device="cuda")
+        col = torch.empty(24_000_000, dtype=torch.int32, device="cuda")
+        dist = torch.empty(24_000_000, dtype=torch.float32, device="cuda")
+        for _ in range(2):
+            cells.build(pos, ps.lo, ps.hi, ps.cell_size, ps.radius, mode=mode)
+            cells.count(rp)
+        stream = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        for step in range(6):
+            d = -0.1 * (pos - 0.5)
+            torch.cuda.synchronize()
+            cells.batch_update_step([rp], [col], [dist], disp=[d], stream=stream)
+            torch.cuda.synchronize()
+            wrp, wcol, wdist = oracle.search_ps(W.ParticleSet(pos.cpu().numpy(), ps.lo, ps.hi, ps.cell_size, ps.radius))
+            np.testing.assert_array_equal(rp.cpu().numpy(), wrp)
+            np.testing.assert_array_equal(col[:len(wcol)].cpu().numpy(), wcol)
+            got = dist[:len(wcol)].cpu().numpy().astype(np.float64)
+            assert np.all(np.abs(got - wdist) <= 1e-6 * wdist)
+        cells.close()
+    finally:
         ctx.close()
