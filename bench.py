@@ -31,13 +31,13 @@ HBM_PEAK_GBS = 8000.0
 #   FETCH_SIZE / WRITE_SIZE (KiB): the copy reads 262,144 KiB fetched and 524,288 KiB
 #     written for 524,288 KiB moved each way, so they scale by 2.000 and 1.000.
 # Reported only while the source is unchanged (the counters belong to that code).
-FILL_TRAFFIC = {"source_sha256_16": "bf2dbcdf8256fa74", "dram_read_bytes": 237.3e6, "dram_write_bytes": 491.4e6,
-                "fetch_kib": 116736, "write_kib": 479923, "fetch_scale": 2.0, "write_scale": 1.0}
+FILL_TRAFFIC = {"source_sha256_16": "87622a8fc8f109f4", "dram_read_bytes": 237.2e6, "dram_write_bytes": 491.5e6,
+                "fetch_kib": 116728, "write_kib": 480010, "fetch_scale": 2.0, "write_scale": 1.0}
 
 
 # VALU wave-instructions per launch (SQ_INSTS_VALU) of the C2 search kernels, from the
 # profile of the same source; like the traffic, reported only while the source is unchanged
-VALU_INSTS = {"source_sha256_16": "bf2dbcdf8256fa74", "k_fill<3,false>": 77699923, "k_count<3,16,false>": 77693658}
+VALU_INSTS = {"source_sha256_16": "87622a8fc8f109f4", "k_fill<3,false>": 79095533, "k_count<3,16,false>": 78639584}
 
 
 def valu_ceilings():

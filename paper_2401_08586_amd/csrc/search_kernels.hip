@@ -2252,9 +2252,9 @@ __device__ __forceinline__ double rlf64(double v, int k)
 // launch on 422 thousand clustered particles, 2.2 G candidates; this 0.41).
 //
 // Fill: it takes the kept bits, or (no room for them) tests again with packed FP16 (or in
-// binary64) and an FP64 recheck. For each chunk the workgroup stages the candidates' original
-// indices and FP64 positions in LDS, then each wavefront runs its targets one at a time over
-// the chunk. Lane L holds a contiguous run of the chunk's candidates, so a target's accepted
+// binary64) and an FP64 recheck. For each chunk the workgroup stages the candidates' indices and
+// positions (in quanta, or binary64) in LDS, then each wavefront runs its targets one at a time
+// over the chunk. Lane L holds a contiguous run of the chunk's candidates, so a target's accepted
 // ones come out lane by lane in row order: one wavefront prefix sum of the lanes' counts
 // places them, they are queued per lane and written 64 at a time, so consecutive lanes store
 // consecutive CSR entries and the row comes out ascending.
