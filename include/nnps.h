@@ -134,8 +134,8 @@ typedef struct nnps_stats {
  *   Valid 0..2^20.
  * dense_max_entries: bound on the summed stencil-union sizes of dense cells per build
  *   (device scratch: 4 bytes per entry, 16 where a set has more than 1,048,576 particles,
- *   allocated as min(3^d n, bound)). Beyond it a build falls back to the block and long-row paths. 0 = default (2^28). Valid
- *   0..2^31-1.
+ *   allocated as min(3^d n, bound)). Beyond it a build falls back to the block and
+ *   long-row paths. 0 = default (2^28). Valid 0..2^31-1.
  * dense_bits_mib: bound (MiB) on the device scratch in which the dense count keeps
  *   every target's accepted bits per candidate chunk (one bit per candidate, 1024
  *   candidates a chunk) so that the fill does not test again. The
